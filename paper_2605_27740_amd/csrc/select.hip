@@ -1,19 +1,29 @@
 // Top-k page selection per (sequence, KV head) row (Section 3.2 of the paper, radix-based top-k).
 //
 // One workgroup per row; the row's scores are read once and stay in registers as order-preserving
-// 32-bit keys. The paper narrows the k-th largest score with two 8-bit radix rounds over bf16 scores;
-// here the scores are fp32 and the selected set has to equal an exact ranking, so the search is:
-//   1. one histogram pass over 2 * threads buckets that are LINEAR in the score between the row's
-//      minimum and maximum (a monotone map, so bucket order never contradicts score order). It finds
-//      the bucket holding the k-th largest score; everything in higher buckets is selected. Linear
-//      buckets spread page scores far better than the leading bits of a float (which are mostly
-//      exponent), so LDS atomics see little same-address contention and the boundary bucket holds
-//      only a handful of candidates.
-//   2. exact resolution among the candidates of the boundary bucket: by pairwise ranking on
-//      (key, page index) when they are few, otherwise by four 8-bit radix rounds over their keys
-//      (this also covers degenerate rows such as all scores equal).
-//   3. an index-ordered compaction (one workgroup scan) that emits the selected logical pages in
-//      ascending order and takes keys tied with the k-th from the lowest page index upward.
+// 32-bit keys (rows of more than 32768 pages are read twice). The paper narrows the k-th largest score with two 8-bit
+// radix rounds over bf16 scores; here the scores are fp32 and the selected set has to equal an exact ranking. What
+// bounds the kernel is a chain of latencies on one compute unit and, for long rows, the instructions spent per key
+// (about 130 wave instructions per 64 keys if every key goes through every step), so the search is:
+//   1. the row's extremes and a lower bound T0 of the k-th key: the smallest of the maxima of disjoint groups of keys,
+//      of which there are at least k. 10 to 35 % of the keys are not below it. Where a thread holds 32 keys those are
+//      gathered in LDS and dealt out again, so the remaining steps see a few keys per thread.
+//   2. one histogram pass over buckets that are LINEAR in the score between T0 and the row's maximum (a monotone map,
+//      so bucket order never contradicts score order). It finds the bucket holding the k-th largest score; everything in
+//      higher buckets is selected. Linear buckets spread page scores far better than the leading bits of a float (which
+//      are mostly exponent), so LDS atomics see little same-address contention and the boundary bucket holds only a
+//      handful of candidates. Every wave scans the histogram for itself, which saves two barriers.
+//   3. exact resolution among the candidates of the boundary bucket: by ranking on (key, page index) when they are few
+//      (up to 64: one per lane, every wave for itself), otherwise by four 8-bit radix rounds over their keys (this also
+//      covers degenerate rows such as all scores equal).
+//   4. an index-ordered compaction that emits the selected logical pages in ascending order and takes keys tied with
+//      the k-th from the lowest page index upward.
+// Kernel us before (a thread owned consecutive pages, every key went through every step) and now, planted normal scores:
+// 8 rows x 2048 pages, k 128: 5.1 / 4.9; 128 x 8192, 256: 9.0 / 8.4; 640 x 4096, 64: 17.0 / 9.6; 16 x 16384, 1024:
+// 13.5 / 12.7; 8 x 32768, 512: 22.4 / 15.0; 8 x 62501, 1024: 67.8 / 29.7; 4 x 131072, 1024: 217 / 43; all scores equal,
+// 128 x 8192: 44 / 20.
+#include <type_traits>
+
 #include "device_utils.hpp"
 #include "kernels.hpp"
 
@@ -23,26 +33,6 @@ namespace {
 constexpr int kMaxRankCandidates = 512;  // above this the boundary bucket is resolved by radix rounds
 constexpr uint32_t kKeyForced = 0xffffffffu;  // key of a page that is selected whatever its score
 constexpr uint32_t kKeyNegInf = 0x007fffffu, kKeyPosInf = 0xff800000u;  // keys of -inf and +inf
-
-// Exclusive prefix sums of two counters at once over the threads of a workgroup (thread order). The pair
-// travels packed in 64 bits; wave_tot: kThreads / 64 slots of LDS. All threads must call it.
-template <int kThreads>
-__device__ __forceinline__ unsigned long long block_exclusive_scan(unsigned long long v,
-                                                                  unsigned long long* wave_tot /*[kThreads/64]*/) {
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int lo = (int)(v & 0xffffffffull), hi = (int)(v >> 32);
-  const int inc_lo = wave_inclusive_scan(lo), inc_hi = wave_inclusive_scan(hi);
-  const unsigned long long inc = (unsigned long long)(uint32_t)inc_lo | ((unsigned long long)(uint32_t)inc_hi << 32);
-  if (lane == kWave - 1) wave_tot[wave] = inc;
-  __syncthreads();
-  unsigned long long base = 0;
-#pragma unroll
-  for (int w = 0; w < kThreads / kWave; ++w) {  // all totals are read at once, not one dependent read per wave
-    const unsigned long long tot = wave_tot[w];
-    base += w < wave ? tot : 0ull;
-  }
-  return base + inc - v;
-}
 
 __device__ __forceinline__ float ordered_to_float(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
@@ -55,6 +45,22 @@ __device__ __forceinline__ int linear_bucket(uint32_t k, float lo, float scale, 
   if (k >= kKeyPosInf) return n_buckets - 1;
   if (k > kKeyNegInf) return min(n_buckets - 1, max(0, (int)((ordered_to_float(k) - lo) * scale)));
   return 0;
+}
+
+// Lanes of one wave whose predicate holds and which come before this lane, added to `acc`.
+__device__ __forceinline__ int lanes_before(unsigned long long mask, int acc) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)acc));
+}
+
+// hist[bin] += 1 for every active lane, as one addition where they all have the same bin: 64 lanes adding to one address
+// take about 800 cycles, and masses of equal keys are what the radix rounds are for.
+__device__ __forceinline__ void add_one(int* hist, int bin) {
+  const unsigned long long active = __ballot(1);
+  if (__all(bin == __builtin_amdgcn_readfirstlane(bin))) {
+    if (lanes_before(active, 0) == 0) atomicAdd(&hist[bin], __popcll(active));
+  } else {
+    atomicAdd(&hist[bin], 1);
+  }
 }
 
 // One round-set of 8-bit radix selection over the keys accepted by `keep(j)`: returns the exact key of
@@ -71,14 +77,14 @@ __device__ __forceinline__ uint32_t radix_threshold(int n_items, KeyAt key_at, K
   for (int round = 0; round < 4; ++round) {
     const int shift = 24 - 8 * round;
     __syncthreads();  // everyone is done with the previous contents of hist
-    if (t < 256) hist[t] = 0;
+    for (int i = t; i < 256; i += kThreads) hist[i] = 0;
     __syncthreads();
     if constexpr (kStatic > 0) {
 #pragma unroll
       for (int j = 0; j < n; ++j) {
         if (keep(j)) {
           const uint32_t k = key_at(j);
-          if (round == 0 || (k >> (shift + 8)) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1);
+          if (round == 0 || (k >> (shift + 8)) == prefix) add_one(hist, (int)((k >> shift) & 255u));
         }
       }
     } else {  // keys come from memory: eight reads are requested before the first one is used
@@ -92,7 +98,7 @@ __device__ __forceinline__ uint32_t radix_threshold(int n_items, KeyAt key_at, K
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          if (kp[u] && (round == 0 || (kk[u] >> (shift + 8)) == prefix)) atomicAdd(&hist[(kk[u] >> shift) & 255u], 1);
+          if (kp[u] && (round == 0 || (kk[u] >> (shift + 8)) == prefix)) add_one(hist, (int)((kk[u] >> shift) & 255u));
       }
     }
     __syncthreads();
@@ -124,22 +130,257 @@ __device__ __forceinline__ uint32_t radix_threshold(int n_items, KeyAt key_at, K
   return prefix;
 }
 
-// kItems keys per thread in registers (blocked: thread t owns pages [t*kItems, (t+1)*kItems)).
-template <int kThreads, int kItems>
+// Keys of the register kernel: as float_to_ordered, but a NaN becomes 1 (still below -inf), so that 0 means "no page".
+__device__ __forceinline__ uint32_t score_key(float f) {
+  const uint32_t u = __float_as_uint(f + 0.f);  // -0 becomes +0
+  const uint32_t k = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+  return f != f ? 1u : k;
+}
+
+// Exclusive prefix of counts[v * kWaves + wave] (kVecs * kWaves counts in LDS, at most 256) for every v, and their total.
+template <int kVecs, int kWaves>
+__device__ __forceinline__ int wave_prefixes(const int* counts, int wave, int (&prefix)[kVecs]) {
+  static_assert(kWaves == 1 || (kVecs * kWaves <= 4 * kWave && kWaves % 4 == 0), "four counts per lane");
+  if constexpr (kWaves == 1) {
+    int sum = 0;
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) { prefix[v] = sum; sum += counts[v]; }
+    return sum;
+  }
+  const int lane = threadIdx.x % kWave;
+  int4 q = make_int4(0, 0, 0, 0);
+  if (4 * lane < kVecs * kWaves) q = *reinterpret_cast<const int4*>(&counts[4 * lane]);
+  const int inc = wave_inclusive_scan(q.x + q.y + q.z + q.w);
+  const int sub = wave % 4;
+  const int pre = inc - (q.w + (sub < 3 ? q.z : 0) + (sub < 2 ? q.y : 0) + (sub < 1 ? q.x : 0));
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) prefix[v] = __builtin_amdgcn_readlane(pre, (v * kWaves + wave) / 4);
+  return __builtin_amdgcn_readlane(inc, kWave - 1);
+}
+
+template <int kThreads>
+struct SelectShared {
+  static constexpr int kWaves = kThreads / kWave;
+  static constexpr int kBuckets = kThreads >= 1024 ? 2048 : (kThreads >= 256 ? 1024 : 256);
+  static constexpr int kMaxRank = kThreads < kMaxRankCandidates ? kThreads : kMaxRankCandidates;
+  // every 16 buckets are followed by a gap of 4 so that the 16-byte reads of the scan spread over the LDS banks
+  static __device__ __forceinline__ int slot(int bucket) { return bucket + ((bucket >> 4) << 2); }
+  __attribute__((aligned(16))) int hist[kBuckets + kBuckets / 4];
+  __attribute__((aligned(16))) int sure_cnt[4 * kWave], tie_cnt[4 * kWave];
+  uint32_t cand_key[kMaxRank];
+  int cand_page[kMaxRank];
+  uint32_t wave_min[kWaves], wave_max[kWaves], wave_low[kWaves];
+  int need, ncand;
+  uint32_t prefix;
+};
+
+// The bucket that holds the kb-th largest counted key, how many of its keys are among the kb, and how many it has.
+// Every wave scans the whole histogram for itself: lane l takes kBuckets / 64 buckets, lane 0 the topmost ones.
+template <int kThreads>
+__device__ __forceinline__ void boundary_bucket(const SelectShared<kThreads>& sh, int kb, int& bstar, int& need, int& ncand) {
+  using Sh = SelectShared<kThreads>;
+  constexpr int kPerLane = Sh::kBuckets / kWave;
+  int cnt[kPerLane];
+  const int b0 = (kWave - 1 - (int)(threadIdx.x % kWave)) * kPerLane;
+  int tot = 0;
+#pragma unroll
+  for (int i = 0; i < kPerLane; i += 4) {
+    const int4 q = *reinterpret_cast<const int4*>(&sh.hist[Sh::slot(b0 + i)]);
+    cnt[i] = q.x; cnt[i + 1] = q.y; cnt[i + 2] = q.z; cnt[i + 3] = q.w;
+    tot += q.x + q.y + q.z + q.w;
+  }
+  const int inc = wave_inclusive_scan(tot);
+  int above = inc - tot, my_b = 0, my_need = 0, my_n = 0;
+  const int src = __ffsll(__ballot(above < kb && kb <= inc)) - 1;  // exactly one lane
+#pragma unroll
+  for (int i = kPerLane - 1; i >= 0; --i) {
+    if (above < kb) { my_b = b0 + i; my_need = kb - above; my_n = cnt[i]; }  // the last one that stays true
+    above += cnt[i];
+  }
+  bstar = __builtin_amdgcn_readlane(my_b, src);
+  need = __builtin_amdgcn_readlane(my_need, src);
+  ncand = __builtin_amdgcn_readlane(my_n, src);
+}
+
+// Where the buckets lie: linear between the scores of the keys kmin and kmax (see linear_bucket).
+struct BucketMap { float lo, scale; };
+__device__ __forceinline__ BucketMap bucket_map(uint32_t kmin, uint32_t kmax, int n_buckets) {
+  BucketMap m = {0.f, 0.f};
+  if (kmin < kmax) {  // at least two distinct finite keys to tell apart
+    m.lo = ordered_to_float(kmin);
+    const float range = ordered_to_float(kmax) - m.lo;
+    if (range > 0.f && range < 3.0e38f) m.scale = (float)(n_buckets - 1) / range;
+    if (!(m.scale < 3.0e38f)) m.scale = 0.f;  // a denormal range: leave everything in one bucket
+  }
+  return m;
+}
+
+// The selection proper over keys in registers: thread t holds kVecs groups of kPer keys; in the order (group, thread,
+// key inside the group) the pages ascend. Keys below T0 (>= 1) are not selected, at least kb keys are not below it.
+// The histogram in `sh` is zero and sh.ncand is 0. All threads call it.
+template <int kThreads, int kVecs, int kPer, typename PageOf>
+__device__ __forceinline__ void select_keys(const uint32_t (&key)[kVecs * kPer], PageOf page_of, uint32_t T0, BucketMap map,
+                                            int kb, int32_t* out, SelectShared<kThreads>& sh) {
+  using Sh = SelectShared<kThreads>;
+  constexpr int kWaves = Sh::kWaves, kBuckets = Sh::kBuckets, kMaxRank = Sh::kMaxRank, kItems = kVecs * kPer;
+  const int t = threadIdx.x, lane = t % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
+
+  // ---- 1. histogram; the bucket of every counted key (-1: not counted) stays in registers unless the keys take most
+  constexpr bool kKeepBuckets = kItems <= 16;
+  int bucket_reg[kKeepBuckets ? kItems : 1];
+  auto make_bucket = [&](int j) { return key[j] >= T0 ? linear_bucket(key[j], map.lo, map.scale, kBuckets) : -1; };
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int bk = make_bucket(j);
+    if (bk >= 0) {
+      if (map.scale == 0.f) add_one(sh.hist, Sh::slot(bk));  // uniform; all finite keys share one bucket
+      else atomicAdd(&sh.hist[Sh::slot(bk)], 1);
+    }
+    if constexpr (kKeepBuckets) bucket_reg[j] = bk;
+  }
+  auto bucket = [&](int j) {
+    if constexpr (kKeepBuckets) return bucket_reg[j];
+    else return make_bucket(j);
+  };
+  __syncthreads();
+  // need: how many of the boundary bucket's ncand keys are selected
+  int bstar, need, ncand;
+  boundary_bucket<kThreads>(sh, kb, bstar, need, ncand);
+
+  // ---- 2. candidates of the boundary bucket, and surely selected pages per (group, wave)
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) {
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int j = kPer * v + i, bk = bucket(j);
+      n += __popcll(__ballot(bk > bstar));
+      if (bk == bstar && ncand <= kMaxRank) {
+        const int at = atomicAdd(&sh.ncand, 1);
+        sh.cand_key[at] = key[j];
+        sh.cand_page[at] = page_of(j);
+      }
+    }
+    if (lane == 0) sh.sure_cnt[v * kWaves + wave] = n;
+  }
+  __syncthreads();
+  int place[kVecs];  // output index of the first selected page of (group v, this wave)
+
+  if (ncand > kMaxRank) {  // a degenerate row (many equal scores, or a range that the buckets cannot resolve)
+    const uint32_t T = radix_threshold<kThreads, kItems>(
+        kItems, [&](int j) { return key[j]; }, [&](int j) { return bucket(j) == bstar; }, need, sh.hist, &sh.prefix,
+        &sh.need);
+    // need: how many keys equal to T are taken, from the lowest page up
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) {
+      int n = 0, e = 0;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        n += __popcll(__ballot(key[kPer * v + i] > T));
+        e += __popcll(__ballot(key[kPer * v + i] == T));
+      }
+      if (lane == 0) { sh.sure_cnt[v * kWaves + wave] = n; sh.tie_cnt[v * kWaves + wave] = e; }
+    }
+    __syncthreads();
+    int ties[kVecs];
+    wave_prefixes<kVecs, kWaves>(sh.sure_cnt, wave, place);
+    wave_prefixes<kVecs, kWaves>(sh.tie_cnt, wave, ties);
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) {
+      int sure_b = place[v], tie_b = ties[v];
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        sure_b = lanes_before(__ballot(key[kPer * v + i] > T), sure_b);
+        tie_b = lanes_before(__ballot(key[kPer * v + i] == T), tie_b);
+      }
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const int j = kPer * v + i;
+        if (key[j] > T) {
+          out[min(tie_b, need) + sure_b++] = page_of(j);
+        } else if (key[j] == T) {
+          if (tie_b < need) out[sure_b + tie_b] = page_of(j);
+          ++tie_b;
+        }
+      }
+    }
+    return;
+  }
+
+  // ---- exact rank of the candidates by (key, page): the last selected one has key T and page tpage
+  uint32_t T;
+  int tpage;
+  wave_prefixes<kVecs, kWaves>(sh.sure_cnt, wave, place);
+  int first_page[kVecs];  // page of (group v, this wave, lane 0): candidates before it lie in earlier groups or waves
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) first_page[v] = __builtin_amdgcn_readfirstlane(page_of(kPer * v));
+  if (ncand <= kWave) {  // one candidate per lane, every wave for itself
+    const uint32_t mk = lane < ncand ? sh.cand_key[lane] : 0u;
+    const int mi = lane < ncand ? sh.cand_page[lane] : 0x7fffffff;
+    int rank = 0;
+    for (int j = 0; j < ncand; ++j) {
+      const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)mk, j);
+      const int ij = __builtin_amdgcn_readlane(mi, j);
+      rank += (kj > mk) || (kj == mk && ij < mi);
+    }
+    const bool sel = lane < ncand && rank < need;
+    const int src = __ffsll(__ballot(lane < ncand && rank == need - 1)) - 1;
+    T = (uint32_t)__builtin_amdgcn_readlane((int)mk, src);
+    tpage = __builtin_amdgcn_readlane(mi, src);
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) place[v] += __popcll(__ballot(sel && mi < first_page[v]));
+  } else {
+    if (t < ncand) {
+      const uint32_t mk = sh.cand_key[t];
+      const int mi = sh.cand_page[t];
+      int rank = 0;
+#pragma unroll 8
+      for (int j = 0; j < ncand; ++j) rank += (sh.cand_key[j] > mk) || (sh.cand_key[j] == mk && sh.cand_page[j] < mi);
+      if (rank == need - 1) { sh.prefix = mk; sh.need = mi; }
+    }
+    __syncthreads();
+    T = sh.prefix;
+    tpage = sh.need;
+    for (int j0 = 0; j0 < ncand; j0 += kWave) {
+      const uint32_t mk = j0 + lane < ncand ? sh.cand_key[j0 + lane] : 0u;
+      const int mi = j0 + lane < ncand ? sh.cand_page[j0 + lane] : 0x7fffffff;
+      const bool sel = mk > T || (mk == T && mi <= tpage);
+#pragma unroll
+      for (int v = 0; v < kVecs; ++v) place[v] += __popcll(__ballot(sel && mi < first_page[v]));
+    }
+  }
+
+  // ---- 3. the selected pages, in page order
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) {
+    bool sel[kPer];
+    int at = place[v];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int j = kPer * v + i;
+      sel[i] = key[j] > T || (key[j] == T && page_of(j) <= tpage);
+      at = lanes_before(__ballot(sel[i]), at);
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      if (sel[i]) out[at++] = page_of(kPer * v + i);
+  }
+}
+
+// One workgroup per row, kVecs 16-byte loads of four scores per thread: thread t holds the pages
+// v * 4 * kThreads + 4 * t + i, so every load of a wave is 1 KiB of consecutive scores.
+template <int kThreads, int kVecs>
 __global__ __launch_bounds__(kThreads) void topk_select_kernel(CacheView c, const float* __restrict__ scores,
                                                                int score_stride, int top_k,
                                                                int32_t* __restrict__ sel_pages,
                                                                int32_t* __restrict__ sel_count) {
-  constexpr int kWaves = kThreads / kWave;
-  constexpr int kBuckets = 2 * kThreads;
-  constexpr int kMaxRank = kThreads < kMaxRankCandidates ? kThreads : kMaxRankCandidates;
-  __shared__ int hist[kBuckets];
-  __shared__ unsigned long long wave_tot[kWaves];
-  __shared__ uint32_t wave_min[kWaves], wave_max[kWaves];
-  __shared__ uint32_t cand_key[kMaxRank];
-  __shared__ int cand_idx[kMaxRank];
-  __shared__ int s_bucket, s_need, s_ncand;
-  __shared__ uint32_t s_prefix;
+  using Sh = SelectShared<kThreads>;
+  constexpr int kWaves = Sh::kWaves, kItems = 4 * kVecs, kBuckets = Sh::kBuckets;
+  constexpr int kDense = 8;                  // keys per thread that are kept when the others are dropped
+  constexpr bool kCompact = kItems == 32;    // fewer keys gain nothing, 64 leave no registers for the second set
+  __shared__ Sh sh;
+  __shared__ uint2 kept[kCompact ? kDense * kThreads : 1];
 
   const int row = blockIdx.x;
   const int b = row / c.Hkv;
@@ -147,7 +388,8 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(CacheView c, cons
   int P = min((N + c.S - 1) / c.S, c.max_pages_hint);
   P = min(P, kThreads * kItems);  // a row longer than the host bound is cut, never overrun
   const int kb = min(top_k, P);
-  const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+  const int t = threadIdx.x, lane = t % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
   int32_t* out = sel_pages + (int64_t)row * top_k;
   const float* srow = scores + (int64_t)row * score_stride;
 
@@ -158,179 +400,118 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(CacheView c, cons
     return;
   }
 
-  const int first = t * kItems;
-  const int nv = max(0, min(kItems, P - first));  // valid items of this thread
-  const int forced_from = P - min(c.force_recent, kb);  // pages from here on are always selected
-
-  uint32_t key[kItems];
-  if constexpr (kItems >= 4) {
+  float4 raw[kVecs];
 #pragma unroll
-    for (int j = 0; j < kItems; j += 4) {
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (j < nv) v = *reinterpret_cast<const float4*>(srow + first + j);  // row stride is padded past P
-      key[j] = float_to_ordered(v.x); key[j + 1] = float_to_ordered(v.y);
-      key[j + 2] = float_to_ordered(v.z); key[j + 3] = float_to_ordered(v.w);
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < kItems; ++j) key[j] = j < nv ? float_to_ordered(srow[first + j]) : 0u;
+  for (int v = 0; v < kVecs; ++v) {
+    const int p = v * 4 * kThreads + 4 * t;
+    raw[v] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (p < P) raw[v] = *reinterpret_cast<const float4*>(srow + p);  // the row is padded to a multiple of 4
   }
-  // an always-selected page takes the largest key there is (above +inf), so it outranks every score
+  uint32_t key[kItems];
 #pragma unroll
-  for (int j = 0; j < kItems; ++j)
-    if (first + j >= forced_from) key[j] = kKeyForced;
+  for (int v = 0; v < kVecs; ++v) {
+    const int n = P - (v * 4 * kThreads + 4 * t);  // pages from this load's first one on
+    key[4 * v] = n > 0 ? score_key(raw[v].x) : 0u;
+    key[4 * v + 1] = n > 1 ? score_key(raw[v].y) : 0u;
+    key[4 * v + 2] = n > 2 ? score_key(raw[v].z) : 0u;
+    key[4 * v + 3] = n > 3 ? score_key(raw[v].w) : 0u;
+  }
+  auto page_of = [&](int j) { return (j / 4) * 4 * kThreads + 4 * t + j % 4; };
+  if (c.force_recent > 0) {
+    // an always-selected page takes the largest key there is (above +inf), so it outranks every score
+    const int forced_from = P - min(c.force_recent, kb);
+#pragma unroll
+    for (int j = 0; j < kItems; ++j)
+      if (page_of(j) >= forced_from && page_of(j) < P) key[j] = kKeyForced;
+  }
 
-  // ---- 1. linear-bucket histogram between the row's smallest and largest finite score
-  uint32_t kmin = 0xffffffffu, kmax = 0u;
+  // The row's smallest and largest finite key, and a lower bound T0 of the k-th key: the smallest of the maxima of
+  // disjoint groups of keys, of which there are at least kb. Groups are the keys of 2^n threads, as many as leave
+  // enough groups; threads without a page do not count.
+  uint32_t kmin = 0xffffffffu, kmax = 0u, low = 0u;
 #pragma unroll
   for (int j = 0; j < kItems; ++j) {
-    if (j < nv && key[j] > kKeyNegInf && key[j] < kKeyPosInf) { kmin = min(kmin, key[j]); kmax = max(kmax, key[j]); }
+    const bool finite = key[j] > kKeyNegInf && key[j] < kKeyPosInf;
+    kmin = min(kmin, finite ? key[j] : 0xffffffffu);
+    kmax = max(kmax, finite ? key[j] : 0u);
+    low = max(low, key[j]);
+  }
+  {
+    const int busy = min(kThreads, (P + 3) / 4);  // threads with a page
+    auto merge = [&](int lanes, uint32_t other) { if (lanes * kb <= busy) low = max(low, other); };
+    merge(2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)low, kDppXor1, 0xf, 0xf, true));
+    merge(4, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)low, kDppXor2, 0xf, 0xf, true));
+    merge(8, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)low, kDppHalfMirror, 0xf, 0xf, true));
+    merge(16, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)low, kDppMirror, 0xf, 0xf, true));
+    if (kb > busy) low = 0u;
+    else if (t >= busy) low = 0xffffffffu;
   }
   kmin = wave_allreduce_minmax<false>(kmin);
   kmax = wave_allreduce_minmax<true>(kmax);
-  if (lane == 0) { wave_min[wave] = kmin; wave_max[wave] = kmax; }
-  for (int i = t; i < kBuckets; i += kThreads) hist[i] = 0;
-  if (t == 0) s_ncand = 0;
+  low = wave_allreduce_minmax<false>(low);
+  if (lane == 0) { sh.wave_min[wave] = kmin; sh.wave_max[wave] = kmax; sh.wave_low[wave] = low; }
+  for (int i = t; i < kBuckets + kBuckets / 4; i += kThreads) sh.hist[i] = 0;
+  if (t == 0) sh.ncand = 0;
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) { kmin = min(kmin, wave_min[w]); kmax = max(kmax, wave_max[w]); }
-  float lo = 0.f, scale = 0.f;
-  if (kmin < kmax) {  // at least two distinct finite scores
-    lo = ordered_to_float(kmin);
-    const float range = ordered_to_float(kmax) - lo;
-    if (range > 0.f && range < 3.0e38f) scale = (float)(kBuckets - 1) / range;
-    if (!(scale < 3.0e38f)) scale = 0.f;  // a denormal range: leave everything in one bucket
+  for (int w = 0; w < kWaves; ++w) {
+    kmin = min(kmin, sh.wave_min[w]); kmax = max(kmax, sh.wave_max[w]); low = min(low, sh.wave_low[w]);
   }
-  // the bucket of every key is kept in registers, unless the keys alone already take most of them
-  constexpr bool kKeepBuckets = kItems <= 32;
-  int bucket_reg[kKeepBuckets ? kItems : 1];
-#pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    if (j < nv) {
-      const int bk = linear_bucket(key[j], lo, scale, kBuckets);
-      atomicAdd(&hist[bk], 1);
-      if constexpr (kKeepBuckets) bucket_reg[j] = bk;
-    } else if constexpr (kKeepBuckets) {
-      bucket_reg[j] = 0;
-    }
-  }
-  auto bucket = [&](int j) {
-    if constexpr (kKeepBuckets) return bucket_reg[j];
-    else return linear_bucket(key[j], lo, scale, kBuckets);
-  };
-  __syncthreads();
-  {  // suffix scan over the buckets: thread t owns buckets kBuckets-1-2t and kBuckets-2-2t
-    const int c_hi = hist[kBuckets - 1 - 2 * t], c_lo = hist[kBuckets - 2 - 2 * t];
-    int above = (int)block_exclusive_scan<kThreads>((unsigned long long)(c_hi + c_lo), wave_tot);
-    if (above < kb && kb <= above + c_hi) { s_bucket = kBuckets - 1 - 2 * t; s_need = kb - above; }
-    above += c_hi;
-    if (above < kb && kb <= above + c_lo) { s_bucket = kBuckets - 2 - 2 * t; s_need = kb - above; }
-  }
-  __syncthreads();
-  const int bstar = s_bucket;
-  int need = s_need;  // how many of the boundary bucket's keys are selected
-  const int ncand = hist[bstar];
+  const uint32_t T0 = max(low, 1u);
+  if (T0 > kKeyNegInf && T0 < kKeyPosInf) kmin = T0;
+  const BucketMap map = bucket_map(kmin, kmax, kBuckets);
 
-  // ---- 2. exact threshold inside the boundary bucket: key T and how many keys equal to T to take
-  uint32_t T;
-  if (ncand <= kMaxRank) {
+  if constexpr (kCompact) {
+    // many keys per thread: the few that are not below T0 are gathered, in page order, and dealt out again
+    int place[kVecs];
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-      if (j < nv && bucket(j) == bstar) {
-        const int slot = atomicAdd(&s_ncand, 1);
-        cand_key[slot] = key[j];
-        cand_idx[slot] = first + j;
-      }
+    for (int v = 0; v < kVecs; ++v) {
+      int n = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) n += __popcll(__ballot(key[4 * v + i] >= T0));
+      if (lane == 0) sh.sure_cnt[v * kWaves + wave] = n;
     }
     __syncthreads();
-    if (t < ncand) {
-      const uint32_t mk = cand_key[t];
-      const int mi = cand_idx[t];
-      int rank = 0, greater = 0;
-      for (int j = 0; j < ncand; ++j) {
-        const uint32_t k = cand_key[j];
-        greater += k > mk;
-        rank += (k > mk) || (k == mk && cand_idx[j] < mi);
-      }
-      if (rank == need - 1) { s_prefix = mk; s_need = need - greater; }
-    }
-    __syncthreads();
-    T = s_prefix;
-    need = s_need;
-  } else {
-    T = radix_threshold<kThreads, kItems>(
-        kItems, [&](int j) { return key[j]; }, [&](int j) { return j < nv && bucket(j) == bstar; }, need, hist,
-        &s_prefix, &s_need);
-  }
-
-  // ---- 3. index-ordered compaction. "sure": above the boundary; "tie": equal to the k-th key.
-  uint32_t sure = 0, tie = 0;
+    const int total = wave_prefixes<kVecs, kWaves>(sh.sure_cnt, wave, place);
+    if (total <= kDense * kThreads) {  // uniform
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    if (j < nv) {
-      const bool in_b = bucket(j) == bstar;
-      sure += (bucket(j) > bstar) || (in_b && key[j] > T);
-      tie += in_b && key[j] == T;
-    }
-  }
-  const unsigned long long before =
-      block_exclusive_scan<kThreads>((unsigned long long)sure | ((unsigned long long)tie << 32), wave_tot);
-  int sure_b = (int)(before & 0xffffffffull), tie_b = (int)(before >> 32);
+      for (int v = 0; v < kVecs; ++v) {
+        int at = place[v];
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    if (j < nv) {
-      const bool in_b = bucket(j) == bstar;
-      if ((bucket(j) > bstar) || (in_b && key[j] > T)) {
-        out[sure_b + min(tie_b, need)] = first + j;
-        ++sure_b;
-      } else if (in_b && key[j] == T) {
-        if (tie_b < need) out[sure_b + tie_b] = first + j;
-        ++tie_b;
+        for (int i = 0; i < 4; ++i) at = lanes_before(__ballot(key[4 * v + i] >= T0), at);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (key[4 * v + i] >= T0) kept[at++] = make_uint2(key[4 * v + i], (uint32_t)page_of(4 * v + i));
       }
+      __syncthreads();
+      uint32_t dkey[kDense];
+      int dpage[kDense];
+#pragma unroll
+      for (int j = 0; j < kDense; ++j) {
+        const int at = j * kThreads + t;
+        const uint2 e = at < total ? kept[at] : make_uint2(0u, 0x7fffffffu);
+        dkey[j] = e.x;
+        dpage[j] = (int)e.y;
+      }
+      select_keys<kThreads, kDense, 1>(dkey, [&](int j) { return dpage[j]; }, T0, map, kb, out, sh);
+      return;
     }
   }
+  select_keys<kThreads, kVecs, 4>(key, page_of, T0, map, kb, out, sh);
 }
 
-// Rows too long for registers: the same three steps as above, but every pass re-reads the scores (they
-// stay in L2). Thread t owns the pages t, t + threads, t + 2*threads, ... so that every read of the row is
-// coalesced, and reads are requested eight at a time. The compaction walks the row in blocks of `threads`
-// consecutive pages and places each selected page by a ballot prefix inside its wave, the wave totals of
-// the block (LDS) and the running totals of the blocks before it, which keeps the output in ascending page
-// order and takes keys tied with the k-th from the lowest page upward.
-template <int kThreads>
-__global__ __launch_bounds__(kThreads) void topk_select_long_kernel(CacheView c, const float* __restrict__ scores,
-                                                                    int score_stride, int top_k,
-                                                                    int32_t* __restrict__ sel_pages,
-                                                                    int32_t* __restrict__ sel_count) {
-  constexpr int kWaves = kThreads / kWave;
-  constexpr int kBuckets = 2 * kThreads;
-  constexpr int kMaxRank = kThreads < kMaxRankCandidates ? kThreads : kMaxRankCandidates;
-  __shared__ int hist[kBuckets];
-  __shared__ unsigned long long wave_tot[kWaves];
-  __shared__ uint32_t wave_min[kWaves], wave_max[kWaves];
-  __shared__ uint32_t cand_key[kMaxRank];
-  __shared__ int cand_idx[kMaxRank];
-  __shared__ int wave_gt[2][kWaves], wave_eq[2][kWaves];
-  __shared__ int s_bucket, s_need, s_ncand;
-  __shared__ uint32_t s_prefix;
-
-  const int row = blockIdx.x;
-  const int b = row / c.Hkv;
-  const int N = c.seq_lens[b];
-  const int P = min((N + c.S - 1) / c.S, c.max_pages_hint);
-  const int kb = min(top_k, P);
+// Selection by re-reading the row in every pass (it stays in L2): histogram between the row's smallest and largest
+// finite key, candidates, compaction. Thread t owns the pages t, t + threads, t + 2*threads, ... so that every read of the
+// row is coalesced, eight reads at a time. The compaction walks the row in blocks of `threads` consecutive pages and
+// places each selected page by a ballot prefix inside its wave, the wave totals of the block (LDS) and the running
+// totals of the blocks before it, which keeps the output in ascending page order and takes keys tied with the k-th from
+// the lowest page upward. The histogram in `sh` is zero and sh.ncand is 0. All threads call it.
+template <int kThreads, typename KeyOf>
+__device__ __forceinline__ void select_reread(KeyOf key_of, int P, int kb, BucketMap map, int32_t* out,
+                                              SelectShared<kThreads>& sh) {
+  using Sh = SelectShared<kThreads>;
+  constexpr int kWaves = Sh::kWaves, kBuckets = Sh::kBuckets, kMaxRank = Sh::kMaxRank;
   const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
-  int32_t* out = sel_pages + (int64_t)row * top_k;
-  const float* srow = scores + (int64_t)row * score_stride;
-
-  for (int i = kb + t; i < top_k; i += kThreads) out[i] = -1;
-  if (t == 0) sel_count[row] = kb;
-  if (kb == P) {
-    for (int i = t; i < P; i += kThreads) out[i] = i;
-    return;
-  }
-  const int forced_from = P - min(c.force_recent, kb);  // pages from here on are always selected
-  auto key_of = [&](int page) { return page >= forced_from ? kKeyForced : float_to_ordered(srow[page]); };
   const int ipt = (P + kThreads - 1) / kThreads;  // strided items per thread; the last ones may fall past P
   auto for_each_key = [&](auto f) {               // f(page, key) for every page this thread owns
     for (int j0 = 0; j0 < ipt; j0 += 8) {
@@ -348,74 +529,47 @@ __global__ __launch_bounds__(kThreads) void topk_select_long_kernel(CacheView c,
     }
   };
 
-  // ---- 1. linear-bucket histogram between the row's smallest and largest finite score
-  uint32_t kmin = 0xffffffffu, kmax = 0u;
-  for_each_key([&](int, uint32_t k) {
-    if (k > kKeyNegInf && k < kKeyPosInf) { kmin = min(kmin, k); kmax = max(kmax, k); }
-  });
-  kmin = wave_allreduce_minmax<false>(kmin);
-  kmax = wave_allreduce_minmax<true>(kmax);
-  if (lane == 0) { wave_min[wave] = kmin; wave_max[wave] = kmax; }
-  for (int i = t; i < kBuckets; i += kThreads) hist[i] = 0;
-  if (t == 0) s_ncand = 0;
+  // ---- 1. histogram
+  auto bucket_of = [&](uint32_t k) { return linear_bucket(k, map.lo, map.scale, kBuckets); };
+  if (map.scale == 0.f) for_each_key([&](int, uint32_t k) { add_one(sh.hist, Sh::slot(bucket_of(k))); });
+  else for_each_key([&](int, uint32_t k) { atomicAdd(&sh.hist[Sh::slot(bucket_of(k))], 1); });
   __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) { kmin = min(kmin, wave_min[w]); kmax = max(kmax, wave_max[w]); }
-  float lo = 0.f, scale = 0.f;
-  if (kmin < kmax) {  // at least two distinct finite scores
-    lo = ordered_to_float(kmin);
-    const float range = ordered_to_float(kmax) - lo;
-    if (range > 0.f && range < 3.0e38f) scale = (float)(kBuckets - 1) / range;
-    if (!(scale < 3.0e38f)) scale = 0.f;  // a denormal range: leave everything in one bucket
-  }
-  auto bucket_of = [&](uint32_t k) { return linear_bucket(k, lo, scale, kBuckets); };
-  for_each_key([&](int, uint32_t k) { atomicAdd(&hist[bucket_of(k)], 1); });
-  __syncthreads();
-  {  // suffix scan over the buckets: thread t owns buckets kBuckets-1-2t and kBuckets-2-2t
-    const int c_hi = hist[kBuckets - 1 - 2 * t], c_lo = hist[kBuckets - 2 - 2 * t];
-    int above = (int)block_exclusive_scan<kThreads>((unsigned long long)(c_hi + c_lo), wave_tot);
-    if (above < kb && kb <= above + c_hi) { s_bucket = kBuckets - 1 - 2 * t; s_need = kb - above; }
-    above += c_hi;
-    if (above < kb && kb <= above + c_lo) { s_bucket = kBuckets - 2 - 2 * t; s_need = kb - above; }
-  }
-  __syncthreads();
-  const int bstar = s_bucket;
-  int need = s_need;  // how many of the boundary bucket's keys are selected
-  const int ncand = hist[bstar];
+  int bstar, need, ncand;  // need: how many of the boundary bucket's ncand keys are selected
+  boundary_bucket<kThreads>(sh, kb, bstar, need, ncand);
 
   // ---- 2. exact threshold inside the boundary bucket: key T and how many keys equal to T to take
   uint32_t T;
   if (ncand <= kMaxRank) {
     for_each_key([&](int page, uint32_t k) {
       if (bucket_of(k) == bstar) {
-        const int slot = atomicAdd(&s_ncand, 1);
-        cand_key[slot] = k;
-        cand_idx[slot] = page;
+        const int at = atomicAdd(&sh.ncand, 1);
+        sh.cand_key[at] = k;
+        sh.cand_page[at] = page;
       }
     });
     __syncthreads();
     if (t < ncand) {
-      const uint32_t mk = cand_key[t];
-      const int mi = cand_idx[t];
+      const uint32_t mk = sh.cand_key[t];
+      const int mi = sh.cand_page[t];
       int rank = 0, greater = 0;
       for (int j = 0; j < ncand; ++j) {
-        const uint32_t k = cand_key[j];
+        const uint32_t k = sh.cand_key[j];
         greater += k > mk;
-        rank += (k > mk) || (k == mk && cand_idx[j] < mi);
+        rank += (k > mk) || (k == mk && sh.cand_page[j] < mi);
       }
-      if (rank == need - 1) { s_prefix = mk; s_need = need - greater; }
+      if (rank == need - 1) { sh.prefix = mk; sh.need = need - greater; }
     }
     __syncthreads();
-    T = s_prefix;
-    need = s_need;
+    T = sh.prefix;
+    need = sh.need;
   } else {
     T = radix_threshold<kThreads, 0>(
         ipt, [&](int j) { return key_of(j * kThreads + t); },
-        [&](int j) { return j * kThreads + t < P && bucket_of(key_of(j * kThreads + t)) == bstar; }, need, hist,
-        &s_prefix, &s_need);
+        [&](int j) { return j * kThreads + t < P && bucket_of(key_of(j * kThreads + t)) == bstar; }, need, sh.hist,
+        &sh.prefix, &sh.need);
   }
 
-  // ---- 3. compaction in page order. "gt": above the boundary; "eq": equal to the k-th key.
+  // ---- 3. compaction in page order. "gt": above the k-th key; "eq": equal to it.
   int gt_run = 0, eq_run = 0;  // such pages in the blocks already walked
   constexpr int kAhead = 8;    // blocks whose keys are read together, ahead of the barriers that walk them
   for (int base0 = 0, it = 0; base0 < P; base0 += kAhead * kThreads) {
@@ -429,17 +583,17 @@ __global__ __launch_bounds__(kThreads) void topk_select_long_kernel(CacheView c,
     for (int u = 0; u < kAhead; ++u, ++it) {
       const int page = base0 + u * kThreads + t;
       if (base0 + u * kThreads >= P) break;  // uniform
-      const int bk = page < P ? bucket_of(kk[u]) : -1;
-      const bool gt = bk > bstar || (bk == bstar && kk[u] > T), eq = bk == bstar && kk[u] == T;
+      const bool gt = page < P && kk[u] > T, eq = page < P && kk[u] == T;
       const unsigned long long bg = __ballot(gt), be = __ballot(eq);
-      const unsigned long long below = (1ull << lane) - 1ull;
-      if (lane == 0) { wave_gt[it & 1][wave] = __popcll(bg); wave_eq[it & 1][wave] = __popcll(be); }
+      int* wave_gt = sh.sure_cnt + (it & 1) * kWaves;
+      int* wave_eq = sh.tie_cnt + (it & 1) * kWaves;
+      if (lane == 0) { wave_gt[wave] = __popcll(bg); wave_eq[wave] = __popcll(be); }
       __syncthreads();  // the buffers alternate, so one barrier per block is enough
-      int gt_before = gt_run + __popcll(bg & below), eq_before = eq_run + __popcll(be & below);
+      int gt_before = lanes_before(bg, gt_run), eq_before = lanes_before(be, eq_run);
       int gt_block = 0, eq_block = 0;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) {
-        const int g = wave_gt[it & 1][w], e = wave_eq[it & 1][w];
+        const int g = wave_gt[w], e = wave_eq[w];
         gt_before += w < wave ? g : 0;
         eq_before += w < wave ? e : 0;
         gt_block += g;
@@ -453,10 +607,165 @@ __global__ __launch_bounds__(kThreads) void topk_select_long_kernel(CacheView c,
   }
 }
 
-template <int kThreads, int kItems>
+// Rows of more keys than the registers hold: the row is read twice in chunks of 32 keys per thread, once for the bound
+// T0 and the extremes and once to gather the keys that are not below T0 in the LDS, in page order; the selection then
+// runs on those. Rows that leave too many (more than kDense * kThreads: a very large k, or masses of equal scores) are
+// selected by re-reading.
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void topk_select_long_kernel(CacheView c, const float* __restrict__ scores,
+                                                                    int score_stride, int top_k,
+                                                                    int32_t* __restrict__ sel_pages,
+                                                                    int32_t* __restrict__ sel_count) {
+  using Sh = SelectShared<kThreads>;
+  constexpr int kWaves = Sh::kWaves, kBuckets = Sh::kBuckets;
+  constexpr int kVecs = 8, kUnitVecs = 4;      // 16-byte loads per thread and chunk; units of the groups for T0
+  constexpr int kChunk = kVecs * 4 * kThreads, kUnit = kUnitVecs * 4 * kThreads;
+  constexpr int kDense = 16;
+  __shared__ Sh sh;
+  __shared__ uint2 kept[kDense * kThreads];
+
+  const int row = blockIdx.x;
+  const int b = row / c.Hkv;
+  const int N = c.seq_lens[b];
+  const int P = min((N + c.S - 1) / c.S, c.max_pages_hint);
+  const int kb = min(top_k, P);
+  const int t = threadIdx.x, lane = t % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  int32_t* out = sel_pages + (int64_t)row * top_k;
+  const float* srow = scores + (int64_t)row * score_stride;
+
+  for (int i = kb + t; i < top_k; i += kThreads) out[i] = -1;
+  if (t == 0) sel_count[row] = kb;
+  if (kb == P) {
+    for (int i = t; i < P; i += kThreads) out[i] = i;
+    return;
+  }
+  const int forced_from = P - min(c.force_recent, kb);  // pages from here on are always selected
+
+  uint32_t key[4 * kVecs];
+  auto page_of = [&](int chunk, int j) { return chunk * kChunk + (j / 4) * 4 * kThreads + 4 * t + j % 4; };
+  auto load_chunk = [&](int chunk) {  // keys of the chunk; 0 past the row's end
+    float4 raw[kVecs];
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) {
+      const int p = page_of(chunk, 4 * v);
+      raw[v] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (p < P) raw[v] = *reinterpret_cast<const float4*>(srow + p);  // the row is padded to a multiple of 4
+    }
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) {
+      const int n = P - page_of(chunk, 4 * v);
+      key[4 * v] = n > 0 ? score_key(raw[v].x) : 0u;
+      key[4 * v + 1] = n > 1 ? score_key(raw[v].y) : 0u;
+      key[4 * v + 2] = n > 2 ? score_key(raw[v].z) : 0u;
+      key[4 * v + 3] = n > 3 ? score_key(raw[v].w) : 0u;
+    }
+    if ((chunk + 1) * kChunk > forced_from) {
+#pragma unroll
+      for (int j = 0; j < 4 * kVecs; ++j)
+        if (page_of(chunk, j) >= forced_from && page_of(chunk, j) < P) key[j] = kKeyForced;
+    }
+  };
+  const int chunks = (P + kChunk - 1) / kChunk;
+
+  // Groups for T0 (see the register kernel): a thread's keys in `per_group` consecutive units, `groups` of them per
+  // thread, the last one with all that follows; with one group per thread, those of 2^n threads together.
+  const int units = P / kUnit, groups = units * kThreads >= kb ? (kb + kThreads - 1) / kThreads : 0;
+  const int per_group = groups > 0 ? units / groups : 0;
+  uint32_t kmin = 0xffffffffu, kmax = 0u, low = 0xffffffffu, group_max = 0u;
+  for (int ch = 0; ch < chunks; ++ch) {
+    load_chunk(ch);
+#pragma unroll
+    for (int u = 0; u < kVecs / kUnitVecs; ++u) {
+      const int unit = ch * (kVecs / kUnitVecs) + u;
+      if (unit > 0 && per_group > 0 && unit % per_group == 0 && unit / per_group < groups) {
+        low = min(low, group_max);
+        group_max = 0u;
+      }
+#pragma unroll
+      for (int i = 0; i < 4 * kUnitVecs; ++i) {
+        const uint32_t k = key[u * 4 * kUnitVecs + i];
+        const bool finite = k > kKeyNegInf && k < kKeyPosInf;
+        kmin = min(kmin, finite ? k : 0xffffffffu);
+        kmax = max(kmax, finite ? k : 0u);
+        group_max = max(group_max, k);
+      }
+    }
+  }
+  {
+    auto merge = [&](int lanes, uint32_t other) { if (lanes * kb <= kThreads) group_max = max(group_max, other); };
+    merge(2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)group_max, kDppXor1, 0xf, 0xf, true));
+    merge(4, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)group_max, kDppXor2, 0xf, 0xf, true));
+    merge(8, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)group_max, kDppHalfMirror, 0xf, 0xf, true));
+    merge(16, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)group_max, kDppMirror, 0xf, 0xf, true));
+    low = groups > 0 ? min(low, group_max) : 0u;
+  }
+  kmin = wave_allreduce_minmax<false>(kmin);
+  kmax = wave_allreduce_minmax<true>(kmax);
+  low = wave_allreduce_minmax<false>(low);
+  if (lane == 0) { sh.wave_min[wave] = kmin; sh.wave_max[wave] = kmax; sh.wave_low[wave] = low; }
+  for (int i = t; i < kBuckets + kBuckets / 4; i += kThreads) sh.hist[i] = 0;
+  if (t == 0) sh.ncand = 0;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    kmin = min(kmin, sh.wave_min[w]); kmax = max(kmax, sh.wave_max[w]); low = min(low, sh.wave_low[w]);
+  }
+  const uint32_t T0 = max(low, 1u);
+
+  int total = groups > 0 ? 0 : kDense * kThreads + 1;  // keys kept so far
+  for (int ch = 0; ch < chunks && total <= kDense * kThreads; ++ch) {  // uniform
+    load_chunk(ch);
+    int* counts = ch % 2 ? sh.tie_cnt : sh.sure_cnt;  // alternating, so one barrier per chunk is enough
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) {
+      int n = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) n += __popcll(__ballot(key[4 * v + i] >= T0));
+      if (lane == 0) counts[v * kWaves + wave] = n;
+    }
+    __syncthreads();
+    int place[kVecs];
+    const int here = wave_prefixes<kVecs, kWaves>(counts, wave, place);
+    if (total + here <= kDense * kThreads) {
+#pragma unroll
+      for (int v = 0; v < kVecs; ++v) {
+        int at = total + place[v];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) at = lanes_before(__ballot(key[4 * v + i] >= T0), at);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (key[4 * v + i] >= T0) kept[at++] = make_uint2(key[4 * v + i], (uint32_t)page_of(ch, 4 * v + i));
+      }
+    }
+    total += here;
+  }
+  __syncthreads();
+  if (total > kDense * kThreads) {
+    auto key_of = [&](int page) { return page >= forced_from ? kKeyForced : score_key(srow[page]); };
+    select_reread<kThreads>(key_of, P, kb, bucket_map(kmin, kmax, kBuckets), out, sh);
+    return;
+  }
+  uint32_t dkey[kDense];
+  int dpage[kDense];
+#pragma unroll
+  for (int j = 0; j < kDense; ++j) {
+    const int at = j * kThreads + t;
+    const uint2 e = at < total ? kept[at] : make_uint2(0u, 0x7fffffffu);
+    dkey[j] = e.x;
+    dpage[j] = (int)e.y;
+  }
+  if (T0 > kKeyNegInf && T0 < kKeyPosInf) kmin = T0;
+  select_keys<kThreads, kDense, 1>(dkey, [&](int j) { return dpage[j]; }, T0, bucket_map(kmin, kmax, kBuckets), kb, out, sh);
+}
+
+template <int kN>
+using Int = std::integral_constant<int, kN>;
+
+template <int kThreads, int kVecs>
 hipError_t launch_t(const CacheView& c, const float* scores, int stride, int top_k, int32_t* sel, int32_t* cnt,
                     hipStream_t st) {
-  topk_select_kernel<kThreads, kItems><<<dim3(c.B * c.Hkv), dim3(kThreads), 0, st>>>(c, scores, stride, top_k, sel, cnt);
+  topk_select_kernel<kThreads, kVecs><<<dim3(c.B * c.Hkv), dim3(kThreads), 0, st>>>(c, scores, stride, top_k, sel, cnt);
   return hipGetLastError();
 }
 
@@ -465,14 +774,28 @@ hipError_t launch_t(const CacheView& c, const float* scores, int stride, int top
 hipError_t launch_select(const CacheView& c, const float* d_scores, int score_stride, int top_k,
                          int32_t* d_sel_pages, int32_t* d_sel_count, hipStream_t stream) {
   const int P = c.max_pages_hint;
-  if (P <= 256) return launch_t<256, 1>(c, d_scores, score_stride, top_k, d_sel_pages, d_sel_count, stream);
-  if (P <= 1024) return launch_t<256, 4>(c, d_scores, score_stride, top_k, d_sel_pages, d_sel_count, stream);
-  if (P <= 2048) return launch_t<512, 4>(c, d_scores, score_stride, top_k, d_sel_pages, d_sel_count, stream);
-  if (P <= 4096) return launch_t<1024, 4>(c, d_scores, score_stride, top_k, d_sel_pages, d_sel_count, stream);
-  if (P <= 8192) return launch_t<1024, 8>(c, d_scores, score_stride, top_k, d_sel_pages, d_sel_count, stream);
-  if (P <= 16384) return launch_t<1024, 16>(c, d_scores, score_stride, top_k, d_sel_pages, d_sel_count, stream);
-  if (P <= 32768) return launch_t<1024, 32>(c, d_scores, score_stride, top_k, d_sel_pages, d_sel_count, stream);
-  if (P <= 65536) return launch_t<1024, 64>(c, d_scores, score_stride, top_k, d_sel_pages, d_sel_count, stream);
+  auto go = [&](auto threads, auto vecs) {
+    return launch_t<decltype(threads)::value, decltype(vecs)::value>(c, d_scores, score_stride, top_k, d_sel_pages,
+                                                                     d_sel_count, stream);
+  };
+  const int rows = c.B * c.Hkv;
+  // The smallest workgroup whose registers hold the row, unless a larger one measured faster; kernel us on rows of
+  // planted normal scores (rows x pages, k):
+  //   640 x 4096, 64: 9.5 with 512 threads, 19 with 1024 (two workgroups of 1024 per compute unit: a second round)
+  //   8 x 2048, 128: 5.4 with 256 threads, 4.9 with 512; 512 x 2048, 64: 7.0 and 7.6
+  //   128 x 8192, 256: 8.4 with 512 threads, 9.2 with 1024; with k = 1024 10.8 and 10.0, but at 512 rows 14.2 and 18.5
+  //   16 x 16384, 256: 10.3 with 512 threads, 11.7 with 1024; with k = 512 17 and 12.2, as a group for T0 is then a
+  //   single thread's keys and more of them are left
+  if (P <= 256) return go(Int<64>(), Int<1>());
+  if (P <= 1024) return go(Int<256>(), Int<1>());
+  if (P <= 2048) return rows > 256 ? go(Int<256>(), Int<2>()) : go(Int<512>(), Int<1>());
+  if (P <= 4096) return go(Int<512>(), Int<2>());
+  if (P <= 8192) return rows <= 256 && top_k > 512 ? go(Int<1024>(), Int<2>()) : go(Int<512>(), Int<4>());
+  if (P <= 16384) return top_k <= 256 ? go(Int<512>(), Int<8>()) : go(Int<1024>(), Int<4>());
+  if (P <= 32768) return go(Int<1024>(), Int<8>());
+  // Beyond that the long kernel (8 x 62501, 1024: 30 us; 48 with all keys in registers), but it re-reads rows that leave
+  // too many keys above T0, which at these lengths is the rule from about k = 2000 on (8 x 65536, 2048: 117 us against 48)
+  if (P <= 65536 && top_k > 1024) return go(Int<1024>(), Int<16>());
   topk_select_long_kernel<1024><<<dim3(c.B * c.Hkv), dim3(1024), 0, stream>>>(c, d_scores, score_stride, top_k,
                                                                               d_sel_pages, d_sel_count);
   return hipGetLastError();

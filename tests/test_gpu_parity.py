@@ -242,6 +242,34 @@ def test_select_row_length_boundaries(gpu_lib, P):
     _crafted_select(P, P - 1, SCORE_MAKERS["normal"])
 
 
+@pytest.mark.parametrize("kind", ["normal", "heavy_ties", "two_values", "descending"])
+@pytest.mark.parametrize("P,top_k", [(700, 300), (6000, 600), (12000, 100), (12000, 300), (30000, 1000), (30000, 1200),
+                                     (60000, 1024), (60000, 1025), (60000, 3000), (65537, 3000), (140000, 2500)])
+def test_select_kernel_variants(gpu_lib, kind, P, top_k):
+    """Both sides of every rule on row length and k, with rows that leave few keys above the lower bound (normal,
+    descending), too many for the gathered list (two_values) and 64 to 512 or more candidates in the boundary bucket."""
+    _crafted_select(P, top_k, SCORE_MAKERS[kind])
+
+
+@pytest.mark.parametrize("B,P,top_k", [(33, 1500, 40), (33, 2048, 300), (33, 8000, 600), (80, 4096, 64)])
+def test_select_many_rows(gpu_lib, B, P, top_k):
+    """More than 256 rows (other workgroup sizes), ragged lengths, duplicated scores."""
+    wl = W.build("rows", 11, dtype=torch.bfloat16, B=B, H=8, Hkv=8, D=64, S=8, seq_lens=[8] * B, top_k=top_k,
+                 key_mode="iid").to(DEV)
+    lens = torch.linspace(0, 8 * P, B).int()
+    wl.page_table, wl.seq_lens = torch.zeros((B, P), dtype=torch.int32, device=DEV), lens.to(DEV)
+    sess = DecodeSession(wl, max_seq_len_hint=8 * P, min_seq_len_hint=0)
+    g = torch.Generator().manual_seed(B + P)
+    scores = (torch.randn((B, 8, (P + 3) // 4 * 4), generator=g) * 50).round() / 8
+    sess.select_topk(scores.to(DEV))
+    sel, cnt = sess.sel_pages.cpu(), sess.sel_count.cpu()
+    for b in range(B):
+        pages = (int(lens[b]) + 7) // 8
+        kb = min(top_k, pages)
+        want = torch.sort(scores[b, :, :pages], dim=-1, descending=True, stable=True)[1][:, :kb].sort(-1)[0].int()
+        assert (cnt[b] == kb).all() and torch.equal(sel[b, :, :kb], want) and (sel[b, :, kb:] == -1).all(), f"sequence {b}"
+
+
 @pytest.mark.parametrize("kind", ["normal", "heavy_ties", "descending", "nan_and_inf", "all_equal"])
 @pytest.mark.parametrize("P,top_k", [(200, 16), (8192, 256), (40000, 64), (70001, 1000)])
 @pytest.mark.parametrize("n", [1, 3, "k", "k+5"])
