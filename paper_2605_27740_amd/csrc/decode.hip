@@ -2,25 +2,27 @@
 //   Eq. 5 of the paper when the list is the selected top-k set, Eq. 4 when it is every page.
 //
 // Split-K: the page list of a row is cut into chunks; one workgroup (4 waves) handles one chunk for all
-// G query heads of the KV head at once, so every K/V byte is read exactly once per step. Inside a wave
+// G query heads of the KV head at once, so every K/V byte is read exactly once per step. bf16 caches: see the
+// matrix-core kernel below. fp32 caches: inside a wave
 // each lane reads 16-byte chunks of K and V rows (a wave-wide load covers a contiguous 1 KiB of the
 // page), the q.k dot products are reduced across the D/vec lanes that share a token with DPP row
 // operations, and each group of lanes that shares a token row keeps its own online-softmax state, so
 // the inner loop has no cross-row communication. States are merged (log-sum-exp) across lane groups,
 // then across the 4 waves through LDS, and the chunk's partial (o, m, l) goes to the workspace; a
 // second small kernel merges the chunks of a row and writes the output in the cache dtype (a row with
-// a single chunk is written by the first kernel itself and the second is not launched).
+// a single chunk is written by the first kernel itself and the second is not launched). The merge stays a launch of its
+// own: done by a row's last workgroup behind an agent-scope release and acquire it costs 8 us more than the launch
+// (131K tokens, 128 rows), and with write-through stores instead of the release the step is no faster either.
 // Logits are kept in the log2 domain (q is pre-multiplied by sm_scale * log2 e) so exp is one v_exp_f32.
+#include <algorithm>
+
 #include "device_utils.hpp"
 #include "kernels.hpp"
 
 namespace unique {
 namespace {
 
-#ifndef UNIQUE_DEC_WAVES
-#define UNIQUE_DEC_WAVES 4
-#endif
-constexpr int kDecWaves = UNIQUE_DEC_WAVES;
+constexpr int kDecWaves = 4;
 constexpr float kNegBig = -1.0e30f;  // finite stand-in for "no logit seen yet"
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -238,18 +240,22 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
 }
 
 
-// ---- bf16 caches: the q.k products of a tile of 16 tokens run on the matrix cores ----
-// v_mfma_f32_16x16x32_bf16 computes D[m][n] += sum_k A[m][k] B[k][n] with A rows m = lane % 16, B columns
-// n = lane % 16, each lane supplying 8 consecutive k of its 16-lane group, and the result held as
-// D[4*(lane/16) + i][lane % 16] in register i. With A = the G query heads (rows >= G are zero) and
-// B = the keys of 16 token slots, lanes 0..15 end up with the logits of one token each for heads 0..3
-// (lanes 16..31 for heads 4..7). A lane reads, for MFMA step s, the 16-byte chunk 4*s + lane/16 of
-// its token's key, so the contraction order inside a step is whatever the hardware pairs up -- the
-// same for A and B. Softmax runs on those lanes (one token per lane, tokens reduced across the 16
-// lanes with DPP), the probabilities go through 1 KiB of LDS per wave to the row layout in which V
-// was loaded (a lane owns a 16-byte chunk of a token's value), and the PV products stay on the
-// vector ALUs. This removes the unpack + FMA + lane-reduction work of the q.k stage, which made the
-// all-VALU kernel issue-bound (VALU busy 67 % on the dense stream).
+// ---- bf16 caches: both products of a tile of 16 tokens run on the matrix cores ----
+// v_mfma_f32_16x16x32_bf16 computes D[m][n] += sum_k A[m][k] B[k][n]: lane L supplies row m = L % 16 of A and column
+// n = L % 16 of B, 8 consecutive k of its 16-lane group L / 16 each, and holds D[4 * (L / 16) + i][L % 16] in register i;
+// v_mfma_f32_16x16x16_bf16 is the same with 4 consecutive k.
+// q.k: A = the keys of 16 token slots, B = the G query heads, repeated over the 16 columns. A lane reads, for step s, the
+// 16-byte chunk 4 * s + L / 16 of its token's key, so the contraction order inside a step is whatever the hardware pairs
+// up -- the same for A and B. Lane L ends up with the logits of tokens 4 * (L / 16) + i for head L % 16 % G.
+// p.V: those are the four k that lane L has to supply for row L % 16 of A, so the probabilities never leave their lane.
+// The probabilities stay fp32: p = hi + mid + lo, three bf16 numbers of 8 bits each, exactly; the columns of the q.k
+// product are G heads times the parts, so that lane L supplies part L % 16 / G of its head (with G = 8 only two parts fit,
+// the third is a second product into the rows of the first). The rows of the parts are summed at the end.
+// V is read so that lane L holds tokens 4 * (L / 16) + j, channels kVB * (L % 16) + e: the halves of the four tokens'
+// words are the B operand of channel e without any exchange between lanes.
+// On the vector ALUs the p.V product alone was 32 * G + 32 instructions per tile at D = 128, which made G = 8 issue-bound.
+// Kernel us before and now, with the chunks as they were: G = 8, 96 rows x 200 pages of 8 KB 43.3 / 36.0; G = 4,
+// 128 x 256 47.0 / 45.8, 256 x 64 pages of 16 KB 47.3 / 44.4 (6.05 TB/s), 640 x 64 pages of 4 KB 36.7 / 34.6.
 // Profiling build (-DUNIQUE_DEC_STAMPS, a second library next to the product one): every wave of the matrix-core
 // kernel records the 100 MHz wall clock at kernel entry, once its page ids are resolved, after its first tile, at
 // the end of its loop and after its stores, after every tile, and the compute unit it ran on, into a device array
@@ -277,14 +283,49 @@ __device__ unsigned long long g_dec_stamps[kStampWaves][kStampSlots];
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+
 __device__ __forceinline__ bf16x8_t as_bf16x8(const Raw16& r) {
   return __builtin_bit_cast(bf16x8_t, r.v);
 }
+// the low / the high halves of two words, `a` in the lower half of the result
+__device__ __forceinline__ uint32_t pack_lo(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+__device__ __forceinline__ s16x4_t as_s16x4(uint32_t a, uint32_t b) {
+  const u32x2_t v = {a, b};
+  return __builtin_bit_cast(s16x4_t, v);
+}
+// x without the lower 16 bits of its mantissa, i.e. the bf16 number in its upper half
+__device__ __forceinline__ float bf16_part(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
 
-#ifndef UNIQUE_DEC_BUFFERS
-#define UNIQUE_DEC_BUFFERS 2
-#endif
-constexpr int kDecBuffers = UNIQUE_DEC_BUFFERS;  // register tiles per wave: one being consumed, the others in flight
+// Reduction over the four 16-lane groups of a wave (lanes with the same L % 16); every lane gets the result.
+template <typename Op>
+__device__ __forceinline__ float rows_allreduce(float x, Op op) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// One value row chunk of kVB bf16 elements (16 or 8 bytes) as raw words.
+template <int kVB, bool kNT>
+__device__ __forceinline__ void load_v(const bf16_t* p, uint32_t (&out)[kVB / 2]) {
+  if constexpr (kVB == 8) {
+    const Raw16 r = load_raw_stream(p, kNT);
+    out[0] = r.v.x; out[1] = r.v.y; out[2] = r.v.z; out[3] = r.v.w;
+  } else {
+    const u32x2_t* src = reinterpret_cast<const u32x2_t*>(p);
+    u32x2_t r;
+    if constexpr (kNT) r = __builtin_nontemporal_load(src);
+    else r = *src;
+    out[0] = r.x; out[1] = r.y;
+  }
+}
+
+// Register tiles per wave: one being consumed, the others in flight. Three are no faster (128 x 256 pages 46.4 us
+// against 45.8, 256 x 64 pages of 16 KB 44.9 against 44.4).
+constexpr int kDecBuffers = 2;
 
 // kNT: K and V are read with non-temporal loads (a launch that streams more than the caches hold).
 template <int D, int S, int G, bool kNT>
@@ -294,12 +335,10 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_ke
     float* __restrict__ part_o, float* __restrict__ part_ml, bf16_t* __restrict__ out, float* __restrict__ lse_out) {
   constexpr int kVec = 8;
   constexpr int kTile = 16;                          // token slots per MFMA tile
-  constexpr int kSteps = D / 32;                     // MFMA steps (and K loads per lane) per tile
-  constexpr int kLanesPerTok = D / kVec;             // V row layout: lanes covering one value row
-  constexpr int kTokPerLoad = kWave / kLanesPerTok;
-  constexpr int kVLoads = kTile / kTokPerLoad;       // V loads per lane per tile
-  constexpr int kGPad = G < 4 ? 4 : G;               // floats per token slot in the LDS exchange
-  constexpr int kGroups = (G + 3) / 4;               // 16-lane groups that hold real heads
+  constexpr int kSteps = D / 32;                     // q.k steps (and K loads per lane) per tile
+  constexpr int kVB = D / 16;                        // channels of a value row per lane
+  constexpr int kSlots = G == 8 ? 16 : 3 * G;        // output rows in use: parts times heads
+  constexpr float kMaxGrowth = 6.f;                  // log2: how far logits may exceed the reference before it moves
   static_assert(G <= 8, "at most 8 query heads per KV head");
 
   const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
@@ -326,31 +365,25 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_ke
   }
   const int end = min(begin + pages_per_split, cnt);
 
-  const int kt = lane % 16, kg = lane / 16;                       // K / logit layout: token slot, lane group
-  const int vr_ = lane / kLanesPerTok, vc_ = lane % kLanesPerTok;  // V layout: token row inside a load, chunk
+  const int kt = lane % 16, kg = lane / 16;  // column (token slot of K, head and part of p, channel block of V); lane group
+  const int part = kt / G;                   // which part of its head's probabilities this lane supplies
 
-  __shared__ float p_lds[kDecWaves][kTile][kGPad];
-  __shared__ float sm_acc[kDecWaves][G][D];
+  __shared__ __attribute__((aligned(16))) float sm_acc[kDecWaves][kSlots][D];
   __shared__ float sm_m[kDecWaves][G], sm_l[kDecWaves][G];
 
-  // A operand: query head kt (zero rows beyond G), the 8 elements of chunk 4*s + kg
+  // B operand of q.k: query head kt % G, the 8 elements of chunk 4*s + kg
   const bf16_t* q_row = q + ((int64_t)b * c.H + hkv * G) * D;  // first query row of the group
   bf16x8_t qa[kSteps];
 #pragma unroll
-  for (int s = 0; s < kSteps; ++s) {
-    Raw16 r = zero_raw();
-    if (kt < G) r = load_raw(q_row + (int64_t)kt * D + (4 * s + kg) * kVec);
-    qa[s] = as_bf16x8(r);
-  }
+  for (int s = 0; s < kSteps; ++s) qa[s] = as_bf16x8(load_raw(q_row + (int64_t)(kt % G) * D + (4 * s + kg) * kVec));
 
-  float m[4], l[4];     // softmax state of heads 4*kg + i: m replicated over the 16 lanes, l a per-lane partial sum
+  // Softmax state of head kt % G. The reference m, the same in all lanes of a head, follows the largest logit but only
+  // moves when one exceeds it by more than kMaxGrowth: probabilities relative to it stay below 2^kMaxGrowth, and most
+  // tiles need neither the maximum over the lanes nor a rescaled output. l is this lane's part of the sum.
+  float m = kNegBig, l = 0.f;
+  f32x4_t acc[kVB];  // acc[e][i]: output row 4 * kg + i (head row % G), channel kVB * kt + e
 #pragma unroll
-  for (int i = 0; i < 4; ++i) { m[i] = kNegBig; l[i] = 0.f; }
-  float acc[G][kVec];   // this lane's chunk of the output rows, summed over its token rows
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int i = 0; i < kVec; ++i) acc[g][i] = 0.f;
+  for (int e = 0; e < kVB; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const bf16_t* kc = reinterpret_cast<const bf16_t*>(c.k_cache);
   const bf16_t* vc = reinterpret_cast<const bf16_t*>(c.v_cache);
@@ -399,70 +432,82 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_ke
     // zero) -- so the pipeline is straight-line code and every wait names exactly the requests that may stay in
     // flight; with predicated loads the compiler waited for ALL outstanding loads before each tile, prefetched
     // ones included. Slots beyond a sequence's length are still never read.
-    Raw16 kb[kDecBuffers][kSteps], vb[kDecBuffers][kVLoads];
-    bool kv[kDecBuffers];
-    auto issue = [&](int tile, Raw16(&kd)[kSteps], Raw16(&vd)[kVLoads], bool& kvalid) {
+    Raw16 kb[kDecBuffers][kSteps];
+    uint32_t vb[kDecBuffers][4][kVB / 2];
+    int kv[kDecBuffers];  // how many of the token slots 4 * kg .. 4 * kg + 3 hold a token (any value <= 0: none)
+    auto issue = [&](int tile, Raw16(&kd)[kSteps], uint32_t(&vd)[4][kVB / 2], int& valid) {
       int phys, ntok, tok;
       slot_info(tile, kt, phys, ntok, tok);
-      kvalid = tok < ntok;
-      const bf16_t* kp = kvalid ? kc + phys * page_stride + head_off + (int64_t)tok * D + kg * kVec : q_row;
+      const bf16_t* kp = tok < ntok ? kc + phys * page_stride + head_off + (int64_t)tok * D + kg * kVec : q_row;
 #pragma unroll
       for (int s = 0; s < kSteps; ++s) kd[s] = load_raw_stream(kp + s * (4 * kVec), kNT);
+      // four consecutive token slots lie in one page
+      slot_info(tile, 4 * kg, phys, ntok, tok);
+      const bf16_t* vp = vc + phys * page_stride + head_off + (int64_t)tok * D + kt * kVB;
+      valid = ntok - tok;
 #pragma unroll
-      for (int j = 0; j < kVLoads; ++j) {
-        slot_info(tile, j * kTokPerLoad + vr_, phys, ntok, tok);
-        const bf16_t* vp = tok < ntok ? vc + phys * page_stride + head_off + (int64_t)tok * D + vc_ * kVec : q_row;
-        vd[j] = load_raw_stream(vp, kNT);
-      }
+      for (int j = 0; j < 4; ++j) load_v<kVB, kNT>(j < valid ? vp + j * D : q_row, vd[j]);
     };
-    auto consume = [&](const Raw16(&kr)[kSteps], const Raw16(&vr)[kVLoads], bool kvalid_cur) {
+    auto consume = [&](const Raw16(&kr)[kSteps], const uint32_t(&vr)[4][kVB / 2], int valid) {
       f32x4_t sacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < kSteps; ++s)
-        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[s], as_bf16x8(kr[s]), sacc, 0, 0, 0);
+        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[s]), qa[s], sacc, 0, 0, 0);
 
-      float alpha[4], pr[4];
+      float x[4];  // logits of token slots 4 * kg + j relative to m, then the probabilities
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float sv = kvalid_cur ? sacc[i] * scale_log2 : -INFINITY;
-        const float mx = group_allreduce<16>(sv, OpMax());
-        const float mnew = fmaxf(m[i], mx);
-        alpha[i] = fast_exp2(m[i] - mnew);
-        m[i] = mnew;
-        pr[i] = fast_exp2(sv - mnew);
-        l[i] = fmaf(l[i], alpha[i], pr[i]);
-      }
-      // probabilities of the 16 token slots to LDS, [slot][head]
-      if (kg < kGroups) *reinterpret_cast<float4*>(&p_lds[wave][kt][4 * kg]) = make_float4(pr[0], pr[1], pr[2], pr[3]);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-      // rescale the running output by alpha of each head (held by lane group g / 4, register g % 4)
+      for (int j = 0; j < 4; ++j) x[j] = j < valid ? fmaf(sacc[j], scale_log2, -m) : -INFINITY;
+      const float top = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+      if (__any(top > kMaxGrowth)) {
+        // (from the logits themselves: m may still be kNegBig)
+        float t = -INFINITY;
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha[g % 4]), 16 * (g / 4)));
+        for (int j = 0; j < 4; ++j) t = j < valid ? fmaxf(t, sacc[j] * scale_log2) : t;
+        const float mnew = fmaxf(m, rows_allreduce(t, OpMax()));
+        const float alpha = fast_exp2(m - mnew);
+        m = mnew;
+        l *= alpha;
 #pragma unroll
-        for (int i = 0; i < kVec; ++i) acc[g][i] *= a;
-      }
+        for (int j = 0; j < 4; ++j) x[j] = j < valid ? fmaf(sacc[j], scale_log2, -m) : -INFINITY;
+        // output row 4 * kg + i belongs to head (4 * kg + i) % G, whose alpha lane (4 * kg + i) % G holds
+        float row_alpha[4];
 #pragma unroll
-      for (int j = 0; j < kVLoads; ++j) {
-        float vf[kVec];
-        unpack_bf16x8(vr[j].v, vf);
-        const int ts = j * kTokPerLoad + vr_;
-        float pg[kGPad];
-#pragma unroll
-        for (int g4 = 0; g4 < kGPad; g4 += 4) {
-          const float4 t = *reinterpret_cast<const float4*>(&p_lds[wave][ts][g4]);
-          pg[g4] = t.x; pg[g4 + 1] = t.y; pg[g4 + 2] = t.z; pg[g4 + 3] = t.w;
+        for (int i = 0; i < 4; ++i) {
+          auto lane_alpha = [&](int n) {
+            return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(alpha), n));
+          };
+          row_alpha[i] = lane_alpha(i % G);
+          if constexpr (G == 8) row_alpha[i] = kg % 2 ? lane_alpha(4 + i) : row_alpha[i];
         }
 #pragma unroll
-        for (int g = 0; g < G; ++g)
+        for (int e = 0; e < kVB; ++e)
 #pragma unroll
-          for (int i = 0; i < kVec; ++i) acc[g][i] = fmaf(pg[g], vf[i], acc[g][i]);
+          for (int i = 0; i < 4; ++i) acc[e][i] *= row_alpha[i];
       }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      uint32_t pa[4], pb[4];  // this lane's part of the probabilities; pb: the third part with G = 8
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float p = fast_exp2(x[j]);
+        l += p;
+        const float r1 = p - bf16_part(p), r2 = r1 - bf16_part(r1);
+        if constexpr (G == 8) {
+          pa[j] = __float_as_uint(part == 0 ? p : r1);
+          pb[j] = part == 0 ? __float_as_uint(r2) : 0u;
+        } else {
+          pa[j] = __float_as_uint(part == 0 ? p : (part == 1 ? r1 : r2));
+        }
+      }
+      const s16x4_t a0 = as_s16x4(pack_hi(pa[0], pa[1]), pack_hi(pa[2], pa[3]));
+      s16x4_t a1 = a0;
+      if constexpr (G == 8) a1 = as_s16x4(pack_hi(pb[0], pb[1]), pack_hi(pb[2], pb[3]));
+#pragma unroll
+      for (int e = 0; e < kVB; ++e) {
+        const int w = e / 2;
+        const s16x4_t v = e % 2 == 0 ? as_s16x4(pack_lo(vr[0][w], vr[1][w]), pack_lo(vr[2][w], vr[3][w]))
+                                     : as_s16x4(pack_hi(vr[0][w], vr[1][w]), pack_hi(vr[2][w], vr[3][w]));
+        acc[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, v, acc[e], 0, 0, 0);
+        if constexpr (G == 8) acc[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, v, acc[e], 0, 0, 0);
+      }
     };
 
 #pragma unroll
@@ -488,25 +533,18 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_ke
   }
 
   DEC_STAMP_AFTER(3, acc[0][0]);  // streaming loop done
-  // the wave's result: sum the per-lane l over the 16 token lanes, and acc over the token rows of the V layout
+  // the wave's result: the sum of the lanes' l, and the output rows as they are (the parts are added below)
+  l = rows_allreduce(l, OpSum());
 #pragma unroll
-  for (int i = 0; i < 4; ++i) l[i] = group_allreduce<16>(l[i], OpSum());
+  for (int i = 0; i < 4; ++i) {
+    if (4 * kg + i < kSlots) {
+      float* dst = &sm_acc[wave][4 * kg + i][kt * kVB];
 #pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int i = 0; i < kVec; ++i) acc[g][i] = cross_group_allreduce<kLanesPerTok>(acc[g][i], OpSum());
-
-  if (vr_ == 0) {
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int i = 0; i < kVec; ++i) sm_acc[wave][g][vc_ * kVec + i] = acc[g][i];
+      for (int e = 0; e < kVB; e += 4)
+        *reinterpret_cast<float4*>(dst + e) = make_float4(acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]);
+    }
   }
-  if (kt == 0 && kg < kGroups) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (4 * kg + i < G) { sm_m[wave][4 * kg + i] = m[i]; sm_l[wave][4 * kg + i] = l[i]; }
-  }
+  if (lane < G) { sm_m[wave][lane] = m; sm_l[wave][lane] = l; }
   __syncthreads();
   const int64_t pbase = (int64_t)row * num_splits + split;
   for (int idx = threadIdx.x; idx < G * D; idx += kDecWaves * kWave) {
@@ -518,7 +556,10 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_ke
 #pragma unroll
     for (int w = 0; w < kDecWaves; ++w) {
       const float sc = fast_exp2(sm_m[w][g] - M);
-      o = fmaf(sm_acc[w][g][d], sc, o);
+      float ow = sm_acc[w][g][d];
+#pragma unroll
+      for (int r = G + g; r < kSlots; r += G) ow += sm_acc[w][r][d];
+      o = fmaf(ow, sc, o);
       L = fmaf(sm_l[w][g], sc, L);
     }
     if (num_splits == 1) {
@@ -599,17 +640,34 @@ __global__ __launch_bounds__(kWave) void paged_decode_merge_kernel(CacheView c, 
   if (lse_out && lane == 0) lse_out[(int64_t)b * c.H + h] = any ? (M + log2f(L)) * kLn2 : -INFINITY;
 }
 
+// How a launch is cut into split-K chunks; computed on the host from bounds only.
+struct SplitPlan {
+  int32_t pages_per_split;  // list entries handled by one workgroup
+  int32_t num_splits;       // grid extent along the split axis (upper bound for every row)
+};
+
+// Partial results are sized for this many chunks per row, the most that any launch below cuts a list into.
+SplitPlan most_splits(int rows, int max_list_len) {
+  constexpr int kGroups = 512, kMaxPages = 256;
+  rows = std::max(rows, 1);
+  max_list_len = std::max(max_list_len, 1);
+  const int wanted = rows >= 256 ? 1 : (kGroups + rows - 1) / rows;
+  int pps = std::max((max_list_len + wanted - 1) / wanted, kDecWaves);  // at least one page per wave
+  // long lists are cut into many equal chunks so that ragged batches balance across the CUs
+  pps = (std::min(pps, kMaxPages) + kDecWaves - 1) / kDecWaves * kDecWaves;
+  return SplitPlan{pps, (max_list_len + pps - 1) / pps};
+}
+
 template <typename T, int D, int S, int G>
 hipError_t launch_t(const CacheView& cv, const void* q, const int32_t* sel, const int32_t* cnt, int sel_stride,
                     int max_list_len, float sm_scale, void* out, float* lse, float* partials, hipStream_t st) {
   CacheView c = cv;
   const int rows = c.B * c.Hkv;
   c.stream_nt = (int64_t)rows * max_list_len * S * D * 2 * (int64_t)sizeof(T) > kStreamNtBytes;
-  const SplitPlan plan = plan_splits(rows, max_list_len);
+  const SplitPlan plan = most_splits(rows, max_list_len);
   float* part_o = partials;
   float* part_ml = partials + (size_t)rows * plan.num_splits * G * D;
   const float scale_log2 = (sm_scale > 0.f ? sm_scale : 1.0f / sqrtf((float)D)) * kLog2e;
-#ifndef UNIQUE_DEC_NO_MFMA
   if constexpr (sizeof(T) == 2) {
     auto go = [&](auto kernel) {
       kernel<<<dim3(plan.num_splits, c.Hkv, c.B), dim3(kDecWaves * kWave), 0, st>>>(
@@ -619,7 +677,6 @@ hipError_t launch_t(const CacheView& cv, const void* q, const int32_t* sel, cons
     if (c.stream_nt) go(paged_decode_partial_mfma_kernel<D, S, G, true>);
     else go(paged_decode_partial_mfma_kernel<D, S, G, false>);
   } else
-#endif
     paged_decode_partial_kernel<T, D, S, G><<<dim3(plan.num_splits, c.Hkv, c.B), dim3(kDecWaves * kWave), 0, st>>>(
         c, reinterpret_cast<const T*>(q), sel, cnt, sel_stride, plan.pages_per_split, plan.num_splits, scale_log2,
         part_o, part_ml, reinterpret_cast<T*>(out), lse);
@@ -798,37 +855,9 @@ bool decode_supported(int dtype, int D, int S, int G) {
          (G == 1 || G == 2 || G == 4 || G == 8);
 }
 
-SplitPlan plan_splits(int rows, int max_list_len) {
-  // aim at ~2 workgroups (8 waves) per CU of a 256-CU device, with at least 1 page per wave; from 256 rows on one
-  // workgroup per row already fills the device, the row is not cut and no merge launch is needed (lists of up to
-  // UNIQUE_DEC_MAX_PPS pages)
-#ifndef UNIQUE_DEC_TARGET_GROUPS
-#define UNIQUE_DEC_TARGET_GROUPS 512
-#endif
-  constexpr int kTargetGroups = UNIQUE_DEC_TARGET_GROUPS;
-#ifndef UNIQUE_DEC_MAX_PPS
-#define UNIQUE_DEC_MAX_PPS 256
-#endif
-  if (rows < 1) rows = 1;
-  if (max_list_len < 1) max_list_len = 1;
-  const int wanted = rows >= 256 ? 1 : (kTargetGroups + rows - 1) / rows;
-  int pps = (max_list_len + wanted - 1) / wanted;
-#ifndef UNIQUE_DEC_MIN_PAGES_PER_WAVE
-#define UNIQUE_DEC_MIN_PAGES_PER_WAVE 1
-#endif
-  if (pps < UNIQUE_DEC_MIN_PAGES_PER_WAVE * kDecWaves) pps = UNIQUE_DEC_MIN_PAGES_PER_WAVE * kDecWaves;
-  // long lists are cut into many equal chunks so that ragged batches balance across the CUs
-  if (pps > UNIQUE_DEC_MAX_PPS) pps = UNIQUE_DEC_MAX_PPS;
-  pps = (pps + kDecWaves - 1) / kDecWaves * kDecWaves;
-  SplitPlan p;
-  p.pages_per_split = pps;
-  p.num_splits = (max_list_len + pps - 1) / pps;
-  return p;
-}
-
 size_t decode_partial_floats(const CacheView& c, int max_list_len) {
   const int rows = c.B * c.Hkv;
-  const SplitPlan plan = plan_splits(rows, max_list_len);
+  const SplitPlan plan = most_splits(rows, max_list_len);
   return (size_t)rows * plan.num_splits * (size_t)(c.H / c.Hkv) * (size_t)(c.D + 2);
 }
 

@@ -28,13 +28,6 @@ struct CacheView {
 // Launches that stream more than this many bytes bypass cache allocation (the Infinity Cache holds 256 MB).
 constexpr int64_t kStreamNtBytes = 96ll << 20;
 
-// How a decode launch is cut into split-K chunks; computed on the host from bounds only.
-struct SplitPlan {
-  int32_t pages_per_split;  // list entries handled by one workgroup
-  int32_t num_splits;       // grid extent along the split axis (upper bound for every row)
-};
-SplitPlan plan_splits(int rows, int max_list_len);
-
 constexpr int kStdBlockBytes = 128;     // bytes reserved after the means of a page record (fp32 stds + pad)
 constexpr int kScoreStrideAlign = 64;  // score rows in the workspace are padded to this many floats
 
