@@ -658,13 +658,42 @@ SplitPlan most_splits(int rows, int max_list_len) {
   return SplitPlan{pps, (max_list_len + pps - 1) / pps};
 }
 
+// A list that is known to be as long as max_list_len says for most rows (a top-k selection) is cut so that the compute
+// units get equal shares. What the busiest of the 256 units has to read bounds the launch: ceil(workgroups / 256) chunks;
+// it reads about 35 KB per us when all are busy, so that below 1.2 times the average share the memory bounds it, and the
+// merge launch that every cut row needs costs as much as 160 KB. Candidates are an uncut row and the largest number of
+// chunks that fills one to four workgroups per unit. Partial + merge kernel us, chosen against (chunks per row):
+//   96 rows x 200 pages of 8 KB: 5 chunks 29.2 + 4.1 (2: 31.4, 3: 40.5, 6: 35.8, uncut: 50.7 without a merge)
+//   128 x 256: 2 chunks 44.8 (3: 53.4, 4: 46.3, uncut 65.5); 16 x 1024: 16 chunks 24.6 (24: 29.3, 32: 25.6)
+//   160 x 32: uncut 10.3 (3: 10.8 + 4.2); 16 x 16: uncut 6.0 (4: 5.4 + 3.4); 192 x 150: uncut 44.1 (4: 42.4 + 4.2)
+SplitPlan plan_splits(int rows, int max_list_len, int page_bytes) {
+  const SplitPlan most = most_splits(rows, max_list_len);
+  constexpr int kCUs = 256;
+  constexpr int64_t kMergeBytes = 160 << 10;
+  rows = std::max(rows, 1);
+  max_list_len = std::max(max_list_len, 1);
+  const int64_t even = (int64_t)rows * max_list_len * page_bytes / kCUs * 6 / 5;
+  SplitPlan best = {0, 0};
+  int64_t best_cost = 0;
+  for (int w = 0; w <= 4; ++w) {
+    const int64_t s = w == 0 ? 1 : std::min<int64_t>((int64_t)kCUs * w / rows, most.num_splits);
+    if (s < 1) continue;
+    const int pps = (int)(((max_list_len + s - 1) / s + kDecWaves - 1) / kDecWaves * kDecWaves);
+    const int n = (max_list_len + pps - 1) / pps;
+    const int64_t share = ((int64_t)rows * n + kCUs - 1) / kCUs * pps * page_bytes;
+    const int64_t cost = std::max(share, even) + (n > 1 ? kMergeBytes : 0);
+    if (best.num_splits == 0 || cost < best_cost) { best = SplitPlan{pps, n}; best_cost = cost; }
+  }
+  return best;
+}
+
 template <typename T, int D, int S, int G>
 hipError_t launch_t(const CacheView& cv, const void* q, const int32_t* sel, const int32_t* cnt, int sel_stride,
                     int max_list_len, float sm_scale, void* out, float* lse, float* partials, hipStream_t st) {
   CacheView c = cv;
   const int rows = c.B * c.Hkv;
   c.stream_nt = (int64_t)rows * max_list_len * S * D * 2 * (int64_t)sizeof(T) > kStreamNtBytes;
-  const SplitPlan plan = most_splits(rows, max_list_len);
+  const SplitPlan plan = sel ? plan_splits(rows, max_list_len, S * D * 2 * (int)sizeof(T)) : most_splits(rows, max_list_len);
   float* part_o = partials;
   float* part_ml = partials + (size_t)rows * plan.num_splits * G * D;
   const float scale_log2 = (sm_scale > 0.f ? sm_scale : 1.0f / sqrtf((float)D)) * kLog2e;

@@ -938,3 +938,18 @@ def test_bf16_decode_moving_softmax_reference(gpu_lib, G, D, S, kind):
                 got = out[b, h * G:(h + 1) * G]
                 assert ((got - want).abs() <= 2 ** -8 * want.abs() + 2e-3).all(), (width, b, h, (got - want).abs().max())
                 assert ((lse[b, h * G:(h + 1) * G] - want_lse).abs() <= 1e-3 + 3e-6 * want_lse.abs()).all(), (width, b, h)
+
+
+@pytest.mark.parametrize("B,k", [(1, 16), (1, 200), (6, 64), (12, 200), (20, 32), (24, 150), (33, 300), (2, 1024)])
+def test_decode_split_plans(gpu_lib, B, k):
+    """Every outcome of the plan (uncut, one to four workgroups per compute unit, more entries than pages): the
+    attention over all pages of a list equals the dense call's, whose chunks are cut differently."""
+    wl = W.build("plans", 13, dtype=torch.bfloat16, B=B, H=16, Hkv=8, D=64, S=8, seq_lens=[8 * k - 3 * (b % 3) for b in range(B)],
+                 top_k=k, key_mode="iid", permute=True).to(DEV)
+    sess = DecodeSession(wl)
+    lists = torch.arange(k, dtype=torch.int32, device=DEV).expand(B, 8, k).contiguous()
+    sess.sparse_paged_decode(sel_pages=lists, sel_count=torch.full((B, 8), k, dtype=torch.int32, device=DEV))
+    sess.dense_paged_decode()
+    # fp32 sums in another order before one rounding to bf16: at most the neighbouring bf16 number
+    assert ((sess.out.float() - sess.out_dense.float()).abs() <= 2 ** -7 * sess.out_dense.float().abs() + 1e-6).all()
+    assert ((sess.lse - sess.lse_dense).abs() <= 1e-5).all()
