@@ -9,6 +9,7 @@
 // passes (mean, then squared deviations from it). A page's record is written by one wave, its stds
 // in one store. Accumulation is fp32.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_utils.hpp"
 #include "kernels.hpp"
@@ -16,11 +17,20 @@
 namespace unique {
 namespace {
 
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+// Stores into a page's record at a byte offset. Cache policy bits of the buffer instructions: 2 = non-temporal,
+// 16 = written through to the memory side of the fabric (sc1).
+template <int kPolicy>
+__device__ __forceinline__ void store_record(__amdgpu_buffer_rsrc_t rec, int off, u32x4_t v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, rec, off, 0, kPolicy);
+}
+template <int kPolicy>
+__device__ __forceinline__ void store_record(__amdgpu_buffer_rsrc_t rec, int off, u32x2_t v) {
+  __builtin_amdgcn_raw_buffer_store_b64(v, rec, off, 0, kPolicy);
+}
+
 constexpr int kStatsWaves = 4;
 constexpr int kStatsMaxPagesPerWave = 32;  // <= wavefront size: lane l keeps the id of the wave's l-th page
-#ifndef UNIQUE_STATS_TARGET_WAVES
-#define UNIQUE_STATS_TARGET_WAVES 65536
-#endif
 
 // (page, head) items per batch: about 8 16-byte loads per lane and batch; two batches are in flight per
 // wave. Larger batches cost registers and with them resident waves (16 loads per batch measured 9 % slower
@@ -34,13 +44,17 @@ struct StatsShape {
   static constexpr int kItems = kLoads >= 8 ? 1 : (kLoads >= 4 ? 2 : 4);
 };
 
-template <typename T, int D, int S>
+// kBulk: a launch that writes more records than the caches keep. Its means are written through, several heads at a time,
+// its stds non-temporally.
+template <typename T, int D, int S, bool kBulk>
 __global__ __launch_bounds__(kStatsWaves* kWave) void page_stats_kernel(CacheView c, const int32_t* tok_begin,
                                                                         const int32_t* tok_end, int pages_per_seq,
                                                                         int items_per_wave) {
   using Sh = StatsShape<T, D, S>;
   constexpr int kVec = Sh::kVec, kLanesPerTok = Sh::kLanesPerTok, kTokPerLoad = Sh::kTokPerLoad;
   constexpr int kLoads = Sh::kLoads, kItems = Sh::kItems;
+  constexpr int kMeanPolicy = kBulk ? 16 : 0;
+  constexpr int kBufferFlags = 0x27000;  // raw buffer of 32-bit elements
   static_assert(kLanesPerTok >= 8 && kLanesPerTok <= 32, "unsupported head_dim for this element type");
 
   const int b = blockIdx.y;
@@ -79,6 +93,10 @@ __global__ __launch_bounds__(kStatsWaves* kWave) void page_stats_kernel(CacheVie
   const int tr = lane / kLanesPerTok;  // key row inside one load
   const int ch = lane % kLanesPerTok;  // 16-byte chunk of the key
   const int64_t mean_bytes = (int64_t)c.Hkv * D * (c.stats_bf16 ? 2 : 4);
+  const int pack = kBulk ? min(span, kTokPerLoad) : 1;  // heads whose means are stored together (power of two)
+  uint32_t held[kVec];
+#pragma unroll
+  for (int i = 0; i < kVec; ++i) held[i] = 0u;
   float my_std = 0.f;  // lane h collects the std of head h until the page's record is complete
 
   struct Item { int phys, n, hkv; };
@@ -144,27 +162,38 @@ __global__ __launch_bounds__(kStatsWaves* kWave) void page_stats_kernel(CacheVie
       }
       ss = group_allreduce<kWave>(ss, OpSum());
 
-      char* rec = reinterpret_cast<char*>(c.page_stats) + (int64_t)m.phys * c.rec_bytes;  // this page's record
-      if (tr == 0) {
-        if (c.stats_bf16) {  // means rounded to bf16 (nearest even); the std above is about the unrounded mean
-          bf16_t* mp = reinterpret_cast<bf16_t*>(rec) + m.hkv * D + ch * kVec;
-          uint32_t wd[kVec / 2];
+      // this page's record (the descriptor bounds every store to it)
+      const __amdgpu_buffer_rsrc_t rec = __builtin_amdgcn_make_buffer_rsrc(
+          reinterpret_cast<char*>(c.page_stats) + (int64_t)m.phys * c.rec_bytes, (short)0, (int)c.rec_bytes, kBufferFlags);
+      // Every lane has the mean of its channels; lane group r keeps that of the r-th of `pack` consecutive heads, which
+      // then leave together (with kBulk 1 KiB of consecutive bf16 means with 16 lanes per key).
+      const bool keep = (m.hkv & (pack - 1)) == tr, full = ((m.hkv + 1) & (pack - 1)) == 0;  // full: wave-uniform
+      const int head = m.hkv - (pack - 1) + tr;
+      if (c.stats_bf16) {  // means rounded to bf16 (nearest even); the std above is about the unrounded mean
 #pragma unroll
-          for (int i = 0; i < kVec; i += 2)
-            wd[i / 2] = (uint32_t)float_to_bf16(mean[i]) | ((uint32_t)float_to_bf16(mean[i + 1]) << 16);
-          if constexpr (kVec == 8) *reinterpret_cast<uint4*>(mp) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
-          else *reinterpret_cast<uint2*>(mp) = make_uint2(wd[0], wd[1]);
-        } else {
-          float* mp = reinterpret_cast<float*>(rec) + m.hkv * D + ch * kVec;
+        for (int i = 0; i < kVec; i += 2) {
+          const uint32_t w = (uint32_t)float_to_bf16(mean[i]) | ((uint32_t)float_to_bf16(mean[i + 1]) << 16);
+          held[i / 2] = keep ? w : held[i / 2];
+        }
+        if (full && tr < pack) {
+          const int off = (head * D + ch * kVec) * 2;
+          if constexpr (kVec == 8) store_record<kMeanPolicy>(rec, off, u32x4_t{held[0], held[1], held[2], held[3]});
+          else store_record<kMeanPolicy>(rec, off, u32x2_t{held[0], held[1]});
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < kVec; ++i) held[i] = keep ? __float_as_uint(mean[i]) : held[i];
+        if (full && tr < pack) {
 #pragma unroll
           for (int i = 0; i < kVec; i += 4)
-            *reinterpret_cast<float4*>(mp + i) = make_float4(mean[i], mean[i + 1], mean[i + 2], mean[i + 3]);
+            store_record<kMeanPolicy>(rec, (head * D + ch * kVec + i) * 4,
+                                      u32x4_t{held[i], held[i + 1], held[i + 2], held[i + 3]});
         }
       }
       if (lane == m.hkv) my_std = sqrtf(ss * inv_n);
       // the stds of the heads this wave owns in the page leave as one contiguous store
       if (((m.hkv + 1) & (span - 1)) == 0 && lane <= m.hkv && lane > m.hkv - span)
-        reinterpret_cast<float*>(rec + mean_bytes)[lane] = my_std;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(my_std), rec, (int)mean_bytes + 4 * lane, 0, kBulk ? 2 : 0);
     }
   };
 
@@ -189,25 +218,36 @@ __global__ __launch_bounds__(kStatsWaves* kWave) void page_stats_kernel(CacheVie
 }
 
 template <typename T, int D>
-hipError_t dispatch_s(const CacheView& cv, const int32_t* tb, const int32_t* te, int pages_per_seq, hipStream_t st) {
-  CacheView c = cv;
+hipError_t dispatch_s(const CacheView& c, const int32_t* tb, const int32_t* te, int pages_per_seq, hipStream_t st) {
+  // What bounds the bulk build is the mixture of a read stream with a few percent of writes: 131072 pages (4.29 GB of keys,
+  // 285 MB of records) take 635 us without any store; a plain stream of the same reads with the same writes beside it
+  // takes 874 to 893. A launch that writes more records than the Infinity Cache keeps therefore writes its means through in
+  // pieces of 1 KiB and its stds, 32 bytes of a line, non-temporally, with 4 items per wave: 896 us in a row with
+  // launches on other buffers and 835 after a kernel that only read, against 1013 and 855 with plain stores (8 items per wave
+  // 905 / 842; stds plain 943 / 830; all non-temporal 878 / 890). Records that fit are better left to the caches: 9 MB of
+  // them 28.4 us, 29.4 non-temporally.
+  const bool bulk = (int64_t)c.B * pages_per_seq * c.rec_bytes > kStreamNtBytes;
+  const int64_t target_waves = bulk ? 262144 : 65536;
   // Enough waves to fill the chip many times over (ragged batches then balance), each with a run of
   // items that amortises its prologue. The run is a power of two, so it is a multiple or a divisor of
   // the (power-of-two) head count: a wave owns whole pages, or an aligned group of heads of one page.
-  auto launch = [&](auto kernel, int k_items) {
+  auto launch = [&](auto page_size) {
+    constexpr int S = decltype(page_size)::value;
+    constexpr int k_items = StatsShape<T, D, S>::kItems;
     const int64_t total = (int64_t)pages_per_seq * c.Hkv;
     // a launch with very few items (the tail-page refresh) gives every item its own wave; otherwise a wave
     // takes at least one full batch
     int64_t ipw = total * c.B <= 4096 ? 1 : k_items;
-    while (ipw * UNIQUE_STATS_TARGET_WAVES < total * c.B && ipw < (int64_t)kStatsMaxPagesPerWave * c.Hkv) ipw *= 2;
+    while (ipw * target_waves < total * c.B && ipw < (int64_t)kStatsMaxPagesPerWave * c.Hkv) ipw *= 2;
     const int64_t waves = (total + ipw - 1) / ipw;
     const dim3 grid((unsigned)((waves + kStatsWaves - 1) / kStatsWaves), c.B), block(kStatsWaves * kWave);
-    kernel<<<grid, block, 0, st>>>(c, tb, te, pages_per_seq, (int)ipw);
+    if (bulk) page_stats_kernel<T, D, S, true><<<grid, block, 0, st>>>(c, tb, te, pages_per_seq, (int)ipw);
+    else page_stats_kernel<T, D, S, false><<<grid, block, 0, st>>>(c, tb, te, pages_per_seq, (int)ipw);
   };
   switch (c.S) {
-    case 8: launch(page_stats_kernel<T, D, 8>, StatsShape<T, D, 8>::kItems); break;
-    case 16: launch(page_stats_kernel<T, D, 16>, StatsShape<T, D, 16>::kItems); break;
-    case 32: launch(page_stats_kernel<T, D, 32>, StatsShape<T, D, 32>::kItems); break;
+    case 8: launch(std::integral_constant<int, 8>()); break;
+    case 16: launch(std::integral_constant<int, 16>()); break;
+    case 32: launch(std::integral_constant<int, 32>()); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
