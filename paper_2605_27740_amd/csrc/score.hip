@@ -10,7 +10,7 @@
 // queries of its (fixed) KV head in registers for the whole kernel. The G partial dot products are
 // reduced over the 8 lanes with three DPP steps. The page-table entries of all of a wave's steps are
 // fetched up front (together with the sequence length and the queries, so the prologue is two memory
-// round trips); two records are in flight per wave, requested with unconditional loads so that the
+// round trips); two or four records are in flight per wave, requested with unconditional loads so that the
 // loop is straight-line code with exact waits. Scores of a tile are staged in LDS and written as one
 // contiguous run per KV head (4-byte scattered stores cost a tenth of the kernel otherwise).
 #include "device_utils.hpp"
@@ -20,15 +20,11 @@ namespace unique {
 namespace {
 
 constexpr int kScoreWaves = 4;
-#ifndef UNIQUE_SCORE_DEPTH
-#define UNIQUE_SCORE_DEPTH 2
-#endif
-#ifndef UNIQUE_SCORE_FULL_TILES
-#define UNIQUE_SCORE_FULL_TILES 512  // full tiles (two per CU) a batch of known-long sequences must supply for the next larger tile
-#endif
-#ifndef UNIQUE_SCORE_FAT_GRID
-#define UNIQUE_SCORE_FAT_GRID 4096  // workgroups above which a launch can afford the next larger tile
-#endif
+// Full tiles that a batch of known-long sequences must supply for the next larger tile: one workgroup per compute unit.
+// One sequence of 62501 pages, bf16 statistics: 128-page tiles (489 workgroups) 23.7 us, 64-page tiles 27.1, as three
+// workgroups fit a unit and 977 take a second round; 12 x 1800 to 3126 pages, fp32, G = 8: 64-page tiles 26.8, 32-page 28.4.
+constexpr int kFullTiles = 256;
+constexpr int kFatGrid = 4096;  // workgroups above which a launch can afford the next larger tile
 constexpr int kRowLanes = 8;                   // lanes per (page, head) row
 constexpr int kRowsPerWave = kWave / kRowLanes;
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -136,7 +132,10 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
                                                                         int refresh_tail, int tile_pages) {
   constexpr int kE = Elem<TS>::kVec;                 // mean elements per 16-byte load
   constexpr int kChunks = D / (kE * kRowLanes);      // 16-byte loads per lane per row
-  constexpr int kDepth = UNIQUE_SCORE_DEPTH;          // records in flight per wave (deeper rings measured no faster)
+  // Records in flight per wave. bf16 means in launches that stream from memory: four (80 x 4096 pages 117 us, two 122);
+  // with fp32 means, twice the bytes, four records are no faster (16 x 8192 pages 87 us, two 86) and cost small launches
+  // 1 us (2048 pages 8.0, two 7.0).
+  constexpr int kDepth = sizeof(TS) == 2 && kNT ? 4 : 2;
 
   const int b = blockIdx.y;
   const int tile0 = blockIdx.x * tile_pages;  // tile_pages logical pages per workgroup (a power of two, 8..256)
@@ -159,6 +158,10 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
     wave_slots = kScoreWaves;
   }
   const int step_pages = wave_slots * pages_per_step;  // pages the workgroup advances per step
+
+  // A tile that may lie beyond its sequence looks at the length before it asks for anything else: in a ragged batch most
+  // workgroups are such tiles, and each kept a slot for the two round trips below (32 x 128 to 4096 pages 22.2 -> 21.8 us).
+  if (tile0 >= c.min_pages_hint && tile0 >= (c.seq_lens[b] + c.S - 1) / c.S) return;
 
   // The sequence length, the page ids of all of this wave's steps (lane L holds entry L = step *
   // pages_per_step + page_in_step) and the queries are requested together; the page-table row always has
@@ -317,8 +320,8 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
   const bool nt = (int64_t)c.B * c.max_pages_hint * c.rec_bytes > kStreamNtBytes;
   // Small tiles balance ragged batches and small launches over the 256 CUs; larger ones save prologues
   // (fewer, longer streams). A tile is doubled while the batch is known to fill the chip with FULL tiles
-  // of the larger size: either every sequence is long enough by the host's lower bound (at least two
-  // workgroups of equal work per CU), or the launch has workgroups to spare whatever the lengths are.
+  // of the larger size: either every sequence is long enough by the host's lower bound (at least one
+  // workgroup of equal work per CU), or the launch has workgroups to spare whatever the lengths are.
   // A wave keeps the page ids of all its steps in its 64 lanes, which caps the tile at 64 pages per wave
   // slot (4 slots up to 8 KV heads, 2 at 16, 1 when one wave steps through all 32 heads of a page alone).
   const int wave_slots = c.Hkv <= 8 ? kScoreWaves : kScoreWaves * kRowsPerWave / c.Hkv;
@@ -326,8 +329,8 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
   constexpr int kMinTile = 8, kNumCUs = 256;
   int tile = 32;
   while (2 * tile <= max_tile &&
-         ((int64_t)c.B * (c.min_pages_hint / (2 * tile)) >= UNIQUE_SCORE_FULL_TILES ||
-          (int64_t)c.B * ((c.max_pages_hint + 2 * tile - 1) / (2 * tile)) >= UNIQUE_SCORE_FAT_GRID))
+         ((int64_t)c.B * (c.min_pages_hint / (2 * tile)) >= kFullTiles ||
+          (int64_t)c.B * ((c.max_pages_hint + 2 * tile - 1) / (2 * tile)) >= kFatGrid))
     tile *= 2;
   // a launch too small to give every CU a workgroup is all latency: shorter tiles spread it over more CUs
   // (one sequence of 32K tokens: 10.7 us with 32-page tiles, 8.7 us with 8-page tiles)
