@@ -39,7 +39,11 @@ __device__ __forceinline__ void write_final(const CacheView& c, T* out, float* l
   if (lse_out && d == 0) lse_out[(int64_t)b * c.H + h] = any ? (M + log2f(L)) * kLn2 : -INFINITY;
 }
 
-template <typename T, int D, int S, int G>
+// kNT: K and V are read with non-temporal loads (a launch that streams more than the caches hold). It is a template
+// parameter because the compiler merges the two loads of a run-time choice into a plain one.
+// us before (predicated loads, run-time choice) and now: 128 rows x 128 pages of 16 KB, G = 4 62.9 / 45.8 (5.9 TB/s);
+// all of 4 x 32768 tokens, G = 8 224 / 197; 2 rows x 16 pages of 8 KB 7.8 / 6.4.
+template <typename T, int D, int S, int G, bool kNT>
 __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
     CacheView c, const T* __restrict__ q, const int32_t* __restrict__ sel_pages,
     const int32_t* __restrict__ sel_count, int sel_stride, int pages_per_split, int num_splits, float scale_log2,
@@ -51,14 +55,22 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
   constexpr int kLoads = S / kTokPerLoad;                       // wave-wide loads per page (K or V)
   constexpr int kTileLoads = kLoads < 4 ? kLoads : 4;           // loads handled per pipeline stage
   constexpr int kTilesPerPage = kLoads / kTileLoads;
+  constexpr int kBuffers = 2;  // register tiles per wave (three and four measured no faster)
   static_assert(S % kTokPerLoad == 0 && kLoads % kTileLoads == 0, "page size / element type combination");
 
   const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
   const int row = b * c.Hkv + hkv;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
+  const int begin = split * pages_per_split;
+  // the first list entry of this lane is requested together with the lengths (see the matrix-core kernel)
+  int first_lp = -1;
+  {
+    const int e = begin + wave + lane * kDecWaves;
+    if (sel_pages && e < min(begin + pages_per_split, sel_stride)) first_lp = sel_pages[(int64_t)row * sel_stride + e];
+  }
   const int N = c.seq_lens[b];
   const int P = min((N + S - 1) / S, c.max_pages_hint);
   const int cnt = sel_pages ? min(sel_count[row], sel_stride) : P;
-  const int begin = split * pages_per_split;
   if (begin >= cnt) {
     if (num_splits == 1) {  // an empty list: the output is defined as zero, the lse as -inf
       for (int idx = threadIdx.x; idx < G * D; idx += kDecWaves * kWave)
@@ -68,13 +80,13 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
   }
   const int end = min(begin + pages_per_split, cnt);
 
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
   const int tr = lane / kLanesPerTok, ch = lane % kLanesPerTok;
 
+  const T* q_row = q + ((int64_t)b * c.H + hkv * G) * D + ch * kVec;  // this lane's chunk of the group's first query
   float qv[G][kVec];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    load_vec(q + ((int64_t)b * c.H + hkv * G + g) * D + ch * kVec, qv[g]);
+    load_vec(q_row + g * D, qv[g]);
 #pragma unroll
     for (int i = 0; i < kVec; ++i) qv[g][i] *= scale_log2;
   }
@@ -98,7 +110,7 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
     {
       const int e = e0 + lane * kDecWaves;
       if (e < end) {
-        const int lp = sel_pages ? sel_pages[(int64_t)row * sel_stride + e] : e;
+        const int lp = !sel_pages ? e : (e0 == begin + wave ? first_lp : sel_pages[(int64_t)row * sel_stride + e]);
         if (lp >= 0 && lp < P) {
           const int ph = c.page_table[(int64_t)b * c.max_pages + lp];
           if (ph >= 0 && (int64_t)ph < c.num_phys) {
@@ -111,45 +123,39 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
     const int n_ent = min(kWave, (end - e0 + kDecWaves - 1) / kDecWaves);
     const int n_tiles = n_ent * kTilesPerPage;
 
-    Raw16 kr[kTileLoads], vr[kTileLoads], kn[kTileLoads], vn[kTileLoads];
-    int ntok_cur = 0, ntok_nxt = 0, tbase_cur = 0, tbase_nxt = 0;
-    auto issue = [&](int it, Raw16(&kd)[kTileLoads], Raw16(&vd)[kTileLoads], int& ntok, int& tbase) {
-      const int ent = it / kTilesPerPage;
+    // A ring of register tiles, one being consumed and the others in flight. Loads are unconditional -- a slot without a
+    // token reads the first query instead, whose probability is zero -- so that every wait is exact (see the
+    // matrix-core kernel; with predicated loads the compiler waits for all of them before each tile).
+    Raw16 kb[kBuffers][kTileLoads], vb[kBuffers][kTileLoads];
+    int left[kBuffers];  // tokens of the page from this lane group's first slot on
+    auto issue = [&](int it, Raw16(&kd)[kTileLoads], Raw16(&vd)[kTileLoads], int& rest) {
+      const int ent = min(it / kTilesPerPage, kWave - 1);
       const int phys = __builtin_amdgcn_readlane(my_phys, ent);
-      ntok = __builtin_amdgcn_readlane(my_ntok, ent);
-      tbase = (it % kTilesPerPage) * kTileLoads * kTokPerLoad;
-      const int64_t page_off = (int64_t)phys * c.kv_page_stride + (int64_t)hkv * c.kv_head_stride + lane_off;
+      const int ntok = it < n_tiles ? __builtin_amdgcn_readlane(my_ntok, ent) : 0;
+      const int tok0 = (it % kTilesPerPage) * kTileLoads * kTokPerLoad + tr;
+      const int64_t off = (int64_t)phys * c.kv_page_stride + (int64_t)hkv * c.kv_head_stride + (int64_t)tok0 * D + lane_off;
+      rest = ntok - tok0;
 #pragma unroll
       for (int j = 0; j < kTileLoads; ++j) {
-        const int tok = tbase + j * kTokPerLoad + tr;
-        if (tok < ntok) {
-          kd[j] = load_raw_stream(kc + page_off + (int64_t)tok * D, c.stream_nt);
-          vd[j] = load_raw_stream(vc + page_off + (int64_t)tok * D, c.stream_nt);
-        } else {
-          kd[j] = zero_raw();
-          vd[j] = zero_raw();
-        }
+        const bool valid = j * kTokPerLoad < rest;
+        kd[j] = load_raw_stream(valid ? kc + off + j * kTokPerLoad * D : q_row, kNT);
+        vd[j] = load_raw_stream(valid ? vc + off + j * kTokPerLoad * D : q_row, kNT);
       }
     };
-
-    issue(0, kr, vr, ntok_cur, tbase_cur);
-    for (int it = 0; it < n_tiles; ++it) {
-      if (it + 1 < n_tiles) issue(it + 1, kn, vn, ntok_nxt, tbase_nxt);
-
+    auto consume = [&](const Raw16(&kr)[kTileLoads], const Raw16(&vr)[kTileLoads], int rest) {
       // logits of this lane group's tokens for the G heads
       float s[kTileLoads][G];
 #pragma unroll
       for (int j = 0; j < kTileLoads; ++j) {
         float kf[kVec];
         unpack_raw(kr[j], kf, (const T*)nullptr);
-        const bool valid = (tbase_cur + j * kTokPerLoad + tr) < ntok_cur;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
           float d = qv[g][0] * kf[0];
 #pragma unroll
           for (int i = 1; i < kVec; ++i) d = fmaf(qv[g][i], kf[i], d);
           d = group_allreduce<kLanesPerTok>(d, OpSum());
-          s[j][g] = valid ? d : -INFINITY;
+          s[j][g] = j * kTokPerLoad < rest ? d : -INFINITY;
         }
       }
       // online softmax update, one state per lane group
@@ -181,11 +187,17 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
 #pragma unroll
           for (int i = 0; i < kVec; ++i) acc[g][i] = fmaf(p[j][g], vf[i], acc[g][i]);
       }
+    };
 
 #pragma unroll
-      for (int j = 0; j < kTileLoads; ++j) { kr[j] = kn[j]; vr[j] = vn[j]; }
-      ntok_cur = ntok_nxt;
-      tbase_cur = tbase_nxt;
+    for (int u = 0; u < kBuffers - 1; ++u) issue(u, kb[u], vb[u], left[u]);
+    for (int t0 = 0; t0 < n_tiles; t0 += kBuffers) {
+#pragma unroll
+      for (int u = 0; u < kBuffers; ++u) {
+        constexpr int kAhead = kBuffers - 1;
+        issue(t0 + u + kAhead, kb[(u + kAhead) % kBuffers], vb[(u + kAhead) % kBuffers], left[(u + kAhead) % kBuffers]);
+        if (u == 0 || t0 + u < n_tiles) consume(kb[u], vb[u], left[u]);  // uniform
+      }
     }
   }
 
@@ -697,18 +709,18 @@ hipError_t launch_t(const CacheView& cv, const void* q, const int32_t* sel, cons
   float* part_o = partials;
   float* part_ml = partials + (size_t)rows * plan.num_splits * G * D;
   const float scale_log2 = (sm_scale > 0.f ? sm_scale : 1.0f / sqrtf((float)D)) * kLog2e;
-  if constexpr (sizeof(T) == 2) {
-    auto go = [&](auto kernel) {
-      kernel<<<dim3(plan.num_splits, c.Hkv, c.B), dim3(kDecWaves * kWave), 0, st>>>(
-          c, reinterpret_cast<const bf16_t*>(q), sel, cnt, sel_stride, plan.pages_per_split, plan.num_splits,
-          scale_log2, part_o, part_ml, reinterpret_cast<bf16_t*>(out), lse);
-    };
-    if (c.stream_nt) go(paged_decode_partial_mfma_kernel<D, S, G, true>);
-    else go(paged_decode_partial_mfma_kernel<D, S, G, false>);
-  } else
-    paged_decode_partial_kernel<T, D, S, G><<<dim3(plan.num_splits, c.Hkv, c.B), dim3(kDecWaves * kWave), 0, st>>>(
+  auto go = [&](auto kernel) {
+    kernel<<<dim3(plan.num_splits, c.Hkv, c.B), dim3(kDecWaves * kWave), 0, st>>>(
         c, reinterpret_cast<const T*>(q), sel, cnt, sel_stride, plan.pages_per_split, plan.num_splits, scale_log2,
         part_o, part_ml, reinterpret_cast<T*>(out), lse);
+  };
+  if constexpr (sizeof(T) == 2) {
+    if (c.stream_nt) go(paged_decode_partial_mfma_kernel<D, S, G, true>);
+    else go(paged_decode_partial_mfma_kernel<D, S, G, false>);
+  } else {
+    if (c.stream_nt) go(paged_decode_partial_kernel<T, D, S, G, true>);
+    else go(paged_decode_partial_kernel<T, D, S, G, false>);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || plan.num_splits == 1) return e;  // one chunk per row: the partial kernel wrote the output
   paged_decode_merge_kernel<T, D, G><<<dim3(c.H, c.B), dim3(kWave), 0, st>>>(

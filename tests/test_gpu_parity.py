@@ -896,22 +896,23 @@ def test_a_plain_c_client_runs_the_whole_path(gpu_lib):
 
 @pytest.mark.parametrize("G,D,S", [(1, 128, 16), (2, 64, 16), (4, 128, 8), (4, 64, 32), (8, 128, 32), (8, 64, 8), (8, 128, 16)])
 @pytest.mark.parametrize("kind", ["up", "down", "spike", "flat"])
-def test_bf16_decode_moving_softmax_reference(gpu_lib, G, D, S, kind):
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_decode_moving_softmax_reference(gpu_lib, dtype, G, D, S, kind):
     """Logits that rise or fall by hundreds along the sequence, jump once, or are all equal, over shuffled lists with
-    entries to be skipped, cut and uncut, against float64. Tolerances: the output is rounded to bf16 (2^-8 relative);
+    entries to be skipped, cut and uncut, against float64. Tolerances: the output may be rounded to bf16 (2^-8 relative);
     logits of magnitude 300 carry an fp32 error of about 300 * 2^-24 * sqrt(D) < 3e-4, which moves a probability, and with
     it an output of |v| <= 6 and the lse, by that much relatively."""
     g = torch.Generator().manual_seed(G * 1000 + D + S)
     B, Hkv, N = 2, 2, 41 * S + 3
-    wl = W.build("ramp", 12, dtype=torch.bfloat16, B=B, H=Hkv * G, Hkv=Hkv, D=D, S=S, seq_lens=[N, N - S + 1], top_k=64,
+    wl = W.build("ramp", 12, dtype=dtype, B=B, H=Hkv * G, Hkv=Hkv, D=D, S=S, seq_lens=[N, N - S + 1], top_k=64,
                  key_mode="iid")
     level = {"up": torch.linspace(-1, 1, 42 * S), "down": torch.linspace(1, -1, 42 * S), "flat": torch.zeros(42 * S),
              "spike": torch.where(torch.arange(42 * S) == 500, 1.0, 0.0)}[kind].view(42, 1, S, 1)
     q_dir = wl.q[0, 0] / wl.q[0, 0].float().norm()
     for b in range(B):  # every query leans on q_dir, the keys follow the level along it
-        wl.q[b] = (wl.q[b].float() + 8 * q_dir.float()).bfloat16()
+        wl.q[b] = (wl.q[b].float() + 8 * q_dir.float()).to(dtype)
         pages = wl.page_table[b, :wl.num_pages(b)].long()
-        wl.k_cache[pages] = (wl.k_cache[pages].float() + 30 * D ** 0.5 * level[:len(pages)] * q_dir.float()).bfloat16()
+        wl.k_cache[pages] = (wl.k_cache[pages].float() + 30 * D ** 0.5 * level[:len(pages)] * q_dir.float()).to(dtype)
     dev = wl.to(DEV)
     sess = DecodeSession(dev)
     for width in (7, 64):  # uncut, and a list long enough to be cut
