@@ -14,15 +14,13 @@
 // own: done by a row's last workgroup behind an agent-scope release and acquire it costs 8 us more than the launch
 // (131K tokens, 128 rows), and with write-through stores instead of the release the step is no faster either.
 // Logits are kept in the log2 domain (q is pre-multiplied by sm_scale * log2 e) so exp is one v_exp_f32.
-#include <algorithm>
-
 #include "device_utils.hpp"
 #include "kernels.hpp"
+#include "split_plan.hpp"
 
 namespace unique {
 namespace {
 
-constexpr int kDecWaves = 4;
 constexpr float kNegBig = -1.0e30f;  // finite stand-in for "no logit seen yet"
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -39,6 +37,19 @@ __device__ __forceinline__ void write_final(const CacheView& c, T* out, float* l
   if (lse_out && d == 0) lse_out[(int64_t)b * c.H + h] = any ? (M + log2f(L)) * kLn2 : -INFINITY;
 }
 
+// The chunk of a workgroup. With SplitPlan::rotate the split is the slowest grid index, so that empty chunks come last, and
+// from one split to the next the rows move on by a head and a sequence: the chunks of a row, which may be the only long
+// one, then lie on different XCDs (workgroups are dealt to the 8 of them in turn) and different compute units there.
+// Selects instead of a branch: with a branch the kernel's arguments arrive in two round trips (0.1 us).
+__device__ __forceinline__ void locate_chunk(const CacheView& c, const SplitPlan& plan, int& split, int& hkv, int& b) {
+  const bool rot = plan.rotate != 0;
+  split = rot ? blockIdx.z : blockIdx.x;
+  const int by = rot ? split : 0;
+  hkv = ((rot ? blockIdx.x : blockIdx.y) + by) & (c.Hkv - 1);  // a power of two
+  b = (rot ? blockIdx.y : blockIdx.z) + (by & (plan.rotate - 1));
+  b -= b >= c.B ? c.B : 0;
+}
+
 // kNT: K and V are read with non-temporal loads (a launch that streams more than the caches hold). It is a template
 // parameter because the compiler merges the two loads of a run-time choice into a plain one.
 // us before (predicated loads, run-time choice) and now: 128 rows x 128 pages of 16 KB, G = 4 62.9 / 45.8 (5.9 TB/s);
@@ -46,7 +57,7 @@ __device__ __forceinline__ void write_final(const CacheView& c, T* out, float* l
 template <typename T, int D, int S, int G, bool kNT>
 __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
     CacheView c, const T* __restrict__ q, const int32_t* __restrict__ sel_pages,
-    const int32_t* __restrict__ sel_count, int sel_stride, int pages_per_split, int num_splits, float scale_log2,
+    const int32_t* __restrict__ sel_count, int sel_stride, SplitPlan plan, float scale_log2,
     float* __restrict__ part_o /*[rows][num_splits][G][D]*/, float* __restrict__ part_ml /*[rows][num_splits][G][2]*/,
     T* __restrict__ out, float* __restrict__ lse_out /* written directly when num_splits == 1 */) {
   constexpr int kVec = Elem<T>::kVec;
@@ -58,7 +69,9 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
   constexpr int kBuffers = 2;  // register tiles per wave (three and four measured no faster)
   static_assert(S % kTokPerLoad == 0 && kLoads % kTileLoads == 0, "page size / element type combination");
 
-  const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
+  const int pages_per_split = plan.pages_per_split, num_splits = plan.num_splits;
+  int split, hkv, b;
+  locate_chunk(c, plan, split, hkv, b);
   const int row = b * c.Hkv + hkv;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
   const int begin = split * pages_per_split;
@@ -278,7 +291,7 @@ constexpr int kStampSlots = 32, kStampWaves = 1 << 14;
 __device__ unsigned long long g_dec_stamps[kStampWaves][kStampSlots];
 #define DEC_STAMP(slot)                                                                                         \
   do {                                                                                                          \
-    const int sw_ = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * kDecWaves + wave;          \
+    const int sw_ = (row * num_splits + split) * kDecWaves + wave;          \
     if (lane == 0 && sw_ < kStampWaves) g_dec_stamps[sw_][slot] = wall_clock64();                               \
   } while (0)
 // the stamp is taken only once `value` (a 32-bit register) has been produced
@@ -343,7 +356,7 @@ constexpr int kDecBuffers = 2;
 template <int D, int S, int G, bool kNT>
 __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_kernel(
     CacheView c, const bf16_t* __restrict__ q, const int32_t* __restrict__ sel_pages,
-    const int32_t* __restrict__ sel_count, int sel_stride, int pages_per_split, int num_splits, float scale_log2,
+    const int32_t* __restrict__ sel_count, int sel_stride, SplitPlan plan, float scale_log2,
     float* __restrict__ part_o, float* __restrict__ part_ml, bf16_t* __restrict__ out, float* __restrict__ lse_out) {
   constexpr int kVec = 8;
   constexpr int kTile = 16;                          // token slots per MFMA tile
@@ -353,7 +366,9 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_ke
   constexpr float kMaxGrowth = 6.f;                  // log2: how far logits may exceed the reference before it moves
   static_assert(G <= 8, "at most 8 query heads per KV head");
 
-  const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
+  const int pages_per_split = plan.pages_per_split, num_splits = plan.num_splits;
+  int split, hkv, b;
+  locate_chunk(c, plan, split, hkv, b);
   const int row = b * c.Hkv + hkv;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
   const int begin = split * pages_per_split;
@@ -534,7 +549,7 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_ke
 #ifdef UNIQUE_DEC_STAMPS
         if (t0 + u < n_tiles && t0 + u < kStampSlots - 6) DEC_STAMP_AFTER(6 + t0 + u, acc[0][0]);  // tile t0 + u consumed
         if (t0 + u == 0) {  // which compute unit this wave runs on (HW_ID: bits 8-11 CU, 13-15 SE; XCC_ID register)
-          const int sw_ = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * kDecWaves + wave;
+          const int sw_ = (row * num_splits + split) * kDecWaves + wave;
           if (lane == 0 && sw_ < kStampWaves)
             g_dec_stamps[sw_][5] = ((unsigned long long)__builtin_amdgcn_s_getreg((4 << 0) | (0 << 6) | (31 << 11)) << 32) |
                                    (unsigned)__builtin_amdgcn_s_getreg((20 << 0) | (0 << 6) | (3 << 11));
@@ -652,67 +667,21 @@ __global__ __launch_bounds__(kWave) void paged_decode_merge_kernel(CacheView c, 
   if (lse_out && lane == 0) lse_out[(int64_t)b * c.H + h] = any ? (M + log2f(L)) * kLn2 : -INFINITY;
 }
 
-// How a launch is cut into split-K chunks; computed on the host from bounds only.
-struct SplitPlan {
-  int32_t pages_per_split;  // list entries handled by one workgroup
-  int32_t num_splits;       // grid extent along the split axis (upper bound for every row)
-};
-
-// Partial results are sized for this many chunks per row, the most that any launch below cuts a list into.
-SplitPlan most_splits(int rows, int max_list_len) {
-  constexpr int kGroups = 512, kMaxPages = 256;
-  rows = std::max(rows, 1);
-  max_list_len = std::max(max_list_len, 1);
-  const int wanted = rows >= 256 ? 1 : (kGroups + rows - 1) / rows;
-  int pps = std::max((max_list_len + wanted - 1) / wanted, kDecWaves);  // at least one page per wave
-  // long lists are cut into many equal chunks so that ragged batches balance across the CUs
-  pps = (std::min(pps, kMaxPages) + kDecWaves - 1) / kDecWaves * kDecWaves;
-  return SplitPlan{pps, (max_list_len + pps - 1) / pps};
-}
-
-// A list that is known to be as long as max_list_len says for most rows (a top-k selection) is cut so that the compute
-// units get equal shares. What the busiest of the 256 units has to read bounds the launch: ceil(workgroups / 256) chunks;
-// it reads about 35 KB per us when all are busy, so that below 1.2 times the average share the memory bounds it, and the
-// merge launch that every cut row needs costs as much as 160 KB. Candidates are an uncut row and the largest number of
-// chunks that fills one to four workgroups per unit. Partial + merge kernel us, chosen against (chunks per row):
-//   96 rows x 200 pages of 8 KB: 5 chunks 29.2 + 4.1 (2: 31.4, 3: 40.5, 6: 35.8, uncut: 50.7 without a merge)
-//   128 x 256: 2 chunks 44.8 (3: 53.4, 4: 46.3, uncut 65.5); 16 x 1024: 16 chunks 24.6 (24: 29.3, 32: 25.6)
-//   160 x 32: uncut 10.3 (3: 10.8 + 4.2); 16 x 16: uncut 6.0 (4: 5.4 + 3.4); 192 x 150: uncut 44.1 (4: 42.4 + 4.2)
-SplitPlan plan_splits(int rows, int max_list_len, int page_bytes) {
-  const SplitPlan most = most_splits(rows, max_list_len);
-  constexpr int kCUs = 256;
-  constexpr int64_t kMergeBytes = 160 << 10;
-  rows = std::max(rows, 1);
-  max_list_len = std::max(max_list_len, 1);
-  const int64_t even = (int64_t)rows * max_list_len * page_bytes / kCUs * 6 / 5;
-  SplitPlan best = {0, 0};
-  int64_t best_cost = 0;
-  for (int w = 0; w <= 4; ++w) {
-    const int64_t s = w == 0 ? 1 : std::min<int64_t>((int64_t)kCUs * w / rows, most.num_splits);
-    if (s < 1) continue;
-    const int pps = (int)(((max_list_len + s - 1) / s + kDecWaves - 1) / kDecWaves * kDecWaves);
-    const int n = (max_list_len + pps - 1) / pps;
-    const int64_t share = ((int64_t)rows * n + kCUs - 1) / kCUs * pps * page_bytes;
-    const int64_t cost = std::max(share, even) + (n > 1 ? kMergeBytes : 0);
-    if (best.num_splits == 0 || cost < best_cost) { best = SplitPlan{pps, n}; best_cost = cost; }
-  }
-  return best;
-}
-
 template <typename T, int D, int S, int G>
 hipError_t launch_t(const CacheView& cv, const void* q, const int32_t* sel, const int32_t* cnt, int sel_stride,
                     int max_list_len, float sm_scale, void* out, float* lse, float* partials, hipStream_t st) {
   CacheView c = cv;
   const int rows = c.B * c.Hkv;
   c.stream_nt = (int64_t)rows * max_list_len * S * D * 2 * (int64_t)sizeof(T) > kStreamNtBytes;
-  const SplitPlan plan = sel ? plan_splits(rows, max_list_len, S * D * 2 * (int)sizeof(T)) : most_splits(rows, max_list_len);
+  const SplitPlan plan = sel ? plan_splits(c.B, c.Hkv, max_list_len, c.max_pages_hint, S * D * 2 * (int)sizeof(T))
+                             : most_splits(rows, max_list_len);
   float* part_o = partials;
   float* part_ml = partials + (size_t)rows * plan.num_splits * G * D;
   const float scale_log2 = (sm_scale > 0.f ? sm_scale : 1.0f / sqrtf((float)D)) * kLog2e;
   auto go = [&](auto kernel) {
-    kernel<<<dim3(plan.num_splits, c.Hkv, c.B), dim3(kDecWaves * kWave), 0, st>>>(
-        c, reinterpret_cast<const T*>(q), sel, cnt, sel_stride, plan.pages_per_split, plan.num_splits, scale_log2,
-        part_o, part_ml, reinterpret_cast<T*>(out), lse);
+    const dim3 grid = plan.rotate ? dim3(c.Hkv, c.B, plan.num_splits) : dim3(plan.num_splits, c.Hkv, c.B);
+    kernel<<<grid, dim3(kDecWaves * kWave), 0, st>>>(c, reinterpret_cast<const T*>(q), sel, cnt, sel_stride, plan, scale_log2,
+                                                     part_o, part_ml, reinterpret_cast<T*>(out), lse);
   };
   if constexpr (sizeof(T) == 2) {
     if (c.stream_nt) go(paged_decode_partial_mfma_kernel<D, S, G, true>);

@@ -1,0 +1,11 @@
+// C interface of the decode's split plan for the CPU tests.
+#include "../../paper_2605_27740_amd/csrc/split_plan.hpp"
+
+extern "C" void most(int rows, int len, int* out) {
+  const unique::SplitPlan p = unique::most_splits(rows, len);
+  out[0] = p.pages_per_split; out[1] = p.num_splits; out[2] = p.rotate;
+}
+extern "C" void plan(int batch, int kv_heads, int len, int max_pages, int page_bytes, int* out) {
+  const unique::SplitPlan p = unique::plan_splits(batch, kv_heads, len, max_pages, page_bytes);
+  out[0] = p.pages_per_split; out[1] = p.num_splits; out[2] = p.rotate;
+}

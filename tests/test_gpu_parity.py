@@ -975,3 +975,68 @@ def test_stats_of_large_launches_are_the_same_bits(gpu_lib, dtype, Hkv, D, S, st
     wide.update_page_stats()
     torch.cuda.synchronize()
     assert torch.equal(narrow.page_stats, wide.page_stats)
+
+
+@pytest.mark.parametrize("dtype,B,Hkv,G,S,stride,P", [
+    (torch.bfloat16, 32, 8, 2, 8, 300, 300),     # 256 rows, uncut: a wave looks up its entries in two rounds
+    (torch.float32, 32, 8, 2, 8, 300, 300),
+    (torch.bfloat16, 32, 8, 1, 8, 521, 521),     # cut into chunks of more than 256 entries, the empty ones last
+    (torch.float32, 37, 8, 1, 8, 521, 500),
+    (torch.bfloat16, 33, 8, 4, 16, 1030, 130),   # lists longer than the sequences have pages
+    (torch.float32, 3, 2, 4, 16, 741, 183),
+    (torch.bfloat16, 3, 2, 8, 32, 741, 183),
+    (torch.bfloat16, 1, 8, 4, 16, 1024, 64),
+    (torch.bfloat16, 1, 1, 1, 16, 2048, 100),
+    (torch.bfloat16, 24, 8, 2, 16, 150, 150),    # lists of very different lengths
+])
+def test_decode_lists_shorter_than_their_bound(gpu_lib, dtype, B, Hkv, G, S, stride, P):
+    """Lists of every length up to their bound, empty and full ones among them, with invalid entries in between, in
+    launches whose plan expects full lists or knows that they cannot be full; every row against float64. Tolerance: the
+    rounding to bf16 is 2^-9 relative (2^-8 allowed), fp32 sums of probabilities times |v| <= 6 err by less than 2e-5."""
+    D = 64
+    g = torch.Generator().manual_seed(stride + B)
+    lens = [max(1, int(P * S * x)) for x in torch.rand((B,), generator=g)]
+    lens[0], lens[-1] = P * S, P * S - 3 if B > 1 else P * S
+    wl = W.build("short", 15, dtype=dtype, B=B, H=Hkv * G, Hkv=Hkv, D=D, S=S, seq_lens=lens, top_k=stride,
+                 key_mode="iid", permute=True)
+    lists = torch.full((B, Hkv, stride), -1, dtype=torch.int32)
+    lists[:, :, 1::5] = 10 ** 6
+    count = torch.randint(0, stride + 1, (B, Hkv), generator=g, dtype=torch.int32)
+    count[0, 0], count[0, -1], count[-1] = stride, 0 if Hkv > 1 else stride, stride
+    for b in range(B):
+        for h in range(Hkv):
+            some = torch.randperm(wl.num_pages(b), generator=g).int()
+            at = torch.randperm(stride, generator=g)[:len(some)]
+            lists[b, h, at] = some[:len(at)]
+    dev = wl.to(DEV)
+    sess = DecodeSession(dev, want_scores=False)
+    sess.out.fill_(7.0)
+    sess.sparse_paged_decode(sel_pages=lists.to(DEV), sel_count=count.to(DEV))
+    out, lse = sess.out.cpu().double(), sess.lse.cpu().double()
+    for b in range(B):
+        n = int(wl.seq_lens[b])
+        for h in range(Hkv):
+            keep = lists[b, h, :count[b, h]].long()
+            keep = keep[(keep >= 0) & (keep < wl.num_pages(b))]
+            hs = slice(h * G, (h + 1) * G)
+            if len(keep) == 0:
+                assert (out[b, hs] == 0).all() and (lse[b, hs] == float("-inf")).all(), (b, h)
+                continue
+            tok = (keep[:, None] * S + torch.arange(S)).view(-1)
+            tok = tok[tok < n]
+            phys = wl.page_table[b, tok // S].long()
+            k, v = (c[phys, h, tok % S].double() for c in (wl.k_cache, wl.v_cache))
+            logits = wl.q[b, hs].double() @ k.T / D ** 0.5
+            want_lse = torch.logsumexp(logits, -1)
+            want = torch.exp(logits - want_lse[:, None]) @ v
+            rel = 2 ** -8 if dtype == torch.bfloat16 else 1e-5
+            assert ((out[b, hs] - want).abs() <= rel * want.abs() + 2e-5).all(), (b, h, (out[b, hs] - want).abs().max())
+            assert ((lse[b, hs] - want_lse).abs() <= 1e-5 * (1 + want_lse.abs())).all(), (b, h)
+    # the one-call step plans its lists like the separate calls: the same bits
+    sess.update_page_stats()
+    sess.sparse_step()
+    torch.cuda.synchronize()
+    apart = [t.clone() for t in (sess.sel_pages, sess.sel_count, sess.out, sess.lse)]
+    sess.decode_step(refresh_tail=True)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, t) for a, t in zip(apart, (sess.sel_pages, sess.sel_count, sess.out, sess.lse)))

@@ -1,0 +1,77 @@
+"""The decode's split plan (csrc/split_plan.hpp, host arithmetic), compiled here without HIP."""
+import ctypes as C
+import os
+import random
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+MORE_BYTES = 256 << 10  # how much longer than a chunk of most_splits a chunk may be
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("plan") / "split_plan.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-ftrapv", "-shared", "-fPIC", "-o", so,
+                    os.path.join(HERE, "c_abi", "split_plan.cpp")], check=True)
+    c = C.CDLL(so)
+
+    class Lib:
+        @staticmethod
+        def most(rows, length):
+            out = (C.c_int * 3)()
+            c.most(rows, length, out)
+            return tuple(out)
+
+        @staticmethod
+        def plan(batch, heads, length, max_pages, page_bytes):
+            out = (C.c_int * 3)()
+            c.plan(batch, heads, length, max_pages, page_bytes, out)
+            return tuple(out)
+    return Lib
+
+
+def test_every_plan_covers_its_list_and_stays_inside_the_workspace(lib):
+    r = random.Random(1)
+    for i in range(20000):
+        batch, heads = r.choice([r.randint(1, 40), r.randint(1, 600)]), 1 << r.randint(0, 5)
+        length = r.choice([r.randint(1, 64), r.randint(1, 2000), r.randint(1, 40000), r.randint(1 << 20, (1 << 31) - 1)])
+        max_pages = r.choice([length, max(1, length // r.randint(1, 40)), length + r.randint(1, 9999) if length < 1 << 30 else length])
+        page = r.choice([64, 128]) * r.choice([8, 16, 32]) * 2 * r.choice([2, 4])
+        where = (batch, heads, length, max_pages, page)
+        pps0, n0, rot0 = lib.most(batch * heads, length)
+        pps, n, rot = lib.plan(*where)
+        assert rot0 == 0 and 4 <= pps0 <= 256 and (n0 - 1) * pps0 < length <= n0 * pps0, where
+        # every entry is visited, no chunk is empty by construction, and the partial results fit
+        assert pps % 4 == 0 and (n - 1) * pps < length <= n * pps and n <= n0, where
+        # a long row among short ones is never left to a few workgroups
+        fits = n == 1 and min(length, max_pages) <= pps0 and length <= 4 * pps0
+        assert pps <= pps0 + MORE_BYTES // page or fits, where
+        assert rot == 0 or (1 <= rot <= batch and rot & (rot - 1) == 0 and 1 < n <= 65535), where
+        assert (rot != 0) == (1 < n <= 65535 and (length > max_pages or batch * heads >= 256)), where
+
+
+@pytest.mark.parametrize("batch,heads,length,max_pages,page,longest", [
+    (32, 8, 1024, 1024, 8192, 256),    # ragged lists of 256 rows
+    (32, 8, 8192, 8192, 8192, 256),    # padded lists of 256 rows
+    (1, 8, 1024, 64, 8192, 16),        # a budget far above the pages of the sequence
+    (4, 8, 1024, 125, 8192, 64),
+    (2, 8, 741, 183, 32768, 24),
+    (24, 8, 150, 150, 8192, 52),       # one long list among short ones
+])
+def test_lists_that_may_be_short_keep_chunks_of_the_finer_cut(lib, batch, heads, length, max_pages, page, longest):
+    assert lib.plan(batch, heads, length, max_pages, page)[0] <= longest
+
+
+@pytest.mark.parametrize("batch,heads,length,page,want", [
+    (12, 8, 200, 8192, (40, 5)), (4, 4, 1024, 8192, (64, 16)), (1, 8, 1024, 8192, (32, 32)), (2, 8, 16, 8192, (16, 1)),
+    (20, 8, 32, 8192, (32, 1)), (80, 8, 64, 4096, (64, 1)), (1, 8, 128, 8192, (4, 32))])
+def test_full_lists_are_cut_into_equal_shares(lib, batch, heads, length, page, want):
+    assert lib.plan(batch, heads, length, 1 << 20, page) == (*want, 0)
+
+
+def test_dense_lists_are_cut_finely(lib):
+    assert lib.most(128, 8192) == (256, 32, 0)   # at most 256 pages per chunk
+    assert lib.most(8, 2048) == (32, 64, 0)      # 512 workgroups
+    assert lib.most(300, 200) == (200, 1, 0)
