@@ -363,7 +363,7 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_ke
   constexpr int kSteps = D / 32;                     // q.k steps (and K loads per lane) per tile
   constexpr int kVB = D / 16;                        // channels of a value row per lane
   constexpr int kSlots = G == 8 ? 16 : 3 * G;        // output rows in use: parts times heads
-  constexpr float kMaxGrowth = 6.f;                  // log2: how far logits may exceed the reference before it moves
+  constexpr float kRoom = 6.f;                       // log2: how far above the largest logit the reference is put
   static_assert(G <= 8, "at most 8 query heads per KV head");
 
   const int pages_per_split = plan.pages_per_split, num_splits = plan.num_splits;
@@ -404,9 +404,10 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_ke
 #pragma unroll
   for (int s = 0; s < kSteps; ++s) qa[s] = as_bf16x8(load_raw(q_row + (int64_t)(kt % G) * D + (4 * s + kg) * kVec));
 
-  // Softmax state of head kt % G. The reference m, the same in all lanes of a head, follows the largest logit but only
-  // moves when one exceeds it by more than kMaxGrowth: probabilities relative to it stay below 2^kMaxGrowth, and most
-  // tiles need neither the maximum over the lanes nor a rescaled output. l is this lane's part of the sum.
+  // Softmax state of head kt % G. The reference m, the same in all lanes of a head, is put kRoom above the largest logit and
+  // only moves when a logit exceeds it: most tiles need neither the maximum over the lanes nor a rescaled output, and
+  // probabilities relative to it are at most 1, so that their products with V stay in its range. l is this lane's
+  // part of the sum.
   float m = kNegBig, l = 0.f;
   f32x4_t acc[kVB];  // acc[e][i]: output row 4 * kg + i (head row % G), channel kVB * kt + e
 #pragma unroll
@@ -485,12 +486,12 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_mfma_ke
 #pragma unroll
       for (int j = 0; j < 4; ++j) x[j] = j < valid ? fmaf(sacc[j], scale_log2, -m) : -INFINITY;
       const float top = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
-      if (__any(top > kMaxGrowth)) {
+      if (__any(top > 0.f)) {
         // (from the logits themselves: m may still be kNegBig)
         float t = -INFINITY;
 #pragma unroll
         for (int j = 0; j < 4; ++j) t = j < valid ? fmaxf(t, sacc[j] * scale_log2) : t;
-        const float mnew = fmaxf(m, rows_allreduce(t, OpMax()));
+        const float mnew = fmaxf(m, rows_allreduce(t, OpMax()) + kRoom);
         const float alpha = fast_exp2(m - mnew);
         m = mnew;
         l *= alpha;

@@ -3,6 +3,7 @@
 Small cases are checked row by row; the benchmark-size configurations are generated on the GPU and checked on
 EVERY row through the oracle's whole-batch drivers. Tolerances are in tests/harness.py.
 """
+import math
 import os
 
 import numpy as np
@@ -1040,3 +1041,27 @@ def test_decode_lists_shorter_than_their_bound(gpu_lib, dtype, B, Hkv, G, S, str
     sess.decode_step(refresh_tail=True)
     torch.cuda.synchronize()
     assert all(torch.equal(a, t) for a, t in zip(apart, (sess.sel_pages, sess.sel_count, sess.out, sess.lse)))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("G", [1, 4, 8])
+def test_decode_values_near_the_top_of_the_float_range(gpu_lib, dtype, G):
+    """Logits that rise by less than 64-fold probabilities along a list, the last page with values of 2^126 and all others
+    with small ones: the output is finite (a weighted mean of the values) and has to be so on the way, too."""
+    B, Hkv, D, S, P = 1, 2, 64, 16, 5
+    wl = W.build("range", 16, dtype=dtype, B=B, H=Hkv * G, Hkv=Hkv, D=D, S=S, seq_lens=[P * S], top_k=P, key_mode="iid")
+    wl.q[:] = 1.0
+    wl.k_cache[:] = 0.0
+    wl.k_cache[wl.page_table[0, P - 1].long(), :, 5, :] = 0.5   # one token, logit 4 = 5.77 in log2, the others 0
+    wl.v_cache[wl.page_table[0, P - 1].long(), :, 5, :] = 2.0 ** 126
+    dev = wl.to(DEV)
+    sess = DecodeSession(dev)
+    # one entry in four is a wave's, so the page of large values is the second tile of a wave that starts low
+    lists = torch.tensor([0, 1, 2, 3, 4], dtype=torch.int32, device=DEV).expand(B, Hkv, P).contiguous()
+    sess.sparse_paged_decode(sel_pages=lists, sel_count=torch.full((B, Hkv), P, dtype=torch.int32, device=DEV))
+    weight = math.exp(4.0) / (math.exp(4.0) + P * S - 1)
+    out = sess.out.double().cpu()
+    assert torch.isfinite(out).all()
+    assert ((out / 2.0 ** 126 - weight).abs() <= 2 ** -8 * weight).all()
+    sess.dense_paged_decode()
+    assert torch.isfinite(sess.out_dense).all()
