@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
         vd[j] = load_raw_stream(valid ? vc + off + j * kTokPerLoad * D : q_row, kNT);
       }
     };
-    auto consume = [&](const Raw16(&kr)[kTileLoads], const Raw16(&vr)[kTileLoads], int rest) {
+    auto consume = [&](const Raw16(&kr)[kTileLoads], Raw16(&vr)[kTileLoads], int rest) {
       // logits of this lane group's tokens for the G heads
       float s[kTileLoads][G];
 #pragma unroll
@@ -190,6 +190,12 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
         l[g] = fmaf(l[g], alpha, psum);
 #pragma unroll
         for (int i = 0; i < kVec; ++i) acc[g][i] *= alpha;
+      }
+      // A filler's value counts as zero: a query that is infinite or NaN must not reach the outputs of the other heads.
+      if (__any(rest <= (kTileLoads - 1) * kTokPerLoad)) {
+#pragma unroll
+        for (int j = 0; j < kTileLoads; ++j)
+          if (j * kTokPerLoad >= rest) vr[j] = zero_raw();
       }
 #pragma unroll
       for (int j = 0; j < kTileLoads; ++j) {

@@ -1065,3 +1065,26 @@ def test_decode_values_near_the_top_of_the_float_range(gpu_lib, dtype, G):
     assert ((out / 2.0 ** 126 - weight).abs() <= 2 ** -8 * weight).all()
     sess.dense_paged_decode()
     assert torch.isfinite(sess.out_dense).all()
+
+
+@pytest.mark.parametrize("G,D,S", [(2, 64, 16), (4, 128, 8), (8, 64, 32)])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_a_bad_query_stays_in_its_own_head(gpu_lib, G, D, S, bad):
+    """fp32 caches: a query that holds an infinity or a NaN leaves the other heads of its group as they are, also where
+    slots without a token (a partial page, skipped entries, a wave's last tile) are computed on fillers."""
+    wl = W.build("badq", 17, dtype=torch.float32, B=2, H=2 * G, Hkv=2, D=D, S=S, seq_lens=[9 * S + 3, 5], top_k=10,
+                 key_mode="iid").to(DEV)
+    sess = DecodeSession(wl)
+    lists = torch.tensor([[9, -1, 2, 7, 10 ** 6, 0, 1], [0, -1, -1, 3, 3, 1, 1]], dtype=torch.int32, device=DEV)
+    lists = lists[:, None].expand(2, 2, 7).contiguous()
+    count = torch.full((2, 2), 7, dtype=torch.int32, device=DEV)
+    sess.sparse_paged_decode(sel_pages=lists, sel_count=count)
+    sess.dense_paged_decode()
+    torch.cuda.synchronize()
+    clean = [t.clone() for t in (sess.out, sess.lse, sess.out_dense, sess.lse_dense)]
+    wl.q[:, 0, 3] = bad  # the first head of the first group
+    sess.sparse_paged_decode(sel_pages=lists, sel_count=count)
+    sess.dense_paged_decode()
+    torch.cuda.synchronize()
+    for was, now in zip(clean, (sess.out, sess.lse, sess.out_dense, sess.lse_dense)):
+        assert torch.equal(was[:, 1:], now[:, 1:])
