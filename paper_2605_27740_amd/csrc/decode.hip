@@ -208,6 +208,13 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
       }
     };
 
+    // A page or less per wave has nothing to prefetch, and the fillers of a pipeline cost it 0.4 us (2 rounds of 8 loads: 8 rows
+    // x 64 pages, D = 64 8.2 / 7.7). With 8 heads the loop suffers from the second copy of the arithmetic (4 x 32768 tokens 97 / 121).
+    if (G < 8 && n_tiles == 1) {
+      issue(0, kb[0], vb[0], left[0]);
+      consume(kb[0], vb[0], left[0]);
+      continue;
+    }
 #pragma unroll
     for (int u = 0; u < kBuffers - 1; ++u) issue(u, kb[u], vb[u], left[u]);
     for (int t0 = 0; t0 < n_tiles; t0 += kBuffers) {
@@ -680,7 +687,8 @@ hipError_t launch_t(const CacheView& cv, const void* q, const int32_t* sel, cons
   CacheView c = cv;
   const int rows = c.B * c.Hkv;
   c.stream_nt = (int64_t)rows * max_list_len * S * D * 2 * (int64_t)sizeof(T) > kStreamNtBytes;
-  const SplitPlan plan = sel ? plan_splits(c.B, c.Hkv, max_list_len, c.max_pages_hint, S * D * 2 * (int)sizeof(T))
+  const SplitPlan plan = sel ? plan_splits(c.B, c.Hkv, max_list_len, c.max_pages_hint, S * D * 2 * (int)sizeof(T),
+                                           sizeof(T) == 4 && G == 8)
                              : most_splits(rows, max_list_len);
   float* part_o = partials;
   float* part_ml = partials + (size_t)rows * plan.num_splits * G * D;

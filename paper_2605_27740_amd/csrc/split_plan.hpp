@@ -41,17 +41,21 @@ inline SplitPlan most_splits(int rows, int max_list_len) {
 // sixteenth of it; all equal shares / this rule): 192 x 150 pages 37.0 / 20.7, 128 x 256 35.7 / 25.8, 256 x 1024 232 / 83.
 // With that bound no mixture of lengths measured slower than most_splits but one: 16 rows of 50 to 60 entries in lists of
 // 600, 14.5 against 13.6. It costs full lists that would be better uncut: 192 x 150 pages 52.4 instead of 47.6.
+// slow_arithmetic (8 query heads on the vector units, fp32 caches): a workgroup alone on its unit takes 1.2 us for a page per
+// wave, so a row goes uncut only 64 KB beyond the cut of most_splits. 8 rows x 16 pages of 8 KB: uncut 11.3, 4 chunks 9.5.
 // Where all entries that can be pages fit one chunk of most_splits, cutting the rest off gains nothing.
 // Lists longer than the sequences have pages and cut lists of 256 rows or more always have empty chunks, and these come last
 // (SplitPlan::rotate): as the fastest grid index they are a regular subset of the workgroups, which leaves whole XCDs and
 // compute units without work. 32 rows x 125 of 1024 pages: 35.1 split first, 21.7 split last; 64 x 256 of 1024: 65.2 and
 // 38.8; 256 rows of 100 to 2000 entries in lists of 8192: 1590 and 296.
-inline SplitPlan plan_splits(int batch, int kv_heads, int max_list_len, int max_pages, int page_bytes) {
+inline SplitPlan plan_splits(int batch, int kv_heads, int max_list_len, int max_pages, int page_bytes,
+                             bool slow_arithmetic) {
   constexpr int64_t kCUs = 256, kMergeBytes = 160 << 10, kLeastBytes = 64 << 10, kMoreBytes = 256 << 10, kMaxGridZ = 65535;
   const int rows = std::max(batch * kv_heads, 1);
   const SplitPlan most = most_splits(rows, max_list_len);
   const int64_t len = std::max(max_list_len, 1), filled = std::min<int64_t>(len, max_pages);
   const int64_t longest = most.pages_per_split + kMoreBytes / page_bytes;
+  const int64_t longest_uncut = most.pages_per_split + (slow_arithmetic ? kMoreBytes / 4 : kMoreBytes) / page_bytes;
   auto cost_of = [&](int64_t pps) {
     const int64_t share = (rows * ((filled + pps - 1) / pps) + kCUs - 1) / kCUs * std::min(pps, filled) * page_bytes;
     return std::max({share, rows * filled * page_bytes / kCUs * 6 / 5, kLeastBytes}) + (pps < len ? kMergeBytes : 0);
@@ -65,7 +69,7 @@ inline SplitPlan plan_splits(int batch, int kv_heads, int max_list_len, int max_
     const int64_t pps = ((len + s - 1) / s + kDecWaves - 1) / kDecWaves * kDecWaves;
     const int64_t n = (len + pps - 1) / pps, cost = cost_of(pps);
     const bool fits = n == 1 && filled <= most.pages_per_split && len <= 4 * most.pages_per_split;
-    if ((pps > longest && !fits) || n > most.num_splits || (w > 1 && cost * 10 > most_cost * 9)) continue;
+    if ((pps > (n == 1 ? longest_uncut : longest) && !fits) || n > most.num_splits || (w > 1 && cost * 10 > most_cost * 9)) continue;
     if (cost < best_cost || (w <= 1 && best_cost == most_cost && cost == most_cost)) {
       best = SplitPlan{(int32_t)pps, (int32_t)n, 0};
       best_cost = cost;

@@ -5,7 +5,7 @@ extern "C" void most(int rows, int len, int* out) {
   const unique::SplitPlan p = unique::most_splits(rows, len);
   out[0] = p.pages_per_split; out[1] = p.num_splits; out[2] = p.rotate;
 }
-extern "C" void plan(int batch, int kv_heads, int len, int max_pages, int page_bytes, int* out) {
-  const unique::SplitPlan p = unique::plan_splits(batch, kv_heads, len, max_pages, page_bytes);
+extern "C" void plan(int batch, int kv_heads, int len, int max_pages, int page_bytes, int slow, int* out) {
+  const unique::SplitPlan p = unique::plan_splits(batch, kv_heads, len, max_pages, page_bytes, slow != 0);
   out[0] = p.pages_per_split; out[1] = p.num_splits; out[2] = p.rotate;
 }
