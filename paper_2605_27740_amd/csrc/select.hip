@@ -227,7 +227,8 @@ __device__ __forceinline__ void select_keys(const uint32_t (&key)[kVecs * kPer],
   const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
 
   // ---- 1. histogram; the bucket of every counted key (-1: not counted) stays in registers unless the keys take most
-  constexpr bool kKeepBuckets = kItems <= 16;
+  // (32 keys per thread, 128 rows x 24000 pages, k = 1025: 19.8 us, 23.0 with buckets made three times)
+  constexpr bool kKeepBuckets = kItems <= 32;
   int bucket_reg[kKeepBuckets ? kItems : 1];
   auto make_bucket = [&](int j) { return key[j] >= T0 ? linear_bucket(key[j], map.lo, map.scale, kBuckets) : -1; };
 #pragma unroll
@@ -368,17 +369,18 @@ __device__ __forceinline__ void select_keys(const uint32_t (&key)[kVecs * kPer],
   }
 }
 
-// One workgroup per row, kVecs 16-byte loads of four scores per thread: thread t holds the pages
-// v * 4 * kThreads + 4 * t + i, so every load of a wave is 1 KiB of consecutive scores.
-template <int kThreads, int kVecs>
+// One workgroup per row, kVecs loads of kPer (one or four) scores per thread: thread t holds the pages
+// (v * kThreads + t) * kPer + i, so every load of a wave is 256 B or 1 KiB of consecutive scores. kCompact: the keys that
+// are not below T0 are gathered and dealt out again.
+template <int kThreads, int kVecs, int kPer, bool kCompact>
 __global__ __launch_bounds__(kThreads) void topk_select_kernel(CacheView c, const float* __restrict__ scores,
                                                                int score_stride, int top_k,
                                                                int32_t* __restrict__ sel_pages,
                                                                int32_t* __restrict__ sel_count) {
   using Sh = SelectShared<kThreads>;
-  constexpr int kWaves = Sh::kWaves, kItems = 4 * kVecs, kBuckets = Sh::kBuckets;
-  constexpr int kDense = 8;                  // keys per thread that are kept when the others are dropped
-  constexpr bool kCompact = kItems == 32;    // fewer keys gain nothing, 64 leave no registers for the second set
+  constexpr int kWaves = Sh::kWaves, kItems = kPer * kVecs, kBuckets = Sh::kBuckets;
+  constexpr int kDense = 8;  // keys per thread that are kept when the others are dropped
+  static_assert(kPer == 4 || (kPer == 1 && !kCompact), "scores per load");
   __shared__ Sh sh;
   __shared__ uint2 kept[kCompact ? kDense * kThreads : 1];
 
@@ -400,23 +402,31 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(CacheView c, cons
     return;
   }
 
-  float4 raw[kVecs];
-#pragma unroll
-  for (int v = 0; v < kVecs; ++v) {
-    const int p = v * 4 * kThreads + 4 * t;
-    raw[v] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (p < P) raw[v] = *reinterpret_cast<const float4*>(srow + p);  // the row is padded to a multiple of 4
-  }
+  auto page_of = [&](int j) { return ((j / kPer) * kThreads + t) * kPer + j % kPer; };
   uint32_t key[kItems];
+  if constexpr (kPer == 1) {
+    float raw[kVecs];
 #pragma unroll
-  for (int v = 0; v < kVecs; ++v) {
-    const int n = P - (v * 4 * kThreads + 4 * t);  // pages from this load's first one on
-    key[4 * v] = n > 0 ? score_key(raw[v].x) : 0u;
-    key[4 * v + 1] = n > 1 ? score_key(raw[v].y) : 0u;
-    key[4 * v + 2] = n > 2 ? score_key(raw[v].z) : 0u;
-    key[4 * v + 3] = n > 3 ? score_key(raw[v].w) : 0u;
+    for (int v = 0; v < kVecs; ++v) raw[v] = page_of(v) < P ? srow[page_of(v)] : 0.f;
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) key[v] = page_of(v) < P ? score_key(raw[v]) : 0u;
+  } else {
+    float4 raw[kVecs];
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) {
+      const int p = page_of(4 * v);
+      raw[v] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (p < P) raw[v] = *reinterpret_cast<const float4*>(srow + p);  // the row is padded to a multiple of 4
+    }
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) {
+      const int n = P - page_of(4 * v);  // pages from this load's first one on
+      key[4 * v] = n > 0 ? score_key(raw[v].x) : 0u;
+      key[4 * v + 1] = n > 1 ? score_key(raw[v].y) : 0u;
+      key[4 * v + 2] = n > 2 ? score_key(raw[v].z) : 0u;
+      key[4 * v + 3] = n > 3 ? score_key(raw[v].w) : 0u;
+    }
   }
-  auto page_of = [&](int j) { return (j / 4) * 4 * kThreads + 4 * t + j % 4; };
   if (c.force_recent > 0) {
     // an always-selected page takes the largest key there is (above +inf), so it outranks every score
     const int forced_from = P - min(c.force_recent, kb);
@@ -437,7 +447,7 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(CacheView c, cons
     low = max(low, key[j]);
   }
   {
-    const int busy = min(kThreads, (P + 3) / 4);  // threads with a page
+    const int busy = min(kThreads, (P + kPer - 1) / kPer);  // threads with a page
     auto merge = [&](int lanes, uint32_t other) { if (lanes * kb <= busy) low = max(low, other); };
     merge(2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)low, kDppXor1, 0xf, 0xf, true));
     merge(4, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)low, kDppXor2, 0xf, 0xf, true));
@@ -497,7 +507,7 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(CacheView c, cons
       return;
     }
   }
-  select_keys<kThreads, kVecs, 4>(key, page_of, T0, map, kb, out, sh);
+  select_keys<kThreads, kVecs, kPer>(key, page_of, T0, map, kb, out, sh);
 }
 
 // Selection by re-reading the row in every pass (it stays in L2): histogram between the row's smallest and largest
@@ -673,7 +683,22 @@ __global__ __launch_bounds__(kThreads) void topk_select_long_kernel(CacheView c,
   const int units = P / kUnit, groups = units * kThreads >= kb ? (kb + kThreads - 1) / kThreads : 0;
   const int per_group = groups > 0 ? units / groups : 0;
   uint32_t kmin = 0xffffffffu, kmax = 0u, low = 0xffffffffu, group_max = 0u;
-  for (int ch = 0; ch < chunks; ++ch) {
+  auto key_of = [&](int page) { return page >= forced_from ? kKeyForced : score_key(srow[page]); };
+  if (units == 0) {  // a short row of a long launch, which will be re-read: the extremes alone (2600 pages: 12.9 -> 10.1 us)
+    for (int p0 = 0; p0 < P; p0 += 8 * kThreads) {
+      uint32_t kk[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) kk[u] = p0 + u * kThreads + t < P ? key_of(p0 + u * kThreads + t) : 0u;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (p0 + u * kThreads >= P) break;  // uniform
+        const bool finite = kk[u] > kKeyNegInf && kk[u] < kKeyPosInf;
+        kmin = min(kmin, finite ? kk[u] : 0xffffffffu);
+        kmax = max(kmax, finite ? kk[u] : 0u);
+      }
+    }
+  }
+  for (int ch = 0; ch < chunks && units > 0; ++ch) {
     load_chunk(ch);
 #pragma unroll
     for (int u = 0; u < kVecs / kUnitVecs; ++u) {
@@ -742,7 +767,6 @@ __global__ __launch_bounds__(kThreads) void topk_select_long_kernel(CacheView c,
   }
   __syncthreads();
   if (total > kDense * kThreads) {
-    auto key_of = [&](int page) { return page >= forced_from ? kKeyForced : score_key(srow[page]); };
     select_reread<kThreads>(key_of, P, kb, bucket_map(kmin, kmax, kBuckets), out, sh);
     return;
   }
@@ -762,10 +786,12 @@ __global__ __launch_bounds__(kThreads) void topk_select_long_kernel(CacheView c,
 template <int kN>
 using Int = std::integral_constant<int, kN>;
 
-template <int kThreads, int kVecs>
+// Gathering by default where a thread holds 32 keys: fewer gain nothing, 64 leave no registers for the second set.
+template <int kThreads, int kVecs, int kPer = 4, bool kCompact = kVecs * kPer == 32>
 hipError_t launch_t(const CacheView& c, const float* scores, int stride, int top_k, int32_t* sel, int32_t* cnt,
                     hipStream_t st) {
-  topk_select_kernel<kThreads, kVecs><<<dim3(c.B * c.Hkv), dim3(kThreads), 0, st>>>(c, scores, stride, top_k, sel, cnt);
+  topk_select_kernel<kThreads, kVecs, kPer, kCompact><<<dim3(c.B * c.Hkv), dim3(kThreads), 0, st>>>(
+      c, scores, stride, top_k, sel, cnt);
   return hipGetLastError();
 }
 
@@ -779,19 +805,25 @@ hipError_t launch_select(const CacheView& c, const float* d_scores, int score_st
                                                                      d_sel_count, stream);
   };
   const int rows = c.B * c.Hkv;
-  // The smallest workgroup whose registers hold the row, unless a larger one measured faster; kernel us on rows of
+  // The smallest workgroup whose registers hold the row, unless another one measured faster; kernel us on rows of
   // planted normal scores (rows x pages, k):
+  //   8 x 256, 16: 3.8 with 256 threads and one key each, 4.1 with one wave; 640 x 256, 4: 4.6 and 4.3
   //   640 x 4096, 64: 9.5 with 512 threads, 19 with 1024 (two workgroups of 1024 per compute unit: a second round)
   //   8 x 2048, 128: 5.4 with 256 threads, 4.9 with 512; 512 x 2048, 64: 7.0 and 7.6
-  //   128 x 8192, 256: 8.4 with 512 threads, 9.2 with 1024; with k = 1024 10.8 and 10.0, but at 512 rows 14.2 and 18.5
+  //   128 x 8192, 256: 8.4 with 512 threads, 9.2 with 1024; with k = 1024 10.8 and 10.0, but at 512 rows 14.2 and 18.5 and
+  //   at 8 x 4097 8.4 and 8.9 (8 x 6000: 9.2 and 9.0)
   //   16 x 16384, 256: 10.3 with 512 threads, 11.7 with 1024; with k = 512 17 and 12.2, as a group for T0 is then a
-  //   single thread's keys and more of them are left
+  //   single thread's keys and more of them are left; 640 x 8193, 512: 20.8 and 32.5, two rounds again
+  //   16 x 32768 and k above the 1024 threads, without a bound: 25.7 with a vain attempt to gather, 20.6 without
+  if (P <= 256 && rows <= 512) return launch_t<256, 1, 1>(c, d_scores, score_stride, top_k, d_sel_pages, d_sel_count, stream);
   if (P <= 256) return go(Int<64>(), Int<1>());
   if (P <= 1024) return go(Int<256>(), Int<1>());
   if (P <= 2048) return rows > 256 ? go(Int<256>(), Int<2>()) : go(Int<512>(), Int<1>());
   if (P <= 4096) return go(Int<512>(), Int<2>());
-  if (P <= 8192) return rows <= 256 && top_k > 512 ? go(Int<1024>(), Int<2>()) : go(Int<512>(), Int<4>());
-  if (P <= 16384) return top_k <= 256 ? go(Int<512>(), Int<8>()) : go(Int<1024>(), Int<4>());
+  if (P <= 8192) return rows <= 256 && top_k > 512 && P > 5120 ? go(Int<1024>(), Int<2>()) : go(Int<512>(), Int<4>());
+  if (P <= 16384) return top_k <= (rows > 256 ? 512 : 256) ? go(Int<512>(), Int<8>()) : go(Int<1024>(), Int<4>());
+  if (P <= 32768 && top_k > 1024)
+    return launch_t<1024, 8, 4, false>(c, d_scores, score_stride, top_k, d_sel_pages, d_sel_count, stream);
   if (P <= 32768) return go(Int<1024>(), Int<8>());
   // Beyond that the long kernel (8 x 62501, 1024: 30 us; 48 with all keys in registers), but it re-reads rows that leave
   // too many keys above T0, which at these lengths is the rule from about k = 2000 on (8 x 65536, 2048: 117 us against 48)

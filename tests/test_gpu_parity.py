@@ -1088,3 +1088,41 @@ def test_a_bad_query_stays_in_its_own_head(gpu_lib, G, D, S, bad):
     torch.cuda.synchronize()
     for was, now in zip(clean, (sess.out, sess.lse, sess.out_dense, sess.lse_dense)):
         assert torch.equal(was[:, 1:], now[:, 1:])
+
+
+@pytest.mark.parametrize("n", [0, 5])
+@pytest.mark.parametrize("B,Hkv,P,top_k", [
+    (6, 2, 256, 40), (65, 8, 200, 30),                                     # one key per thread; one wave per row
+    (3, 4, 5120, 600), (3, 4, 5121, 600), (33, 8, 8200, 512), (3, 4, 8200, 512),
+    (3, 4, 20000, 1024), (3, 4, 20000, 1025), (2, 2, 32768, 20000),
+    (9, 2, 40000, 300), (9, 2, 70001, 900), (9, 2, 70001, 40000)])         # short rows of a long launch
+def test_select_ragged_rows(gpu_lib, B, Hkv, P, top_k, n):
+    """Rows of every length under one bound, scores with ties, infinities, NaN and equal rows among them, with and without
+    pages that are always kept: the set of a stable sort."""
+    S = 8
+    wl = W.build("ragsel", 18, dtype=torch.bfloat16, B=B, H=Hkv, Hkv=Hkv, D=64, S=S, seq_lens=[S] * B, top_k=top_k,
+                 key_mode="iid").to(DEV)
+    rng = np.random.default_rng(P + B)
+    pages = [int(x) for x in rng.integers(1, P + 1, size=B)]
+    for i, x in enumerate([P, 1, top_k, top_k + 1, 255, 4097, 16384, 16385, 0]):
+        if i < B and x <= P:
+            pages[i] = x
+    wl.page_table = torch.zeros((B, P), dtype=torch.int32, device=DEV)
+    wl.seq_lens = torch.tensor([S * p - (p > 1) for p in pages], dtype=torch.int32, device=DEV)
+    sess = DecodeSession(wl, max_seq_len_hint=S * P, min_seq_len_hint=0, force_recent_pages=n, want_scores=False)
+    kinds = sorted(SCORE_MAKERS)
+    scores = np.zeros((B, Hkv, (P + 3) // 4 * 4), np.float32)
+    for b in range(B):
+        for h in range(Hkv):
+            scores[b, h, :P] = SCORE_MAKERS[kinds[(b * Hkv + h) % len(kinds)]](P, b * Hkv + h)
+    sess.select_topk(torch.from_numpy(scores).to(DEV))
+    sel, cnt = sess.sel_pages.cpu().numpy(), sess.sel_count.cpu().numpy()
+    for b, p in enumerate(pages):
+        kb = min(top_k, p)
+        nf = min(n, kb)
+        for h in range(Hkv):
+            sc = scores[b, h, :p - nf].astype(np.float64) + 0.0
+            nan = np.isnan(sc)
+            order = np.lexsort((np.arange(p - nf), -np.where(nan, -np.inf, sc), nan))
+            want = np.sort(np.concatenate([order[:kb - nf], np.arange(p - nf, p)]))
+            assert cnt[b, h] == kb and np.array_equal(sel[b, h, :kb], want) and (sel[b, h, kb:] == -1).all(), (b, h, p)
