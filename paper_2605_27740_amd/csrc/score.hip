@@ -15,16 +15,12 @@
 // contiguous run per KV head (4-byte scattered stores cost a tenth of the kernel otherwise).
 #include "device_utils.hpp"
 #include "kernels.hpp"
+#include "score_tile.hpp"
 
 namespace unique {
 namespace {
 
 constexpr int kScoreWaves = 4;
-// Full tiles that a batch of known-long sequences must supply for the next larger tile: one workgroup per compute unit.
-// One sequence of 62501 pages, bf16 statistics: 128-page tiles (489 workgroups) 23.7 us, 64-page tiles 27.1, as three
-// workgroups fit a unit and 977 take a second round; 12 x 1800 to 3126 pages, fp32, G = 8: 64-page tiles 26.8, 32-page 28.4.
-constexpr int kFullTiles = 256;
-constexpr int kFatGrid = 4096;  // workgroups above which a launch can afford the next larger tile
 constexpr int kRowLanes = 8;                   // lanes per (page, head) row
 constexpr int kRowsPerWave = kWave / kRowLanes;
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -161,7 +157,9 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
 
   // A tile that may lie beyond its sequence looks at the length before it asks for anything else: in a ragged batch most
   // workgroups are such tiles, and each kept a slot for the two round trips below (32 x 128 to 4096 pages 22.2 -> 21.8 us).
-  if (tile0 >= c.min_pages_hint && tile0 >= (c.seq_lens[b] + c.S - 1) / c.S) return;
+  // Without a known bound every tile would look first, which costs an even batch 3 % (16 x 8192 pages of one head 40.6 ->
+  // 41.9).
+  if (c.min_pages_hint > 0 && tile0 >= c.min_pages_hint && tile0 >= (c.seq_lens[b] + c.S - 1) / c.S) return;
 
   // The sequence length, the page ids of all of this wave's steps (lane L holds entry L = step *
   // pages_per_step + page_in_step) and the queries are requested together; the page-table row always has
@@ -318,23 +316,10 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
                     bool refresh_tail, hipStream_t st) {
   const CacheView& c = cv;
   const bool nt = (int64_t)c.B * c.max_pages_hint * c.rec_bytes > kStreamNtBytes;
-  // Small tiles balance ragged batches and small launches over the 256 CUs; larger ones save prologues
-  // (fewer, longer streams). A tile is doubled while the batch is known to fill the chip with FULL tiles
-  // of the larger size: either every sequence is long enough by the host's lower bound (at least one
-  // workgroup of equal work per CU), or the launch has workgroups to spare whatever the lengths are.
   // A wave keeps the page ids of all its steps in its 64 lanes, which caps the tile at 64 pages per wave
   // slot (4 slots up to 8 KV heads, 2 at 16, 1 when one wave steps through all 32 heads of a page alone).
   const int wave_slots = c.Hkv <= 8 ? kScoreWaves : kScoreWaves * kRowsPerWave / c.Hkv;
-  const int max_tile = 64 * wave_slots;
-  constexpr int kMinTile = 8, kNumCUs = 256;
-  int tile = 32;
-  while (2 * tile <= max_tile &&
-         ((int64_t)c.B * (c.min_pages_hint / (2 * tile)) >= kFullTiles ||
-          (int64_t)c.B * ((c.max_pages_hint + 2 * tile - 1) / (2 * tile)) >= kFatGrid))
-    tile *= 2;
-  // a launch too small to give every CU a workgroup is all latency: shorter tiles spread it over more CUs
-  // (one sequence of 32K tokens: 10.7 us with 32-page tiles, 8.7 us with 8-page tiles)
-  while (tile > kMinTile && (int64_t)c.B * ((c.max_pages_hint + tile - 1) / tile) < kNumCUs) tile /= 2;
+  const int tile = score_tile(c.B, c.Hkv, D, c.max_pages_hint, c.min_pages_hint, 64 * wave_slots);
   dim3 grid((c.max_pages_hint + tile - 1) / tile, c.B), block(kScoreWaves * kWave);
   const size_t lds = (size_t)c.Hkv * tile * sizeof(float);
   auto go = [&](auto kernel) {

@@ -1,4 +1,5 @@
-// C interface of the decode's split plan for the CPU tests.
+// C interface of the launch rules for the CPU tests.
+#include "../../paper_2605_27740_amd/csrc/score_tile.hpp"
 #include "../../paper_2605_27740_amd/csrc/split_plan.hpp"
 
 extern "C" void most(int rows, int len, int* out) {
@@ -8,4 +9,7 @@ extern "C" void most(int rows, int len, int* out) {
 extern "C" void plan(int batch, int kv_heads, int len, int max_pages, int page_bytes, int slow, int* out) {
   const unique::SplitPlan p = unique::plan_splits(batch, kv_heads, len, max_pages, page_bytes, slow != 0);
   out[0] = p.pages_per_split; out[1] = p.num_splits; out[2] = p.rotate;
+}
+extern "C" int tile(int batch, int kv_heads, int head_dim, int max_pages, int min_pages, int max_tile) {
+  return unique::score_tile(batch, kv_heads, head_dim, max_pages, min_pages, max_tile);
 }

@@ -1,4 +1,4 @@
-"""The decode's split plan (csrc/split_plan.hpp, host arithmetic), compiled here without HIP."""
+"""The rules by which launches are cut (csrc/split_plan.hpp, csrc/score_tile.hpp: host arithmetic), compiled here without HIP."""
 import ctypes as C
 import os
 import random
@@ -12,9 +12,9 @@ MORE_BYTES = 256 << 10  # how much longer than a chunk of most_splits a chunk ma
 
 @pytest.fixture(scope="module")
 def lib(tmp_path_factory):
-    so = str(tmp_path_factory.mktemp("plan") / "split_plan.so")
+    so = str(tmp_path_factory.mktemp("rules") / "launch_rules.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-ftrapv", "-shared", "-fPIC", "-o", so,
-                    os.path.join(HERE, "c_abi", "split_plan.cpp")], check=True)
+                    os.path.join(HERE, "c_abi", "launch_rules.cpp")], check=True)
     c = C.CDLL(so)
 
     class Lib:
@@ -29,6 +29,10 @@ def lib(tmp_path_factory):
             out = (C.c_int * 3)()
             c.plan(batch, heads, length, max_pages, page_bytes, slow, out)
             return tuple(out)
+
+        @staticmethod
+        def tile(batch, heads, head_dim, max_pages, min_pages, max_tile=256):
+            return c.tile(batch, heads, head_dim, max_pages, min_pages, max_tile)
     return Lib
 
 
@@ -82,3 +86,24 @@ def test_eight_heads_on_the_vector_units_are_cut_sooner(lib):
     assert lib.plan(2, 4, 16, 2048, 8192) == (16, 1, 0)
     assert lib.plan(2, 4, 16, 2048, 8192, 1) == (4, 4, 0)
     assert lib.plan(2, 4, 12, 2048, 8192, 1) == (12, 1, 0)
+
+
+def test_score_tiles_are_powers_of_two_within_their_bounds(lib):
+    r = random.Random(2)
+    for _ in range(20000):
+        batch, heads = r.choice([r.randint(1, 40), r.randint(1, 65535)]), 1 << r.randint(0, 5)
+        most = r.choice([r.randint(1, 3000), r.randint(1, 70000), r.randint(1, 1 << 28)])
+        least = r.choice([0, most, r.randint(0, most)])
+        max_tile = 256 if heads <= 8 else 2048 // heads
+        t = lib.tile(batch, heads, r.choice([64, 128]), most, least, max_tile)
+        assert 8 <= t <= max_tile and t & (t - 1) == 0, (batch, heads, most, least)
+        if t > 32:  # larger tiles only where the batch supplies full ones for every unit, or the grid is large anyway
+            assert batch * (least // t) >= 256 or batch * -(-most // t) >= 4096, (batch, heads, most, least)
+
+
+@pytest.mark.parametrize("batch,heads,head_dim,pages,want", [
+    (4, 8, 128, 4096, 32), (16, 8, 128, 2048, 64), (4, 8, 128, 8192, 64), (8, 8, 64, 8192, 128), (30, 8, 128, 3000, 128),
+    (16, 8, 128, 8192, 256), (1, 8, 128, 62501, 128), (3, 8, 128, 9000, 64), (1, 8, 64, 62501, 64), (4, 1, 128, 4096, 64),
+    (8, 1, 128, 8192, 128), (1, 8, 128, 2048, 8)])
+def test_score_tiles_of_even_batches(lib, batch, heads, head_dim, pages, want):
+    assert lib.tile(batch, heads, head_dim, pages, pages) == want
