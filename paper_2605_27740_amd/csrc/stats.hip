@@ -13,6 +13,7 @@
 
 #include "device_utils.hpp"
 #include "kernels.hpp"
+#include "stats_bulk.hpp"
 
 namespace unique {
 namespace {
@@ -219,14 +220,7 @@ __global__ __launch_bounds__(kStatsWaves* kWave) void page_stats_kernel(CacheVie
 
 template <typename T, int D>
 hipError_t dispatch_s(const CacheView& c, const int32_t* tb, const int32_t* te, int pages_per_seq, hipStream_t st) {
-  // What bounds the bulk build is the mixture of a read stream with a few percent of writes: 131072 pages (4.29 GB of keys,
-  // 285 MB of records) take 635 us without any store; a plain stream of the same reads with the same writes beside it
-  // takes 874 to 893. A launch that writes more records than the Infinity Cache keeps therefore writes its means through in
-  // pieces of 1 KiB and its stds, 32 bytes of a line, non-temporally, with 4 items per wave: 896 us in a row with
-  // launches on other buffers and 835 after a kernel that only read, against 1013 and 855 with plain stores (8 items per wave
-  // 905 / 842; stds plain 943 / 830; all non-temporal 878 / 890). Records that fit are better left to the caches: 9 MB of
-  // them 28.4 us, 29.4 non-temporally.
-  const bool bulk = (int64_t)c.B * pages_per_seq * c.rec_bytes > kStreamNtBytes;
+  const bool bulk = stats_bulk((int64_t)c.B * pages_per_seq * c.rec_bytes, D, c.S, (int)sizeof(T), c.stats_bf16);
   const int64_t target_waves = bulk ? 262144 : 65536;
   // Enough waves to fill the chip many times over (ragged batches then balance), each with a run of
   // items that amortises its prologue. The run is a power of two, so it is a multiple or a divisor of
@@ -241,8 +235,13 @@ hipError_t dispatch_s(const CacheView& c, const int32_t* tb, const int32_t* te, 
     while (ipw * target_waves < total * c.B && ipw < (int64_t)kStatsMaxPagesPerWave * c.Hkv) ipw *= 2;
     const int64_t waves = (total + ipw - 1) / ipw;
     const dim3 grid((unsigned)((waves + kStatsWaves - 1) / kStatsWaves), c.B), block(kStatsWaves * kWave);
-    if (bulk) page_stats_kernel<T, D, S, true><<<grid, block, 0, st>>>(c, tb, te, pages_per_seq, (int)ipw);
-    else page_stats_kernel<T, D, S, false><<<grid, block, 0, st>>>(c, tb, te, pages_per_seq, (int)ipw);
+    if constexpr (stats_bulk(INT64_MAX, D, S, (int)sizeof(T), true)) {  // at some size
+      if (bulk) {
+        page_stats_kernel<T, D, S, true><<<grid, block, 0, st>>>(c, tb, te, pages_per_seq, (int)ipw);
+        return;
+      }
+    }
+    page_stats_kernel<T, D, S, false><<<grid, block, 0, st>>>(c, tb, te, pages_per_seq, (int)ipw);
   };
   switch (c.S) {
     case 8: launch(std::integral_constant<int, 8>()); break;

@@ -1,6 +1,7 @@
 // C interface of the launch rules for the CPU tests.
 #include "../../paper_2605_27740_amd/csrc/score_tile.hpp"
 #include "../../paper_2605_27740_amd/csrc/split_plan.hpp"
+#include "../../paper_2605_27740_amd/csrc/stats_bulk.hpp"
 
 extern "C" void most(int rows, int len, int* out) {
   const unique::SplitPlan p = unique::most_splits(rows, len);
@@ -12,4 +13,7 @@ extern "C" void plan(int batch, int kv_heads, int len, int max_pages, int page_b
 }
 extern "C" int tile(int batch, int kv_heads, int head_dim, int max_pages, int min_pages, int max_tile) {
   return unique::score_tile(batch, kv_heads, head_dim, max_pages, min_pages, max_tile);
+}
+extern "C" int bulk(long long record_bytes, int head_dim, int page_size, int key_bytes, int bf16_means) {
+  return unique::stats_bulk(record_bytes, head_dim, page_size, key_bytes, bf16_means != 0);
 }

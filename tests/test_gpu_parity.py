@@ -959,15 +959,16 @@ def test_decode_split_plans(gpu_lib, B, k):
 
 @pytest.mark.parametrize("stats_dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("dtype,Hkv,D,S", [(torch.bfloat16, 8, 128, 16), (torch.bfloat16, 1, 128, 8), (torch.bfloat16, 2, 64, 32),
-                                           (torch.bfloat16, 32, 64, 16), (torch.float32, 4, 128, 16), (torch.float32, 16, 64, 8)])
+                                           (torch.bfloat16, 32, 64, 16), (torch.float32, 4, 128, 16), (torch.float32, 16, 64, 8),
+                                           (torch.bfloat16, 32, 64, 32), (torch.float32, 16, 64, 16)])
 def test_stats_of_large_launches_are_the_same_bits(gpu_lib, dtype, Hkv, D, S, stats_dtype):
-    """A launch whose bounds say that it writes more than 96 MB stores the means another way (several heads at a time,
-    written through): the same sequences behind a wide page table give the same records, pad bytes untouched."""
+    """A launch whose bounds say that it writes more than 144 or 288 MB stores the means another way (several heads at a
+    time, written through): the same sequences behind a wide page table give the same records, pad bytes untouched."""
     wl = W.build("wide", 14, dtype=dtype, B=3, H=Hkv, Hkv=Hkv, D=D, S=S, seq_lens=[37 * S + 5, 1, 12 * S], top_k=4,
                  key_mode="shift", permute=True).to(DEV)
     narrow = DecodeSession(wl, stats_dtype=stats_dtype)
     narrow.update_page_stats()
-    width = (96 << 20) // (wl.B * narrow.page_stats.shape[1]) + 64
+    width = (288 << 20) // (wl.B * narrow.page_stats.shape[1]) + 64
     table = torch.zeros((wl.B, width), dtype=torch.int32, device=DEV)
     table[:, :wl.max_pages] = wl.page_table
     import dataclasses

@@ -1,4 +1,5 @@
-"""The rules by which launches are cut (csrc/split_plan.hpp, csrc/score_tile.hpp: host arithmetic), compiled here without HIP."""
+"""The rules by which launches are cut (csrc/split_plan.hpp, csrc/score_tile.hpp, csrc/stats_bulk.hpp: host
+arithmetic), compiled here without HIP."""
 import ctypes as C
 import os
 import random
@@ -33,6 +34,10 @@ def lib(tmp_path_factory):
         @staticmethod
         def tile(batch, heads, head_dim, max_pages, min_pages, max_tile=256):
             return c.tile(batch, heads, head_dim, max_pages, min_pages, max_tile)
+
+        @staticmethod
+        def bulk(mb, head_dim, page_size, key_bytes, bf16_means):
+            return bool(c.bulk(C.c_longlong(mb << 20), head_dim, page_size, key_bytes, int(bf16_means)))
     return Lib
 
 
@@ -107,3 +112,13 @@ def test_score_tiles_are_powers_of_two_within_their_bounds(lib):
     (8, 1, 128, 8192, 128), (1, 8, 128, 2048, 8)])
 def test_score_tiles_of_even_batches(lib, batch, heads, head_dim, pages, want):
     assert lib.tile(batch, heads, head_dim, pages, pages) == want
+
+
+@pytest.mark.parametrize("head_dim,page_size,key_bytes,bf16_means,least_mb", [
+    (128, 16, 2, True, 144), (64, 32, 2, True, 144), (128, 16, 4, False, 144), (128, 16, 4, True, 144),
+    (128, 8, 2, True, 288), (64, 16, 2, True, None), (64, 8, 2, True, None), (128, 16, 2, False, None),
+    (128, 32, 2, False, None)])
+def test_statistics_are_written_past_the_caches_where_that_measured_faster(lib, head_dim, page_size, key_bytes, bf16_means,
+                                                                           least_mb):
+    assert not lib.bulk(least_mb or 1 << 20, head_dim, page_size, key_bytes, bf16_means)
+    assert lib.bulk((least_mb or 1 << 20) + 1, head_dim, page_size, key_bytes, bf16_means) == (least_mb is not None)
