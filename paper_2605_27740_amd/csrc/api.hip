@@ -102,7 +102,6 @@ int make_view(const unique_cache_desc* d, unique::CacheView* v, bool need_stats,
   v->min_pages_hint = (int)std::min<int64_t>(d->min_seq_len_hint / d->page_size, hint_pages);
   v->stats_bf16 = d->stats_dtype == UNIQUE_DTYPE_BF16;
   v->rec_bytes = unique_page_stats_record_bytes(d);
-  v->stream_nt = 0;
   const int64_t tile = (int64_t)d->page_size * d->head_dim;
   v->kv_head_stride = d->kv_head_stride ? d->kv_head_stride : tile;
   v->kv_page_stride = d->kv_page_stride ? d->kv_page_stride : (int64_t)d->num_kv_heads * v->kv_head_stride;

@@ -288,12 +288,15 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
 // p.V: those are the four k that lane L has to supply for row L % 16 of A, so the probabilities never leave their lane.
 // The probabilities stay fp32: p = hi + mid + lo, three bf16 numbers of 8 bits each, exactly; the columns of the q.k
 // product are G heads times the parts, so that lane L supplies part L % 16 / G of its head (with G = 8 only two parts fit,
-// the third is a second product into the rows of the first). The rows of the parts are summed at the end.
+// the third is a second product into the rows of the first). The rows of the parts are summed at the end. An infinite value
+// gives NaN, not an infinity: the lower parts of p are often zero (inputs are assumed finite).
 // V is read so that lane L holds tokens 4 * (L / 16) + j, channels kVB * (L % 16) + e: the halves of the four tokens'
 // words are the B operand of channel e without any exchange between lanes.
 // On the vector ALUs the p.V product alone was 32 * G + 32 instructions per tile at D = 128, which made G = 8 issue-bound.
 // Kernel us before and now, with the chunks as they were: G = 8, 96 rows x 200 pages of 8 KB 43.3 / 36.0; G = 4,
-// 128 x 256 47.0 / 45.8, 256 x 64 pages of 16 KB 47.3 / 44.4 (6.05 TB/s), 640 x 64 pages of 4 KB 36.7 / 34.6.
+// 128 x 256 47.0 / 45.8, 256 x 64 pages of 16 KB 47.3 / 44.4 (6.05 TB/s), 640 x 64 pages of 4 KB 36.7 / 34.6. G = 1 and 2,
+// which use 3 and 6 of the 16 output rows, gain little but lose nothing, although G = 1 at D = 128 now has two waves per
+// SIMD and had three: 640 x 64 pages of 8 KB, G = 1 61.6 / 60.7, G = 2 62.4 / 60.8 (8 rows x 64 pages, G = 1: 8.5 / 8.8).
 // Profiling build (-DUNIQUE_DEC_STAMPS, a second library next to the product one): every wave of the matrix-core
 // kernel records the 100 MHz wall clock at kernel entry, once its page ids are resolved, after its first tile, at
 // the end of its loop and after its stores, after every tile, and the compute unit it ran on, into a device array
@@ -682,11 +685,10 @@ __global__ __launch_bounds__(kWave) void paged_decode_merge_kernel(CacheView c, 
 }
 
 template <typename T, int D, int S, int G>
-hipError_t launch_t(const CacheView& cv, const void* q, const int32_t* sel, const int32_t* cnt, int sel_stride,
+hipError_t launch_t(const CacheView& c, const void* q, const int32_t* sel, const int32_t* cnt, int sel_stride,
                     int max_list_len, float sm_scale, void* out, float* lse, float* partials, hipStream_t st) {
-  CacheView c = cv;
   const int rows = c.B * c.Hkv;
-  c.stream_nt = (int64_t)rows * max_list_len * S * D * 2 * (int64_t)sizeof(T) > kStreamNtBytes;
+  const bool stream_nt = (int64_t)rows * max_list_len * S * D * 2 * (int64_t)sizeof(T) > kStreamNtBytes;
   const SplitPlan plan = sel ? plan_splits(c.B, c.Hkv, max_list_len, c.max_pages_hint, S * D * 2 * (int)sizeof(T),
                                            sizeof(T) == 4 && G == 8)
                              : most_splits(rows, max_list_len);
@@ -699,10 +701,10 @@ hipError_t launch_t(const CacheView& cv, const void* q, const int32_t* sel, cons
                                                      part_o, part_ml, reinterpret_cast<T*>(out), lse);
   };
   if constexpr (sizeof(T) == 2) {
-    if (c.stream_nt) go(paged_decode_partial_mfma_kernel<D, S, G, true>);
+    if (stream_nt) go(paged_decode_partial_mfma_kernel<D, S, G, true>);
     else go(paged_decode_partial_mfma_kernel<D, S, G, false>);
   } else {
-    if (c.stream_nt) go(paged_decode_partial_kernel<T, D, S, G, true>);
+    if (stream_nt) go(paged_decode_partial_kernel<T, D, S, G, true>);
     else go(paged_decode_partial_kernel<T, D, S, G, false>);
   }
   hipError_t e = hipGetLastError();

@@ -136,12 +136,4 @@ __device__ __forceinline__ float cross_group_allreduce(float x, Op op) {
   return x;
 }
 
-// Order-preserving map of fp32 to uint32 (larger float -> larger key); NaN maps to 0, below everything.
-__device__ __forceinline__ uint32_t float_to_ordered(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return 0u;
-  if (u == 0x80000000u) u = 0u;  // -0 and +0 compare equal
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 }  // namespace unique

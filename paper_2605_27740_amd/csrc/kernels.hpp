@@ -19,7 +19,6 @@ struct CacheView {
   int32_t min_pages_hint;     // host lower bound on full pages of every sequence (0: unknown); sizes tiles only
   int32_t stats_bf16;         // 1: means stored as bf16, 0: fp32
   int64_t rec_bytes;          // bytes per page record of page_stats
-  int32_t stream_nt;          // set per launch: read the streamed operand with non-temporal loads
   int64_t kv_page_stride;     // elements between consecutive physical pages of k_cache (and of v_cache)
   int64_t kv_head_stride;     // elements between consecutive KV heads inside a page
   int32_t force_recent;       // the last this-many logical pages of a sequence are always selected (0: none)

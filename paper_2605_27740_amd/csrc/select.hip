@@ -1,27 +1,29 @@
 // Top-k page selection per (sequence, KV head) row (Section 3.2 of the paper, radix-based top-k).
 //
-// One workgroup per row; the row's scores are read once and stay in registers as order-preserving
-// 32-bit keys (rows of more than 32768 pages are read twice). The paper narrows the k-th largest score with two 8-bit
-// radix rounds over bf16 scores; here the scores are fp32 and the selected set has to equal an exact ranking. What
-// bounds the kernel is a chain of latencies on one compute unit and, for long rows, the instructions spent per key
-// (about 130 wave instructions per 64 keys if every key goes through every step), so the search is:
+// One workgroup per row; the row's scores are read once and stay in registers as order-preserving 32-bit keys (rows of
+// more than 32768 pages are read twice or more, except up to 65536 pages with k > 1024). The paper narrows the k-th
+// largest score with two 8-bit radix rounds over bf16 scores; here the scores are fp32 and the selected set has to equal
+// an exact ranking. What bounds the kernel is a chain of latencies on one compute unit and, for long rows, the
+// instructions spent per key (about 130 wave instructions per 64 keys if every key goes through every step), so the
+// search is:
 //   1. the row's extremes and a lower bound T0 of the k-th key: the smallest of the maxima of disjoint groups of keys,
-//      of which there are at least k. 10 to 35 % of the keys are not below it. Where a thread holds 32 keys those are
-//      gathered in LDS and dealt out again, so the remaining steps see a few keys per thread.
+//      of which there are at least k. 10 to 35 % of the keys are not below it. Where a thread holds 32 keys and
+//      k is at most 1024 those are gathered in LDS and dealt out again, so the remaining steps see a few keys per thread.
 //   2. one histogram pass over buckets that are LINEAR in the score between T0 and the row's maximum (a monotone map,
 //      so bucket order never contradicts score order). It finds the bucket holding the k-th largest score; everything in
 //      higher buckets is selected. Linear buckets spread page scores far better than the leading bits of a float (which
 //      are mostly exponent), so LDS atomics see little same-address contention and the boundary bucket holds only a
 //      handful of candidates. Every wave scans the histogram for itself, which saves two barriers.
 //   3. exact resolution among the candidates of the boundary bucket: by ranking on (key, page index) when they are few
-//      (up to 64: one per lane, every wave for itself), otherwise by four 8-bit radix rounds over their keys (this also
-//      covers degenerate rows such as all scores equal).
+//      (up to 64: one per lane, every wave for itself; up to 512 or the workgroup's threads: one per thread, pairwise),
+//      otherwise by four 8-bit radix rounds over their keys (this also covers degenerate rows such as all scores equal).
 //   4. an index-ordered compaction that emits the selected logical pages in ascending order and takes keys tied with
 //      the k-th from the lowest page index upward.
 // Kernel us before (a thread owned consecutive pages, every key went through every step) and now, planted normal scores:
-// 8 rows x 2048 pages, k 128: 5.1 / 4.9; 128 x 8192, 256: 9.0 / 8.4; 640 x 4096, 64: 17.0 / 9.6; 16 x 16384, 1024:
-// 13.5 / 12.7; 8 x 32768, 512: 22.4 / 15.0; 8 x 62501, 1024: 67.8 / 29.7; 4 x 131072, 1024: 217 / 43; all scores equal,
-// 128 x 8192: 44 / 20.
+// 8 rows x 256 pages, k 16: 3.8 / 3.8; 8 x 2048, 128: 5.1 / 4.9; 128 x 8192, 256: 9.0 / 8.4; 640 x 4096, 64: 17.0 / 9.6;
+// 16 x 16384, 1024: 13.5 / 12.7; 8 x 32768, 512: 22.4 / 15.0; 128 x 24000, 3000: 25.7 / 21.8; 8 x 62501, 1024: 67.8 / 29.7;
+// 4 x 131072, 1024: 217 / 43; all scores equal, 128 x 8192: 44 / 20. A few sizes are slower: 8 x 4097, 16 7.2 / 7.6; 8 x 8193,
+// 300 10.5 / 11.3; rows of 2600 pages under a bound of 131072 8.4 / 9.9; scores of five values, 16 x 131072 432 / 447.
 #include <type_traits>
 
 #include "device_utils.hpp"
@@ -130,7 +132,8 @@ __device__ __forceinline__ uint32_t radix_threshold(int n_items, KeyAt key_at, K
   return prefix;
 }
 
-// Keys of the register kernel: as float_to_ordered, but a NaN becomes 1 (still below -inf), so that 0 means "no page".
+// Order-preserving map of fp32 to uint32 (a larger score has a larger key; -0 and +0 are equal). A NaN becomes 1, below
+// -inf, and 0 means "no page".
 __device__ __forceinline__ uint32_t score_key(float f) {
   const uint32_t u = __float_as_uint(f + 0.f);  // -0 becomes +0
   const uint32_t k = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
