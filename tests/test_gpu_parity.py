@@ -796,8 +796,10 @@ def test_range_update_touches_only_its_pages(gpu_lib):
         Hn.check_stats_row(sess, oc, b, 3, pages=list(touched[b]))
 
 
-def test_results_are_bitwise_reproducible(gpu_lib):
-    wl = W.config3(batch=2, context=8192, top_k=64).to(DEV)
+@pytest.mark.parametrize("seq_lens", [[8192, 8192], [8192, 37, 5001, 16, 3000]])
+def test_results_are_bitwise_reproducible(gpu_lib, seq_lens):
+    wl = W.build("twice", 4, dtype=torch.bfloat16, B=len(seq_lens), H=32, Hkv=8, D=128, S=16, seq_lens=seq_lens, top_k=64,
+                 key_mode="shift", permute=True).to(DEV)
     outs = []
     for _ in range(2):
         sess = DecodeSession(wl)
@@ -900,12 +902,14 @@ def test_a_plain_c_client_runs_the_whole_path(gpu_lib):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_decode_moving_softmax_reference(gpu_lib, dtype, G, D, S, kind):
     """Logits that rise or fall by hundreds along the sequence, jump once, or are all equal, over shuffled lists with
-    entries to be skipped, cut and uncut, against float64. Tolerances: the output may be rounded to bf16 (2^-8 relative);
-    logits of magnitude 300 carry an fp32 error of about 300 * 2^-24 * sqrt(D) < 3e-4, which moves a probability, and with
-    it an output of |v| <= 6 and the lse, by that much relatively."""
+    entries to be skipped, short ones and ones long enough to be cut for every page size, against float64. Tolerances: an
+    fp32 logit errs by at most 12 roundings (4 products in a lane, 5 sums over lanes, the scale, the exponent's argument)
+    of the sum of its terms' magnitudes, which moves a probability, and with it the lse, by that much relatively and an
+    output by twice that times the largest |v|; sums of up to 700 probabilities add 2e-6 of it. A bf16 output is rounded
+    on top of that (2^-9, 2^-8 allowed)."""
     g = torch.Generator().manual_seed(G * 1000 + D + S)
     B, Hkv, N = 2, 2, 41 * S + 3
-    wl = W.build("ramp", 12, dtype=dtype, B=B, H=Hkv * G, Hkv=Hkv, D=D, S=S, seq_lens=[N, N - S + 1], top_k=64,
+    wl = W.build("ramp", 12, dtype=dtype, B=B, H=Hkv * G, Hkv=Hkv, D=D, S=S, seq_lens=[N, N - S + 1], top_k=400,
                  key_mode="iid")
     level = {"up": torch.linspace(-1, 1, 42 * S), "down": torch.linspace(1, -1, 42 * S), "flat": torch.zeros(42 * S),
              "spike": torch.where(torch.arange(42 * S) == 500, 1.0, 0.0)}[kind].view(42, 1, S, 1)
@@ -916,7 +920,7 @@ def test_decode_moving_softmax_reference(gpu_lib, dtype, G, D, S, kind):
         wl.k_cache[pages] = (wl.k_cache[pages].float() + 30 * D ** 0.5 * level[:len(pages)] * q_dir.float()).to(dtype)
     dev = wl.to(DEV)
     sess = DecodeSession(dev)
-    for width in (7, 64):  # uncut, and a list long enough to be cut
+    for width in (7, 64, 400):  # uncut but for the largest fp32 pages; as the page size decides; cut
         lists = torch.full((B, Hkv, width), -1, dtype=torch.int32)
         for b in range(B):
             for h in range(Hkv):
@@ -938,14 +942,17 @@ def test_decode_moving_softmax_reference(gpu_lib, dtype, G, D, S, kind):
                 want_lse = torch.logsumexp(logits, -1)
                 want = torch.exp(logits - want_lse[:, None]) @ v
                 got = out[b, h * G:(h + 1) * G]
-                assert ((got - want).abs() <= 2 ** -8 * want.abs() + 2e-3).all(), (width, b, h, (got - want).abs().max())
-                assert ((lse[b, h * G:(h + 1) * G] - want_lse).abs() <= 1e-3 + 3e-6 * want_lse.abs()).all(), (width, b, h)
+                err = 12 * 2.0 ** -24 * (wl.q[b, h * G:(h + 1) * G].double().abs() @ k.abs().T).max() / D ** 0.5
+                rel = 2 ** -8 if dtype == torch.bfloat16 else 0.0
+                assert ((got - want).abs() <= rel * want.abs() + (2 * err + 2e-6) * v.abs().max()).all(), (width, b, h, (got - want).abs().max())
+                assert ((lse[b, h * G:(h + 1) * G] - want_lse).abs() <= err + 2e-6 + 2.0 ** -23 * want_lse.abs()).all(), (width, b, h)
 
 
 @pytest.mark.parametrize("B,k", [(1, 16), (1, 200), (6, 64), (12, 200), (20, 32), (24, 150), (33, 300), (2, 1024)])
 def test_decode_split_plans(gpu_lib, B, k):
-    """Every outcome of the plan (uncut, one to four workgroups per compute unit, more entries than pages): the
-    attention over all pages of a list equals the dense call's, whose chunks are cut differently."""
+    """Full lists: uncut, cut in two unequal or equal chunks, 16 and 25 chunks: the attention over all pages of a list equals
+    the dense call's, whose chunks are cut differently. (Lists shorter than their bound, or longer than the sequences have
+    pages: test_decode_lists_shorter_than_their_bound.)"""
     wl = W.build("plans", 13, dtype=torch.bfloat16, B=B, H=16, Hkv=8, D=64, S=8, seq_lens=[8 * k - 3 * (b % 3) for b in range(B)],
                  top_k=k, key_mode="iid", permute=True).to(DEV)
     sess = DecodeSession(wl)
