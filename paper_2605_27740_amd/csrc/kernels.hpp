@@ -5,8 +5,9 @@
 
 namespace unique {
 
-// Device pointers and dimensions of the paged cache, passed by value to every kernel.
-struct CacheView {
+// Device pointers and dimensions of the paged cache, passed by value to every kernel. Aligned so that the arguments behind it
+// start on a 16-byte boundary and are fetched whole (the merge kernel of one 32K sequence takes 4.34 us 8 bytes further on, 4.12 so).
+struct alignas(16) CacheView {
   const void* k_cache;        // [num_phys][Hkv][S][D]
   const void* v_cache;
   void* page_stats;           // [num_phys] records: Hkv*D means (fp32 or bf16), Hkv fp32 stds, pad to kStdBlockBytes
