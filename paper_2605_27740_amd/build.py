@@ -11,6 +11,9 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libunique_gfx950.so")
 SOURCES = ["api.hip", "stats.hip", "score.hip", "select.hip", "decode.hip"]
+# step.hip is compiled once per element type and head dimension (object file, defines)
+STEP_VARIANTS = [(f"step_{t}_{d}.o", [f"-DUNIQUE_STEP_T={c}", f"-DUNIQUE_STEP_D={d}"])
+                 for t, c in (("bf16", "uint16_t"), ("f32", "float")) for d in (128, 64)]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed fp32 instructions are kept off for the device pass on purpose
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -22,8 +25,8 @@ def _deps_mtime() -> float:
     return max(os.path.getmtime(p) for p in paths)
 
 
-def _compile(src: str, extra: list[str]) -> str:
-    obj = os.path.join(OBJ_DIR, src.replace(".hip", ".o"))
+def _compile(src: str, extra: list[str], obj_name: str | None = None) -> str:
+    obj = os.path.join(OBJ_DIR, obj_name or src.replace(".hip", ".o"))
     cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
@@ -41,7 +44,9 @@ def build_library(force: bool = False, extra_flags: list[str] | None = None, job
     os.makedirs(OBJ_DIR, exist_ok=True)
     extra = list(extra_flags or [])
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        objs = list(ex.map(lambda s: _compile(s, extra), SOURCES))
+        jobs_ = [ex.submit(_compile, "step.hip", extra + defs, obj) for obj, defs in STEP_VARIANTS]
+        jobs_ += [ex.submit(_compile, s, extra) for s in SOURCES]
+        objs = [j.result() for j in jobs_]
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
@@ -71,6 +76,7 @@ def build_profiling_library(force: bool = False) -> str:
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed for the profiling build of {os.path.basename(src)}:\n{r.stderr}")
     objs = [j[2] for j in jobs] + [os.path.join(OBJ_DIR, s.replace(".hip", ".o")) for s in SOURCES if s != "decode.hip"]
+    objs += [os.path.join(OBJ_DIR, obj) for obj, _ in STEP_VARIANTS]
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", PROF_LIB_PATH, *objs],
                        capture_output=True, text=True)
     if r.returncode != 0:

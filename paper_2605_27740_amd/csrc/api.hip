@@ -10,6 +10,7 @@
 #include <mutex>
 
 #include "kernels.hpp"
+#include "step_rule.hpp"
 
 namespace {
 
@@ -172,14 +173,32 @@ int decode_step_check(const unique_cache_desc* desc, const void* d_q, int32_t to
   return UNIQUE_OK;
 }
 
-// Score -> select -> decode on one buffer: the score rows are consumed by the select kernel before the decode
-// kernel reuses the buffer for its partials.
+// Bytes of scratch with which a step may select and attend in one kernel: the score rows are still being read when the first
+// partial results are written, so these lie behind them.
+size_t fused_bytes(const unique::CacheView& v, const unique::SplitPlan& plan) {
+  return round_up(score_bytes(v), kAlign) + (plan.num_splits > 1 ? unique::plan_partial_floats(v, plan) * sizeof(float) : 0);
+}
+
+// Score -> select -> decode on one buffer of `bytes` bytes. In separate kernels the score rows are consumed by the select
+// kernel before the decode kernel reuses the buffer for its partials.
 int decode_step_launch(const unique::CacheView& v, const void* d_q, int32_t top_k, float lambda, float sm_scale,
                        int32_t refresh_tail, int32_t* d_sel_pages, int32_t* d_sel_count, void* d_out, float* d_lse_out,
-                       float* buf, hipStream_t st) {
+                       float* buf, size_t bytes, hipStream_t st) {
   const int stride = score_stride_of(v);
   hipError_t e = unique::launch_score(v, d_q, lambda, buf, stride, nullptr, refresh_tail != 0, st);
   if (e != hipSuccess) return hip_fail(e, "page score launch");
+  const unique::SplitPlan plan = unique::selection_plan(v, top_k);
+  if (unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan) && bytes >= fused_bytes(v, plan)) {
+    float* partials = buf + round_up(score_bytes(v), kAlign) / sizeof(float);
+    const unique::StepArgs a = {d_q, buf, stride, top_k, d_sel_pages, d_sel_count, sm_scale, d_out, d_lse_out, partials};
+    e = v.dtype == UNIQUE_DTYPE_F32 ? (v.D == 64 ? unique::launch_select_decode<float, 64>(v, a, st)
+                                                 : unique::launch_select_decode<float, 128>(v, a, st))
+                                    : (v.D == 64 ? unique::launch_select_decode<uint16_t, 64>(v, a, st)
+                                                 : unique::launch_select_decode<uint16_t, 128>(v, a, st));
+    if (e == hipSuccess && plan.num_splits > 1)
+      e = unique::launch_merge(v, d_sel_count, top_k, plan, partials, d_out, d_lse_out, st);
+    return e == hipSuccess ? UNIQUE_OK : hip_fail(e, "select and decode launch");
+  }
   e = unique::launch_select(v, buf, stride, top_k, d_sel_pages, d_sel_count, st);
   if (e != hipSuccess) return hip_fail(e, "top-k select launch");
   e = unique::launch_decode(v, d_q, d_sel_pages, d_sel_count, top_k, top_k, sm_scale, d_out, d_lse_out, buf, st);
@@ -211,6 +230,9 @@ int unique_workspace_bytes(const unique_cache_desc* desc, int32_t top_k, size_t*
   const size_t sp = decode_bytes(v, top_k), de = decode_bytes(v, v.max_pages_hint);
   if (sp > need) need = sp;
   if (de > need) need = de;
+  // more than any call insists on: with this much a decode step may take one kernel for selection and attention
+  const unique::SplitPlan plan = unique::selection_plan(v, top_k);
+  if (unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan)) need = std::max(need, fused_bytes(v, plan));
   *out_bytes = round_up(need, kAlign);
   return UNIQUE_OK;
 }
@@ -323,7 +345,7 @@ int unique_decode_step(const unique_cache_desc* desc, const void* d_q, int32_t t
   rc = check_workspace(d_workspace, workspace_bytes, region);
   if (rc != UNIQUE_OK) return rc;
   return decode_step_launch(v, d_q, top_k, lambda, sm_scale, refresh_tail, d_sel_pages, d_sel_count, d_out, d_lse_out,
-                            reinterpret_cast<float*>(d_workspace), (hipStream_t)stream);
+                            reinterpret_cast<float*>(d_workspace), workspace_bytes, (hipStream_t)stream);
 }
 
 int unique_decode_step_static(const unique_cache_desc* desc, const void* d_q, int32_t top_k, float lambda,
@@ -340,7 +362,7 @@ int unique_decode_step_static(const unique_cache_desc* desc, const void* d_q, in
   rc = static_scratch(&ws);
   if (rc != UNIQUE_OK) return rc;
   return decode_step_launch(v, d_q, top_k, lambda, sm_scale, refresh_tail, d_sel_pages, d_sel_count, d_out, d_lse_out,
-                            reinterpret_cast<float*>(ws), (hipStream_t)stream);
+                            reinterpret_cast<float*>(ws), UNIQUE_STATIC_SCRATCH_BYTES, (hipStream_t)stream);
 }
 
 int unique_dense_paged_decode(const unique_cache_desc* desc, const void* d_q, float sm_scale, void* d_out,

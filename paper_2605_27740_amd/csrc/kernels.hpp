@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "split_plan.hpp"
+
 namespace unique {
 
 // Device pointers and dimensions of the paged cache, passed by value to every kernel. Aligned so that the arguments behind it
@@ -50,6 +52,34 @@ hipError_t launch_select(const CacheView& c, const float* d_scores, int score_st
 hipError_t launch_decode(const CacheView& c, const void* d_q, const int32_t* d_sel_pages,
                          const int32_t* d_sel_count, int sel_stride, int max_list_len, float sm_scale,
                          void* d_out, float* d_lse_out, float* d_partials, hipStream_t stream);
+
+// Attention over the page lists of a selection and the merge of its chunks: what launch_decode does for the list d_sel_pages
+// of stride top_k, as the plan, the arguments and the parts that launch_select_decode shares with it.
+struct StepArgs {
+  const void* q;
+  const float* scores;   // [rows][score_stride]
+  int score_stride, top_k;
+  int32_t* sel_pages;
+  int32_t* sel_count;
+  float sm_scale;
+  void* out;
+  float* lse_out;
+  float* partials;       // must not overlap the scores
+};
+SplitPlan selection_plan(const CacheView& c, int top_k);
+size_t plan_partial_floats(const CacheView& c, const SplitPlan& plan);
+bool decode_streams(const CacheView& c, int max_list_len);  // K and V are read with non-temporal loads
+float decode_scale_log2(const CacheView& c, float sm_scale);
+hipError_t launch_merge(const CacheView& c, const int32_t* d_sel_count, int sel_stride, const SplitPlan& plan, float* d_partials,
+                        void* d_out, float* d_lse_out, hipStream_t stream);
+
+// Selection and attention in one kernel (step_rule.hpp says for which steps); a cut row needs launch_merge behind it.
+template <typename T, int D>
+hipError_t launch_select_decode(const CacheView& c, const StepArgs& a, hipStream_t stream);
+template <> hipError_t launch_select_decode<float, 64>(const CacheView& c, const StepArgs& a, hipStream_t stream);
+template <> hipError_t launch_select_decode<float, 128>(const CacheView& c, const StepArgs& a, hipStream_t stream);
+template <> hipError_t launch_select_decode<uint16_t, 64>(const CacheView& c, const StepArgs& a, hipStream_t stream);
+template <> hipError_t launch_select_decode<uint16_t, 128>(const CacheView& c, const StepArgs& a, hipStream_t stream);
 
 // floats of split-K partial storage needed for a list of at most max_list_len pages per row
 size_t decode_partial_floats(const CacheView& c, int max_list_len);

@@ -1,0 +1,26 @@
+// Which decode steps select and attend in one kernel. Host arithmetic on the launch's bounds only (no HIP), so that it can be
+// checked without a GPU.
+#pragma once
+#include <stdint.h>
+
+#include "split_plan.hpp"
+
+namespace unique {
+
+constexpr int kStepMaxPages = 4096;  // pages of a row: 16 scores per thread
+constexpr int kStepMaxTopK = 256;    // list entries that a workgroup keeps in the LDS
+
+// Saved are a launch and the round trips of writing and reading the list, paid is a selection by four waves in every
+// workgroup of a cut row. us of a whole step in separate kernels / so (bf16, 8 KV heads, G = 4, D = 128, pages of 16, fp32 means):
+//   1 x 2048 pages, k = 128 22.2 / 19.7; 1 x 4096, 64 22.7 / 19.7; 8 x 1000, 64 25.3 / 22.3; 40 x 64, 8 20.6 / 18.6;
+//   80 x 1000, 64 124.7 / 121.1 (uncut rows)
+// From some k on too many keys are gathered: 1 x 2048, 512 25.5 / 28.6; 1 x 1000, 300 23.1 / 24.2 (a bound on the k-th key needs
+// more than k groups of four pages; up to 512 pages it does not matter: 8 x 250, 200 34.0 / 32.4).
+// Workgroups that wait for a free unit select when the others already stream: 24 x 1000 pages cut in 5, 960 workgroups, 48.6 /
+// 47.2; but 31 x 4096, 64 120.6 / 122.4, so those rows are left apart from 512 workgroups on.
+inline bool step_fuses(int rows, int max_pages, int top_k, const SplitPlan& plan) {
+  if (max_pages > kStepMaxPages || top_k > kStepMaxTopK || (max_pages > 512 && 4 * top_k > max_pages)) return false;
+  return plan.num_splits == 1 || (int64_t)rows * plan.num_splits * std::max(max_pages, 2048) <= 1024 * 2048;
+}
+
+}  // namespace unique

@@ -2,6 +2,7 @@
 #include "../../paper_2605_27740_amd/csrc/score_tile.hpp"
 #include "../../paper_2605_27740_amd/csrc/split_plan.hpp"
 #include "../../paper_2605_27740_amd/csrc/stats_bulk.hpp"
+#include "../../paper_2605_27740_amd/csrc/step_rule.hpp"
 
 extern "C" void most(int rows, int len, int* out) {
   const unique::SplitPlan p = unique::most_splits(rows, len);
@@ -16,4 +17,8 @@ extern "C" int tile(int batch, int kv_heads, int head_dim, int max_pages, int mi
 }
 extern "C" int bulk(long long record_bytes, int head_dim, int page_size, int key_bytes, int bf16_means) {
   return unique::stats_bulk(record_bytes, head_dim, page_size, key_bytes, bf16_means != 0);
+}
+extern "C" int fuses(int batch, int kv_heads, int max_pages, int top_k, int page_bytes) {
+  return unique::step_fuses(batch * kv_heads, max_pages, top_k,
+                            unique::plan_splits(batch, kv_heads, top_k, max_pages, page_bytes, false));
 }

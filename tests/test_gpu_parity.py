@@ -1134,3 +1134,50 @@ def test_select_ragged_rows(gpu_lib, B, Hkv, P, top_k, n):
             order = np.lexsort((np.arange(p - nf), -np.where(nan, -np.inf, sc), nan))
             want = np.sort(np.concatenate([order[:kb - nf], np.arange(p - nf, p)]))
             assert cnt[b, h] == kb and np.array_equal(sel[b, h, :kb], want) and (sel[b, h, kb:] == -1).all(), (b, h, p)
+
+
+@pytest.mark.parametrize("P", [1, 5, 127, 256, 512, 513, 1023, 1024, 1025, 2048, 2049, 4095, 4096, 4097])
+def test_step_with_the_selection_in_the_attention_kernel(gpu_lib, P):
+    """unique_decode_step on planted scores against the separate calls, at the edges of the rows, budgets and score
+    distributions that it serves in one kernel: every output is the same bits. Also with the smallest workspace that is
+    accepted, with which it has to take two kernels."""
+    ks = sorted({1, min(P, 7), max(1, P // 4), max(1, min(P - 1, 200)), 256, 257})
+    wl = W.build("planted", 9, dtype=torch.bfloat16 if P % 2 else torch.float32, B=2, H=8, Hkv=2, D=64, S=8,
+                 seq_lens=[8 * P, max(8 * P - 3 - 8 * (P // 3), 1)], top_k=1, key_mode="iid", permute=True, poison=False).to(DEV)
+    wl.q.zero_()
+    wl.q[..., 0] = 1.0
+    for kind in ("normal", "heavy_ties", "all_equal", "two_values", "nan_and_inf", "huge_range"):
+        for recent, k in [(0, k) for k in ks] + [(3, ks[len(ks) // 2])]:
+            apart = DecodeSession(wl, top_k=k, force_recent_pages=recent, min_seq_len_hint=0)
+            step = DecodeSession(wl, top_k=k, force_recent_pages=recent, min_seq_len_hint=0)
+            apart.page_stats.zero_()
+            for b in range(2):
+                for h in range(2):
+                    n = wl.num_pages(b)
+                    sc = torch.from_numpy(SCORE_MAKERS[kind](n, 10 * b + h).astype(np.float32)).to(DEV)
+                    apart.page_mean[wl.page_table[b, :n].long(), h, 0] = sc
+            step.page_stats.copy_(apart.page_stats)
+            apart.score_select_topk()
+            apart.sparse_paged_decode()
+            step.decode_step(refresh_tail=False)
+
+            def same():
+                torch.cuda.synchronize()
+                for name in ("sel_pages", "sel_count", "lse"):
+                    assert torch.equal(getattr(apart, name), getattr(step, name)), (name, kind, k, recent)
+                assert torch.equal(apart.out.view(torch.uint8), step.out.view(torch.uint8)), (kind, k, recent)
+
+            same()
+            if kind != "normal":
+                continue
+            whole, size = step.workspace, 256
+            while True:  # refused sizes are refused before anything is launched
+                step.workspace = whole[:size]
+                try:
+                    step.decode_step(refresh_tail=False)
+                    break
+                except binding.UniqueError as e:
+                    assert e.code == binding.ERR_WORKSPACE
+                    size += 256
+            assert size <= whole.numel()
+            same()

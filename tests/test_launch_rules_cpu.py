@@ -38,6 +38,10 @@ def lib(tmp_path_factory):
         @staticmethod
         def bulk(mb, head_dim, page_size, key_bytes, bf16_means):
             return bool(c.bulk(C.c_longlong(mb << 20), head_dim, page_size, key_bytes, int(bf16_means)))
+
+        @staticmethod
+        def fuses(batch, heads, max_pages, top_k, page_bytes=8192):
+            return bool(c.fuses(batch, heads, max_pages, top_k, page_bytes))
     return Lib
 
 
@@ -122,3 +126,10 @@ def test_statistics_are_written_past_the_caches_where_that_measured_faster(lib, 
                                                                            least_mb):
     assert not lib.bulk(least_mb or 1 << 20, head_dim, page_size, key_bytes, bf16_means)
     assert lib.bulk((least_mb or 1 << 20) + 1, head_dim, page_size, key_bytes, bf16_means) == (least_mb is not None)
+
+
+@pytest.mark.parametrize("batch,heads,pages,top_k,want", [
+    (1, 8, 4096, 256, True), (1, 8, 4097, 256, False), (1, 8, 4096, 257, False), (1, 8, 512, 200, True), (1, 8, 513, 200, False),
+    (80, 8, 4096, 64, True), (24, 8, 1000, 64, True), (31, 8, 4096, 64, False)])
+def test_steps_that_select_and_attend_in_one_kernel(lib, batch, heads, pages, top_k, want):
+    assert lib.fuses(batch, heads, pages, top_k) == want
