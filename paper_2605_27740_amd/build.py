@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libunique_gfx950.so")
-SOURCES = ["api.hip", "stats.hip", "score.hip", "select.hip", "decode.hip"]
+SOURCES = ["api.hip", "stats.hip", "score.hip", "select.hip", "select_grouped.hip", "decode.hip"]
 # step.hip is compiled once per element type and head dimension (object file, defines)
 STEP_VARIANTS = [(f"step_{t}_{d}.o", [f"-DUNIQUE_STEP_T={c}", f"-DUNIQUE_STEP_D={d}"])
                  for t, c in (("bf16", "uint16_t"), ("f32", "float")) for d in (128, 64)]

@@ -173,6 +173,16 @@ int decode_step_check(const unique_cache_desc* desc, const void* d_q, int32_t to
   return UNIQUE_OK;
 }
 
+// Group maxima of the scores, for the selections that use them: the workspace may hold them behind the score rows.
+size_t group_max_bytes(const unique::CacheView& v) {
+  return (size_t)v.B * v.Hkv * (score_stride_of(v) / unique::kGroupPages) * sizeof(uint32_t);
+}
+uint32_t* group_max_in(const unique::CacheView& v, int32_t top_k, float* buf, size_t bytes) {
+  const size_t at = round_up(score_bytes(v), kAlign);
+  if (!unique::select_uses_groups(v, top_k) || bytes < at + group_max_bytes(v)) return nullptr;
+  return reinterpret_cast<uint32_t*>(buf + at / sizeof(float));
+}
+
 // Bytes of scratch with which a step may select and attend in one kernel: the score rows are still being read when the first
 // partial results are written, so these lie behind them.
 size_t fused_bytes(const unique::CacheView& v, const unique::SplitPlan& plan) {
@@ -185,7 +195,8 @@ int decode_step_launch(const unique::CacheView& v, const void* d_q, int32_t top_
                        int32_t refresh_tail, int32_t* d_sel_pages, int32_t* d_sel_count, void* d_out, float* d_lse_out,
                        float* buf, size_t bytes, hipStream_t st) {
   const int stride = score_stride_of(v);
-  hipError_t e = unique::launch_score(v, d_q, lambda, buf, stride, nullptr, refresh_tail != 0, st);
+  uint32_t* group_max = group_max_in(v, top_k, buf, bytes);
+  hipError_t e = unique::launch_score(v, d_q, lambda, buf, stride, nullptr, group_max, refresh_tail != 0, st);
   if (e != hipSuccess) return hip_fail(e, "page score launch");
   const unique::SplitPlan plan = unique::selection_plan(v, top_k);
   if (unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan) && bytes >= fused_bytes(v, plan)) {
@@ -199,7 +210,7 @@ int decode_step_launch(const unique::CacheView& v, const void* d_q, int32_t top_
       e = unique::launch_merge(v, d_sel_count, top_k, plan, partials, d_out, d_lse_out, st);
     return e == hipSuccess ? UNIQUE_OK : hip_fail(e, "select and decode launch");
   }
-  e = unique::launch_select(v, buf, stride, top_k, d_sel_pages, d_sel_count, st);
+  e = unique::launch_select(v, buf, group_max, stride, top_k, d_sel_pages, d_sel_count, st);
   if (e != hipSuccess) return hip_fail(e, "top-k select launch");
   e = unique::launch_decode(v, d_q, d_sel_pages, d_sel_count, top_k, top_k, sm_scale, d_out, d_lse_out, buf, st);
   return e == hipSuccess ? UNIQUE_OK : hip_fail(e, "sparse decode launch");
@@ -230,9 +241,11 @@ int unique_workspace_bytes(const unique_cache_desc* desc, int32_t top_k, size_t*
   const size_t sp = decode_bytes(v, top_k), de = decode_bytes(v, v.max_pages_hint);
   if (sp > need) need = sp;
   if (de > need) need = de;
-  // more than any call insists on: with this much a decode step may take one kernel for selection and attention
+  // more than any call insists on: with this much a decode step may take one kernel for selection and attention, and a
+  // selection may use the group maxima
   const unique::SplitPlan plan = unique::selection_plan(v, top_k);
   if (unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan)) need = std::max(need, fused_bytes(v, plan));
+  if (unique::select_uses_groups(v, top_k)) need = std::max(need, round_up(score_bytes(v), kAlign) + group_max_bytes(v));
   *out_bytes = round_up(need, kAlign);
   return UNIQUE_OK;
 }
@@ -274,9 +287,10 @@ int unique_score_select_topk(const unique_cache_desc* desc, const void* d_q, int
   if (rc != UNIQUE_OK) return rc;
   float* scores = reinterpret_cast<float*>(d_workspace);
   const int stride = score_stride_of(v);
-  hipError_t e = unique::launch_score(v, d_q, lambda, scores, stride, d_scores_out, false, (hipStream_t)stream);
+  uint32_t* group_max = group_max_in(v, top_k, scores, workspace_bytes);
+  hipError_t e = unique::launch_score(v, d_q, lambda, scores, stride, d_scores_out, group_max, false, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "page score launch");
-  e = unique::launch_select(v, scores, stride, top_k, d_sel_pages, d_sel_count, (hipStream_t)stream);
+  e = unique::launch_select(v, scores, group_max, stride, top_k, d_sel_pages, d_sel_count, (hipStream_t)stream);
   return e == hipSuccess ? UNIQUE_OK : hip_fail(e, "top-k select launch");
 }
 
@@ -292,7 +306,7 @@ int unique_page_scores(const unique_cache_desc* desc, const void* d_q, float lam
   if (score_stride < v.max_pages_hint || score_stride % 4 != 0)
     return fail(UNIQUE_ERR_INVALID_ARG, "score_stride %d must be a multiple of 4 and >= %d pages", score_stride,
                 v.max_pages_hint);
-  const hipError_t e = unique::launch_score(v, d_q, lambda, d_scores, score_stride, nullptr, false, (hipStream_t)stream);
+  const hipError_t e = unique::launch_score(v, d_q, lambda, d_scores, score_stride, nullptr, nullptr, false, (hipStream_t)stream);
   return e == hipSuccess ? UNIQUE_OK : hip_fail(e, "page score launch");
 }
 
@@ -308,7 +322,7 @@ int unique_select_topk(const unique_cache_desc* desc, const float* d_scores, int
   if (score_stride < v.max_pages_hint || score_stride % 4 != 0)
     return fail(UNIQUE_ERR_INVALID_ARG, "score_stride %d must be a multiple of 4 and >= %d pages", score_stride,
                 v.max_pages_hint);
-  const hipError_t e = unique::launch_select(v, d_scores, score_stride, top_k, d_sel_pages, d_sel_count,
+  const hipError_t e = unique::launch_select(v, d_scores, nullptr, score_stride, top_k, d_sel_pages, d_sel_count,
                                              (hipStream_t)stream);
   return e == hipSuccess ? UNIQUE_OK : hip_fail(e, "top-k select launch");
 }

@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
       }
     }
   };
-  decode_chunk<D, S, G, kNT>(c, q, chunk, lookup, scale_log2, to, sh);
+  decode_chunk<D, S, G, kNT>(c, q, chunk, wave, lane, lookup, scale_log2, to, sh);
 }
 
 // Log-sum-exp merge of the chunk partials of one (sequence, query head); writes out (and lse).

@@ -75,7 +75,7 @@ struct DecodeShared {  // the waves' results, merged at the end; bf16 caches: ou
 // us before (predicated loads, run-time choice) and now: 128 rows x 128 pages of 16 KB, G = 4 62.9 / 45.8 (5.9 TB/s);
 // all of 4 x 32768 tokens, G = 8 224 / 197; 2 rows x 16 pages of 8 KB 7.8 / 6.4.
 template <int D, int S, int G, bool kNT, typename Lookup>
-__device__ __forceinline__ void decode_chunk(const CacheView& c, const float* __restrict__ q, const Chunk& k, Lookup lookup,
+__device__ __forceinline__ void decode_chunk(const CacheView& c, const float* __restrict__ q, const Chunk& k, int wave, int lane, Lookup lookup,
                                              float scale_log2, const ChunkOut<float>& to, DecodeShared<float, D, G>& sh) {
   using T = float;
   constexpr int kVec = Elem<T>::kVec;
@@ -87,7 +87,6 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const float* __
   constexpr int kBuffers = 2;  // register tiles per wave (three and four measured no faster)
   static_assert(S % kTokPerLoad == 0 && kLoads % kTileLoads == 0, "page size / element type combination");
 
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
   const int hkv = k.hkv, b = k.b, row = k.row, split = k.split, begin = k.begin, end = k.end, num_splits = to.num_splits;
 
   const int tr = lane / kLanesPerTok, ch = lane % kLanesPerTok;
@@ -351,7 +350,7 @@ constexpr int kDecBuffers = 2;
 
 // kNT: K and V are read with non-temporal loads (a launch that streams more than the caches hold).
 template <int D, int S, int G, bool kNT, typename Lookup>
-__device__ __forceinline__ void decode_chunk(const CacheView& c, const bf16_t* __restrict__ q, const Chunk& k, Lookup lookup,
+__device__ __forceinline__ void decode_chunk(const CacheView& c, const bf16_t* __restrict__ q, const Chunk& k, int wave, int lane, Lookup lookup,
                                              float scale_log2, const ChunkOut<bf16_t>& to, DecodeShared<bf16_t, D, G>& sh) {
   constexpr int kVec = 8;
   constexpr int kTile = 16;                          // token slots per MFMA tile
@@ -361,7 +360,6 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const bf16_t* _
   constexpr float kRoom = 6.f;                       // log2: how far above the largest logit the reference is put
   static_assert(G <= 8, "at most 8 query heads per KV head");
 
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
   const int hkv = k.hkv, b = k.b, row = k.row, split = k.split, begin = k.begin, end = k.end, num_splits = to.num_splits;
 
   const int kt = lane % 16, kg = lane / 16;  // column (token slot of K, head and part of p, channel block of V); lane group

@@ -108,6 +108,14 @@ __device__ __forceinline__ int wave_inclusive_scan(int x) {
   return x;
 }
 
+// Order-preserving map of fp32 to uint32 (a larger score has a larger key; -0 and +0 are equal). A NaN becomes 1, below
+// -inf, and 0 means "no page".
+__device__ __forceinline__ uint32_t score_key(float f) {
+  const uint32_t u = __float_as_uint(f + 0.f);  // -0 becomes +0
+  const uint32_t k = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+  return f != f ? 1u : k;
+}
+
 struct OpSum { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
 struct OpMax { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 

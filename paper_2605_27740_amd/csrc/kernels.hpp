@@ -32,6 +32,7 @@ constexpr int64_t kStreamNtBytes = 96ll << 20;
 
 constexpr int kStdBlockBytes = 128;     // bytes reserved after the means of a page record (fp32 stds + pad)
 constexpr int kScoreStrideAlign = 64;  // score rows in the workspace are padded to this many floats
+constexpr int kGroupPages = 8;         // consecutive pages that share an entry of the group maxima
 
 bool stats_supported(int dtype, int D, int S);
 bool score_supported(int dtype, int D, int G, int Hkv);
@@ -42,11 +43,19 @@ hipError_t launch_stats(const CacheView& c, const int32_t* d_tok_begin, const in
 
 // refresh_tail: the workgroup that scores the last page of a sequence first recomputes that page's
 // statistics from the keys (the same arithmetic as launch_stats) and stores them.
+// d_group_max: [rows][score_stride / kGroupPages], the largest key (score_key) of every group of pages; null: not wanted.
 hipError_t launch_score(const CacheView& c, const void* d_q, float lambda, float* d_scores, int score_stride,
-                        float* d_scores_out, bool refresh_tail, hipStream_t stream);
+                        float* d_scores_out, uint32_t* d_group_max, bool refresh_tail, hipStream_t stream);
 
-hipError_t launch_select(const CacheView& c, const float* d_scores, int score_stride, int top_k,
+// d_group_max: of the same scores, or null
+hipError_t launch_select(const CacheView& c, const float* d_scores, const uint32_t* d_group_max, int score_stride, int top_k,
                          int32_t* d_sel_pages, int32_t* d_sel_count, hipStream_t stream);
+
+// The selection for rows whose group maxima are known, which reads only the groups that can hold a selected page; whether a
+// launch is one of those that it is the faster one for.
+bool select_uses_groups(const CacheView& c, int top_k);
+hipError_t launch_select_grouped(const CacheView& c, const float* d_scores, const uint32_t* d_group_max, int score_stride,
+                                 int top_k, int32_t* d_sel_pages, int32_t* d_sel_count, hipStream_t stream);
 
 // d_sel_pages == nullptr: attend every page of each sequence (dense).
 hipError_t launch_decode(const CacheView& c, const void* d_q, const int32_t* d_sel_pages,

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
                                                                         float lambda, float* __restrict__ scores,
                                                                         int score_stride,
                                                                         float* __restrict__ scores_out,
-                                                                        int refresh_tail, int tile_pages) {
+                                                                        uint32_t* __restrict__ group_max, int refresh_tail, int tile_pages) {
   constexpr int kE = Elem<TS>::kVec;                 // mean elements per 16-byte load
   constexpr int kChunks = D / (kE * kRowLanes);      // 16-byte loads per lane per row
   // Records in flight per wave. bf16 means in launches that stream from memory: four (80 x 4096 pages 117 us, two 122);
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
 
   const char* stats = reinterpret_cast<const char*>(c.page_stats);
   const int64_t std_off = (int64_t)c.Hkv * D * (int64_t)sizeof(TS);  // byte offset of the stds inside a record
-  extern __shared__ float tile_scores[];  // [Hkv][tile_pages]
+  extern __shared__ __attribute__((aligned(16))) float tile_scores[];  // [Hkv][tile_pages]
 
   const int n_steps = (tile_end - (tile0 + wave_slot * pages_per_step) + step_pages - 1) / step_pages;  // may be <= 0
   const int my_phys = (my_page < tile_end && my_phys_raw >= 0 && (int64_t)my_phys_raw < c.num_phys) ? my_phys_raw : -1;
@@ -309,11 +309,28 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
       if (scores_out) scores_out[((int64_t)b * c.Hkv + h) * c.max_pages + tile0 + pp] = v;
     }
   }
+  if (group_max) {  // a thread per group of pages; tiles are multiples of it
+    for (int idx = threadIdx.x; idx < c.Hkv * tile_pages / kGroupPages; idx += kScoreWaves * kWave) {
+      const int first = idx * kGroupPages, h = first >> tshift, pp = first & (tile_pages - 1);
+      if (pp >= tile_len) continue;
+      float top = __uint_as_float(0x7fc00000u);  // the maximum ignores NaN
+#pragma unroll
+      for (int i = 0; i < kGroupPages; i += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(&tile_scores[first + i]);
+        top = fmaxf(top, v.x);
+        top = pp + i + 1 < tile_len ? fmaxf(top, v.y) : top;
+        top = pp + i + 2 < tile_len ? fmaxf(top, v.z) : top;
+        top = pp + i + 3 < tile_len ? fmaxf(top, v.w) : top;
+        if (pp + i + 4 >= tile_len) break;
+      }
+      group_max[((int64_t)b * c.Hkv + h) * (score_stride / kGroupPages) + (tile0 + pp) / kGroupPages] = score_key(top);
+    }
+  }
 }
 
 template <typename T, int D, int G>
 hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* scores, int stride, float* out,
-                    bool refresh_tail, hipStream_t st) {
+                    uint32_t* group_max, bool refresh_tail, hipStream_t st) {
   const CacheView& c = cv;
   const bool nt = (int64_t)c.B * c.max_pages_hint * c.rec_bytes > kStreamNtBytes;
   // A wave keeps the page ids of all its steps in its 64 lanes, which caps the tile at 64 pages per wave
@@ -323,7 +340,7 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
   dim3 grid((c.max_pages_hint + tile - 1) / tile, c.B), block(kScoreWaves * kWave);
   const size_t lds = (size_t)c.Hkv * tile * sizeof(float);
   auto go = [&](auto kernel) {
-    kernel<<<grid, block, lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, scores, stride, out, refresh_tail,
+    kernel<<<grid, block, lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, scores, stride, out, group_max, refresh_tail,
                                      tile);
   };
   if (c.stats_bf16) {
@@ -338,12 +355,12 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
 
 template <typename T, int D>
 hipError_t dispatch_g(const CacheView& c, const void* q, float lambda, float* scores, int stride, float* out,
-                      bool refresh_tail, hipStream_t st) {
+                      uint32_t* group_max, bool refresh_tail, hipStream_t st) {
   switch (c.H / c.Hkv) {
-    case 1: return launch_t<T, D, 1>(c, q, lambda, scores, stride, out, refresh_tail, st);
-    case 2: return launch_t<T, D, 2>(c, q, lambda, scores, stride, out, refresh_tail, st);
-    case 4: return launch_t<T, D, 4>(c, q, lambda, scores, stride, out, refresh_tail, st);
-    case 8: return launch_t<T, D, 8>(c, q, lambda, scores, stride, out, refresh_tail, st);
+    case 1: return launch_t<T, D, 1>(c, q, lambda, scores, stride, out, group_max, refresh_tail, st);
+    case 2: return launch_t<T, D, 2>(c, q, lambda, scores, stride, out, group_max, refresh_tail, st);
+    case 4: return launch_t<T, D, 4>(c, q, lambda, scores, stride, out, group_max, refresh_tail, st);
+    case 8: return launch_t<T, D, 8>(c, q, lambda, scores, stride, out, group_max, refresh_tail, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -358,13 +375,13 @@ bool score_supported(int dtype, int D, int G, int Hkv) {
 }
 
 hipError_t launch_score(const CacheView& c, const void* d_q, float lambda, float* d_scores, int score_stride,
-                        float* d_scores_out, bool refresh_tail, hipStream_t stream) {
+                        float* d_scores_out, uint32_t* d_group_max, bool refresh_tail, hipStream_t stream) {
   if (c.dtype == 0) {
-    return c.D == 64 ? dispatch_g<float, 64>(c, d_q, lambda, d_scores, score_stride, d_scores_out, refresh_tail, stream)
-                     : dispatch_g<float, 128>(c, d_q, lambda, d_scores, score_stride, d_scores_out, refresh_tail, stream);
+    return c.D == 64 ? dispatch_g<float, 64>(c, d_q, lambda, d_scores, score_stride, d_scores_out, d_group_max, refresh_tail, stream)
+                     : dispatch_g<float, 128>(c, d_q, lambda, d_scores, score_stride, d_scores_out, d_group_max, refresh_tail, stream);
   }
-  return c.D == 64 ? dispatch_g<bf16_t, 64>(c, d_q, lambda, d_scores, score_stride, d_scores_out, refresh_tail, stream)
-                   : dispatch_g<bf16_t, 128>(c, d_q, lambda, d_scores, score_stride, d_scores_out, refresh_tail, stream);
+  return c.D == 64 ? dispatch_g<bf16_t, 64>(c, d_q, lambda, d_scores, score_stride, d_scores_out, d_group_max, refresh_tail, stream)
+                   : dispatch_g<bf16_t, 128>(c, d_q, lambda, d_scores, score_stride, d_scores_out, d_group_max, refresh_tail, stream);
 }
 
 }  // namespace unique

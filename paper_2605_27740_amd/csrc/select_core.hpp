@@ -107,14 +107,6 @@ __device__ __forceinline__ uint32_t radix_threshold(int n_items, KeyAt key_at, K
   return prefix;
 }
 
-// Order-preserving map of fp32 to uint32 (a larger score has a larger key; -0 and +0 are equal). A NaN becomes 1, below
-// -inf, and 0 means "no page".
-__device__ __forceinline__ uint32_t score_key(float f) {
-  const uint32_t u = __float_as_uint(f + 0.f);  // -0 becomes +0
-  const uint32_t k = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-  return f != f ? 1u : k;
-}
-
 // Exclusive prefix of counts[v * kWaves + wave] (kVecs * kWaves counts in LDS, at most 256) for every v, and their total.
 template <int kVecs, int kWaves>
 __device__ __forceinline__ int wave_prefixes(const int* counts, int wave, int (&prefix)[kVecs]) {
@@ -418,6 +410,113 @@ __device__ __forceinline__ uint32_t bound_row(const uint32_t (&key)[kVecs * kPer
   if (T0 > kKeyNegInf && T0 < kKeyPosInf) kmin = T0;
   map = bucket_map(kmin, kmax, kBuckets);
   return T0;
+}
+
+// Selection by re-reading the row in every pass (it stays in L2): histogram between the row's smallest and largest
+// finite key, candidates, compaction. Thread t owns the pages t, t + threads, t + 2*threads, ... so that every read of the
+// row is coalesced, eight reads at a time. The compaction walks the row in blocks of `threads` consecutive pages and
+// places each selected page by a ballot prefix inside its wave, the wave totals of the block (LDS) and the running
+// totals of the blocks before it, which keeps the output in ascending page order and takes keys tied with the k-th from
+// the lowest page upward. The histogram in `sh` is zero and sh.ncand is 0. All threads call it.
+template <int kThreads, typename KeyOf>
+__device__ __forceinline__ void select_reread(KeyOf key_of, int P, int kb, BucketMap map, int32_t* out,
+                                              SelectShared<kThreads>& sh) {
+  using Sh = SelectShared<kThreads>;
+  constexpr int kWaves = Sh::kWaves, kBuckets = Sh::kBuckets, kMaxRank = Sh::kMaxRank;
+  const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+  const int ipt = (P + kThreads - 1) / kThreads;  // strided items per thread; the last ones may fall past P
+  auto for_each_key = [&](auto f) {               // f(page, key) for every page this thread owns
+    for (int j0 = 0; j0 < ipt; j0 += 8) {
+      uint32_t kk[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int page = (j0 + u) * kThreads + t;
+        kk[u] = page < P ? key_of(page) : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int page = (j0 + u) * kThreads + t;
+        if (page < P) f(page, kk[u]);
+      }
+    }
+  };
+
+  // ---- 1. histogram
+  auto bucket_of = [&](uint32_t k) { return linear_bucket(k, map.lo, map.scale, kBuckets); };
+  if (map.scale == 0.f) for_each_key([&](int, uint32_t k) { add_one(sh.hist, Sh::slot(bucket_of(k))); });
+  else for_each_key([&](int, uint32_t k) { atomicAdd(&sh.hist[Sh::slot(bucket_of(k))], 1); });
+  __syncthreads();
+  int bstar, need, ncand;  // need: how many of the boundary bucket's ncand keys are selected
+  boundary_bucket<kThreads>(sh, kb, bstar, need, ncand);
+
+  // ---- 2. exact threshold inside the boundary bucket: key T and how many keys equal to T to take
+  uint32_t T;
+  if (ncand <= kMaxRank) {
+    for_each_key([&](int page, uint32_t k) {
+      if (bucket_of(k) == bstar) {
+        const int at = atomicAdd(&sh.ncand, 1);
+        sh.cand_key[at] = k;
+        sh.cand_page[at] = page;
+      }
+    });
+    __syncthreads();
+    if (t < ncand) {
+      const uint32_t mk = sh.cand_key[t];
+      const int mi = sh.cand_page[t];
+      int rank = 0, greater = 0;
+      for (int j = 0; j < ncand; ++j) {
+        const uint32_t k = sh.cand_key[j];
+        greater += k > mk;
+        rank += (k > mk) || (k == mk && sh.cand_page[j] < mi);
+      }
+      if (rank == need - 1) { sh.prefix = mk; sh.need = need - greater; }
+    }
+    __syncthreads();
+    T = sh.prefix;
+    need = sh.need;
+  } else {
+    T = radix_threshold<kThreads, 0>(
+        ipt, [&](int j) { return key_of(j * kThreads + t); },
+        [&](int j) { return j * kThreads + t < P && bucket_of(key_of(j * kThreads + t)) == bstar; }, need, sh.hist,
+        &sh.prefix, &sh.need);
+  }
+
+  // ---- 3. compaction in page order. "gt": above the k-th key; "eq": equal to it.
+  int gt_run = 0, eq_run = 0;  // such pages in the blocks already walked
+  constexpr int kAhead = 8;    // blocks whose keys are read together, ahead of the barriers that walk them
+  for (int base0 = 0, it = 0; base0 < P; base0 += kAhead * kThreads) {
+    uint32_t kk[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int page = base0 + u * kThreads + t;
+      kk[u] = page < P ? key_of(page) : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u, ++it) {
+      const int page = base0 + u * kThreads + t;
+      if (base0 + u * kThreads >= P) break;  // uniform
+      const bool gt = page < P && kk[u] > T, eq = page < P && kk[u] == T;
+      const unsigned long long bg = __ballot(gt), be = __ballot(eq);
+      int* wave_gt = sh.sure_cnt + (it & 1) * kWaves;
+      int* wave_eq = sh.tie_cnt + (it & 1) * kWaves;
+      if (lane == 0) { wave_gt[wave] = __popcll(bg); wave_eq[wave] = __popcll(be); }
+      __syncthreads();  // the buffers alternate, so one barrier per block is enough
+      int gt_before = lanes_before(bg, gt_run), eq_before = lanes_before(be, eq_run);
+      int gt_block = 0, eq_block = 0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const int g = wave_gt[w], e = wave_eq[w];
+        gt_before += w < wave ? g : 0;
+        eq_before += w < wave ? e : 0;
+        gt_block += g;
+        eq_block += e;
+      }
+      if (gt) out[gt_before + min(eq_before, need)] = page;
+      else if (eq && eq_before < need) out[gt_before + eq_before] = page;
+      gt_run += gt_block;
+      eq_run += eq_block;
+    }
+  }
 }
 
 }  // namespace

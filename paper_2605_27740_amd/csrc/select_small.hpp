@@ -19,7 +19,7 @@ template <int kThreads, int kVecs>
 struct SmallShared {
   static constexpr int kWaves = kThreads / kWave;
   uint32_t group_max[kThreads * kVecs];
-  __attribute__((aligned(16))) int counts[2][kVecs * kWaves];
+  __attribute__((aligned(16))) int counts[2][kVecs * kWaves], turns[2 * kWaves];
   __attribute__((aligned(16))) uint2 kept[kSmallCap + kWave];  // key, page; the last ones are for lanes without a key
 };
 
@@ -38,8 +38,14 @@ __device__ __forceinline__ int count_above(const uint32_t (&v)[kN], uint32_t x) 
     if constexpr (kBatch == 4) asm volatile("" : "+s"(m[0]), "+s"(m[1]), "+s"(m[2]), "+s"(m[3]));
     if constexpr (kBatch == 8)
       asm volatile("" : "+s"(m[0]), "+s"(m[1]), "+s"(m[2]), "+s"(m[3]), "+s"(m[4]), "+s"(m[5]), "+s"(m[6]), "+s"(m[7]));
+    int c[kBatch];
 #pragma unroll
-    for (int r = 0; r < kBatch; ++r) n += __popcll(m[r]);
+    for (int r = 0; r < kBatch; ++r) c[r] = __popcll(m[r]);
+#pragma unroll
+    for (int d = 1; d < kBatch; d *= 2)  // a tree: a chain of additions waits for each of them
+#pragma unroll
+      for (int r = 0; r + d < kBatch; r += 2 * d) c[r] += c[r + d];
+    n += c[0];
   }
   return n;
 }
@@ -61,6 +67,93 @@ __device__ __forceinline__ uint32_t bisect(uint32_t lo, uint32_t hi, int k, int 
   return lo;
 }
 
+// The same from known counts at lo and hi, and only to the value with exactly k above it or the largest with more: two rounds of
+// three aim at it along the line between the counts, which halves the rounds (9 to 5 where a third of the keys is to go) and
+// costs as much as counting some keys.
+template <typename Count>
+__device__ __forceinline__ uint32_t bisect_exact(uint32_t lo, uint32_t hi, int n_lo, int n_hi, int k, Count count) {
+#pragma unroll 1
+  for (int i = 0; n_lo != k && hi - lo > 1u; ++i) {
+    uint32_t step = (hi - lo) / 2;
+    if (i % 3 != 2) {
+      const float part = (float)(n_lo - k) * __builtin_amdgcn_rcpf((float)(n_lo - n_hi));
+      step = (uint32_t)((float)(hi - lo) * part);
+      step = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(max(step, 1u), hi - lo - 1u));
+    }
+    const int n = count(lo + step);
+    if (n >= k) { lo += step; n_lo = n; }
+    else { hi = lo + step; n_hi = n; }
+  }
+  return lo;
+}
+
+// bisect over the keys of a whole workgroup, kN per thread; turns: 2 * waves ints of LDS. All threads call it.
+template <int kThreads, int kN>
+__device__ __forceinline__ uint32_t bisect_spread(const uint32_t (&v)[kN], uint32_t lo, uint32_t hi, int k, int enough, int* turns) {
+  constexpr int kWaves = kThreads / kWave;
+  static_assert(kWaves % 4 == 0, "counts are read four at a time");
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int turn = 0;
+  return bisect(lo, hi, k, enough, [&](uint32_t x) {
+    const int n = count_above(v, x);
+    turn ^= kWaves;  // the counts of one round are read while those of the next are written
+    if (lane == 0) turns[turn + wave] = n;
+    __syncthreads();
+    int sum = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; w += 4) {
+      const int4 q = *reinterpret_cast<const int4*>(&turns[turn + w]);
+      sum += q.x + q.y + q.z + q.w;
+    }
+    return __builtin_amdgcn_readfirstlane(sum);
+  });
+}
+
+// The kb largest of a workgroup's keys, of which more than kb lie above `low`, in the order (v, thread, i) of key[kPer * v + i]:
+// emit(at, j) once per selected key. above, equal: kVecs * waves ints each, 16-byte aligned, turns as above; all of them unused by
+// others since the last barrier. All threads call it.
+template <int kThreads, int kVecs, int kPer, typename Emit>
+__device__ __forceinline__ void select_spread(const uint32_t (&key)[kVecs * kPer], uint32_t low, uint32_t high, int kb, Emit emit,
+                                              int* above, int* equal, int* turns) {
+  constexpr int kWaves = kThreads / kWave;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  // the k-th key, or (exactly kb keys above T - 1) a value that only selected keys reach
+  const uint32_t T = bisect_spread<kThreads>(key, low, high, kb, kb, turns) + 1u;
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) {
+    int n = 0, e = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      n += __popcll(__ballot(key[kPer * v + i] > T));
+      e += __popcll(__ballot(key[kPer * v + i] == T));
+    }
+    if (lane == 0) { above[v * kWaves + wave] = n; equal[v * kWaves + wave] = e; }
+  }
+  __syncthreads();
+  int place[kVecs], ties[kVecs];
+  const int need = kb - wave_prefixes<kVecs, kWaves>(above, wave, place);  // keys equal to T that are taken, the first ones
+  wave_prefixes<kVecs, kWaves>(equal, wave, ties);
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) {
+    int sure_b = place[v], tie_b = ties[v];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      sure_b = lanes_before(__ballot(key[kPer * v + i] > T), sure_b);
+      tie_b = lanes_before(__ballot(key[kPer * v + i] == T), tie_b);
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int j = kPer * v + i;
+      if (key[j] > T) {
+        emit(min(tie_b, need) + sure_b++, j);
+      } else if (key[j] == T) {
+        if (tie_b < need) emit(sure_b + tie_b, j);
+        ++tie_b;
+      }
+    }
+  }
+}
+
 // A lower bound (>= 1) of the k-th largest key from n = 64 * kN group maxima, at least k of them above 0: a value that k to
 // about 9/8 k groups reach.
 template <int kN>
@@ -78,42 +171,53 @@ __device__ __forceinline__ uint32_t bound_of_maxima(const uint32_t* group_max, i
   return bisect(least > 0u ? least - 1u : 0u, top, k, k + k / 8, [&](uint32_t x) { return count_above(m, x); }) + 1u;
 }
 
-// The kb largest of `total` <= 64 * kN gathered keys, of which all are above `low`, in page order. Every wave finds them all:
-// emit(r, at, page, phys) says that the page, which the lane holds as its r-th, is the at-th selected one, or with at = -1
-// that it is none. The physical pages are looked up while the search runs.
-template <int kN, typename Emit>
-__device__ __forceinline__ void select_gathered(const uint2* kept, int total, uint32_t low, int kb, const int32_t* page_table,
-                                                Emit emit) {
+// The kb largest of `total` <= 64 * kN gathered keys, of which all are above `low` and none above `top`, in page order, by one
+// wave: emit(r, at, page) says that the page, which the lane holds as its r-th, is the at-th selected one, or with at = -1 that
+// it is none. ahead(page) is called for all kN pages of the lanes (0: none) before the search.
+template <int kN, typename Emit, typename Ahead>
+__device__ __forceinline__ void select_gathered(const uint2* kept, int total, uint32_t low, uint32_t top, int kb, Emit emit,
+                                                Ahead ahead) {
   const int lane = threadIdx.x % kWave;
-  uint32_t key[kN], top = 0u;
-  int page[kN], phys[kN];
+  uint32_t key[kN];
+  int page[kN];
 #pragma unroll
   for (int r = 0; r < kN; ++r) {
     const uint2 e = kept[r * kWave + lane];  // (what lies behind the last one is not used)
     key[r] = r * kWave + lane < total ? e.x : 0u;
     page[r] = r * kWave + lane < total ? (int)e.y : 0;
   }
-#pragma unroll
-  for (int r = 0; r < kN; ++r) {
-    phys[r] = page_table[page[r]];
-    top = max(top, key[r]);
-  }
-  top = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<true>(top));
+  ahead(page);
   // x with exactly kb keys above it, or the largest x with more: the next value is then the k-th key
+  auto count = [&](uint32_t y) { return count_above(key, y); };
   uint32_t x = low;
-  if (total > kb) x = bisect(low, top, kb, kb, [&](uint32_t y) { return count_above(key, y); });
+  if constexpr (kN >= 8) x = bisect_exact(low, top, total, 0, kb, count);
+  else if (total > kb) x = bisect(low, top, kb, kb, count);
+  int at = 0, ties = 0;
+  if (count_above(key, x) == kb) {
+#pragma unroll
+    for (int r = 0; r < kN; ++r) {
+      const bool mine = key[r] > x;
+      const unsigned long long sel = __ballot(mine);
+      emit(r, mine ? lanes_before(sel, at) : -1, page[r]);
+      at += __popcll(sel);
+    }
+    return;
+  }
   const uint32_t T = x + 1u;
   const int need = kb - count_above(key, T);  // keys equal to T that are taken, from the lowest page up
-  int at = 0, ties = 0;
 #pragma unroll
   for (int r = 0; r < kN; ++r) {
     const unsigned long long tie = __ballot(key[r] == T);
     const bool mine = key[r] > T || (key[r] == T && lanes_before(tie, ties) < need);
     const unsigned long long sel = __ballot(mine);
-    emit(r, mine ? lanes_before(sel, at) : -1, page[r], phys[r]);
+    emit(r, mine ? lanes_before(sel, at) : -1, page[r]);
     at += __popcll(sel);
     ties += __popcll(tie);
   }
+}
+template <int kN, typename Emit>
+__device__ __forceinline__ void select_gathered(const uint2* kept, int total, uint32_t low, uint32_t top, int kb, Emit emit) {
+  select_gathered<kN>(kept, total, low, top, kb, emit, [](const int(&)[kN]) {});
 }
 
 // Thread t holds the keys of the pages row_page(j) (0: no page); 0 < kb < P; page_table: the row's, of at least one entry.
@@ -179,60 +283,30 @@ __device__ __forceinline__ void select_small(const uint32_t (&key)[4 * kVecs], i
       }
     }
     __syncthreads();
-    if (total <= 2 * kWave) select_gathered<2>(sh.kept, total, T0 - 1u, kb, page_table, emit_all);
-    else if (total <= 4 * kWave) select_gathered<4>(sh.kept, total, T0 - 1u, kb, page_table, emit_all);
-    else if (total <= 8 * kWave) select_gathered<8>(sh.kept, total, T0 - 1u, kb, page_table, emit_all);
-    else select_gathered<16>(sh.kept, total, T0 - 1u, kb, page_table, emit_all);
+    auto gathered = [&](auto per_lane) {
+      constexpr int kN = decltype(per_lane)::value;
+      int phys[kN];  // looked up while the search runs
+      uint32_t top = 0u;
+#pragma unroll
+      for (int r = 0; r < kN; ++r) top = max(top, r * kWave + lane < total ? sh.kept[r * kWave + lane].x : 0u);
+      top = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<true>(top));
+      select_gathered<kN>(sh.kept, total, T0 - 1u, top, kb, [&](int r, int at, int page) { emit_all(r, at, page, phys[r]); },
+                          [&](const int(&page)[kN]) {
+#pragma unroll
+                            for (int r = 0; r < kN; ++r) phys[r] = page_table[page[r]];
+                          });
+    };
+    if (total <= 2 * kWave) gathered(std::integral_constant<int, 2>());
+    else if (total <= 4 * kWave) gathered(std::integral_constant<int, 4>());
+    else if (total <= 8 * kWave) gathered(std::integral_constant<int, 8>());
+    else gathered(std::integral_constant<int, 16>());
     return;
   }
   if constexpr (kThreads * kVecs * 4 > kSmallCap) {
-    // Masses of equal scores, or a k beyond the groups: bisection over the keys in the registers of all waves.
-    int turn = 0;
-    const uint32_t x = bisect(T0 - 1u, 0xffffffffu, kb, kb, [&](uint32_t y) {
-      const int n = count_above(key, y);
-      turn ^= 1;
-      if (lane == 0) sh.group_max[turn * kWaves + wave] = (uint32_t)n;
-      __syncthreads();
-      int sum = 0;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) sum += (int)sh.group_max[turn * kWaves + w];
-      return __builtin_amdgcn_readfirstlane(sum);
-    });
-    const uint32_t T = x + 1u;  // the k-th key, or (exactly kb keys above x) a value that only selected keys reach
-    __syncthreads();            // the counts of the gathering have been read by all
-#pragma unroll
-    for (int v = 0; v < kVecs; ++v) {
-      int n = 0, e = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        n += __popcll(__ballot(key[4 * v + i] > T));
-        e += __popcll(__ballot(key[4 * v + i] == T));
-      }
-      if (lane == 0) { sh.counts[0][v * kWaves + wave] = n; sh.counts[1][v * kWaves + wave] = e; }
-    }
-    __syncthreads();
-    int ties[kVecs];
-    const int need = kb - wave_prefixes<kVecs, kWaves>(sh.counts[0], wave, place);
-    wave_prefixes<kVecs, kWaves>(sh.counts[1], wave, ties);
-#pragma unroll
-    for (int v = 0; v < kVecs; ++v) {
-      int sure_b = place[v], tie_b = ties[v];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        sure_b = lanes_before(__ballot(key[4 * v + i] > T), sure_b);
-        tie_b = lanes_before(__ballot(key[4 * v + i] == T), tie_b);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int j = 4 * v + i;
-        if (key[j] > T) {
-          emit_own(min(tie_b, need) + sure_b++, page_of(j));
-        } else if (key[j] == T) {
-          if (tie_b < need) emit_own(sure_b + tie_b, page_of(j));
-          ++tie_b;
-        }
-      }
-    }
+    // masses of equal scores, or a k beyond the groups: the keys in the registers of all waves
+    __syncthreads();  // the counts have been read by all
+    select_spread<kThreads, kVecs, 4>(key, T0 - 1u, 0xffffffffu, kb, [&](int at, int j) { emit_own(at, page_of(j)); },
+                                      sh.counts[0], sh.counts[1], sh.turns);
     __syncthreads();
   }
 }

@@ -29,7 +29,7 @@ __global__ __launch_bounds__(kThreads) void select_decode_kernel(
   int split, hkv, b;
   locate_chunk(c, plan, split, hkv, b);
   const int row = b * c.Hkv + hkv;
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t % kWave, wave = __builtin_amdgcn_readfirstlane(t / kWave);  // wave: scalar
   // the scores are requested together with the sequence length: score rows are as long as the launch's bound on the pages
   auto page_of = [](int j) { return row_page<kThreads, kPer>(j); };
   const float* srow = scores + (int64_t)row * score_stride;
@@ -65,12 +65,11 @@ __global__ __launch_bounds__(kThreads) void select_decode_kernel(
 #pragma unroll
     for (int v = 0; v < kVecs; ++v) keys_of(raw[v], P - page_of(4 * v), key + 4 * v);
     force_recent_keys<kThreads, kVecs, kPer>(key, P, kb, c.force_recent);
-    const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
     // Every wave knows the whole selection. It keeps the entries that it will attend over itself (see decode_chunk), so no
     // barrier is needed before it reads them back.
     auto emit_all = [&](int r, int at, int page, int ph) {
       const bool mine = at >= begin && at < end && (at - begin) % kDecWaves == wave;
-      list[mine ? at - begin : kStepMaxTopK + t % kWave] = make_int2(ph, page);
+      list[mine ? at - begin : kStepMaxTopK + lane] = make_int2(ph, page);
       if (split == 0 && r % kDecWaves == wave && at >= 0) sel_row[at] = page;
     };
     auto emit_own = [&](int at, int page) {
@@ -90,7 +89,7 @@ __global__ __launch_bounds__(kThreads) void select_decode_kernel(
     }
   };
   const Chunk chunk = {split, hkv, b, row, begin, end, N};
-  decode_chunk<D, S, G, kNT>(c, q, chunk, lookup, scale_log2, to, dec);
+  decode_chunk<D, S, G, kNT>(c, q, chunk, wave, lane, lookup, scale_log2, to, dec);
 }
 
 template <typename T, int D, int S, int G>

@@ -1181,3 +1181,36 @@ def test_step_with_the_selection_in_the_attention_kernel(gpu_lib, P):
                     size += 256
             assert size <= whole.numel()
             same()
+
+
+@pytest.mark.parametrize("P,ks", [(4097, (1, 170)), (4104, (33,)), (8191, (341,)), (8200, (5, 256)), (16384, (682,)), (16385, (64,)),
+                                  (32769, (1024, 1280)), (65536, (1280,)), (65543, (1,)), (131072, (1280,)), (131073, (64,))])
+def test_selection_from_group_maxima(gpu_lib, P, ks):
+    """unique_score_select_topk, which selects from the group maxima of the score kernel at these lengths and budgets,
+    against unique_select_topk on its own scores, which reads every score: the same lists. A long and a short sequence,
+    one of whose waves has few groups; scores with more groups at the bound than are gathered (five_values, all_equal)."""
+    wl = W.build("groups", 9, dtype=torch.bfloat16, B=2, H=2, Hkv=2, D=64, S=8, seq_lens=[8, 8], top_k=1, key_mode="iid",
+                 poison=False).to(DEV)
+    pool = 1 << 15
+    wl.k_cache = torch.zeros((pool, 2, 8, 64), dtype=torch.bfloat16, device=DEV)
+    wl.v_cache = wl.k_cache
+    wl.page_table = torch.arange(2 * P, dtype=torch.int32, device=DEV).remainder(pool).view(2, P)
+    wl.seq_lens = torch.tensor([8 * P - 3, 8 * (P // 5) + 1], dtype=torch.int32, device=DEV)
+    wl.q.zero_()
+    wl.q[..., 0] = 1.0
+    makers = {**SCORE_MAKERS, "five_values": lambda n, s: np.random.default_rng(s).integers(0, 5, size=n).astype(np.float64)}
+    for kind in ("normal", "heavy_ties", "all_equal", "five_values", "nan_and_inf", "ascending"):
+        for k, recent in [(k, r) for k in ks for r in (0, 9)]:
+            sess = DecodeSession(wl, top_k=k, force_recent_pages=recent, min_seq_len_hint=0)
+            sess.page_stats.zero_()
+            for h in range(2):
+                sess.page_mean[:, h, 0] = torch.from_numpy(makers[kind](pool, h).astype(np.float32)).to(DEV)
+            sess.score_select_topk()
+            torch.cuda.synchronize()
+            sel, cnt = sess.sel_pages.clone(), sess.sel_count.clone()
+            padded = torch.full((2, 2, (P + 3) // 4 * 4), float("nan"), device=DEV)
+            padded[..., :P] = sess.scores
+            sess.sel_pages.fill_(-7)
+            sess.select_topk(padded)
+            torch.cuda.synchronize()
+            assert torch.equal(sel, sess.sel_pages) and torch.equal(cnt, sess.sel_count), (kind, k, recent)
