@@ -11,9 +11,9 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libunique_gfx950.so")
 SOURCES = ["api.hip", "stats.hip", "score.hip", "select.hip", "select_grouped.hip", "decode.hip"]
-# step.hip is compiled once per element type and head dimension (object file, defines)
-STEP_VARIANTS = [(f"step_{t}_{d}.o", [f"-DUNIQUE_STEP_T={c}", f"-DUNIQUE_STEP_D={d}"])
-                 for t, c in (("bf16", "uint16_t"), ("f32", "float")) for d in (128, 64)]
+# compiled once per element type and head dimension: (source, object file, defines)
+VARIANTS = [(f"{src}.hip", f"{src}_{t}_{d}.o", [f"-DUNIQUE_ELEM={c}", f"-DUNIQUE_DIM={d}"])
+            for src in ("step", "dense") for t, c in (("bf16", "uint16_t"), ("f32", "float")) for d in (128, 64)]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed fp32 instructions are kept off for the device pass on purpose
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -44,7 +44,7 @@ def build_library(force: bool = False, extra_flags: list[str] | None = None, job
     os.makedirs(OBJ_DIR, exist_ok=True)
     extra = list(extra_flags or [])
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        jobs_ = [ex.submit(_compile, "step.hip", extra + defs, obj) for obj, defs in STEP_VARIANTS]
+        jobs_ = [ex.submit(_compile, src, extra + defs, obj) for src, obj, defs in VARIANTS]
         jobs_ += [ex.submit(_compile, s, extra) for s in SOURCES]
         objs = [j.result() for j in jobs_]
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
@@ -76,7 +76,7 @@ def build_profiling_library(force: bool = False) -> str:
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed for the profiling build of {os.path.basename(src)}:\n{r.stderr}")
     objs = [j[2] for j in jobs] + [os.path.join(OBJ_DIR, s.replace(".hip", ".o")) for s in SOURCES if s != "decode.hip"]
-    objs += [os.path.join(OBJ_DIR, obj) for obj, _ in STEP_VARIANTS]
+    objs += [os.path.join(OBJ_DIR, obj) for _, obj, _ in VARIANTS]
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", PROF_LIB_PATH, *objs],
                        capture_output=True, text=True)
     if r.returncode != 0:

@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "decode_core.hpp"
+#include "dense_plan.hpp"
 
 namespace unique {
 namespace {
@@ -32,6 +33,7 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
   int split, hkv, b;
   locate_chunk(c, plan, split, hkv, b);
   const int row = b * c.Hkv + hkv;
+  const int64_t chunk_slot = (int64_t)row * num_splits + split;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
   const int begin = split * plan.pages_per_split;
   DEC_STAMP(0);  // kernel entry
@@ -50,7 +52,7 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
     write_empty<T, D, G>(c, to, b, hkv);
     return;
   }
-  const Chunk chunk = {split, hkv, b, row, begin, min(begin + plan.pages_per_split, cnt), N};
+  const Chunk chunk = {hkv, b, begin, min(begin + plan.pages_per_split, cnt), N, chunk_slot};
   auto lookup = [&](int e, bool first, int& phys, int& ntok) {
     const int lp = !sel_pages ? e : (first ? first_lp : sel_pages[(int64_t)row * sel_stride + e]);
     if (lp >= 0 && lp < P) {
@@ -64,69 +66,19 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
   decode_chunk<D, S, G, kNT>(c, q, chunk, wave, lane, lookup, scale_log2, to, sh);
 }
 
-// Log-sum-exp merge of the chunk partials of one (sequence, query head); writes out (and lse).
-// One wave per head. Lane s takes the (m, l) pair of chunk s, so the maximum, the per-chunk scales and the
-// normaliser come from two wave reductions instead of a serial pass; the output rows of the chunks are then
-// accumulated with the scale of chunk s broadcast from lane s, eight independent loads in flight at a time
-// (a thread per element walking the chunks one dependent load after the other took 8 us for 32 chunks).
 template <typename T, int D, int G>
 __global__ __launch_bounds__(kWave) void paged_decode_merge_kernel(CacheView c, const int32_t* __restrict__ sel_count,
                                                                    int sel_stride, bool dense, int pages_per_split,
                                                                    int num_splits, const float* __restrict__ part_o,
                                                                    const float* __restrict__ part_ml,
                                                                    T* __restrict__ out, float* __restrict__ lse_out) {
-  constexpr int kPer = D / kWave;  // output elements per lane (1 or 2)
-  static_assert(kPer == 1 || kPer == 2, "head_dim 64 or 128");
-  const int h = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
-  const int hkv = h / G, g = h % G;
-  const int row = b * c.Hkv + hkv;
+  const int h = blockIdx.x, b = blockIdx.y;
+  const int row = b * c.Hkv + h / G;
   const int N = c.seq_lens[b];
   const int P = min((N + c.S - 1) / c.S, c.max_pages_hint);
   const int cnt = dense ? P : min(sel_count[row], sel_stride);
   const int ns = min(num_splits, (cnt + pages_per_split - 1) / pages_per_split);
-  const int64_t base = (int64_t)row * num_splits;
-  const float2* ml = reinterpret_cast<const float2*>(part_ml);  // (m, l) per (row, chunk, head)
-
-  float M = kNegBig;
-  for (int s0 = 0; s0 < ns; s0 += kWave)
-    if (s0 + lane < ns) M = fmaxf(M, ml[(base + s0 + lane) * G + g].x);
-  M = group_allreduce<kWave>(M, OpMax());
-
-  float L = 0.f, o[kPer];
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) o[i] = 0.f;
-  for (int s0 = 0; s0 < ns; s0 += kWave) {
-    float sc = 0.f;
-    if (s0 + lane < ns) {
-      const float2 v = ml[(base + s0 + lane) * G + g];
-      sc = fast_exp2(v.x - M);
-      L = fmaf(v.y, sc, L);
-    }
-    const int n = min(kWave, ns - s0);
-    const float* po = part_o + ((base + s0) * G + g) * D + lane * kPer;
-    // blocks of eight chunks; a slot past the last chunk re-reads that chunk with the zero scale of its lane
-    for (int j0 = 0; j0 < n; j0 += 8) {
-      float2 v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float* src = po + (int64_t)min(j0 + u, n - 1) * G * D;
-        if constexpr (kPer == 2) v[u] = *reinterpret_cast<const float2*>(src);
-        else v[u] = make_float2(src[0], 0.f);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float scj = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sc), j0 + u));
-        o[0] = fmaf(v[u].x, scj, o[0]);
-        if constexpr (kPer == 2) o[1] = fmaf(v[u].y, scj, o[1]);
-      }
-    }
-  }
-  L = group_allreduce<kWave>(L, OpSum());
-  const bool any = L > 0.f;
-  T* dst = out + ((int64_t)b * c.H + h) * D + lane * kPer;
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) store_elem(dst + i, any ? o[i] / L : 0.f);
-  if (lse_out && lane == 0) lse_out[(int64_t)b * c.H + h] = any ? (M + log2f(L)) * kLn2 : -INFINITY;
+  merge_chunks<T, D, G>(c, b, h, (int64_t)row * num_splits, ns, part_o, part_ml, out, lse_out);
 }
 
 template <typename T, int D, int S, int G>
@@ -360,6 +312,11 @@ hipError_t launch_merge(const CacheView& c, const int32_t* d_sel_count, int sel_
 hipError_t launch_decode(const CacheView& c, const void* d_q, const int32_t* d_sel_pages,
                          const int32_t* d_sel_count, int sel_stride, int max_list_len, float sm_scale,
                          void* d_out, float* d_lse_out, float* d_partials, hipStream_t stream) {
+  if (!d_sel_pages && dense_balances(c.B, c.Hkv, c.max_pages_hint, c.S * c.D * 2 * (c.dtype == 0 ? 4 : 2))) {
+    auto run = [&](auto launch) { return launch(c, d_q, sm_scale, d_out, d_lse_out, d_partials, stream); };
+    return c.dtype == 0 ? (c.D == 64 ? run(launch_dense<float, 64>) : run(launch_dense<float, 128>))
+                        : (c.D == 64 ? run(launch_dense<bf16_t, 64>) : run(launch_dense<bf16_t, 128>));
+  }
   const SplitPlan plan = d_sel_pages ? selection_plan(c, max_list_len) : most_splits(c.B * c.Hkv, max_list_len);
   const bool nt = decode_streams(c, max_list_len);
   auto go = [&](auto dispatch) {

@@ -41,16 +41,17 @@ __device__ __forceinline__ void locate_chunk(const CacheView& c, const SplitPlan
 // Where a workgroup's results go: the chunk's part of the workspace, or the output if the row has one chunk.
 template <typename T>
 struct ChunkOut {
-  float* part_o;   // [rows][num_splits][G][D]
-  float* part_ml;  // [rows][num_splits][G][2]
+  float* part_o;   // [slots][G][D], a slot per chunk
+  float* part_ml;  // [slots][G][2]
   T* out;          // written directly when num_splits == 1
   float* lse_out;
   int num_splits;
 };
 
-// A chunk: entries [begin, end) of the list of sequence b and KV head hkv, and the sequence's length.
+// A chunk: entries [begin, end) of the list of sequence b and KV head hkv, the sequence's length, and the slot of its results.
 struct Chunk {
-  int split, hkv, b, row, begin, end, N;
+  int hkv, b, begin, end, N;
+  int64_t slot;
 };
 
 // An empty list: the output is defined as zero, the lse as -inf.
@@ -87,7 +88,8 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const float* __
   constexpr int kBuffers = 2;  // register tiles per wave (three and four measured no faster)
   static_assert(S % kTokPerLoad == 0 && kLoads % kTileLoads == 0, "page size / element type combination");
 
-  const int hkv = k.hkv, b = k.b, row = k.row, split = k.split, begin = k.begin, end = k.end, num_splits = to.num_splits;
+  const int hkv = k.hkv, b = k.b, begin = k.begin, end = k.end, num_splits = to.num_splits;
+  const int64_t chunk_slot = k.slot;
 
   const int tr = lane / kLanesPerTok, ch = lane % kLanesPerTok;
 
@@ -233,7 +235,7 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const float* __
     for (int g = 0; g < G; ++g) { sh.m[wave][g] = m[g]; sh.l[wave][g] = l[g]; }
   }
   __syncthreads();
-  const int64_t pbase = (int64_t)row * num_splits + split;
+  const int64_t pbase = chunk_slot;
   for (int idx = threadIdx.x; idx < G * D; idx += kDecWaves * kWave) {
     const int g = idx / D, d = idx % D;
     float M = sh.m[0][g];
@@ -287,7 +289,7 @@ constexpr int kStampSlots = 32, kStampWaves = 1 << 14;
 __device__ unsigned long long g_dec_stamps[kStampWaves][kStampSlots];
 #define DEC_STAMP(slot)                                                                                         \
   do {                                                                                                          \
-    const int sw_ = (row * num_splits + split) * kDecWaves + wave;          \
+    const int64_t sw_ = chunk_slot * kDecWaves + wave;                                                              \
     if (lane == 0 && sw_ < kStampWaves) g_dec_stamps[sw_][slot] = wall_clock64();                               \
   } while (0)
 // the stamp is taken only once `value` (a 32-bit register) has been produced
@@ -360,7 +362,8 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const bf16_t* _
   constexpr float kRoom = 6.f;                       // log2: how far above the largest logit the reference is put
   static_assert(G <= 8, "at most 8 query heads per KV head");
 
-  const int hkv = k.hkv, b = k.b, row = k.row, split = k.split, begin = k.begin, end = k.end, num_splits = to.num_splits;
+  const int hkv = k.hkv, b = k.b, begin = k.begin, end = k.end, num_splits = to.num_splits;
+  const int64_t chunk_slot = k.slot;
 
   const int kt = lane % 16, kg = lane / 16;  // column (token slot of K, head and part of p, channel block of V); lane group
   const int part = kt / G;                   // which part of its head's probabilities this lane supplies
@@ -505,7 +508,7 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const bf16_t* _
 #ifdef UNIQUE_DEC_STAMPS
         if (t0 + u < n_tiles && t0 + u < kStampSlots - 6) DEC_STAMP_AFTER(6 + t0 + u, acc[0][0]);  // tile t0 + u consumed
         if (t0 + u == 0) {  // which compute unit this wave runs on (HW_ID: bits 8-11 CU, 13-15 SE; XCC_ID register)
-          const int sw_ = (row * num_splits + split) * kDecWaves + wave;
+          const int64_t sw_ = chunk_slot * kDecWaves + wave;
           if (lane == 0 && sw_ < kStampWaves)
             g_dec_stamps[sw_][5] = ((unsigned long long)__builtin_amdgcn_s_getreg((4 << 0) | (0 << 6) | (31 << 11)) << 32) |
                                    (unsigned)__builtin_amdgcn_s_getreg((20 << 0) | (0 << 6) | (3 << 11));
@@ -529,7 +532,7 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const bf16_t* _
   }
   if (lane < G) { sh.m[wave][lane] = m; sh.l[wave][lane] = l; }
   __syncthreads();
-  const int64_t pbase = (int64_t)row * num_splits + split;
+  const int64_t pbase = chunk_slot;
   for (int idx = threadIdx.x; idx < G * D; idx += kDecWaves * kWave) {
     const int g = idx / D, d = idx % D;
     float M = sh.m[0][g];
@@ -556,6 +559,62 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const bf16_t* _
     }
   }
   DEC_STAMP(4);  // partial results stored
+}
+
+// Log-sum-exp merge of the chunk partials of one (sequence, query head); writes out (and lse).
+// One wave per head. Lane s takes the (m, l) pair of chunk s, so the maximum, the per-chunk scales and the
+// normaliser come from two wave reductions instead of a serial pass; the output rows of the chunks are then
+// accumulated with the scale of chunk s broadcast from lane s, eight independent loads in flight at a time
+// (a thread per element walking the chunks one dependent load after the other took 8 us for 32 chunks).
+template <typename T, int D, int G>
+__device__ __forceinline__ void merge_chunks(const CacheView& c, int b, int h, int64_t base /*the row's first slot*/, int ns,
+                                             const float* __restrict__ part_o, const float* __restrict__ part_ml,
+                                             T* __restrict__ out, float* __restrict__ lse_out) {
+  constexpr int kPer = D / kWave;  // output elements per lane (1 or 2)
+  static_assert(kPer == 1 || kPer == 2, "head_dim 64 or 128");
+  const int lane = threadIdx.x, g = h % G;
+  const float2* ml = reinterpret_cast<const float2*>(part_ml);  // (m, l) per (row, chunk, head)
+
+  float M = kNegBig;
+  for (int s0 = 0; s0 < ns; s0 += kWave)
+    if (s0 + lane < ns) M = fmaxf(M, ml[(base + s0 + lane) * G + g].x);
+  M = group_allreduce<kWave>(M, OpMax());
+
+  float L = 0.f, o[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) o[i] = 0.f;
+  for (int s0 = 0; s0 < ns; s0 += kWave) {
+    float sc = 0.f;
+    if (s0 + lane < ns) {
+      const float2 v = ml[(base + s0 + lane) * G + g];
+      sc = fast_exp2(v.x - M);
+      L = fmaf(v.y, sc, L);
+    }
+    const int n = min(kWave, ns - s0);
+    const float* po = part_o + ((base + s0) * G + g) * D + lane * kPer;
+    // blocks of eight chunks; a slot past the last chunk re-reads that chunk with the zero scale of its lane
+    for (int j0 = 0; j0 < n; j0 += 8) {
+      float2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float* src = po + (int64_t)min(j0 + u, n - 1) * G * D;
+        if constexpr (kPer == 2) v[u] = *reinterpret_cast<const float2*>(src);
+        else v[u] = make_float2(src[0], 0.f);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float scj = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sc), j0 + u));
+        o[0] = fmaf(v[u].x, scj, o[0]);
+        if constexpr (kPer == 2) o[1] = fmaf(v[u].y, scj, o[1]);
+      }
+    }
+  }
+  L = group_allreduce<kWave>(L, OpSum());
+  const bool any = L > 0.f;
+  T* dst = out + ((int64_t)b * c.H + h) * D + lane * kPer;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) store_elem(dst + i, any ? o[i] / L : 0.f);
+  if (lse_out && lane == 0) lse_out[(int64_t)b * c.H + h] = any ? (M + log2f(L)) * kLn2 : -INFINITY;
 }
 
 }  // namespace

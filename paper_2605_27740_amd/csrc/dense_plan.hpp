@@ -1,0 +1,31 @@
+// Which dense decodes are cut by the lengths on the device (dense.hip), and into how many chunks at most. Host arithmetic on the
+// launch's bounds only (no HIP), so that it can be checked without a GPU.
+#pragma once
+#include <stdint.h>
+
+#include "split_plan.hpp"
+
+namespace unique {
+
+constexpr int kDenseSlots = 512;    // workgroups that run at the same time: two on each of the 256 compute units
+constexpr int kDensePages = 256;    // pages of a chunk from which on twice the workgroups are used
+constexpr int kDenseMaxBatch = 64;  // a lane per sequence
+
+// Chunks of the whole batch, at most as many as the partial results of most_splits hold.
+inline int dense_max_chunks(int rows, int max_pages) {
+  const int64_t all = (int64_t)rows * most_splits(rows, max_pages).num_splits;
+  const int64_t wanted = std::max<int64_t>((int64_t)rows * max_pages / (kDenseSlots * kDensePages), 1) * kDenseSlots;
+  return (int)std::min(all, wanted);
+}
+
+// Finding the cut costs 1 us, so launches that can read less than 64 MB keep most_splits (2 sequences of up to 4000 tokens, 8 KV heads:
+// 12.9 us, so 14.4). us of the whole call before / now (bf16, 8 KV heads, G = 4, D = 128, pages of 16): 4 sequences of 6K to 30K tokens
+// 66.4 / 43.2; 8 of 2K to 60K 205 / 163; 16 of 1K to 16K 124 / 62; even ones 8 x 16384 86.6 / 87.2, 16 x 30000 311 / 299,
+// 5 x 7000 31.1 / 30.3. More rows than half the slots, and a single sequence, have nothing to gain.
+inline bool dense_balances(int batch, int kv_heads, int max_pages, int page_bytes) {
+  const int64_t rows = (int64_t)batch * kv_heads;
+  if (batch < 2 || batch > kDenseMaxBatch || rows > kDenseSlots / 2 || rows * max_pages > INT32_MAX) return false;
+  return most_splits((int)rows, max_pages).num_splits > 1 && rows * max_pages * page_bytes >= (64ll << 20);
+}
+
+}  // namespace unique

@@ -90,6 +90,19 @@ template <> hipError_t launch_select_decode<float, 128>(const CacheView& c, cons
 template <> hipError_t launch_select_decode<uint16_t, 64>(const CacheView& c, const StepArgs& a, hipStream_t stream);
 template <> hipError_t launch_select_decode<uint16_t, 128>(const CacheView& c, const StepArgs& a, hipStream_t stream);
 
+// Attention over every page, cut by the lengths on the device (dense_plan.hpp says for which launches).
+template <typename T, int D>
+hipError_t launch_dense(const CacheView& c, const void* d_q, float sm_scale, void* d_out, float* d_lse_out, float* d_partials,
+                        hipStream_t stream);
+template <> hipError_t launch_dense<float, 64>(const CacheView& c, const void* d_q, float sm_scale, void* d_out, float* d_lse_out,
+                                         float* d_partials, hipStream_t stream);
+template <> hipError_t launch_dense<float, 128>(const CacheView& c, const void* d_q, float sm_scale, void* d_out, float* d_lse_out,
+                                         float* d_partials, hipStream_t stream);
+template <> hipError_t launch_dense<uint16_t, 64>(const CacheView& c, const void* d_q, float sm_scale, void* d_out, float* d_lse_out,
+                                         float* d_partials, hipStream_t stream);
+template <> hipError_t launch_dense<uint16_t, 128>(const CacheView& c, const void* d_q, float sm_scale, void* d_out, float* d_lse_out,
+                                         float* d_partials, hipStream_t stream);
+
 // floats of split-K partial storage needed for a list of at most max_list_len pages per row
 size_t decode_partial_floats(const CacheView& c, int max_list_len);
 

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kThreads) void select_decode_kernel(
       ntok = min(S, N - entry.y * S);
     }
   };
-  const Chunk chunk = {split, hkv, b, row, begin, end, N};
+  const Chunk chunk = {hkv, b, begin, end, N, (int64_t)row * plan.num_splits + split};
   decode_chunk<D, S, G, kNT>(c, q, chunk, wave, lane, lookup, scale_log2, to, dec);
 }
 
@@ -125,13 +125,13 @@ hipError_t dispatch_g(const CacheView& c, const StepArgs& a, hipStream_t st) {
 
 }  // namespace
 
-// One translation unit per element type and head dimension: UNIQUE_STEP_T, UNIQUE_STEP_D.
+// One translation unit per element type and head dimension: UNIQUE_ELEM, UNIQUE_DIM.
 template <>
-hipError_t launch_select_decode<UNIQUE_STEP_T, UNIQUE_STEP_D>(const CacheView& c, const StepArgs& a, hipStream_t st) {
+hipError_t launch_select_decode<UNIQUE_ELEM, UNIQUE_DIM>(const CacheView& c, const StepArgs& a, hipStream_t st) {
   switch (c.S) {
-    case 8: return dispatch_g<UNIQUE_STEP_T, UNIQUE_STEP_D, 8>(c, a, st);
-    case 16: return dispatch_g<UNIQUE_STEP_T, UNIQUE_STEP_D, 16>(c, a, st);
-    case 32: return dispatch_g<UNIQUE_STEP_T, UNIQUE_STEP_D, 32>(c, a, st);
+    case 8: return dispatch_g<UNIQUE_ELEM, UNIQUE_DIM, 8>(c, a, st);
+    case 16: return dispatch_g<UNIQUE_ELEM, UNIQUE_DIM, 16>(c, a, st);
+    case 32: return dispatch_g<UNIQUE_ELEM, UNIQUE_DIM, 32>(c, a, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -1,4 +1,5 @@
 // C interface of the launch rules for the CPU tests.
+#include "../../paper_2605_27740_amd/csrc/dense_plan.hpp"
 #include "../../paper_2605_27740_amd/csrc/score_tile.hpp"
 #include "../../paper_2605_27740_amd/csrc/split_plan.hpp"
 #include "../../paper_2605_27740_amd/csrc/stats_bulk.hpp"
@@ -21,4 +22,8 @@ extern "C" int bulk(long long record_bytes, int head_dim, int page_size, int key
 extern "C" int fuses(int batch, int kv_heads, int max_pages, int top_k, int page_bytes) {
   return unique::step_fuses(batch * kv_heads, max_pages, top_k,
                             unique::plan_splits(batch, kv_heads, top_k, max_pages, page_bytes, false));
+}
+extern "C" int dense_chunks(int rows, int max_pages) { return unique::dense_max_chunks(rows, max_pages); }
+extern "C" int dense_balances(int batch, int kv_heads, int max_pages, int page_bytes) {
+  return unique::dense_balances(batch, kv_heads, max_pages, page_bytes);
 }

@@ -1214,3 +1214,45 @@ def test_selection_from_group_maxima(gpu_lib, P, ks):
             sess.select_topk(padded)
             torch.cuda.synchronize()
             assert torch.equal(sel, sess.sel_pages) and torch.equal(cnt, sess.sel_count), (kind, k, recent)
+
+
+@pytest.mark.parametrize("dtype,Hkv,G,D,S,lens", [
+    (torch.float32, 8, 4, 128, 16, [1, 0, 5000, 77]),            # one long sequence, an empty one, one token
+    (torch.float32, 32, 1, 64, 8, [640, 641, 8, 7, 9, 100]),     # fewer pages than chunks
+    (torch.bfloat16, 8, 8, 128, 16, [2048] * 8),                 # an even batch
+    (torch.bfloat16, 2, 2, 64, 32, [300 + 97 * i for i in range(64)]),   # a sequence in every lane
+    (torch.bfloat16, 4, 4, 128, 8, [0, 0, 3]),                   # next to nothing
+    (torch.float32, 16, 2, 64, 32, [20000, 12345, 1]),
+    (torch.bfloat16, 8, 4, 128, 16, [150_000, 30_001, 129_999, 90_000]),  # more than 512 chunks of 256 pages
+])
+def test_dense_decode_cut_by_the_lengths_on_the_device(gpu_lib, dtype, Hkv, G, D, S, lens):
+    """A dense decode whose chunks come from the lengths on the device (a launch that could read 64 MB or more, which the
+    wide page table makes of small batches too) against the attention over the list of all pages, which is cut by the
+    host. fp32 sums in another order differ by less than 1e-5; bf16 outputs may round to the neighbouring number: of 7
+    stored mantissa bits, 2^(e-7) away for a value from 2^e on, at most 2^-7 of it."""
+    B, wide = len(lens), 40_000
+    lens_pages = [-(-n // S) for n in lens]
+    wl = W.build("dense", 21, dtype=dtype, B=B, H=Hkv * G, Hkv=Hkv, D=D, S=S, seq_lens=[max(n, 1) for n in lens], top_k=8,
+                 key_mode="iid", permute=True).to(DEV)
+    table = torch.full((B, wide), -1, dtype=torch.int32, device=DEV)
+    table[:, :wl.page_table.shape[1]] = wl.page_table
+    wl.page_table = table
+    wl.seq_lens = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    longest = max(lens_pages)
+    sess = DecodeSession(wl, top_k=max(longest, 1), max_seq_len_hint=wide * S, min_seq_len_hint=0, want_scores=False)
+    sess.dense_paged_decode()
+    pages = torch.arange(longest, dtype=torch.int32, device=DEV).expand(B, Hkv, longest).contiguous()
+    count = torch.tensor(lens_pages, dtype=torch.int32, device=DEV)[:, None].expand(B, Hkv).contiguous()
+    sess.sparse_paged_decode(sel_pages=pages, sel_count=count)
+    torch.cuda.synchronize()
+    a, b = sess.out_dense.double(), sess.out.double()
+    tol = 1e-5 if dtype == torch.float32 else 2.0 ** -7
+    assert ((a - b).abs() <= tol * b.abs().clamp(min=1e-2 if dtype == torch.bfloat16 else 1.0)).all()
+    la, lb = sess.lse_dense.double(), sess.lse.double()
+    assert torch.equal(torch.isinf(la), torch.isinf(lb))
+    fin = ~torch.isinf(lb)
+    assert ((la - lb)[fin].abs() <= 1e-5 * lb[fin].abs().clamp(min=1.0)).all()
+    first = sess.out_dense.clone()
+    sess.dense_paged_decode()
+    torch.cuda.synchronize()
+    assert torch.equal(first.view(torch.uint8), sess.out_dense.view(torch.uint8))

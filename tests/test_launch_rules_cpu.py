@@ -42,6 +42,8 @@ def lib(tmp_path_factory):
         @staticmethod
         def fuses(batch, heads, max_pages, top_k, page_bytes=8192):
             return bool(c.fuses(batch, heads, max_pages, top_k, page_bytes))
+
+        dense_chunks, dense_balances = c.dense_chunks, c.dense_balances
     return Lib
 
 
@@ -133,3 +135,19 @@ def test_statistics_are_written_past_the_caches_where_that_measured_faster(lib, 
     (80, 8, 4096, 64, True), (24, 8, 1000, 64, True), (31, 8, 4096, 64, False)])
 def test_steps_that_select_and_attend_in_one_kernel(lib, batch, heads, pages, top_k, want):
     assert lib.fuses(batch, heads, pages, top_k) == want
+
+
+def test_chunks_of_a_balanced_dense_batch_fit_the_workspace_and_leave_room_to_cut(lib):
+    r = random.Random(3)
+    seen = 0
+    for _ in range(20000):
+        batch, heads, pages = r.randint(1, 70), 1 << r.randint(0, 5), r.choice([r.randint(1, 500), r.randint(1, 70000)])
+        if not lib.dense_balances(batch, heads, pages, r.choice([2048, 8192, 32768])):
+            continue
+        seen += 1
+        rows, n = batch * heads, lib.dense_chunks(batch * heads, pages)
+        assert 2 <= batch <= 64 and rows < n <= rows * lib.most(rows, pages)[1], (batch, heads, pages)
+        assert n % 512 == 0 or n == rows * lib.most(rows, pages)[1], (batch, heads, pages)
+    assert seen > 3000
+    assert not lib.dense_balances(2, 8, 250, 8192) and lib.dense_balances(5, 8, 438, 8192)
+    assert not lib.dense_balances(1, 8, 100000, 8192) and not lib.dense_balances(33, 8, 4096, 8192)
