@@ -196,12 +196,16 @@ int decode_step_launch(const unique::CacheView& v, const void* d_q, int32_t top_
                        float* buf, size_t bytes, hipStream_t st) {
   const int stride = score_stride_of(v);
   uint32_t* group_max = group_max_in(v, top_k, buf, bytes);
-  hipError_t e = unique::launch_score(v, d_q, lambda, buf, stride, nullptr, group_max, refresh_tail != 0, st);
-  if (e != hipSuccess) return hip_fail(e, "page score launch");
   const unique::SplitPlan plan = unique::selection_plan(v, top_k);
-  if (unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan) && bytes >= fused_bytes(v, plan)) {
-    float* partials = buf + round_up(score_bytes(v), kAlign) / sizeof(float);
-    const unique::StepArgs a = {d_q, buf, stride, top_k, d_sel_pages, d_sel_count, sm_scale, d_out, d_lse_out, partials};
+  const bool fuses = unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan);
+  const bool whole = fuses && unique::step_is_whole(v.max_pages_hint, v.D * (v.stats_bf16 ? 2 : 4), unique::decode_streams(v, top_k));
+  hipError_t e = hipSuccess;
+  if (!whole) e = unique::launch_score(v, d_q, lambda, buf, stride, nullptr, group_max, refresh_tail != 0, st);
+  if (e != hipSuccess) return hip_fail(e, "page score launch");
+  if (whole || (fuses && bytes >= fused_bytes(v, plan))) {
+    float* partials = whole ? buf : buf + round_up(score_bytes(v), kAlign) / sizeof(float);
+    const unique::StepArgs a = {d_q, whole ? nullptr : buf, stride, top_k, lambda, refresh_tail != 0, d_sel_pages, d_sel_count,
+                                sm_scale, d_out, d_lse_out, partials};
     e = v.dtype == UNIQUE_DTYPE_F32 ? (v.D == 64 ? unique::launch_select_decode<float, 64>(v, a, st)
                                                  : unique::launch_select_decode<float, 128>(v, a, st))
                                     : (v.D == 64 ? unique::launch_select_decode<uint16_t, 64>(v, a, st)

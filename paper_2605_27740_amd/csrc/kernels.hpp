@@ -66,8 +66,10 @@ hipError_t launch_decode(const CacheView& c, const void* d_q, const int32_t* d_s
 // of stride top_k, as the plan, the arguments and the parts that launch_select_decode shares with it.
 struct StepArgs {
   const void* q;
-  const float* scores;   // [rows][score_stride]
+  const float* scores;   // [rows][score_stride]; null: the kernel scores the pages, too (step_is_whole)
   int score_stride, top_k;
+  float lambda;          // of those scores
+  int refresh_tail;
   int32_t* sel_pages;
   int32_t* sel_count;
   float sm_scale;

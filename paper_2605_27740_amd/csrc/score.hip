@@ -13,108 +13,30 @@
 // round trips); two or four records are in flight per wave, requested with unconditional loads so that the
 // loop is straight-line code with exact waits. Scores of a tile are staged in LDS and written as one
 // contiguous run per KV head (4-byte scattered stores cost a tenth of the kernel otherwise).
-#include "device_utils.hpp"
-#include "kernels.hpp"
+#include "score_core.hpp"
 #include "score_tile.hpp"
 
 namespace unique {
 namespace {
 
 constexpr int kScoreWaves = 4;
-constexpr int kRowLanes = 8;                   // lanes per (page, head) row
-constexpr int kRowsPerWave = kWave / kRowLanes;
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-
-// kE consecutive query elements, loaded as raw 32-bit words, as floats (kE = 4 or 8)
-template <int kE>
-__device__ __forceinline__ void unpack_q(const uint32_t (&w)[kE], float (&out)[kE], const float*) {
-#pragma unroll
-  for (int i = 0; i < kE; ++i) out[i] = bits_to_float(w[i]);
-}
-template <int kE>
-__device__ __forceinline__ void unpack_q(const uint32_t (&w)[kE / 2], float (&out)[kE], const bf16_t*) {
-#pragma unroll
-  for (int i = 0; i < kE / 2; ++i) {
-    out[2 * i] = bits_to_float(w[i] << 16);
-    out[2 * i + 1] = bits_to_float(w[i] & 0xffff0000u);
-  }
-}
-
 // Statistics of the last (possibly partial) page of sequence b, recomputed from the keys by the whole
-// workgroup: wave w takes KV heads w, w+4, ... The lane layout, the order of every sum and the
-// cross-lane reductions are those of the bulk statistics kernel, so the stored record is bit-identical
-// to what unique_update_page_stats writes. The page size is a run-time value here, so the loads are
-// predicated up to the largest supported page (32 tokens).
+// workgroup: wave w takes KV heads w, w+4, ... The page size is a run-time value here.
 template <typename T, int D>
 __device__ __forceinline__ void refresh_tail_record(const CacheView& c, int b, int N, int P) {
-  constexpr int kVec = Elem<T>::kVec;
-  constexpr int kLanesPerTok = D / kVec;
-  constexpr int kTokPerLoad = kWave / kLanesPerTok;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
-  const int tr = lane / kLanesPerTok, ch = lane % kLanesPerTok;
   const int p = P - 1, S = c.S;
   const int n = min(S, N - p * S);
   const int64_t phys = c.page_table[(int64_t)b * c.max_pages + p];
   if (phys < 0 || phys >= c.num_phys || n < 1) return;
   char* rec = reinterpret_cast<char*>(c.page_stats) + phys * c.rec_bytes;
-  const int64_t mean_bytes = (int64_t)c.Hkv * D * (c.stats_bf16 ? 2 : 4);
-  const float inv_n = 1.0f / (float)n;
-  constexpr int kMaxLoads = 32 / kTokPerLoad;  // page_size <= 32
+  const int elem = c.stats_bf16 ? 2 : 4;
   for (int hkv = wave; hkv < c.Hkv; hkv += kScoreWaves) {
-    const T* base = reinterpret_cast<const T*>(c.k_cache) + phys * c.kv_page_stride + hkv * c.kv_head_stride + ch * kVec;
-    // the page is read once and kept as raw 16-byte chunks; both passes unpack from registers
-    Raw16 raw[kMaxLoads];
-#pragma unroll
-    for (int j = 0; j < kMaxLoads; ++j) {
-      const int tok = j * kTokPerLoad + tr;
-      raw[j] = tok < n ? load_raw(base + (int64_t)tok * D) : zero_raw();
-    }
-    float sum[kVec];
-#pragma unroll
-    for (int i = 0; i < kVec; ++i) sum[i] = 0.f;
-#pragma unroll
-    for (int j = 0; j < kMaxLoads; ++j) {
-      if (j * kTokPerLoad + tr < n) {
-        float x[kVec];
-        unpack_raw(raw[j], x, (const T*)nullptr);
-#pragma unroll
-        for (int i = 0; i < kVec; ++i) sum[i] += x[i];
-      }
-    }
-    float mean[kVec];
-#pragma unroll
-    for (int i = 0; i < kVec; ++i) mean[i] = cross_group_allreduce<kLanesPerTok>(sum[i], OpSum()) * inv_n;
-    float ss = 0.f;
-#pragma unroll
-    for (int j = 0; j < kMaxLoads; ++j) {
-      if (j * kTokPerLoad + tr < n) {
-        float x[kVec];
-        unpack_raw(raw[j], x, (const T*)nullptr);
-#pragma unroll
-        for (int i = 0; i < kVec; ++i) {
-          const float dev = x[i] - mean[i];
-          ss = fmaf(dev, dev, ss);  // explicit: both statistics paths must round identically
-        }
-      }
-    }
-    ss = group_allreduce<kWave>(ss, OpSum());
-    if (tr == 0) {
-      if (c.stats_bf16) {
-        bf16_t* m = reinterpret_cast<bf16_t*>(rec) + hkv * D + ch * kVec;
-        uint32_t w[kVec / 2];
-#pragma unroll
-        for (int i = 0; i < kVec; i += 2)
-          w[i / 2] = (uint32_t)float_to_bf16(mean[i]) | ((uint32_t)float_to_bf16(mean[i + 1]) << 16);
-        if constexpr (kVec == 8) *reinterpret_cast<uint4*>(m) = make_uint4(w[0], w[1], w[2], w[3]);
-        else *reinterpret_cast<uint2*>(m) = make_uint2(w[0], w[1]);
-      } else {
-        float* m = reinterpret_cast<float*>(rec) + hkv * D + ch * kVec;
-#pragma unroll
-        for (int i = 0; i < kVec; i += 4)
-          *reinterpret_cast<float4*>(m + i) = make_float4(mean[i], mean[i + 1], mean[i + 2], mean[i + 3]);
-      }
-    }
-    if (lane == 0) reinterpret_cast<float*>(rec + mean_bytes)[hkv] = sqrtf(ss * inv_n);
+    PageRefresh<T, D, 32> page;  // page_size <= 32
+    page.request(reinterpret_cast<const T*>(c.k_cache) + phys * c.kv_page_stride + hkv * c.kv_head_stride, n, lane);
+    page.reduce(n, lane);
+    page.store_mean(rec + (int64_t)hkv * D * elem, c.stats_bf16, lane);
+    if (lane == 0) reinterpret_cast<float*>(rec + (int64_t)c.Hkv * D * elem)[hkv] = page.std;
   }
 }
 
@@ -126,8 +48,8 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
                                                                         int score_stride,
                                                                         float* __restrict__ scores_out,
                                                                         uint32_t* __restrict__ group_max, int refresh_tail, int tile_pages) {
-  constexpr int kE = Elem<TS>::kVec;                 // mean elements per 16-byte load
-  constexpr int kChunks = D / (kE * kRowLanes);      // 16-byte loads per lane per row
+  using Scorer = RowScorer<T, TS, D, G>;
+  constexpr int kE = Scorer::kE, kChunks = Scorer::kChunks;
   // Records in flight per wave. bf16 means in launches that stream from memory: four (80 x 4096 pages 117 us, two 122);
   // with fp32 means, twice the bytes, four records are no faster (16 x 8192 pages 87 us, two 86) and cost small launches
   // 1 us (2048 pages 8.0, two 7.0).
@@ -172,27 +94,8 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
     if (my_page < min(tile0 + tile_pages, c.max_pages_hint)) my_phys_raw = pt[my_page];
   }
   const int N = c.seq_lens[b];
-  // raw query words of this lane's row: kE elements per chunk, for each of the G heads of the group
-  constexpr int kQWords = kE * (int)sizeof(T) / 4;
-  uint32_t qraw[G][kChunks][kQWords];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-#pragma unroll
-    for (int j = 0; j < kChunks; ++j) {
-      const uint32_t* qsrc = reinterpret_cast<const uint32_t*>(q + ((int64_t)b * c.H + hkv * G + g) * D +
-                                                               j * (kE * kRowLanes) + cl * kE);
-      if constexpr (kQWords == 2) {
-        const uint2 v = *reinterpret_cast<const uint2*>(qsrc);
-        qraw[g][j][0] = v.x; qraw[g][j][1] = v.y;
-      } else {
-#pragma unroll
-        for (int w = 0; w < kQWords; w += 4) {
-          const uint4 v = *reinterpret_cast<const uint4*>(qsrc + w);
-          qraw[g][j][w] = v.x; qraw[g][j][w + 1] = v.y; qraw[g][j][w + 2] = v.z; qraw[g][j][w + 3] = v.w;
-        }
-      }
-    }
-  }
+  Scorer scorer;
+  scorer.request(q + ((int64_t)b * c.H + hkv * G) * D, cl);
   const int P = min((N + c.S - 1) / c.S, c.max_pages_hint);  // pages beyond the host bound are ignored
   if (tile0 >= P) return;
   const int tile_end = min(tile0 + tile_pages, P);
@@ -201,13 +104,6 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
     __threadfence_block();
     __syncthreads();
   }
-
-  // bf16 queries against bf16 means: packed bf16 pairs go straight into v_dot2_f32_bf16 (two products
-  // per instruction accumulated in fp32, no unpacking); every other combination multiplies in fp32.
-  constexpr bool kDot2 = sizeof(T) == 2 && sizeof(TS) == 2;
-  float qv[kDot2 ? 1 : G][kChunks][kE];
-  uint32_t qp[kDot2 ? G : 1][kChunks][kE / 2];
-  float off[G];
 
   const char* stats = reinterpret_cast<const char*>(c.page_stats);
   const int64_t std_off = (int64_t)c.Hkv * D * (int64_t)sizeof(TS);  // byte offset of the stds inside a record
@@ -235,61 +131,14 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
     sd = reinterpret_cast<const float*>(rec + std_off)[hkv];
   };
   auto consume = [&](int st, const Raw16(&mc)[kChunks], float sd_cur, int phys_cur) {
-    float mf[kDot2 ? 1 : kChunks][kE];
-    if constexpr (!kDot2) {
-#pragma unroll
-      for (int j = 0; j < kChunks; ++j) unpack_raw(mc[j], mf[j], (const TS*)nullptr);
-    }
-    float best = 0.f;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      float dot = 0.f;
-      if constexpr (kDot2) {
-#pragma unroll
-        for (int j = 0; j < kChunks; ++j) {
-          const uint32_t mw[4] = {mc[j].v.x, mc[j].v.y, mc[j].v.z, mc[j].v.w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            dot = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, qp[g][j][i]),
-                                                  __builtin_bit_cast(bf16x2_t, mw[i]), dot, false);
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < kChunks; ++j)
-#pragma unroll
-          for (int i = 0; i < kE; ++i) dot = fmaf(qv[g][j][i], mf[j][i], dot);
-      }
-      dot = group_allreduce<kRowLanes>(dot, OpSum());
-      const float sc = fmaf(off[g], sd_cur, dot);
-      best = (g == 0) ? sc : fmaxf(best, sc);
-    }
+    const float best = scorer.score(mc, sd_cur);
     const int p = tile0 + (wave_slot + st * wave_slots) * pages_per_step + page_in_step;
     // a page whose table entry points outside the pool gets NaN, which ranks below every score
     if (cl == 0 && p < tile_end) tile_scores[hkv * tile_pages + p - tile0] = phys_cur >= 0 ? best : __uint_as_float(0x7fc00000u);
   };
 #pragma unroll
   for (int u = 0; u < kDepth; ++u) issue(u, ring[u], ring_sd[u], ring_phys[u]);
-  // the queries arrived with the page ids; they are unpacked while the first records are on their way
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    float qq = 0.f;
-#pragma unroll
-    for (int j = 0; j < kChunks; ++j) {
-      float qf[kE];
-      unpack_q<kE>(qraw[g][j], qf, (const T*)nullptr);
-#pragma unroll
-      for (int i = 0; i < kE; ++i) qq = fmaf(qf[i], qf[i], qq);
-      if constexpr (kDot2) {
-#pragma unroll
-        for (int i = 0; i < kE / 2; ++i) qp[g][j][i] = qraw[g][j][i];
-      } else {
-#pragma unroll
-        for (int i = 0; i < kE; ++i) qv[g][j][i] = qf[i];
-      }
-    }
-    qq = group_allreduce<kRowLanes>(qq, OpSum());
-    off[g] = lambda * sqrtf(qq);
-  }
+  scorer.unpack(lambda);  // the queries arrived with the page ids; they are unpacked while the first records are on their way
   for (int st0 = 0; st0 < n_steps; st0 += kDepth) {
 #pragma unroll
     for (int u = 0; u < kDepth; ++u) {

@@ -1,12 +1,13 @@
 // Selection and attention of a decode step in one kernel: every workgroup of a row's chunks selects the row's top-k pages for
 // itself (select_small.hpp) and attends over its chunk of them (decode_core.hpp); the first chunk's workgroup also writes the
 // list out. A launch and the round trips between the two kernels fall away: the list stays in the LDS, the physical page
-// beside each entry, looked up while the search for the k-th key runs.
-// The selection is exact and the attention that of the decode kernel, in the same order: the same bits as in separate kernels.
+// beside each entry, looked up while the search for the k-th key runs. Of short rows every workgroup makes the scores, too.
+// Scores, selection and attention are those of the separate kernels, in the same order: the same bits.
 // What bounds it where the launch is small is a chain of latencies: of 17 200 cycles of a workgroup for one sequence of 2048
 // pages, k = 128, the arguments, length and scores take 1800, the keys 900, the bound T0 2100, gathering 1700, the k-th key
 // 2200, the list 1600, the attention over one page per wave 6900. Kernel us, selection + attention apart 5.2 + 5.8, so 8.5.
 #include "decode_core.hpp"
+#include "score_core.hpp"
 #include "select_small.hpp"
 #include "step_rule.hpp"
 
@@ -15,36 +16,26 @@ namespace {
 
 constexpr int kThreads = kDecWaves * kWave;
 
-// kVecs: 16-byte loads of scores per thread.
-template <typename T, int D, int S, int G, bool kNT, int kVecs>
-__global__ __launch_bounds__(kThreads) void select_decode_kernel(
-    CacheView c, const T* __restrict__ q, const float* __restrict__ scores, int score_stride, int top_k,
-    int32_t* __restrict__ sel_pages, int32_t* __restrict__ sel_count, SplitPlan plan, float scale_log2,
-    float* __restrict__ part_o, float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse_out) {
-  constexpr int kPer = 4, kItems = kVecs * kPer;
-  __shared__ SmallShared<kThreads, kVecs> sel;  // apart from `dec`: a wave may be done before another one has its list
-  __shared__ DecodeShared<T, D, G> dec;
-  __shared__ int2 list[kStepMaxTopK + kWave];  // physical page, logical page; the last ones are for lanes without an entry
+template <typename T, int D, int G, int kVecs>
+struct StepShared {
+  SmallShared<kThreads, kVecs> sel;  // apart from `dec`: a wave may be done before another one has its list
+  DecodeShared<T, D, G> dec;
+  int2 list[kStepMaxTopK + kWave];   // physical page, logical page; the last ones are for lanes without an entry
+};
 
-  int split, hkv, b;
-  locate_chunk(c, plan, split, hkv, b);
+// What a step does to one chunk once the row's scores are in registers, row_page(j) for raw[j / 4]. All threads call it.
+template <typename T, int D, int S, int G, bool kNT, int kVecs>
+__device__ __forceinline__ void select_and_attend(const CacheView& c, const T* __restrict__ q, const float4 (&raw)[kVecs], int split,
+                                                  int hkv, int b, int N, int P, int top_k, int32_t* __restrict__ sel_pages,
+                                                  int32_t* __restrict__ sel_count, const SplitPlan& plan, float scale_log2,
+                                                  const ChunkOut<T>& to, StepShared<T, D, G, kVecs>& sh) {
+  constexpr int kPer = 4, kItems = kVecs * kPer;
   const int row = b * c.Hkv + hkv;
   const int t = threadIdx.x, lane = t % kWave, wave = __builtin_amdgcn_readfirstlane(t / kWave);  // wave: scalar
-  // the scores are requested together with the sequence length: score rows are as long as the launch's bound on the pages
   auto page_of = [](int j) { return row_page<kThreads, kPer>(j); };
-  const float* srow = scores + (int64_t)row * score_stride;
   const int32_t* pt = c.page_table + (int64_t)b * c.max_pages;
-  float4 raw[kVecs];
-#pragma unroll
-  for (int v = 0; v < kVecs; ++v) {
-    raw[v] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (page_of(4 * v) < score_stride) raw[v] = *reinterpret_cast<const float4*>(srow + page_of(4 * v));
-  }
-  const int N = c.seq_lens[b];
-  const int P = min(min((N + S - 1) / S, c.max_pages_hint), kThreads * kItems);
   const int kb = min(top_k, P);
   const int begin = split * plan.pages_per_split, end = min(begin + plan.pages_per_split, kb);
-  const ChunkOut<T> to = {part_o, part_ml, out, lse_out, plan.num_splits};
   int32_t* sel_row = sel_pages + (int64_t)row * top_k;
   if (split == 0) {
     for (int i = kb + t; i < top_k; i += kThreads) sel_row[i] = -1;
@@ -58,7 +49,7 @@ __global__ __launch_bounds__(kThreads) void select_decode_kernel(
   if (kb == P) {  // every page is selected
     for (int p = t; p < P; p += kThreads)
       if (split == 0) sel_row[p] = p;
-    for (int p = begin + t; p < end; p += kThreads) list[p - begin] = make_int2(pt[p], p);
+    for (int p = begin + t; p < end; p += kThreads) sh.list[p - begin] = make_int2(pt[p], p);
     __syncthreads();
   } else {
     uint32_t key[kItems];
@@ -69,27 +60,147 @@ __global__ __launch_bounds__(kThreads) void select_decode_kernel(
     // barrier is needed before it reads them back.
     auto emit_all = [&](int r, int at, int page, int ph) {
       const bool mine = at >= begin && at < end && (at - begin) % kDecWaves == wave;
-      list[mine ? at - begin : kStepMaxTopK + lane] = make_int2(ph, page);
+      sh.list[mine ? at - begin : kStepMaxTopK + lane] = make_int2(ph, page);
       if (split == 0 && r % kDecWaves == wave && at >= 0) sel_row[at] = page;
     };
     auto emit_own = [&](int at, int page) {
       if (split == 0) sel_row[at] = page;
-      if (at >= begin && at < end) list[at - begin] = make_int2(pt[page], page);
+      if (at >= begin && at < end) sh.list[at - begin] = make_int2(pt[page], page);
     };
-    select_small<kThreads, kVecs>(key, P, kb, pt, emit_all, emit_own, sel);
+    select_small<kThreads, kVecs>(key, P, kb, pt, emit_all, emit_own, sh.sel);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
 
   auto lookup = [&](int e, bool, int& ph, int& ntok) {
-    const int2 entry = list[e - begin];
+    const int2 entry = sh.list[e - begin];
     if (entry.x >= 0 && (int64_t)entry.x < c.num_phys) {
       ph = entry.x;
       ntok = min(S, N - entry.y * S);
     }
   };
   const Chunk chunk = {hkv, b, begin, end, N, (int64_t)row * plan.num_splits + split};
-  decode_chunk<D, S, G, kNT>(c, q, chunk, wave, lane, lookup, scale_log2, to, dec);
+  decode_chunk<D, S, G, kNT>(c, q, chunk, wave, lane, lookup, scale_log2, to, sh.dec);
+}
+
+// kVecs: 16-byte loads of scores per thread.
+template <typename T, int D, int S, int G, bool kNT, int kVecs>
+__global__ __launch_bounds__(kThreads) void select_decode_kernel(
+    CacheView c, const T* __restrict__ q, const float* __restrict__ scores, int score_stride, int top_k,
+    int32_t* __restrict__ sel_pages, int32_t* __restrict__ sel_count, SplitPlan plan, float scale_log2,
+    float* __restrict__ part_o, float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse_out) {
+  __shared__ StepShared<T, D, G, kVecs> sh;
+  int split, hkv, b;
+  locate_chunk(c, plan, split, hkv, b);
+  // the scores are requested together with the sequence length: score rows are as long as the launch's bound on the pages
+  const float* srow = scores + ((int64_t)b * c.Hkv + hkv) * score_stride;
+  float4 raw[kVecs];
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) {
+    const int p = row_page<kThreads, 4>(4 * v);
+    raw[v] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (p < score_stride) raw[v] = *reinterpret_cast<const float4*>(srow + p);
+  }
+  const int N = c.seq_lens[b];
+  const int P = min(min((N + S - 1) / S, c.max_pages_hint), kThreads * 4 * kVecs);
+  const ChunkOut<T> to = {part_o, part_ml, out, lse_out, plan.num_splits};
+  select_and_attend<T, D, S, G, kNT, kVecs>(c, q, raw, split, hkv, b, N, P, top_k, sel_pages, sel_count, plan, scale_log2, to, sh);
+}
+
+// The whole step of a small launch in one kernel: every workgroup also scores its row's pages, with the arithmetic and in the
+// lanes of the score kernel. The last page's statistics are refreshed by one wave, which scores that page with them; the first
+// chunk's workgroup stores them (the others' loads of that record are not used).
+template <typename T, typename TS, int D, int S, int G>
+__global__ __launch_bounds__(kThreads) void whole_step_kernel(
+    CacheView c, const T* __restrict__ q, float lambda, int refresh_tail, int top_k, int32_t* __restrict__ sel_pages,
+    int32_t* __restrict__ sel_count, SplitPlan plan, float scale_log2, float* __restrict__ part_o, float* __restrict__ part_ml,
+    T* __restrict__ out, float* __restrict__ lse_out) {
+  using Scorer = RowScorer<T, TS, D, G>;
+  constexpr int kChunks = Scorer::kChunks, kE = Scorer::kE;
+  constexpr int kSteps = G == 8 ? 2 : 4;                     // rows in flight per lane (eight queries leave fewer registers)
+  constexpr int kStepPages = kDecWaves * kRowsPerWave;       // pages that the workgroup scores at a time
+  __shared__ StepShared<T, D, G, 1> sh;
+  __shared__ __attribute__((aligned(16))) float row_scores[kStepWholePages];
+  __shared__ __attribute__((aligned(16))) TS tail_mean[D];
+
+  int split, hkv, b;
+  locate_chunk(c, plan, split, hkv, b);
+  const int t = threadIdx.x, lane = t % kWave, wave = __builtin_amdgcn_readfirstlane(t / kWave);  // wave: scalar
+  const int row8 = lane / kRowLanes, cl = lane % kRowLanes;
+  const int32_t* pt = c.page_table + (int64_t)b * c.max_pages;
+  auto page_at = [&](int st) { return (st * kDecWaves + wave) * kRowsPerWave + row8; };
+  int ids[kSteps];
+  auto request_ids = [&](int st0) {
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) ids[u] = page_at(st0 + u) < c.max_pages_hint ? pt[page_at(st0 + u)] : -1;
+  };
+  request_ids(0);
+  Scorer scorer;
+  scorer.request(q + ((int64_t)b * c.H + hkv * G) * D, cl);
+  const int N = c.seq_lens[b];
+  const int P = min(min((N + S - 1) / S, c.max_pages_hint), kStepWholePages);
+
+  // the last page: its keys are on their way while the other pages are scored
+  constexpr int kTailWave = kDecWaves - 1;
+  PageRefresh<T, D, S> tail;
+  const int n_tail = min(S, N - (P - 1) * S);
+  int tail_phys = -1;
+  if (refresh_tail && wave == kTailWave && P > 0 && n_tail > 0) {  // uniform
+    tail_phys = pt[P - 1];
+    if (tail_phys < 0 || (int64_t)tail_phys >= c.num_phys) tail_phys = -1;
+    else tail.request(reinterpret_cast<const T*>(c.k_cache) + (int64_t)tail_phys * c.kv_page_stride + (int64_t)hkv * c.kv_head_stride, n_tail, lane);
+  }
+
+  char* stats = reinterpret_cast<char*>(c.page_stats);
+  const int64_t std_off = (int64_t)c.Hkv * D * (int64_t)sizeof(TS);  // byte offset of the stds inside a record
+  const int steps = (P + kStepPages - 1) / kStepPages;
+  bool first = true;
+  for (int st0 = 0; st0 < steps; st0 += kSteps) {
+    Raw16 md[kSteps][kChunks];
+    float sd[kSteps];
+    bool valid[kSteps];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {  // a row without a page reads the first bytes of the statistics
+      valid[u] = page_at(st0 + u) < P && ids[u] >= 0 && (int64_t)ids[u] < c.num_phys;
+      const char* rec = stats + (valid[u] ? (int64_t)ids[u] : 0) * c.rec_bytes;
+      const TS* src = reinterpret_cast<const TS*>(rec) + hkv * D + cl * kE;
+#pragma unroll
+      for (int j = 0; j < kChunks; ++j) md[u][j] = load_raw(src + j * (kE * kRowLanes));
+      sd[u] = reinterpret_cast<const float*>(rec + std_off)[hkv];
+    }
+    request_ids(st0 + kSteps);
+    if (first) scorer.unpack(lambda);
+    first = false;
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+      const float s = scorer.score(md[u], sd[u]);
+      const int p = page_at(st0 + u);
+      const bool fresh = refresh_tail && p == P - 1 && valid[u] && n_tail > 0;  // the tail wave's
+      // a page whose table entry points outside the pool gets NaN, which ranks below every score
+      if (cl == 0 && p < P && !fresh) row_scores[p] = valid[u] ? s : __uint_as_float(0x7fc00000u);
+    }
+  }
+  if (tail_phys >= 0) {  // uniform; the tail wave
+    if (first) scorer.unpack(lambda);
+    tail.reduce(n_tail, lane);
+    tail.store_mean(tail_mean, sizeof(TS) == 2, lane);
+    if (split == 0) {
+      char* rec = stats + (int64_t)tail_phys * c.rec_bytes;
+      tail.store_mean(rec + (int64_t)hkv * D * (int)sizeof(TS), sizeof(TS) == 2, lane);
+      if (lane == 0) reinterpret_cast<float*>(rec + std_off)[hkv] = tail.std;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    Raw16 md[kChunks];
+#pragma unroll
+    for (int j = 0; j < kChunks; ++j) md[j] = load_raw(&tail_mean[cl * kE + j * (kE * kRowLanes)]);
+    const float s = scorer.score(md, tail.std);
+    if (lane == 0) row_scores[P - 1] = s;
+  }
+  __syncthreads();
+  const float4 raw[1] = {*reinterpret_cast<const float4*>(&row_scores[min(4 * t, kStepWholePages - 4)])};
+  const ChunkOut<T> to = {part_o, part_ml, out, lse_out, plan.num_splits};
+  select_and_attend<T, D, S, G, false, 1>(c, q, raw, split, hkv, b, N, P, top_k, sel_pages, sel_count, plan, scale_log2, to, sh);
 }
 
 template <typename T, int D, int S, int G>
@@ -112,13 +223,31 @@ hipError_t launch_t(const CacheView& c, const StepArgs& a, hipStream_t st) {
   return stream_nt ? go(select_decode_kernel<T, D, S, G, true, 4>) : go(select_decode_kernel<T, D, S, G, false, 4>);
 }
 
+template <typename T, int D, int S, int G>
+hipError_t launch_whole_t(const CacheView& c, const StepArgs& a, hipStream_t st) {
+  const SplitPlan plan = selection_plan(c, a.top_k);
+  float* part_ml = a.partials + (size_t)c.B * c.Hkv * plan.num_splits * G * D;
+  auto go = [&](auto kernel) {
+    const dim3 grid = plan.rotate ? dim3(c.Hkv, c.B, plan.num_splits) : dim3(plan.num_splits, c.Hkv, c.B);
+    kernel<<<grid, dim3(kThreads), 0, st>>>(c, reinterpret_cast<const T*>(a.q), a.lambda, a.refresh_tail, a.top_k, a.sel_pages,
+                                            a.sel_count, plan, decode_scale_log2(c, a.sm_scale), a.partials, part_ml,
+                                            reinterpret_cast<T*>(a.out), a.lse_out);
+    return hipGetLastError();
+  };
+  return c.stats_bf16 ? go(whole_step_kernel<T, bf16_t, D, S, G>) : go(whole_step_kernel<T, float, D, S, G>);
+}
+
 template <typename T, int D, int S>
 hipError_t dispatch_g(const CacheView& c, const StepArgs& a, hipStream_t st) {
+  auto go = [&](auto group) {
+    constexpr int G = decltype(group)::value;
+    return a.scores ? launch_t<T, D, S, G>(c, a, st) : launch_whole_t<T, D, S, G>(c, a, st);
+  };
   switch (c.H / c.Hkv) {
-    case 1: return launch_t<T, D, S, 1>(c, a, st);
-    case 2: return launch_t<T, D, S, 2>(c, a, st);
-    case 4: return launch_t<T, D, S, 4>(c, a, st);
-    case 8: return launch_t<T, D, S, 8>(c, a, st);
+    case 1: return go(std::integral_constant<int, 1>());
+    case 2: return go(std::integral_constant<int, 2>());
+    case 4: return go(std::integral_constant<int, 4>());
+    case 8: return go(std::integral_constant<int, 8>());
     default: return hipErrorInvalidValue;
   }
 }

@@ -10,6 +10,8 @@ namespace unique {
 constexpr int kStepMaxPages = 4096;  // pages of a row: 16 scores per thread
 constexpr int kStepMaxTopK = 256;    // list entries that a workgroup keeps in the LDS
 
+constexpr int kStepWholePages = 384;  // pages of a row that are scored in the same kernel, too
+
 // Saved are a launch and the round trips of writing and reading the list, paid is a selection by four waves in every
 // workgroup of a cut row. us of a whole step in separate kernels / so (bf16, 8 KV heads, G = 4, D = 128, pages of 16, fp32 means):
 //   1 x 2048 pages, k = 128 22.2 / 19.7; 1 x 4096, 64 22.7 / 19.7; 8 x 1000, 64 25.3 / 22.3; 40 x 64, 8 20.6 / 18.6;
@@ -21,6 +23,17 @@ constexpr int kStepMaxTopK = 256;    // list entries that a workgroup keeps in t
 inline bool step_fuses(int rows, int max_pages, int top_k, const SplitPlan& plan) {
   if (max_pages > kStepMaxPages || top_k > kStepMaxTopK || (max_pages > 512 && 4 * top_k > max_pages)) return false;
   return plan.num_splits == 1 || (int64_t)rows * plan.num_splits * std::max(max_pages, 2048) <= 1024 * 2048;
+}
+
+// Steps whose rows are so short that every workgroup of a row's chunks scores the row for itself: one launch, at most with a merge
+// behind it. us of a whole step, three or four kernels / two or three / so (bf16, 8 KV heads, G = 4, D = 128, pages of 16, fp32 means):
+//   1 x 64 pages, k = 8 15.5 / 13.9 / 10.8; 1 x 128, 64 18.3 / - / 13.5; 16 x 128, 16 17.9 / 16.4 / 13.3; 80 x 64, 8 26.2 / 25.0 / 24.3;
+//   1 x 250, 200 19.9 / 19.5 / 17.3; the toy model (2 heads, fp32, D = 64, 128 pages, k = 16) 14.9 / 13.5 / 11.4
+// Reading a row's means takes one compute unit longer than a launch costs from 128 KB on: 16 x 270 pages 18.4 / 15.8, but 4 x 320,
+// k = 64 18.7 / 20.5 and 4 x 512, 64 19.1 / 23.2; rows of 256 bytes: 2 x 400, 16 heads, G = 8 21.8 / 20.4, 6 x 500, G = 1 21.6 / 20.0,
+// 10 x 500, G = 8 21.0 / 22.2.
+inline bool step_is_whole(int max_pages, int mean_bytes, bool streams) {
+  return max_pages <= (mean_bytes > 256 ? 256 : kStepWholePages) && !streams;
 }
 
 }  // namespace unique

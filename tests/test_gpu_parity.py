@@ -1256,3 +1256,41 @@ def test_dense_decode_cut_by_the_lengths_on_the_device(gpu_lib, dtype, Hkv, G, D
     sess.dense_paged_decode()
     torch.cuda.synchronize()
     assert torch.equal(first.view(torch.uint8), sess.out_dense.view(torch.uint8))
+
+
+@pytest.mark.parametrize("stats_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("dtype,Hkv,G,D,S,pages,top_k", [
+    (torch.float32, 2, 4, 64, 16, (128, 1), 16), (torch.bfloat16, 8, 4, 128, 16, (256, 255, 33), 40),
+    (torch.bfloat16, 8, 4, 128, 16, (257, 32, 31), 40), (torch.bfloat16, 1, 8, 128, 32, (97, 64), 200),
+    (torch.float32, 4, 8, 128, 8, (256, 7, 8, 9), 64), (torch.bfloat16, 32, 2, 64, 8, (384, 383), 100),
+    (torch.float32, 16, 1, 64, 32, (385, 384, 12), 96), (torch.bfloat16, 4, 1, 128, 8, (40,) * 90, 5)])
+def test_whole_step_in_one_kernel(gpu_lib, dtype, Hkv, G, D, S, pages, top_k, stats_dtype):
+    """Steps short enough to be one kernel, at the edges of the rows that it scores itself, against the separate calls
+    over an append flow: full, partial and fresh last pages, an empty sequence, page ids outside the pool, always-selected
+    pages. Statistics, lists and outputs are the same bits."""
+    lens = [S * p - (3 * i) % S for i, p in enumerate(pages)]
+    wl = W.build("whole", 13, dtype=dtype, B=len(lens), H=Hkv * G, Hkv=Hkv, D=D, S=S, seq_lens=lens, top_k=top_k,
+                 key_mode="shift", permute=True, spare_tokens=3).to(DEV)
+    hint = max(lens)  # appended tokens beyond the longest sequence's bound are ignored, as in the separate calls
+    if len(lens) > 2:
+        wl.page_table[1, 0], wl.page_table[2, -1 if pages[2] == wl.page_table.shape[1] else pages[2] - 1] = -5, 1 << 30
+    for recent in (0, 2):
+        apart = DecodeSession(wl, stats_dtype=stats_dtype, force_recent_pages=recent, max_seq_len_hint=hint)
+        step = DecodeSession(wl, stats_dtype=stats_dtype, force_recent_pages=recent, max_seq_len_hint=hint)
+        apart.update_page_stats()
+        step.update_page_stats()
+        before = wl.seq_lens.clone()
+        for i in range(3):
+            wl.seq_lens.copy_(before - (2 - i) * (before > 2 - i).int())
+            if i == 2 and len(lens) == 2:
+                wl.seq_lens[1] = 0
+            end = wl.seq_lens.clone()
+            apart.update_page_stats(end - 1, end, 1)
+            apart.score_select_topk()
+            apart.sparse_paged_decode()
+            step.decode_step(refresh_tail=True)
+            torch.cuda.synchronize()
+            for name in ("page_stats", "sel_pages", "sel_count", "lse"):
+                assert torch.equal(getattr(apart, name), getattr(step, name)), (name, i, recent)
+            assert torch.equal(apart.out.view(torch.uint8), step.out.view(torch.uint8)), (i, recent)
+        wl.seq_lens.copy_(before)
