@@ -266,6 +266,10 @@ def main():
         flusher.before_step(i)
         step()
     kernels_cold = kernel_trace(torch, traced_step, min(K, 20))
+    def traced_calls(i):  # a step may select and attend in one kernel; the separate calls never do
+        flusher.before_step(i)
+        separate_step()
+    call_kernels_cold = kernel_trace(torch, traced_calls, min(K, 20))
     flusher.restore()
     stages = staged(lambda i: None)
     sess.score_select_topk()          # leave the selection of the original queries in place
@@ -365,9 +369,9 @@ def main():
            "call_cold": entry(nb, stages_cold["sparse_paged_decode"]["median"]),
            "call_warm": entry(nb, stages["sparse_paged_decode"]["median"]),
            "partial_kernel_cold": None, "merge_kernel_cold_us": None}
-    if isinstance(kernels_cold, dict) and "error" not in kernels_cold:
-        part = [v for k, v in kernels_cold.items() if k.startswith("paged_decode_partial")]
-        merge = [v for k, v in kernels_cold.items() if k.startswith("paged_decode_merge")]
+    if isinstance(call_kernels_cold, dict) and "error" not in call_kernels_cold:
+        part = [v for k, v in call_kernels_cold.items() if k.startswith("paged_decode_partial")]
+        merge = [v for k, v in call_kernels_cold.items() if k.startswith("paged_decode_merge")]
         if part:
             sdk["partial_kernel_cold"] = entry(nb, part[0]["median"])
         if merge:

@@ -107,7 +107,9 @@ typedef struct unique_cache_desc {
 } unique_cache_desc;
 
 /* Bytes of device workspace that any of the calls below may need for this descriptor and top_k
- * (score rows, split-K partial results). Pass a buffer at least this large, 256-byte aligned.
+ * (score rows, maxima of groups of pages, split-K partial results). Pass a buffer at least this large, 256-byte
+ * aligned. A call that is given less is refused only if the score rows or the partial results alone do not fit; with
+ * what lies between it runs more kernels to the same results.
  * The contents need no initialisation and carry nothing between calls; calls that may overlap in time
  * (different streams) need a workspace each. */
 int unique_workspace_bytes(const unique_cache_desc* desc, int32_t top_k, size_t* out_bytes);
@@ -175,8 +177,9 @@ int unique_sparse_paged_decode(const unique_cache_desc* desc, const void* d_q, c
 /* One whole decode step in a single call: [refresh of the last page's statistics +] Eq. 6 scores, top-k
  * selection, Eq. 5 sparse attention. The results are bit-identical to unique_update_page_stats (on the last
  * token of every sequence, when refresh_tail != 0) followed by unique_score_select_topk and
- * unique_sparse_paged_decode with sel_stride = top_k; the statistics refresh runs inside the score kernel
- * (the workgroup that scores the last page recomputes its record first, same arithmetic), which saves a launch.
+ * unique_sparse_paged_decode with sel_stride = top_k, in fewer kernels: the statistics refresh runs inside the one
+ * that scores (same arithmetic), selection and attention are one kernel for budgets of up to 256 pages, and short rows
+ * are scored in that one, too.
  *   refresh_tail : non-zero = recompute the statistics record of the page holding token seq_lens[b]-1 of every
  *                  sequence before scoring (what a serving loop needs after appending one token).
  *   outputs      : d_sel_pages / d_sel_count as unique_score_select_topk, d_out / d_lse_out as
@@ -190,7 +193,7 @@ int unique_decode_step(const unique_cache_desc* desc, const void* d_q, int32_t t
  * bit, but the score rows and split-K partials live in a scratch array of UNIQUE_STATIC_SCRATCH_BYTES that is part
  * of the library's device image (each GPU the library runs on holds its own copy until the process ends). The call
  * allocates and frees nothing and calls no allocating routine; inputs and outputs are still the caller's.
- *   - A step that needs more scratch than that (unique_workspace_bytes says how much a descriptor and top_k need)
+ *   - A step whose score rows or partial results exceed that (what unique_workspace_bytes returns is always enough)
  *     returns UNIQUE_ERR_WORKSPACE and launches nothing; use unique_decode_step then.
  *   - The device that owns `stream` must be the current device. The first call on a device looks up the array's
  *     address there (no allocation); make that first call outside graph capture.

@@ -11,9 +11,11 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libunique_gfx950.so")
 SOURCES = ["api.hip", "stats.hip", "score.hip", "select.hip", "select_grouped.hip", "decode.hip"]
-# compiled once per element type and head dimension: (source, object file, defines)
-VARIANTS = [(f"{src}.hip", f"{src}_{t}_{d}.o", [f"-DUNIQUE_ELEM={c}", f"-DUNIQUE_DIM={d}"])
-            for src in ("step", "dense") for t, c in (("bf16", "uint16_t"), ("f32", "float")) for d in (128, 64)]
+# compiled once per element type, head dimension and, for the largest, page size: (source, object file, defines)
+_TYPES = [(t, c, d) for t, c in (("bf16", "uint16_t"), ("f32", "float")) for d in (128, 64)]
+VARIANTS = [("step.hip", f"step_{t}_{d}_{s}.o", [f"-DUNIQUE_ELEM={c}", f"-DUNIQUE_DIM={d}", f"-DUNIQUE_PAGE={s}"])
+            for t, c, d in _TYPES for s in (8, 16, 32)]
+VARIANTS += [("dense.hip", f"dense_{t}_{d}.o", [f"-DUNIQUE_ELEM={c}", f"-DUNIQUE_DIM={d}"]) for t, c, d in _TYPES]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed fp32 instructions are kept off for the device pass on purpose
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",

@@ -183,10 +183,26 @@ uint32_t* group_max_in(const unique::CacheView& v, int32_t top_k, float* buf, si
   return reinterpret_cast<uint32_t*>(buf + at / sizeof(float));
 }
 
+// Where a step's partial results lie while its scores, and the group maxima of long rows, are still being read.
+size_t partials_at(const unique::CacheView& v) {
+  return round_up(score_bytes(v), kAlign) + (v.max_pages_hint > unique::kStepMaxPages ? round_up(group_max_bytes(v), kAlign) : 0);
+}
+
 // Bytes of scratch with which a step may select and attend in one kernel: the score rows are still being read when the first
 // partial results are written, so these lie behind them.
 size_t fused_bytes(const unique::CacheView& v, const unique::SplitPlan& plan) {
-  return round_up(score_bytes(v), kAlign) + (plan.num_splits > 1 ? unique::plan_partial_floats(v, plan) * sizeof(float) : 0);
+  return partials_at(v) + (plan.num_splits > 1 ? unique::plan_partial_floats(v, plan) * sizeof(float) : 0);
+}
+
+template <typename T, int D>
+hipError_t launch_select_decode_of(const unique::CacheView& v, const unique::StepArgs& a, hipStream_t st) {
+  return v.S == 8 ? unique::launch_select_decode<T, D, 8>(v, a, st)
+                  : (v.S == 16 ? unique::launch_select_decode<T, D, 16>(v, a, st) : unique::launch_select_decode<T, D, 32>(v, a, st));
+}
+hipError_t launch_select_decode(const unique::CacheView& v, const unique::StepArgs& a, hipStream_t st) {
+  if (v.dtype == UNIQUE_DTYPE_F32)
+    return v.D == 64 ? launch_select_decode_of<float, 64>(v, a, st) : launch_select_decode_of<float, 128>(v, a, st);
+  return v.D == 64 ? launch_select_decode_of<uint16_t, 64>(v, a, st) : launch_select_decode_of<uint16_t, 128>(v, a, st);
 }
 
 // Score -> select -> decode on one buffer of `bytes` bytes. In separate kernels the score rows are consumed by the select
@@ -203,13 +219,10 @@ int decode_step_launch(const unique::CacheView& v, const void* d_q, int32_t top_
   if (!whole) e = unique::launch_score(v, d_q, lambda, buf, stride, nullptr, group_max, refresh_tail != 0, st);
   if (e != hipSuccess) return hip_fail(e, "page score launch");
   if (whole || (fuses && bytes >= fused_bytes(v, plan))) {
-    float* partials = whole ? buf : buf + round_up(score_bytes(v), kAlign) / sizeof(float);
-    const unique::StepArgs a = {d_q, whole ? nullptr : buf, stride, top_k, lambda, refresh_tail != 0, d_sel_pages, d_sel_count,
+    float* partials = whole ? buf : buf + partials_at(v) / sizeof(float);
+    const unique::StepArgs a = {d_q, whole ? nullptr : buf, group_max, stride, top_k, lambda, refresh_tail != 0, d_sel_pages, d_sel_count,
                                 sm_scale, d_out, d_lse_out, partials};
-    e = v.dtype == UNIQUE_DTYPE_F32 ? (v.D == 64 ? unique::launch_select_decode<float, 64>(v, a, st)
-                                                 : unique::launch_select_decode<float, 128>(v, a, st))
-                                    : (v.D == 64 ? unique::launch_select_decode<uint16_t, 64>(v, a, st)
-                                                 : unique::launch_select_decode<uint16_t, 128>(v, a, st));
+    e = launch_select_decode(v, a, st);
     if (e == hipSuccess && plan.num_splits > 1)
       e = unique::launch_merge(v, d_sel_count, top_k, plan, partials, d_out, d_lse_out, st);
     return e == hipSuccess ? UNIQUE_OK : hip_fail(e, "select and decode launch");

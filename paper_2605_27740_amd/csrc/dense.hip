@@ -16,33 +16,45 @@ namespace {
 
 // The chunks of a batch, the same in every wave that asks: lane b holds those of sequence b.
 struct BatchChunks {
-  int pages;   // of sequence `lane`
+  int len;     // tokens of sequence `lane`
+  int pages;
   int chunks;  // per row of that sequence
   int before;  // chunks per head of the sequences before it
 };
 
-__device__ __forceinline__ int chunks_of(int pages, float inv_chunk) {  // (any number >= 1 is a valid cut)
-  return pages > 0 ? max(1, (int)ceilf((float)pages * inv_chunk)) : 0;
-}
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x), kWave - 1); }
 
+// Quotients are approximate where any value will do: a row may be cut into any number of chunks from one on, as long as all of
+// them have a workgroup. With the first length below they have: sum of ceil(pages / length) <= total / length + rows, and the margin
+// of a thousandth is far above the errors of the reciprocal and of pages as floats.
 __device__ __forceinline__ BatchChunks cut_batch(const CacheView& c, int S, int max_chunks) {
   const int lane = threadIdx.x % kWave;
   BatchChunks bc;
-  const int N = lane < c.B ? c.seq_lens[lane] : 0;
-  bc.pages = max(0, min((N + S - 1) / S, c.max_pages_hint));
+  bc.len = lane < c.B ? c.seq_lens[lane] : 0;
+  bc.pages = max(0, min((bc.len + S - 1) / S, c.max_pages_hint));
   const int rows = c.B * c.Hkv;
-  const int total = __builtin_amdgcn_readlane(wave_inclusive_scan(bc.pages), kWave - 1) * c.Hkv;
-  // a lane tries a chunk length: from an equal share on, up to the one that is enough with every row's last chunk nearly empty
+  const int total = wave_sum(bc.pages) * c.Hkv;
   const int slots = min(max(total / (kDenseSlots * kDensePages), 1) * kDenseSlots, max_chunks);
-  const int least = total / slots, most = total / (slots - rows) + 2;
-  const int mine = max(least + 1 + (int)((int64_t)(most - least) * lane / (kWave - 1)), kDecWaves);
-  const float inv = 1.0f / (float)mine;
-  int n = 0;
-  for (int b = 0; b < c.B; ++b) n += chunks_of(__builtin_amdgcn_readlane(bc.pages, b), inv);
-  const unsigned long long fits = __ballot(n * c.Hkv <= slots);
-  const int best = fits ? __ffsll(fits) - 1 : kWave - 1;  // (the last one always fits)
-  const float best_inv = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(inv), best));
-  bc.chunks = chunks_of(bc.pages, best_inv);
+  auto cut = [&](float length) {
+    return bc.pages > 0 ? max(1, (int)ceilf((float)bc.pages * __builtin_amdgcn_rcpf(length))) : 0;
+  };
+  // The chunk length is at least an equal share, and at most what is enough even if every row's last chunk is nearly empty;
+  // bisection down to a 64th of the length. Equally long sequences have as many chunks per row as there is room for.
+  const float share = (float)total * __builtin_amdgcn_rcpf((float)slots);
+  float fits = fmaxf((float)total * __builtin_amdgcn_rcpf((float)(slots - rows)) * 1.001f + 1.f, (float)kDecWaves), fails = share;
+  bc.chunks = cut(fits);
+  if (__ballot(lane < c.B && bc.pages != __builtin_amdgcn_readfirstlane(bc.pages)) == 0) {
+    const int most = (bc.pages + kDecWaves - 1) / kDecWaves;  // of at least a page per wave
+    bc.chunks = lane < c.B ? min(slots / rows, most) : 0;
+  } else {
+#pragma unroll 1
+    while (fits - fails > fits * (1.f / 64.f) && fits > (float)kDecWaves) {
+      const float length = fmaxf(0.5f * (fits + fails), (float)kDecWaves);
+      const int chunks = cut(length);
+      if (wave_sum(chunks) * c.Hkv <= slots) { fits = length; bc.chunks = chunks; }
+      else fails = length;
+    }
+  }
   bc.before = wave_inclusive_scan(bc.chunks) - bc.chunks;
   return bc;
 }
@@ -62,7 +74,7 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_dense_kernel(Ca
   const int i = w - __builtin_amdgcn_readlane(bc.before, b) * c.Hkv;  // chunk `split` of head hkv
   const int hkv = i / n, split = i % n, len = (P + n - 1) / n;
   const int begin = split * len, end = min(begin + len, P);
-  const int N = c.seq_lens[b];
+  const int N = __builtin_amdgcn_readlane(bc.len, b);
   const ChunkOut<T> to = {part_o, part_ml, nullptr, nullptr, 2};
   const Chunk chunk = {hkv, b, begin, max(begin, end), N, w};
   auto lookup = [&](int e, bool, int& phys, int& ntok) {

@@ -9,6 +9,7 @@ namespace unique {
 
 constexpr int kDenseSlots = 512;    // workgroups that run at the same time: two on each of the 256 compute units
 constexpr int kDensePages = 256;    // pages of a chunk from which on twice the workgroups are used
+constexpr int64_t kDenseLeastBytes = 96ll << 20;
 constexpr int kDenseMaxBatch = 64;  // a lane per sequence
 
 // Chunks of the whole batch, at most as many as the partial results of most_splits hold.
@@ -18,14 +19,15 @@ inline int dense_max_chunks(int rows, int max_pages) {
   return (int)std::min(all, wanted);
 }
 
-// Finding the cut costs 1 us, so launches that can read less than 64 MB keep most_splits (2 sequences of up to 4000 tokens, 8 KV heads:
-// 12.9 us, so 14.4). us of the whole call before / now (bf16, 8 KV heads, G = 4, D = 128, pages of 16): 4 sequences of 6K to 30K tokens
-// 66.4 / 43.2; 8 of 2K to 60K 205 / 163; 16 of 1K to 16K 124 / 62; even ones 8 x 16384 86.6 / 87.2, 16 x 30000 311 / 299,
-// 5 x 7000 31.1 / 30.3. More rows than half the slots, and a single sequence, have nothing to gain.
+// Finding the cut costs 0.5 us or more in both kernels, which launches that cannot read 96 MB do not get back (2 sequences of up to 4000
+// tokens, 8 KV heads: 12.9 us with most_splits, 14.4 so; 4 of 2048, fp32: 18.9 and 20.5). us of the whole call before / now (bf16,
+// 8 KV heads, G = 4, D = 128, pages of 16): 4 sequences of 6K to 30K tokens 66.4 / 43.2; 8 of 2K to 60K, 1012 MB 205 / 163; 16 of 1K
+// to 16K 128 / 70; even ones 8 x 16384 86.6 / 86.5, 16 x 30000 312 / 299, 5 x 7000 31.3 / 30.1. More rows than half the slots, and a
+// single sequence, have nothing to gain.
 inline bool dense_balances(int batch, int kv_heads, int max_pages, int page_bytes) {
   const int64_t rows = (int64_t)batch * kv_heads;
   if (batch < 2 || batch > kDenseMaxBatch || rows > kDenseSlots / 2 || rows * max_pages > INT32_MAX) return false;
-  return most_splits((int)rows, max_pages).num_splits > 1 && rows * max_pages * page_bytes >= (64ll << 20);
+  return most_splits((int)rows, max_pages).num_splits > 1 && rows * max_pages * page_bytes >= kDenseLeastBytes;
 }
 
 }  // namespace unique

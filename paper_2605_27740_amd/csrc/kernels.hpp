@@ -67,6 +67,7 @@ hipError_t launch_decode(const CacheView& c, const void* d_q, const int32_t* d_s
 struct StepArgs {
   const void* q;
   const float* scores;   // [rows][score_stride]; null: the kernel scores the pages, too (step_is_whole)
+  const uint32_t* group_max;  // of those scores, for rows of more than kStepMaxPages pages
   int score_stride, top_k;
   float lambda;          // of those scores
   int refresh_tail;
@@ -85,12 +86,13 @@ hipError_t launch_merge(const CacheView& c, const int32_t* d_sel_count, int sel_
                         void* d_out, float* d_lse_out, hipStream_t stream);
 
 // Selection and attention in one kernel (step_rule.hpp says for which steps); a cut row needs launch_merge behind it.
-template <typename T, int D>
+template <typename T, int D, int S>
 hipError_t launch_select_decode(const CacheView& c, const StepArgs& a, hipStream_t stream);
-template <> hipError_t launch_select_decode<float, 64>(const CacheView& c, const StepArgs& a, hipStream_t stream);
-template <> hipError_t launch_select_decode<float, 128>(const CacheView& c, const StepArgs& a, hipStream_t stream);
-template <> hipError_t launch_select_decode<uint16_t, 64>(const CacheView& c, const StepArgs& a, hipStream_t stream);
-template <> hipError_t launch_select_decode<uint16_t, 128>(const CacheView& c, const StepArgs& a, hipStream_t stream);
+#define UNIQUE_DECLARE(T, D, S) template <> hipError_t launch_select_decode<T, D, S>(const CacheView&, const StepArgs&, hipStream_t);
+#define UNIQUE_DECLARE_PAGES(T, D) UNIQUE_DECLARE(T, D, 8) UNIQUE_DECLARE(T, D, 16) UNIQUE_DECLARE(T, D, 32)
+UNIQUE_DECLARE_PAGES(float, 64) UNIQUE_DECLARE_PAGES(float, 128) UNIQUE_DECLARE_PAGES(uint16_t, 64) UNIQUE_DECLARE_PAGES(uint16_t, 128)
+#undef UNIQUE_DECLARE_PAGES
+#undef UNIQUE_DECLARE
 
 // Attention over every page, cut by the lengths on the device (dense_plan.hpp says for which launches).
 template <typename T, int D>

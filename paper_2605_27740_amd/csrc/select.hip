@@ -269,7 +269,7 @@ __global__ __launch_bounds__(kThreads) void topk_select_long_kernel(CacheView c,
   }
   __syncthreads();
   if (total > kDense * kThreads) {
-    select_reread<kThreads>(key_of, P, kb, bucket_map(kmin, kmax, kBuckets), out, sh);
+    select_reread<kThreads>(key_of, P, kb, bucket_map(kmin, kmax, kBuckets), [&](int at, int page) { out[at] = page; }, sh);
     return;
   }
   uint32_t dkey[kDense];

@@ -417,9 +417,10 @@ __device__ __forceinline__ uint32_t bound_row(const uint32_t (&key)[kVecs * kPer
 // row is coalesced, eight reads at a time. The compaction walks the row in blocks of `threads` consecutive pages and
 // places each selected page by a ballot prefix inside its wave, the wave totals of the block (LDS) and the running
 // totals of the blocks before it, which keeps the output in ascending page order and takes keys tied with the k-th from
-// the lowest page upward. The histogram in `sh` is zero and sh.ncand is 0. All threads call it.
-template <int kThreads, typename KeyOf>
-__device__ __forceinline__ void select_reread(KeyOf key_of, int P, int kb, BucketMap map, int32_t* out,
+// the lowest page upward. emit(at, page): the page is the at-th selected one.
+// The histogram in `sh` is zero and sh.ncand is 0. All threads call it.
+template <int kThreads, typename KeyOf, typename Emit>
+__device__ __forceinline__ void select_reread(KeyOf key_of, int P, int kb, BucketMap map, Emit emit,
                                               SelectShared<kThreads>& sh) {
   using Sh = SelectShared<kThreads>;
   constexpr int kWaves = Sh::kWaves, kBuckets = Sh::kBuckets, kMaxRank = Sh::kMaxRank;
@@ -511,8 +512,8 @@ __device__ __forceinline__ void select_reread(KeyOf key_of, int P, int kb, Bucke
         gt_block += g;
         eq_block += e;
       }
-      if (gt) out[gt_before + min(eq_before, need)] = page;
-      else if (eq && eq_before < need) out[gt_before + eq_before] = page;
+      if (gt) emit(gt_before + min(eq_before, need), page);
+      else if (eq && eq_before < need) emit(gt_before + eq_before, page);
       gt_run += gt_block;
       eq_run += eq_block;
     }

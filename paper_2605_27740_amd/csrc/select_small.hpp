@@ -220,6 +220,32 @@ __device__ __forceinline__ void select_gathered(const uint2* kept, int total, ui
   select_gathered<kN>(kept, total, low, top, kb, emit, [](const int(&)[kN]) {});
 }
 
+// The kb largest of `total` <= kSmallCap gathered keys, all above `low`, by every wave for itself, with their physical pages from the
+// row's page table (of at least one entry), which are looked up while the search runs: emit_all(r, at, page, phys), see
+// select_gathered.
+template <typename EmitAll>
+__device__ __forceinline__ void select_kept(const uint2* kept, int total, uint32_t low, int kb, const int32_t* page_table,
+                                            EmitAll emit_all) {
+  const int lane = threadIdx.x % kWave;
+  auto gathered = [&](auto per_lane) {
+    constexpr int kN = decltype(per_lane)::value;
+    int phys[kN];
+    uint32_t top = 0u;
+#pragma unroll
+    for (int r = 0; r < kN; ++r) top = max(top, r * kWave + lane < total ? kept[r * kWave + lane].x : 0u);
+    top = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<true>(top));
+    select_gathered<kN>(kept, total, low, top, kb, [&](int r, int at, int page) { emit_all(r, at, page, phys[r]); },
+                        [&](const int(&page)[kN]) {
+#pragma unroll
+                          for (int r = 0; r < kN; ++r) phys[r] = page_table[page[r]];
+                        });
+  };
+  if (total <= 2 * kWave) gathered(std::integral_constant<int, 2>());
+  else if (total <= 4 * kWave) gathered(std::integral_constant<int, 4>());
+  else if (total <= 8 * kWave) gathered(std::integral_constant<int, 8>());
+  else gathered(std::integral_constant<int, 16>());
+}
+
 // Thread t holds the keys of the pages row_page(j) (0: no page); 0 < kb < P; page_table: the row's, of at least one entry.
 // emit_all(r, at, page, phys) is called by every wave for all that its lanes hold (see select_gathered); if too many keys are left to
 // gather, emit_own(at, page) is called once per selected page instead, followed by a barrier.
@@ -283,23 +309,7 @@ __device__ __forceinline__ void select_small(const uint32_t (&key)[4 * kVecs], i
       }
     }
     __syncthreads();
-    auto gathered = [&](auto per_lane) {
-      constexpr int kN = decltype(per_lane)::value;
-      int phys[kN];  // looked up while the search runs
-      uint32_t top = 0u;
-#pragma unroll
-      for (int r = 0; r < kN; ++r) top = max(top, r * kWave + lane < total ? sh.kept[r * kWave + lane].x : 0u);
-      top = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<true>(top));
-      select_gathered<kN>(sh.kept, total, T0 - 1u, top, kb, [&](int r, int at, int page) { emit_all(r, at, page, phys[r]); },
-                          [&](const int(&page)[kN]) {
-#pragma unroll
-                            for (int r = 0; r < kN; ++r) phys[r] = page_table[page[r]];
-                          });
-    };
-    if (total <= 2 * kWave) gathered(std::integral_constant<int, 2>());
-    else if (total <= 4 * kWave) gathered(std::integral_constant<int, 4>());
-    else if (total <= 8 * kWave) gathered(std::integral_constant<int, 8>());
-    else gathered(std::integral_constant<int, 16>());
+    select_kept(sh.kept, total, T0 - 1u, kb, page_table, emit_all);
     return;
   }
   if constexpr (kThreads * kVecs * 4 > kSmallCap) {

@@ -8,7 +8,7 @@
 // 2200, the list 1600, the attention over one page per wave 6900. Kernel us, selection + attention apart 5.2 + 5.8, so 8.5.
 #include "decode_core.hpp"
 #include "score_core.hpp"
-#include "select_small.hpp"
+#include "select_groups.hpp"
 #include "step_rule.hpp"
 
 namespace unique {
@@ -16,23 +16,23 @@ namespace {
 
 constexpr int kThreads = kDecWaves * kWave;
 
-template <typename T, int D, int G, int kVecs>
+template <typename T, int D, int G, typename Select>
 struct StepShared {
-  SmallShared<kThreads, kVecs> sel;  // apart from `dec`: a wave may be done before another one has its list
+  Select sel;                       // apart from `dec`: a wave may be done before another one has its list
   DecodeShared<T, D, G> dec;
-  int2 list[kStepMaxTopK + kWave];   // physical page, logical page; the last ones are for lanes without an entry
+  int2 list[kStepMaxTopK + kWave];  // physical page, logical page; the last ones are for lanes without an entry
 };
 
-// What a step does to one chunk once the row's scores are in registers, row_page(j) for raw[j / 4]. All threads call it.
-template <typename T, int D, int S, int G, bool kNT, int kVecs>
-__device__ __forceinline__ void select_and_attend(const CacheView& c, const T* __restrict__ q, const float4 (&raw)[kVecs], int split,
-                                                  int hkv, int b, int N, int P, int top_k, int32_t* __restrict__ sel_pages,
-                                                  int32_t* __restrict__ sel_count, const SplitPlan& plan, float scale_log2,
-                                                  const ChunkOut<T>& to, StepShared<T, D, G, kVecs>& sh) {
-  constexpr int kPer = 4, kItems = kVecs * kPer;
+// What a step does to one chunk once the scores are known. select(kb, page_table, emit_all, emit_own) selects kb < P pages: either it
+// calls emit_all in every wave for all that its lanes hold (see select_gathered), or emit_own once per selected page and
+// then a barrier. All threads call it.
+template <typename T, int D, int S, int G, bool kNT, typename Shared, typename Select>
+__device__ __forceinline__ void select_and_attend(const CacheView& c, const T* __restrict__ q, int split, int hkv, int b, int N, int P,
+                                                  int top_k, int32_t* __restrict__ sel_pages, int32_t* __restrict__ sel_count,
+                                                  const SplitPlan& plan, float scale_log2, const ChunkOut<T>& to, Shared& sh,
+                                                  Select select) {
   const int row = b * c.Hkv + hkv;
   const int t = threadIdx.x, lane = t % kWave, wave = __builtin_amdgcn_readfirstlane(t / kWave);  // wave: scalar
-  auto page_of = [](int j) { return row_page<kThreads, kPer>(j); };
   const int32_t* pt = c.page_table + (int64_t)b * c.max_pages;
   const int kb = min(top_k, P);
   const int begin = split * plan.pages_per_split, end = min(begin + plan.pages_per_split, kb);
@@ -52,10 +52,6 @@ __device__ __forceinline__ void select_and_attend(const CacheView& c, const T* _
     for (int p = begin + t; p < end; p += kThreads) sh.list[p - begin] = make_int2(pt[p], p);
     __syncthreads();
   } else {
-    uint32_t key[kItems];
-#pragma unroll
-    for (int v = 0; v < kVecs; ++v) keys_of(raw[v], P - page_of(4 * v), key + 4 * v);
-    force_recent_keys<kThreads, kVecs, kPer>(key, P, kb, c.force_recent);
     // Every wave knows the whole selection. It keeps the entries that it will attend over itself (see decode_chunk), so no
     // barrier is needed before it reads them back.
     auto emit_all = [&](int r, int at, int page, int ph) {
@@ -67,7 +63,7 @@ __device__ __forceinline__ void select_and_attend(const CacheView& c, const T* _
       if (split == 0) sel_row[at] = page;
       if (at >= begin && at < end) sh.list[at - begin] = make_int2(pt[page], page);
     };
-    select_small<kThreads, kVecs>(key, P, kb, pt, emit_all, emit_own, sh.sel);
+    select(kb, pt, emit_all, emit_own);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
@@ -83,13 +79,30 @@ __device__ __forceinline__ void select_and_attend(const CacheView& c, const T* _
   decode_chunk<D, S, G, kNT>(c, q, chunk, wave, lane, lookup, scale_log2, to, sh.dec);
 }
 
+// The selection from scores in registers, row_page(j) for raw[j / 4].
+template <int kVecs>
+struct SelectFromScores {
+  const CacheView& c;
+  const float4 (&raw)[kVecs];
+  int P;
+  SmallShared<kThreads, kVecs>& sh;
+  template <typename EmitAll, typename EmitOwn>
+  __device__ __forceinline__ void operator()(int kb, const int32_t* page_table, EmitAll emit_all, EmitOwn emit_own) const {
+    uint32_t key[4 * kVecs];
+#pragma unroll
+    for (int v = 0; v < kVecs; ++v) keys_of(raw[v], P - row_page<kThreads, 4>(4 * v), key + 4 * v);
+    force_recent_keys<kThreads, kVecs, 4>(key, P, kb, c.force_recent);
+    select_small<kThreads, kVecs>(key, P, kb, page_table, emit_all, emit_own, sh);
+  }
+};
+
 // kVecs: 16-byte loads of scores per thread.
 template <typename T, int D, int S, int G, bool kNT, int kVecs>
 __global__ __launch_bounds__(kThreads) void select_decode_kernel(
     CacheView c, const T* __restrict__ q, const float* __restrict__ scores, int score_stride, int top_k,
     int32_t* __restrict__ sel_pages, int32_t* __restrict__ sel_count, SplitPlan plan, float scale_log2,
     float* __restrict__ part_o, float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse_out) {
-  __shared__ StepShared<T, D, G, kVecs> sh;
+  __shared__ StepShared<T, D, G, SmallShared<kThreads, kVecs>> sh;
   int split, hkv, b;
   locate_chunk(c, plan, split, hkv, b);
   // the scores are requested together with the sequence length: score rows are as long as the launch's bound on the pages
@@ -104,7 +117,51 @@ __global__ __launch_bounds__(kThreads) void select_decode_kernel(
   const int N = c.seq_lens[b];
   const int P = min(min((N + S - 1) / S, c.max_pages_hint), kThreads * 4 * kVecs);
   const ChunkOut<T> to = {part_o, part_ml, out, lse_out, plan.num_splits};
-  select_and_attend<T, D, S, G, kNT, kVecs>(c, q, raw, split, hkv, b, N, P, top_k, sel_pages, sel_count, plan, scale_log2, to, sh);
+  select_and_attend<T, D, S, G, kNT>(c, q, split, hkv, b, N, P, top_k, sel_pages, sel_count, plan, scale_log2, to, sh,
+                                     SelectFromScores<kVecs>{c, raw, P, sh.sel});
+}
+
+// The same for longer rows, from the maxima of their groups of pages.
+constexpr int kGroupVecs = kStepMaxGroupPages / (4 * kGroupPages * kThreads);
+struct SelectFromGroups {
+  const CacheView& c;
+  const float* srow;
+  const uint32_t* grow;
+  int P;
+  struct Shared {
+    GroupShared<kThreads, 4, kSmallCap> groups;
+    SelectShared<kThreads> reread;
+  };
+  Shared& sh;
+  template <typename EmitAll, typename EmitOwn>
+  __device__ __forceinline__ void operator()(int kb, const int32_t* page_table, EmitAll emit_all, EmitOwn emit_own) const {
+    const int forced_from = P - min(c.force_recent, kb);
+    Gathered<4> got;
+    gather_from_groups<kThreads, kGroupVecs>(srow, grow, P, kb, forced_from, got, sh.groups);
+    if (got.total >= 0 && got.total <= kSmallCap) {  // uniform
+      select_kept(sh.groups.kept, got.total, got.T0 - 1u, kb, page_table, emit_all);
+    } else {
+      select_by_rereading<kThreads>(srow, P, kb, forced_from, emit_own, sh.reread);
+      __syncthreads();
+    }
+  }
+};
+
+template <typename T, int D, int S, int G, bool kNT>
+__global__ __launch_bounds__(kThreads) void select_groups_decode_kernel(
+    CacheView c, const T* __restrict__ q, const float* __restrict__ scores, const uint32_t* __restrict__ group_max, int score_stride,
+    int top_k, int32_t* __restrict__ sel_pages, int32_t* __restrict__ sel_count, SplitPlan plan, float scale_log2,
+    float* __restrict__ part_o, float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse_out) {
+  __shared__ StepShared<T, D, G, SelectFromGroups::Shared> sh;
+  int split, hkv, b;
+  locate_chunk(c, plan, split, hkv, b);
+  const int64_t row = (int64_t)b * c.Hkv + hkv;
+  const int N = c.seq_lens[b];
+  const int P = min(min((N + S - 1) / S, c.max_pages_hint), kStepMaxGroupPages);
+  const ChunkOut<T> to = {part_o, part_ml, out, lse_out, plan.num_splits};
+  select_and_attend<T, D, S, G, kNT>(
+      c, q, split, hkv, b, N, P, top_k, sel_pages, sel_count, plan, scale_log2, to, sh,
+      SelectFromGroups{c, scores + row * score_stride, group_max + row * (score_stride / kGroupPages), P, sh.sel});
 }
 
 // The whole step of a small launch in one kernel: every workgroup also scores its row's pages, with the arithmetic and in the
@@ -119,7 +176,7 @@ __global__ __launch_bounds__(kThreads) void whole_step_kernel(
   constexpr int kChunks = Scorer::kChunks, kE = Scorer::kE;
   constexpr int kSteps = G == 8 ? 2 : 4;                     // rows in flight per lane (eight queries leave fewer registers)
   constexpr int kStepPages = kDecWaves * kRowsPerWave;       // pages that the workgroup scores at a time
-  __shared__ StepShared<T, D, G, 1> sh;
+  __shared__ StepShared<T, D, G, SmallShared<kThreads, 1>> sh;
   __shared__ __attribute__((aligned(16))) float row_scores[kStepWholePages];
   __shared__ __attribute__((aligned(16))) TS tail_mean[D];
 
@@ -200,7 +257,8 @@ __global__ __launch_bounds__(kThreads) void whole_step_kernel(
   __syncthreads();
   const float4 raw[1] = {*reinterpret_cast<const float4*>(&row_scores[min(4 * t, kStepWholePages - 4)])};
   const ChunkOut<T> to = {part_o, part_ml, out, lse_out, plan.num_splits};
-  select_and_attend<T, D, S, G, false, 1>(c, q, raw, split, hkv, b, N, P, top_k, sel_pages, sel_count, plan, scale_log2, to, sh);
+  select_and_attend<T, D, S, G, false>(c, q, split, hkv, b, N, P, top_k, sel_pages, sel_count, plan, scale_log2, to, sh,
+                                       SelectFromScores<1>{c, raw, P, sh.sel});
 }
 
 template <typename T, int D, int S, int G>
@@ -216,6 +274,16 @@ hipError_t launch_t(const CacheView& c, const StepArgs& a, hipStream_t st) {
                                             reinterpret_cast<T*>(a.out), a.lse_out);
     return hipGetLastError();
   };
+  if (a.group_max) {
+    auto go_groups = [&](auto kernel) {
+      const dim3 grid = plan.rotate ? dim3(c.Hkv, c.B, plan.num_splits) : dim3(plan.num_splits, c.Hkv, c.B);
+      kernel<<<grid, dim3(kThreads), 0, st>>>(c, reinterpret_cast<const T*>(a.q), a.scores, a.group_max, a.score_stride, a.top_k,
+                                              a.sel_pages, a.sel_count, plan, decode_scale_log2(c, a.sm_scale), a.partials, part_ml,
+                                              reinterpret_cast<T*>(a.out), a.lse_out);
+      return hipGetLastError();
+    };
+    return stream_nt ? go_groups(select_groups_decode_kernel<T, D, S, G, true>) : go_groups(select_groups_decode_kernel<T, D, S, G, false>);
+  }
   if (c.max_pages_hint <= 4 * kThreads)
     return stream_nt ? go(select_decode_kernel<T, D, S, G, true, 1>) : go(select_decode_kernel<T, D, S, G, false, 1>);
   if (c.max_pages_hint <= 8 * kThreads)
@@ -254,15 +322,10 @@ hipError_t dispatch_g(const CacheView& c, const StepArgs& a, hipStream_t st) {
 
 }  // namespace
 
-// One translation unit per element type and head dimension: UNIQUE_ELEM, UNIQUE_DIM.
+// One translation unit per element type, head dimension and page size: UNIQUE_ELEM, UNIQUE_DIM, UNIQUE_PAGE.
 template <>
-hipError_t launch_select_decode<UNIQUE_ELEM, UNIQUE_DIM>(const CacheView& c, const StepArgs& a, hipStream_t st) {
-  switch (c.S) {
-    case 8: return dispatch_g<UNIQUE_ELEM, UNIQUE_DIM, 8>(c, a, st);
-    case 16: return dispatch_g<UNIQUE_ELEM, UNIQUE_DIM, 16>(c, a, st);
-    case 32: return dispatch_g<UNIQUE_ELEM, UNIQUE_DIM, 32>(c, a, st);
-    default: return hipErrorInvalidValue;
-  }
+hipError_t launch_select_decode<UNIQUE_ELEM, UNIQUE_DIM, UNIQUE_PAGE>(const CacheView& c, const StepArgs& a, hipStream_t st) {
+  return dispatch_g<UNIQUE_ELEM, UNIQUE_DIM, UNIQUE_PAGE>(c, a, st);
 }
 
 }  // namespace unique

@@ -8,6 +8,7 @@
 namespace unique {
 
 constexpr int kStepMaxPages = 4096;  // pages of a row: 16 scores per thread
+constexpr int kStepMaxGroupPages = 32768;  // pages of a row that is selected from by its group maxima: 16 of them per thread
 constexpr int kStepMaxTopK = 256;    // list entries that a workgroup keeps in the LDS
 
 constexpr int kStepWholePages = 384;  // pages of a row that are scored in the same kernel, too
@@ -20,8 +21,11 @@ constexpr int kStepWholePages = 384;  // pages of a row that are scored in the s
 // more than k groups of four pages; up to 512 pages it does not matter: 8 x 250, 200 34.0 / 32.4).
 // Workgroups that wait for a free unit select when the others already stream: 24 x 1000 pages cut in 5, 960 workgroups, 48.6 /
 // 47.2; but 31 x 4096, 64 120.6 / 122.4, so those rows are left apart from 512 workgroups on.
+// Longer rows, from their group maxima, in kernels of their own (select_grouped.hip) / so: 1 x 4200, 64 24.8 / 22.1; 1 x 8192, 256 29.0 /
+// 27.8; 16 x 8192, 256 143.8 / 141.8; 1 x 32768, 128 41.7 / 40.0; 4 x 16384, 64 62.9 / 60.7.
 inline bool step_fuses(int rows, int max_pages, int top_k, const SplitPlan& plan) {
-  if (max_pages > kStepMaxPages || top_k > kStepMaxTopK || (max_pages > 512 && 4 * top_k > max_pages)) return false;
+  if (max_pages > kStepMaxGroupPages || top_k > kStepMaxTopK || (max_pages > 512 && 4 * top_k > max_pages)) return false;
+  if (max_pages > kStepMaxPages) return 24 * top_k <= max_pages && (plan.num_splits == 1 || (int64_t)rows * plan.num_splits <= 512);
   return plan.num_splits == 1 || (int64_t)rows * plan.num_splits * std::max(max_pages, 2048) <= 1024 * 2048;
 }
 

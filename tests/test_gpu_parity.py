@@ -1136,12 +1136,12 @@ def test_select_ragged_rows(gpu_lib, B, Hkv, P, top_k, n):
             assert cnt[b, h] == kb and np.array_equal(sel[b, h, :kb], want) and (sel[b, h, kb:] == -1).all(), (b, h, p)
 
 
-@pytest.mark.parametrize("P", [1, 5, 127, 256, 512, 513, 1023, 1024, 1025, 2048, 2049, 4095, 4096, 4097])
+@pytest.mark.parametrize("P", [1, 5, 127, 256, 512, 513, 1023, 1024, 1025, 2048, 2049, 4095, 4096, 4097, 4104, 6144, 8193, 32768, 32769])
 def test_step_with_the_selection_in_the_attention_kernel(gpu_lib, P):
     """unique_decode_step on planted scores against the separate calls, at the edges of the rows, budgets and score
     distributions that it serves in one kernel: every output is the same bits. Also with the smallest workspace that is
     accepted, with which it has to take two kernels."""
-    ks = sorted({1, min(P, 7), max(1, P // 4), max(1, min(P - 1, 200)), 256, 257})
+    ks = sorted({1, min(P, 7), max(1, min(P // 4, 1100)), max(1, P // 24), max(1, min(P - 1, 200)), 256, 257})
     wl = W.build("planted", 9, dtype=torch.bfloat16 if P % 2 else torch.float32, B=2, H=8, Hkv=2, D=64, S=8,
                  seq_lens=[8 * P, max(8 * P - 3 - 8 * (P // 3), 1)], top_k=1, key_mode="iid", permute=True, poison=False).to(DEV)
     wl.q.zero_()
@@ -1226,7 +1226,7 @@ def test_selection_from_group_maxima(gpu_lib, P, ks):
     (torch.bfloat16, 8, 4, 128, 16, [150_000, 30_001, 129_999, 90_000]),  # more than 512 chunks of 256 pages
 ])
 def test_dense_decode_cut_by_the_lengths_on_the_device(gpu_lib, dtype, Hkv, G, D, S, lens):
-    """A dense decode whose chunks come from the lengths on the device (a launch that could read 64 MB or more, which the
+    """A dense decode whose chunks come from the lengths on the device (a launch that could read 96 MB or more, which the
     wide page table makes of small batches too) against the attention over the list of all pages, which is cut by the
     host. fp32 sums in another order differ by less than 1e-5; bf16 outputs may round to the neighbouring number: of 7
     stored mantissa bits, 2^(e-7) away for a value from 2^e on, at most 2^-7 of it."""
