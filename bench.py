@@ -485,7 +485,7 @@ def phase_stamps(args, dev):
         torch.cuda.synchronize()
         assert hip.hipMemset(ptr, 0, C.c_size_t(nbytes)) == 0
         flusher.before_step(it)
-        sess.decode_step(refresh_tail=True)
+        sess.sparse_step()  # the separate calls: a step may select and attend in one kernel, which has no stamps
         torch.cuda.synchronize()
         host = np.zeros((waves.value, slots.value), np.uint64)
         assert hip.hipMemcpy(C.c_void_p(host.ctypes.data), ptr, C.c_size_t(nbytes), 2) == 0

@@ -4,7 +4,7 @@
 // leaves some compute units with two full chunks and others with one: 8 sequences of 2000 to 60000 tokens read 811 MB in 142 us,
 // 5.7 TB/s, where an even batch reaches 6.7. Here every workgroup adds up the pages of the batch, finds the smallest
 // chunk with which the non-empty chunks fit the workgroups that run at the same time (or a multiple of them), cuts every row into
-// chunks of equal length not above that, and takes the chunk of its index. That batch now takes 126 us, 6.4 TB/s; 32 sequences of 4K
+// chunks of equal length not above that, and takes the chunk of its index. That batch now takes 128 us, 6.3 TB/s; 32 sequences of 4K
 // to 131K tokens (5.7 GB) 1832 before, 911 now. Other sizes: dense_plan.hpp.
 #include <type_traits>
 
