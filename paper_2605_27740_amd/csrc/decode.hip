@@ -2,8 +2,8 @@
 //   Eq. 5 of the paper when the list is the selected top-k set, Eq. 4 when it is every page.
 //
 // Split-K: the page list of a row is cut into chunks; one workgroup (4 waves) handles one chunk for all
-// G query heads of the KV head at once, so every K/V byte is read exactly once per step. bf16 caches: see the
-// matrix-core kernel below. fp32 caches: inside a wave
+// G query heads of the KV head at once, so every K/V byte is read exactly once per step. The work on a chunk
+// is decode_core.hpp, which also has what is said of bf16 caches. fp32 caches: inside a wave
 // each lane reads 16-byte chunks of K and V rows (a wave-wide load covers a contiguous 1 KiB of the
 // page), the q.k dot products are reduced across the D/vec lanes that share a token with DPP row
 // operations, and each group of lanes that shares a token row keeps its own online-softmax state, so
@@ -14,7 +14,6 @@
 // own: done by a row's last workgroup behind an agent-scope release and acquire it costs 8 us more than the launch
 // (131K tokens, 128 rows), and with write-through stores instead of the release the step is no faster either.
 // Logits are kept in the log2 domain (q is pre-multiplied by sm_scale * log2 e) so exp is one v_exp_f32.
-#include "device_utils.hpp"
 #include <type_traits>
 
 #include "decode_core.hpp"

@@ -20,6 +20,7 @@ namespace unique {
 namespace {
 
 constexpr int kScoreWaves = 4;
+
 // Statistics of the last (possibly partial) page of sequence b, recomputed from the keys by the whole
 // workgroup: wave w takes KV heads w, w+4, ... The page size is a run-time value here.
 template <typename T, int D>

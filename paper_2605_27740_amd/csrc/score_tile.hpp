@@ -11,7 +11,7 @@ namespace unique {
 // Enough is two per compute unit. kernel us with tiles of 32 / 64 / 128 / 256 pages, 8 heads, G = 4, not in the caches:
 //   4 x 4096 pages, D = 128, bf16 means 10.0 / 11.5 / 17.1 / 28.6; 4 x 8192 18.1 / 16.0 / 18.1 / 28.6; fp32 means 24.4 / 24.5 /
 //   24.0 / 33.4; 8 x 8192, D = 64, bf16 means 18.0 / 17.0 / 18.2 / 26.6; 30 x 3000, fp32 means 63.5 / 63.7 / 62.9 / 70.2
-// One per unit is enough where the smaller tiles need a second round (D = 128: three workgroups fit a unit, D = 64: five
+// One per unit is enough where the smaller tiles need a second round (D = 128: three workgroups fit a unit, four with bf16 queries and G = 4, D = 64: five
 // to seven), and for up to 128 pages of a single head, of which a wave takes 8 at a time:
 //   1 x 50000, D = 128, bf16 means 22.2 / 23.4 / 23.1 / 21.9 (26.1 with two records in flight); 3 x 9000 17.7 / 15.1 / 20.0;
 //   4 x 4096 pages of one head, G = 8, fp32 means 7.7 / 6.0 / 6.7 / 8.6

@@ -1,5 +1,5 @@
-"""The rules by which launches are cut (csrc/split_plan.hpp, csrc/score_tile.hpp, csrc/stats_bulk.hpp: host
-arithmetic), compiled here without HIP."""
+"""The rules by which launches are cut (csrc/split_plan.hpp, score_tile.hpp, stats_bulk.hpp, step_rule.hpp, dense_plan.hpp:
+host arithmetic), compiled here without HIP."""
 import ctypes as C
 import os
 import random
