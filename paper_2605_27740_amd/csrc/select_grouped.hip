@@ -2,12 +2,9 @@
 //
 // A row belongs to one workgroup, whose loads bound the selection of a long row: 62501 scores are 250 KB for one compute unit,
 // read twice. Here the maxima are read instead. At least k groups reach the k-th largest of them, T0, so the k-th score does,
-// too, and only the groups that reach T0 -- about k -- can hold a selected page: their scores alone are read, an eighth of the
-// row plus 8 k of them. T0 and then the exact k-th key
-// are found by bisection over keys in registers.
-// One wave makes the last step, whose rounds would need barriers of all the others.
-// What bounds it is a chain of such steps on one compute unit, of 30 900 cycles for 62501 pages, k = 1024: maxima 3900, T0 5600,
-// list of the groups 2300, their scores 5300, gathering 3800, the k-th key 6400, the output 3000.
+// too, and only the groups that reach T0 -- about k -- can hold a selected page: their scores alone are read, an eighth of the row
+// plus 8 k of them. T0 and then the exact k-th key are found by bisection over keys in registers. One wave makes the last step,
+// whose rounds would need barriers of all the others. What bounds it is that chain of steps on one compute unit.
 #include <algorithm>
 #include <type_traits>
 
@@ -23,10 +20,9 @@ __global__ __launch_bounds__(kThreads) void topk_select_grouped_kernel(CacheView
                                                                        int score_stride, int top_k,
                                                                        int32_t* __restrict__ sel_pages,
                                                                        int32_t* __restrict__ sel_count) {
-  constexpr int kVecs = 8;       // 16-byte loads of scores per thread
-  constexpr int kKept = 4096;    // keys from T0 on
+  constexpr int kVecs = 8;            // 16-byte loads of scores per thread
+  constexpr int kKept = 24 * kWave;   // keys from T0 on: what one wave holds
   __shared__ GroupShared<kThreads, kVecs, kKept> sh;
-  __shared__ SelectShared<kThreads> reread;
 
   const int row = blockIdx.x;
   const int b = row / c.Hkv;
@@ -48,53 +44,30 @@ __global__ __launch_bounds__(kThreads) void topk_select_grouped_kernel(CacheView
     return;
   }
   const int forced_from = P - min(c.force_recent, kb);  // pages from here on are always selected
-  Gathered<kVecs> got;
-  gather_from_groups<kThreads, kGroupVecs>(srow, grow, P, kb, forced_from, got, sh);
+  const Gathered got = gather_from_groups<kThreads, kGroupVecs>(srow, grow, P, kb, forced_from, sh);
   const int total = got.total;
-  if (total < 0) {
-    select_by_rereading<kThreads>(srow, P, kb, forced_from, [&](int at, int page) { out[at] = page; }, reread);
-    return;
-  }
-  if (total > kKept) {  // uniform
-    __syncthreads();    // the counts have been read by all
-    select_spread<kThreads, kVecs, 4>(got.key, got.T0 - 1u, got.top, kb,
-                                      [&](int at, int j) { out[at] = got.first[j / 4] + j % 4; }, sh.counts[0], sh.counts[1], sh.turns);
-    return;
-  }
 
-  // the k-th of them: one wave alone, whose rounds need no barrier, while they fit its registers
+  // the k-th of them: one wave alone, whose rounds need no barrier
   // (stores at -1 lie outside the buffer and are dropped, which costs less than a branch)
   const __amdgpu_buffer_rsrc_t list = __builtin_amdgcn_make_buffer_rsrc(out, 0, kb * 4, 0x27000);
   auto emit = [&](int, int at, int page) { __builtin_amdgcn_raw_buffer_store_b32(page, list, at * 4, 0, 0); };
-  if (total <= 24 * kWave) {
-    if (wave > 0) return;
-    if (total <= 4 * kWave) select_gathered<4>(sh.kept, total, got.T0 - 1u, got.top, kb, emit);
-    else if (total <= 8 * kWave) select_gathered<8>(sh.kept, total, got.T0 - 1u, got.top, kb, emit);
-    else if (total <= 16 * kWave) select_gathered<16>(sh.kept, total, got.T0 - 1u, got.top, kb, emit);
-    else select_gathered<24>(sh.kept, total, got.T0 - 1u, got.top, kb, emit);
-    return;
-  }
-  constexpr int kDense = kKept / kThreads;
-  uint32_t dkey[kDense];
-  int dpage[kDense];
-#pragma unroll
-  for (int j = 0; j < kDense; ++j) {
-    const uint2 e = sh.kept[j * kThreads + t];  // (what lies behind the last one is not used)
-    dkey[j] = j * kThreads + t < total ? e.x : 0u;
-    dpage[j] = (int)e.y;
-  }
-  select_spread<kThreads, kDense, 1>(dkey, got.T0 - 1u, got.top, kb, [&](int at, int j) { out[at] = dpage[j]; },
-                                     sh.counts[0], sh.counts[1], sh.turns);
+  if (wave > 0) return;
+  if (total <= 4 * kWave) select_gathered<4>(sh.kept, total, got.T0 - 1u, got.top, kb, emit);
+  else if (total <= 8 * kWave) select_gathered<8>(sh.kept, total, got.T0 - 1u, got.top, kb, emit);
+  else if (total <= 16 * kWave) select_gathered<16>(sh.kept, total, got.T0 - 1u, got.top, kb, emit);
+  else select_gathered<kKept / kWave>(sh.kept, total, got.T0 - 1u, got.top, kb, emit);
 }
 
 }  // namespace
 
 // Worth it while the kept groups are a small part of the row and fit the workgroup's registers (2048 of them, k and a quarter
-// and some more). Kernel us of select.hip / this one, planted normal scores, 8 rows: 4097 pages, k 64 7.5 / 5.4; 8192, 64 8.6 / 5.4;
-// 8192, 256 8.9 / 6.7; 12000, 500 12.0 / 9.4; 16384, 64 9.7 / 6.0; 32768, 64 13.9 / 6.9; 62501, 64 27.0 / 8.5; 62501, 1024 29.4 /
-// 14.0; 125001, 1024 44.8 / 17.1; and 128 rows: 16384, 680 13.8 / 12.8. Not worth it: 4097, 340 7.6 / 7.7; 16384, 1024 (128 rows)
-// 14.0 / 16.4; 62501, 2000 44.6 / 176 (too many groups). The maxima cost the score kernel 0.3 us (1 us of 90 at 16 x 16384 pages).
-// Masses of equal scores that more groups reach are selected by re-reading: 16 x 62501 scores of five values 85 / 288.
+// and some more). Kernel us of select.hip / this one, planted normal scores, 8 rows: 4097 pages, k 64 7.8 / 5.9; 8192, 64 8.6 / 5.4;
+// 12000, 500 11.9 / 9.0; 16384, 64 9.7 / 6.8; 32768, 64 13.9 / 7.6; 62501, 1024 29.6 / 14.1; 64 rows: 8192, 256 8.9 / 7.3; 128 rows:
+// 16384, 680 13.5 / 11.0; 16 rows: 125001, 1024 45.2 / 18.3. Not worth it: 4097, 340 7.6 / 7.7; 16384, 1024 (128 rows) 14.0 / 16.4;
+// 62501, 2000 44.6 / 176 (too many groups). The maxima cost the score kernel 0.3 us (1 us of 90 at 16 x 16384 pages).
+// Scores that rise by two standard deviations along the row need a tighter bound and take longer, not longer than there but where k
+// is near its limit: 4097, 64 7.8 / 7.4; 8192, 256 8.4 / 9.4; 12000, 500 11.5 / 12.0; 16384, 680 12.8 / 14.4; 62501, 1024 28.7 /
+// 16.7. Scores of five values: 8192, 256 19.4 / 7.9; 62501, 1024 40.8 / 17.6; 125001, 1024 431 / 26.5.
 bool select_uses_groups(const CacheView& c, int top_k) {
   const int P = c.max_pages_hint;
   return P > 4096 && P <= 131072 && top_k <= std::min(P / 24, 1280);

@@ -10,34 +10,32 @@ template <int kThreads, int kVecs, int kCap>
 struct GroupShared {
   static constexpr int kWaves = kThreads / kWave;
   static constexpr int kMaxGroups = kVecs * kThreads / 2;  // kept groups: two 16-byte loads of scores each
-  static constexpr int kCounts = (kVecs > kCap / kThreads ? kVecs : kCap / kThreads) * kWaves;
+  static constexpr int kCounts = kVecs * kWaves;
   uint32_t wave_min[kWaves], wave_max[kWaves];
   __attribute__((aligned(16))) int counts[2][kCounts], turns[2 * kWaves];
   int group_list[kMaxGroups + kWave];  // the last ones are for lanes without a group
   uint2 kept[kCap + kWave];            // key, page
 };
 
-// A row's gathered keys: `total` of them, all from T0 on and none above top, in sh.kept in page order if they fit; more than
-// kCap are left in the registers (key, and the first page of every four), and with more groups than kMaxGroups total is -1.
-template <int kVecs>
+// A row's gathered keys: `total` of them, at most kCap, all from T0 on and none above top, in sh.kept in page order.
 struct Gathered {
   uint32_t T0, top;
   int total;
-  uint32_t key[4 * kVecs];
-  int first[kVecs];
 };
 
-// 0 < kb < P; pages from forced_from on are always selected. All threads call it; ends with a barrier if the keys are in sh.kept.
+// 0 < kb < P, kb at most kCap and 8/9 of kMaxGroups; pages from forced_from on are always selected. All threads
+// call it; ends with a barrier.
 template <int kThreads, int kGroupVecs, int kVecs, int kCap>
-__device__ __forceinline__ void gather_from_groups(const float* srow, const uint32_t* grow, int P, int kb, int forced_from,
-                                                   Gathered<kVecs>& got, GroupShared<kThreads, kVecs, kCap>& sh) {
+__device__ __forceinline__ Gathered gather_from_groups(const float* srow, const uint32_t* grow, int P, int kb, int forced_from,
+                                                       GroupShared<kThreads, kVecs, kCap>& sh) {
   constexpr int kWaves = kThreads / kWave, kMaxGroups = GroupShared<kThreads, kVecs, kCap>::kMaxGroups;
+  static_assert(kGroupVecs <= kVecs, "the counts hold either");
   const int t = threadIdx.x, lane = t % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
   const int groups = (P + kGroupPages - 1) / kGroupPages;
   auto& counts = sh.counts;
-  auto& key = got.key;
-  auto& first = got.first;
+  uint32_t key[4 * kVecs];
+  int first[kVecs];  // the first page of every four keys
 
   // ---- 1. T0, a value that at least kb groups reach
   uint32_t gkey[4 * kGroupVecs], top = 0u, least = 0xffffffffu;
@@ -59,7 +57,7 @@ __device__ __forceinline__ void gather_from_groups(const float* srow, const uint
     }
   }
   // Every wave finds a bound that its share of kb of its own groups reaches; the smallest bound then has kb groups. That costs
-  // a fifth more groups than a bound over all of them and no barrier per round.
+  // a fifth more groups than a bound over all of them, and no barrier per round, where the scores do not depend on the position.
   uint32_t T0 = 1u;
   top = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<true>(top));
   {
@@ -75,7 +73,7 @@ __device__ __forceinline__ void gather_from_groups(const float* srow, const uint
     if (kb <= groups && of_wave > 0 && !(drop && of_wave < kFull)) {  // uniform
       least = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<false>(least));
       const int share = (int)(((int64_t)kb * of_wave + counted - 1) / counted);
-      mine = bisect(least - 1u, top, share, share + share / 8, [&](uint32_t x) { return count_above(gkey, x); }) + 1u;
+      mine = bisect(least - 1u, top, of_wave, share, share + share / 8, [&](uint32_t x) { return count_above(gkey, x); }) + 1u;
     }
     if (lane == 0) { sh.wave_max[wave] = top; sh.wave_min[wave] = mine; }
     __syncthreads();
@@ -88,22 +86,16 @@ __device__ __forceinline__ void gather_from_groups(const float* srow, const uint
 
   // ---- 2. the groups from T0 on, in page order
   int place[kVecs], gplace[kGroupVecs];
-  {
-    int(*gcounts) = counts[0];
-#pragma unroll
-    for (int v = 0; v < kGroupVecs; ++v) {
-      int n = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) n += __popcll(__ballot(gkey[4 * v + i] >= T0));
-      if (lane == 0) gcounts[v * kWaves + wave] = n;
-    }
-    __syncthreads();
+  int kept_groups = place_from<kThreads, kGroupVecs, 4>(gkey, T0, counts[0], gplace);
+  // Scores that rise or fall along the row give the waves poor bounds (several times kb groups), and many groups may be equal, of
+  // which the first are enough: each holds a key that equals the bound. Quotas of more waves leave more, so their number counts.
+  // step of 8192 pages, k = 256, as it is / with the rows that have too many groups read again: rising by two standard
+  // deviations 28.3 / 60.9 us, five values 29.2 / 109; 32768 pages, five values 44 / 378. Groups dealt to the waves in turn, so
+  // that their shares are alike, cost scores without an order 0.5 to 1 us and left the rising ones where they are.
+  if (kept_groups > min(kb + kb / 2 + 12 * kWaves, kMaxGroups)) {  // uniform
+    T0 = tighten<kThreads, kGroupVecs, 4>(gkey, T0, top, kept_groups, kb, kb + kb / 8, counts[1], sh.turns);
+    kept_groups = place_from<kThreads, kGroupVecs, 4>(gkey, T0, counts[0], gplace);
   }
-  const int kept_groups = wave_prefixes<kGroupVecs, kWaves>(counts[0], wave, gplace);
-  got.T0 = T0;
-  got.top = top;
-  got.total = -1;
-  if (kept_groups > kMaxGroups) return;  // uniform
 #pragma unroll
   for (int v = 0; v < kGroupVecs; ++v) {
     int at = gplace[v];
@@ -143,19 +135,11 @@ __device__ __forceinline__ void gather_from_groups(const float* srow, const uint
   }
 
   // ---- 4. those from T0 on are gathered, in page order
-#pragma unroll
-  for (int v = 0; v < kVecs; ++v) {
-    int n = 0;
-    if (v < loads) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) n += __popcll(__ballot(key[4 * v + i] >= T0));
-    }
-    if (lane == 0) counts[1][v * kWaves + wave] = n;
+  int total = place_from<kThreads, kVecs, 4>(key, T0, counts[1], place, loads);
+  if (total > kCap) {  // uniform
+    T0 = tighten<kThreads, kVecs, 4>(key, T0, top, total, kb, (kb + kCap) / 2, counts[0], sh.turns);
+    total = place_from<kThreads, kVecs, 4>(key, T0, counts[1], place, loads);
   }
-  __syncthreads();
-  const int total = wave_prefixes<kVecs, kWaves>(counts[1], wave, place);
-  got.total = total;
-  if (total > kCap) return;  // uniform
 #pragma unroll
   for (int v = 0; v < kVecs; ++v) {
     if (v >= loads) break;
@@ -170,34 +154,7 @@ __device__ __forceinline__ void gather_from_groups(const float* srow, const uint
     }
   }
   __syncthreads();
-
-}
-
-// Masses of equal scores, of which more groups reach the bound than are gathered: select by re-reading the row. emit(at, page).
-template <int kThreads, typename Emit>
-__device__ __forceinline__ void select_by_rereading(const float* srow, int P, int kb, int forced_from, Emit emit,
-                                                    SelectShared<kThreads>& sh) {
-  constexpr int kWaves = kThreads / kWave;
-  const int t = threadIdx.x, lane = t % kWave;
-  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
-  auto key_of = [&](int page) { return page >= forced_from ? kKeyForced : score_key(srow[page]); };
-  uint32_t kmin = 0xffffffffu, kmax = 0u;
-  for (int p = t; p < P; p += kThreads) {
-    const uint32_t k = key_of(p);
-    const bool finite = k > kKeyNegInf && k < kKeyPosInf;
-    kmin = min(kmin, finite ? k : 0xffffffffu);
-    kmax = max(kmax, finite ? k : 0u);
-  }
-  kmin = wave_allreduce_minmax<false>(kmin);
-  kmax = wave_allreduce_minmax<true>(kmax);
-    if (lane == 0) { sh.wave_min[wave] = kmin; sh.wave_max[wave] = kmax; }
-  constexpr int kBuckets = SelectShared<kThreads>::kBuckets;
-  for (int i = t; i < kBuckets + kBuckets / 4; i += kThreads) sh.hist[i] = 0;
-  if (t == 0) sh.ncand = 0;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) { kmin = min(kmin, sh.wave_min[w]); kmax = max(kmax, sh.wave_max[w]); }
-  select_reread<kThreads>(key_of, P, kb, bucket_map(kmin, kmax, kBuckets), emit, sh);
+  return {T0, top, total};
 }
 
 }  // namespace

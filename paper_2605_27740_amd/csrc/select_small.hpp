@@ -4,7 +4,8 @@
 // One workgroup is bound by the instructions that it spends per key and by its barriers. So every key is looked at as little
 // as possible: a lower bound T0 of the k-th key comes from the maxima of disjoint groups of keys (the k-th largest maximum
 // is one: k groups reach it), found by bisection in registers; the keys from T0 on -- about k and a third more -- are gathered
-// in the LDS in page order, and every wave bisects for the exact k-th of them by itself. Three barriers, and no atomics.
+// in the LDS in page order, and every wave bisects for the exact k-th of them by itself. Three barriers, and no atomics. Where more
+// keys reach T0 than the LDS has room for (masses of ties), the bound is first made tighter, with a barrier per round.
 #pragma once
 #include <type_traits>
 
@@ -28,6 +29,7 @@ struct SmallShared {
 template <int kN>
 __device__ __forceinline__ int count_above(const uint32_t (&v)[kN], uint32_t x) {
   constexpr int kBatch = kN < 8 ? kN : 8;
+  static_assert((kBatch & (kBatch - 1)) == 0 && kN % kBatch == 0, "whole batches");
   int n = 0;
 #pragma unroll
   for (int r0 = 0; r0 < kN; r0 += kBatch) {
@@ -50,54 +52,63 @@ __device__ __forceinline__ int count_above(const uint32_t (&v)[kN], uint32_t x) 
   return n;
 }
 
-// A value x with count(x) >= k, from lo (count(lo) >= k) and hi (count(hi) < k), where count falls with x: the first one met
-// with count(x) <= enough, or the largest such x. At most 32 rounds.
+// A value x with count(x) >= k, from lo (count(lo) = n_lo >= k) and hi (count(hi) < k), where count falls with x: the first one met
+// with count(x) <= enough, or the largest x. At most 32 rounds.
 template <typename Count>
-__device__ __forceinline__ uint32_t bisect(uint32_t lo, uint32_t hi, int k, int enough, Count count) {
-  if (hi - lo <= 1u) return lo;
-  bool stop;
+__device__ __forceinline__ uint32_t bisect(uint32_t lo, uint32_t hi, int n_lo, int k, int enough, Count count) {
 #pragma unroll 1
-  do {
+  while ((n_lo > enough) & (hi - lo > 1u)) {
     const uint32_t mid = lo + (hi - lo) / 2;
     const int n = count(mid);
     lo = n >= k ? mid : lo;
+    n_lo = n >= k ? n : n_lo;
     hi = n >= k ? hi : mid;
-    stop = ((n >= k) & (n <= enough)) | (hi - lo <= 1u);
-  } while (!stop);
-  return lo;
-}
-
-// The same from known counts at lo and hi, and only to the value with exactly k above it or the largest with more: two rounds of
-// three aim at it along the line between the counts, which halves the rounds (9 to 5 where a third of the keys is to go) and
-// costs as much as counting some keys.
-template <typename Count>
-__device__ __forceinline__ uint32_t bisect_exact(uint32_t lo, uint32_t hi, int n_lo, int n_hi, int k, Count count) {
-#pragma unroll 1
-  for (int i = 0; n_lo != k && hi - lo > 1u; ++i) {
-    uint32_t step = (hi - lo) / 2;
-    if (i % 3 != 2) {
-      const float part = (float)(n_lo - k) * __builtin_amdgcn_rcpf((float)(n_lo - n_hi));
-      step = (uint32_t)((float)(hi - lo) * part);
-      step = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(max(step, 1u), hi - lo - 1u));
-    }
-    const int n = count(lo + step);
-    if (n >= k) { lo += step; n_lo = n; }
-    else { hi = lo + step; n_hi = n; }
   }
   return lo;
 }
 
-// bisect over the keys of a whole workgroup, kN per thread; turns: 2 * waves ints of LDS. All threads call it.
+// The same from known counts at lo and hi, with rounds that aim at `enough` along the line between the counts. That halves the number
+// of rounds (9 to 5 where a third of the keys is to go) and costs as much as counting some keys. Keys are nearly logarithms of the
+// scores, which suits the tail of a distribution; across many octaves, zero above all, the line is drawn between the scores
+// themselves (8192 pages that score -p / 8192, k = 256: 31.1 us with keys alone, 27.3 so). An aim that leaves more than half of the
+// keys' range is followed by two halvings: where most keys are equal, every aim does. Leaves count(x) in n_lo.
+template <typename Count>
+__device__ __forceinline__ uint32_t bisect_aimed(uint32_t lo, uint32_t hi, int& n_lo, int n_hi, int k, int enough, Count count) {
+  constexpr uint32_t kOctaves = 4u << 23;
+  int halvings = 0;
+#pragma unroll 1
+  while ((n_lo > enough) & (hi - lo > 1u)) {
+    const uint32_t width = hi - lo;
+    uint32_t x = lo + width / 2;
+    if (halvings == 0) {
+      const float part = (float)(n_lo - enough) * __builtin_amdgcn_rcpf((float)(n_lo - n_hi));
+      uint32_t aim = lo + (uint32_t)((float)width * part);
+      if (width > kOctaves) {
+        const float from = ordered_to_float(lo), f = fmaf(ordered_to_float(hi) - from, part, from);
+        aim = fabsf(f) < 3.0e38f ? score_key(f) : x;  // infinite or no number: halve
+      }
+      x = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(max(aim, lo + 1u), hi - 1u));
+    }
+    const int n = count(x);
+    if (n >= k) { lo = x; n_lo = n; }
+    else { hi = x; n_hi = n; }
+    halvings = halvings > 0 ? halvings - 1 : (hi - lo > width / 2 ? 2 : 0);
+  }
+  return lo;
+}
+
+// Number of a workgroup's keys above x, kN per thread; turns: 2 * waves ints of LDS. All threads call it; it holds a barrier.
 template <int kThreads, int kN>
-__device__ __forceinline__ uint32_t bisect_spread(const uint32_t (&v)[kN], uint32_t lo, uint32_t hi, int k, int enough, int* turns) {
-  constexpr int kWaves = kThreads / kWave;
+struct SpreadCount {
+  static constexpr int kWaves = kThreads / kWave;
   static_assert(kWaves % 4 == 0, "counts are read four at a time");
-  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint32_t (&v)[kN];
+  int* turns;
   int turn = 0;
-  return bisect(lo, hi, k, enough, [&](uint32_t x) {
+  __device__ __forceinline__ int operator()(uint32_t x) {
     const int n = count_above(v, x);
     turn ^= kWaves;  // the counts of one round are read while those of the next are written
-    if (lane == 0) turns[turn + wave] = n;
+    if (threadIdx.x % kWave == 0) turns[turn + threadIdx.x / kWave] = n;
     __syncthreads();
     int sum = 0;
 #pragma unroll
@@ -106,52 +117,71 @@ __device__ __forceinline__ uint32_t bisect_spread(const uint32_t (&v)[kN], uint3
       sum += q.x + q.y + q.z + q.w;
     }
     return __builtin_amdgcn_readfirstlane(sum);
-  });
-}
+  }
+};
 
-// The kb largest of a workgroup's keys, of which more than kb lie above `low`, in the order (v, thread, i) of key[kPer * v + i]:
-// emit(at, j) once per selected key. above, equal: kVecs * waves ints each, 16-byte aligned, turns as above; all of them unused by
-// others since the last barrier. All threads call it.
-template <int kThreads, int kVecs, int kPer, typename Emit>
-__device__ __forceinline__ void select_spread(const uint32_t (&key)[kVecs * kPer], uint32_t low, uint32_t high, int kb, Emit emit,
-                                              int* above, int* equal, int* turns) {
+// A bound T0 that `total` > enough >= kb of a workgroup's keys reach is raised until at most `enough` do. Where so many are equal that
+// none between kb and `enough` does, the first ones of them, in the order (v, thread, i) of key[kPer * v + i], are left that make kb,
+// and the others become 0: of equal keys the first are selected. equal: kVecs * waves ints, 16-byte aligned, turns as above; both
+// unused by others since the last barrier. All threads call it; no thread returns before all have come.
+template <int kThreads, int kVecs, int kPer>
+__device__ __forceinline__ uint32_t tighten(uint32_t (&key)[kVecs * kPer], uint32_t T0, uint32_t top, int total, int kb, int enough,
+                                            int* equal, int* turns) {
   constexpr int kWaves = kThreads / kWave;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  // the k-th key, or (exactly kb keys above T - 1) a value that only selected keys reach
-  const uint32_t T = bisect_spread<kThreads>(key, low, high, kb, kb, turns) + 1u;
+  SpreadCount<kThreads, kVecs * kPer> count{key, turns};
+  // T0 is often the key that masses of others equal
+  const int above = count(T0);
+  uint32_t T = T0;
+  int n = total;
+  if (above >= kb) {
+    n = above;
+    T = bisect_aimed(T0, top, n, 0, kb, enough, [&](uint32_t x) { return count(x); }) + 1u;
+  }
+  if (n <= enough) return T;  // uniform
 #pragma unroll
   for (int v = 0; v < kVecs; ++v) {
-    int n = 0, e = 0;
+    int e = 0;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      n += __popcll(__ballot(key[kPer * v + i] > T));
-      e += __popcll(__ballot(key[kPer * v + i] == T));
-    }
-    if (lane == 0) { above[v * kWaves + wave] = n; equal[v * kWaves + wave] = e; }
+    for (int i = 0; i < kPer; ++i) e += __popcll(__ballot(key[kPer * v + i] == T));
+    if (lane == 0) equal[v * kWaves + wave] = e;
   }
   __syncthreads();
-  int place[kVecs], ties[kVecs];
-  const int need = kb - wave_prefixes<kVecs, kWaves>(above, wave, place);  // keys equal to T that are taken, the first ones
-  wave_prefixes<kVecs, kWaves>(equal, wave, ties);
+  int ties[kVecs];
+  const int rest = kb - n + wave_prefixes<kVecs, kWaves>(equal, wave, ties);  // how many of the equal ones are left
 #pragma unroll
   for (int v = 0; v < kVecs; ++v) {
-    int sure_b = place[v], tie_b = ties[v];
+    int tie = ties[v];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) tie = lanes_before(__ballot(key[kPer * v + i] == T), tie);
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      sure_b = lanes_before(__ballot(key[kPer * v + i] > T), sure_b);
-      tie_b = lanes_before(__ballot(key[kPer * v + i] == T), tie_b);
-    }
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int j = kPer * v + i;
-      if (key[j] > T) {
-        emit(min(tie_b, need) + sure_b++, j);
-      } else if (key[j] == T) {
-        if (tie_b < need) emit(sure_b + tie_b, j);
-        ++tie_b;
-      }
+      const bool is = key[kPer * v + i] == T;
+      if (is && tie >= rest) key[kPer * v + i] = 0u;
+      tie += is;
     }
   }
+  return T;
+}
+
+// counts[v * waves + wave] = keys from T0 on, of the wave's with that v; a barrier; their prefixes (see wave_prefixes) and their total.
+// The keys with v >= used (uniform) are all 0.
+template <int kThreads, int kVecs, int kPer>
+__device__ __forceinline__ int place_from(const uint32_t (&key)[kVecs * kPer], uint32_t T0, int* counts, int (&place)[kVecs],
+                                          int used = kVecs) {
+  constexpr int kWaves = kThreads / kWave;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+#pragma unroll
+  for (int v = 0; v < kVecs; ++v) {
+    int n = 0;
+    if (v < used) {
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) n += __popcll(__ballot(key[kPer * v + i] >= T0));
+    }
+    if (lane == 0) counts[v * kWaves + wave] = n;
+  }
+  __syncthreads();
+  return wave_prefixes<kVecs, kWaves>(counts, wave, place);
 }
 
 // A lower bound (>= 1) of the k-th largest key from n = 64 * kN group maxima, at least k of them above 0: a value that k to
@@ -164,11 +194,11 @@ __device__ __forceinline__ uint32_t bound_of_maxima(const uint32_t* group_max, i
   for (int r = 0; r < kN; ++r) {
     m[r] = group_max[r * kWave + lane];
     top = max(top, m[r]);
-    least = min(least, m[r]);
+    least = min(least, m[r] - 1u);  // (0, no key, wraps around)
   }
   top = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<true>(top));
   least = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<false>(least));
-  return bisect(least > 0u ? least - 1u : 0u, top, k, k + k / 8, [&](uint32_t x) { return count_above(m, x); }) + 1u;
+  return bisect(least, top, kN * kWave, k, k + k / 8, [&](uint32_t x) { return count_above(m, x); }) + 1u;
 }
 
 // The kb largest of `total` <= 64 * kN gathered keys, of which all are above `low` and none above `top`, in page order, by one
@@ -190,10 +220,13 @@ __device__ __forceinline__ void select_gathered(const uint2* kept, int total, ui
   // x with exactly kb keys above it, or the largest x with more: the next value is then the k-th key
   auto count = [&](uint32_t y) { return count_above(key, y); };
   uint32_t x = low;
-  if constexpr (kN >= 8) x = bisect_exact(low, top, total, 0, kb, count);
-  else if (total > kb) x = bisect(low, top, kb, kb, count);
+  int n = total;
+  const int above = total > 2 * kb ? count(low + 1u) : kb;  // so many only if many equal the first one
+  if (above < kb) top = low + 1u;
+  if constexpr (kN >= 8) x = bisect_aimed(low, top, n, 0, kb, kb, count);
+  else { x = bisect(low, top, total, kb, kb, count); n = count(x); }
   int at = 0, ties = 0;
-  if (count_above(key, x) == kb) {
+  if (n == kb) {
 #pragma unroll
     for (int r = 0; r < kN; ++r) {
       const bool mine = key[r] > x;
@@ -246,15 +279,14 @@ __device__ __forceinline__ void select_kept(const uint2* kept, int total, uint32
   else gathered(std::integral_constant<int, 16>());
 }
 
-// Thread t holds the keys of the pages row_page(j) (0: no page); 0 < kb < P; page_table: the row's, of at least one entry.
-// emit_all(r, at, page, phys) is called by every wave for all that its lanes hold (see select_gathered); if too many keys are left to
-// gather, emit_own(at, page) is called once per selected page instead, followed by a barrier.
-template <int kThreads, int kVecs, typename EmitAll, typename EmitOwn>
-__device__ __forceinline__ void select_small(const uint32_t (&key)[4 * kVecs], int P, int kb, const int32_t* page_table,
-                                             EmitAll emit_all, EmitOwn emit_own, SmallShared<kThreads, kVecs>& sh) {
+// Thread t holds the keys of the pages row_page(j) (0: no page), which may be changed; 0 < kb < P, kb at most half of kSmallCap;
+// page_table: the row's, of at least one entry. emit_all(r, at, page, phys) is called by every wave for all that its lanes hold
+// (see select_gathered).
+template <int kThreads, int kVecs, typename EmitAll>
+__device__ __forceinline__ void select_small(uint32_t (&key)[4 * kVecs], int P, int kb, const int32_t* page_table,
+                                             EmitAll emit_all, SmallShared<kThreads, kVecs>& sh) {
   constexpr int kWaves = kThreads / kWave;
   const int t = threadIdx.x, lane = t % kWave;
-  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
   auto page_of = [](int j) { return row_page<kThreads, 4>(j); };
 
   // ---- 1. T0: groups are the keys of a thread, or of a half or a quarter of its loads where that makes too few groups.
@@ -285,40 +317,28 @@ __device__ __forceinline__ void select_small(const uint32_t (&key)[4 * kVecs], i
   }
 
   // ---- 2. the keys from T0 on, in page order
+  int place[kVecs];
+  int total = place_from<kThreads, kVecs, 4>(key, T0, sh.counts[0], place);
+  if constexpr (kThreads * kVecs * 4 > kSmallCap) {
+    if (total > kSmallCap) {  // uniform: masses of equal scores, or a k beyond the groups
+      T0 = tighten<kThreads, kVecs, 4>(key, T0, 0xffffffffu, total, kb, kSmallCap / 2, sh.counts[1], sh.turns);
+      total = place_from<kThreads, kVecs, 4>(key, T0, sh.counts[0], place);
+    }
+  }
 #pragma unroll
   for (int v = 0; v < kVecs; ++v) {
-    int n = 0;
+    int at = place[v];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) n += __popcll(__ballot(key[4 * v + i] >= T0));
-    if (lane == 0) sh.counts[0][v * kWaves + wave] = n;
+    for (int i = 0; i < 4; ++i) at = lanes_before(__ballot(key[4 * v + i] >= T0), at);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {  // without branches: they cost more than the stores that they save
+      const bool in = key[4 * v + i] >= T0;
+      sh.kept[in ? at : kSmallCap + lane] = make_uint2(key[4 * v + i], (uint32_t)page_of(4 * v + i));
+      at += in;
+    }
   }
   __syncthreads();
-  int place[kVecs];
-  const int total = wave_prefixes<kVecs, kWaves>(sh.counts[0], wave, place);
-  if (total <= kSmallCap) {  // uniform
-#pragma unroll
-    for (int v = 0; v < kVecs; ++v) {
-      int at = place[v];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) at = lanes_before(__ballot(key[4 * v + i] >= T0), at);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {  // without branches: they cost more than the stores that they save
-        const bool in = key[4 * v + i] >= T0;
-        sh.kept[in ? at : kSmallCap + lane] = make_uint2(key[4 * v + i], (uint32_t)page_of(4 * v + i));
-        at += in;
-      }
-    }
-    __syncthreads();
-    select_kept(sh.kept, total, T0 - 1u, kb, page_table, emit_all);
-    return;
-  }
-  if constexpr (kThreads * kVecs * 4 > kSmallCap) {
-    // masses of equal scores, or a k beyond the groups: the keys in the registers of all waves
-    __syncthreads();  // the counts have been read by all
-    select_spread<kThreads, kVecs, 4>(key, T0 - 1u, 0xffffffffu, kb, [&](int at, int j) { emit_own(at, page_of(j)); },
-                                      sh.counts[0], sh.counts[1], sh.turns);
-    __syncthreads();
-  }
+  select_kept(sh.kept, total, T0 - 1u, kb, page_table, emit_all);
 }
 
 }  // namespace

@@ -3,9 +3,9 @@
 // list out. A launch and the round trips between the two kernels fall away: the list stays in the LDS, the physical page
 // beside each entry, looked up while the search for the k-th key runs. Of short rows every workgroup makes the scores, too.
 // Scores, selection and attention are those of the separate kernels, in the same order: the same bits.
-// What bounds it where the launch is small is a chain of latencies: of 17 200 cycles of a workgroup for one sequence of 2048
-// pages, k = 128, the arguments, length and scores take 1800, the keys 900, the bound T0 2100, gathering 1700, the k-th key
-// 2200, the list 1600, the attention over one page per wave 6900. Kernel us, selection + attention apart 5.2 + 5.8, so 8.5.
+// What bounds it where the launch is small is a chain of latencies: the arguments, the length and the scores, the bound T0, the keys
+// from it on, the k-th of them, the list, and one page per wave. Kernel us for one sequence of 2048 pages, k = 128: selection and
+// attention apart 5.0 + 5.1, so 8.0.
 #include "decode_core.hpp"
 #include "score_core.hpp"
 #include "select_groups.hpp"
@@ -23,9 +23,8 @@ struct StepShared {
   int2 list[kStepMaxTopK + kWave];  // physical page, logical page; the last ones are for lanes without an entry
 };
 
-// What a step does to one chunk once the scores are known. select(kb, page_table, emit_all, emit_own) selects kb < P pages: either it
-// calls emit_all in every wave for all that its lanes hold (see select_gathered), or emit_own once per selected page and
-// then a barrier. All threads call it.
+// What a step does to one chunk once the scores are known. select(kb, page_table, emit_all) selects kb < P pages: it calls emit_all in
+// every wave for all that its lanes hold (see select_gathered). All threads call it.
 template <typename T, int D, int S, int G, bool kNT, typename Shared, typename Select>
 __device__ __forceinline__ void select_and_attend(const CacheView& c, const T* __restrict__ q, int split, int hkv, int b, int N, int P,
                                                   int top_k, int32_t* __restrict__ sel_pages, int32_t* __restrict__ sel_count,
@@ -59,11 +58,7 @@ __device__ __forceinline__ void select_and_attend(const CacheView& c, const T* _
       sh.list[mine ? at - begin : kStepMaxTopK + lane] = make_int2(ph, page);
       if (split == 0 && r % kDecWaves == wave && at >= 0) sel_row[at] = page;
     };
-    auto emit_own = [&](int at, int page) {
-      if (split == 0) sel_row[at] = page;
-      if (at >= begin && at < end) sh.list[at - begin] = make_int2(pt[page], page);
-    };
-    select(kb, pt, emit_all, emit_own);
+    select(kb, pt, emit_all);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
@@ -86,13 +81,13 @@ struct SelectFromScores {
   const float4 (&raw)[kVecs];
   int P;
   SmallShared<kThreads, kVecs>& sh;
-  template <typename EmitAll, typename EmitOwn>
-  __device__ __forceinline__ void operator()(int kb, const int32_t* page_table, EmitAll emit_all, EmitOwn emit_own) const {
+  template <typename EmitAll>
+  __device__ __forceinline__ void operator()(int kb, const int32_t* page_table, EmitAll emit_all) const {
     uint32_t key[4 * kVecs];
 #pragma unroll
     for (int v = 0; v < kVecs; ++v) keys_of(raw[v], P - row_page<kThreads, 4>(4 * v), key + 4 * v);
     force_recent_keys<kThreads, kVecs, 4>(key, P, kb, c.force_recent);
-    select_small<kThreads, kVecs>(key, P, kb, page_table, emit_all, emit_own, sh);
+    select_small<kThreads, kVecs>(key, P, kb, page_table, emit_all, sh);
   }
 };
 
@@ -128,22 +123,12 @@ struct SelectFromGroups {
   const float* srow;
   const uint32_t* grow;
   int P;
-  struct Shared {
-    GroupShared<kThreads, 4, kSmallCap> groups;
-    SelectShared<kThreads> reread;
-  };
+  using Shared = GroupShared<kThreads, 4, kSmallCap>;
   Shared& sh;
-  template <typename EmitAll, typename EmitOwn>
-  __device__ __forceinline__ void operator()(int kb, const int32_t* page_table, EmitAll emit_all, EmitOwn emit_own) const {
-    const int forced_from = P - min(c.force_recent, kb);
-    Gathered<4> got;
-    gather_from_groups<kThreads, kGroupVecs>(srow, grow, P, kb, forced_from, got, sh.groups);
-    if (got.total >= 0 && got.total <= kSmallCap) {  // uniform
-      select_kept(sh.groups.kept, got.total, got.T0 - 1u, kb, page_table, emit_all);
-    } else {
-      select_by_rereading<kThreads>(srow, P, kb, forced_from, emit_own, sh.reread);
-      __syncthreads();
-    }
+  template <typename EmitAll>
+  __device__ __forceinline__ void operator()(int kb, const int32_t* page_table, EmitAll emit_all) const {
+    const Gathered got = gather_from_groups<kThreads, kGroupVecs>(srow, grow, P, kb, P - min(c.force_recent, kb), sh);
+    select_kept(sh.kept, got.total, got.T0 - 1u, kb, page_table, emit_all);
   }
 };
 

@@ -22,7 +22,9 @@ constexpr int kStepWholePages = 384;  // pages of a row that are scored in the s
 // Workgroups that wait for a free unit select when the others already stream: 24 x 1000 pages cut in 5, 960 workgroups, 48.6 /
 // 47.2; but 31 x 4096, 64 120.6 / 122.4, so those rows are left apart from 512 workgroups on.
 // Longer rows, from their group maxima, in kernels of their own (select_grouped.hip) / so: 1 x 4200, 64 24.8 / 22.1; 1 x 8192, 256 29.0 /
-// 27.8; 16 x 8192, 256 143.8 / 141.8; 1 x 32768, 128 41.7 / 40.0; 4 x 16384, 64 62.9 / 60.7.
+// 27.8; 16 x 8192, 256 143.8 / 141.8; 1 x 32768, 128 41.7 / 40.0; 4 x 16384, 64 62.9 / 60.7. Scores that rise by two standard deviations
+// along the row, with a selection that reads every score / so: 1 x 8192, 256 27.7 / 28.3; 16 x 8192, 256 141.4 / 142.6; 1 x 4200, 64
+// 22.2 / 22.0; 4 x 16384, 64 63.0 / 60.4; 1 x 32768, 256 47.9 / 43.9.
 inline bool step_fuses(int rows, int max_pages, int top_k, const SplitPlan& plan) {
   if (max_pages > kStepMaxGroupPages || top_k > kStepMaxTopK || (max_pages > 512 && 4 * top_k > max_pages)) return false;
   if (max_pages > kStepMaxPages) return 24 * top_k <= max_pages && (plan.num_splits == 1 || (int64_t)rows * plan.num_splits <= 512);
