@@ -188,7 +188,7 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
   const int wave_slots = c.Hkv <= 8 ? kScoreWaves : kScoreWaves * kRowsPerWave / c.Hkv;
   const int tile = score_tile(c.B, c.Hkv, D, c.max_pages_hint, c.min_pages_hint, 64 * wave_slots);
   dim3 grid((c.max_pages_hint + tile - 1) / tile, c.B), block(kScoreWaves * kWave);
-  const size_t lds = (size_t)c.Hkv * tile * sizeof(float);
+  const size_t lds = (size_t)score_lds(c.Hkv * tile * (int)sizeof(float), (int)sizeof(T), D, G, (int64_t)grid.x * grid.y);
   auto go = [&](auto kernel) {
     kernel<<<grid, block, lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, scores, stride, out, group_max, refresh_tail,
                                      tile);

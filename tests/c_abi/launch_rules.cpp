@@ -27,3 +27,6 @@ extern "C" int dense_chunks(int rows, int max_pages) { return unique::dense_max_
 extern "C" int dense_balances(int batch, int kv_heads, int max_pages, int page_bytes) {
   return unique::dense_balances(batch, kv_heads, max_pages, page_bytes);
 }
+extern "C" int lds(int scores, int elem_bytes, int head_dim, int group, int workgroups) {
+  return unique::score_lds(scores, elem_bytes, head_dim, group, workgroups);
+}

@@ -43,7 +43,7 @@ def lib(tmp_path_factory):
         def fuses(batch, heads, max_pages, top_k, page_bytes=8192):
             return bool(c.fuses(batch, heads, max_pages, top_k, page_bytes))
 
-        dense_chunks, dense_balances = c.dense_chunks, c.dense_balances
+        dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
     return Lib
 
 
@@ -152,3 +152,18 @@ def test_chunks_of_a_balanced_dense_batch_fit_the_workspace_and_leave_room_to_cu
     assert seen > 2000
     assert not lib.dense_balances(4, 8, 383, 8192) and lib.dense_balances(4, 8, 384, 8192)  # 96 MB
     assert not lib.dense_balances(1, 8, 100000, 8192) and not lib.dense_balances(33, 8, 4096, 8192)
+
+
+@pytest.mark.parametrize("elem_bytes,head_dim,group,most", [(2, 128, 4, 3), (4, 64, 1, 7), (4, 64, 2, 6), (2, 128, 1, None), (2, 128, 8, None),
+                                                            (2, 64, 4, None), (4, 128, 4, None), (4, 64, 4, None)])
+def test_score_workgroups_per_unit_where_the_registers_allow_one_too_many(lib, elem_bytes, head_dim, group, most):
+    """The LDS of a compute unit (160 KB, handed out in pieces of at most 2 KB) holds exactly `most` workgroups of a launch
+    that could otherwise be on the chip at once; a workgroup never gets less than its scores take."""
+    for scores in (32, 4096, 32768):
+        for workgroups in (1, 1024, 1176, 4096):
+            got = lib.lds(scores, elem_bytes, head_dim, group, workgroups)
+            assert got >= scores
+            if most is None or workgroups > 2560:
+                assert got == scores
+            elif scores < 8192:
+                assert -(-got // 2048) * 2048 * most <= 160 << 10 < got // 128 * 128 * (most + 1)
