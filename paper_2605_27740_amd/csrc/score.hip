@@ -41,14 +41,14 @@ __device__ __forceinline__ void refresh_tail_record(const CacheView& c, int b, i
   }
 }
 
-// T: element type of q; TS: element type of the stored means (float, or bf16_t for bf16 statistics).
+// T: element type of q; TS: element type of the stored means (float, or bf16_t for bf16 statistics). The arguments are in an order
+// without gaps: 8 bytes more cost a small launch 0.2 us (16 x 400 pages 7.5 / 7.3).
 // kNT: the records are read with non-temporal loads (a launch that streams more than the caches hold).
 template <typename T, typename TS, int D, int G, bool kNT>
-__global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheView c, const T* __restrict__ q,
-                                                                        float lambda, float* __restrict__ scores,
-                                                                        int score_stride,
-                                                                        float* __restrict__ scores_out,
-                                                                        uint32_t* __restrict__ group_max, int refresh_tail, int tile_pages) {
+__global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheView c, const T* __restrict__ q, float lambda, int score_stride,
+                                                                        float* __restrict__ scores, float* __restrict__ scores_out,
+                                                                        uint32_t* __restrict__ group_max, int refresh_tail,
+                                                                        int tile_pages) {
   using Scorer = RowScorer<T, TS, D, G>;
   constexpr int kE = Scorer::kE, kChunks = Scorer::kChunks;
   // Records in flight per wave. bf16 means in launches that stream from memory: four (80 x 4096 pages 117 us, two 122);
@@ -190,8 +190,7 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
   dim3 grid((c.max_pages_hint + tile - 1) / tile, c.B), block(kScoreWaves * kWave);
   const size_t lds = (size_t)score_lds(c.Hkv * tile * (int)sizeof(float), (int)sizeof(T), D, G, (int64_t)grid.x * grid.y);
   auto go = [&](auto kernel) {
-    kernel<<<grid, block, lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, scores, stride, out, group_max, refresh_tail,
-                                     tile);
+    kernel<<<grid, block, lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, stride, scores, out, group_max, refresh_tail, tile);
   };
   if (c.stats_bf16) {
     if (nt) go(page_score_kernel<T, bf16_t, D, G, true>);

@@ -48,8 +48,9 @@ inline int score_lds(int scores, int elem_bytes, int head_dim, int group, int64_
   int most = 0;  // workgroups per unit; 0: what the registers allow
   if (elem_bytes == 2 && head_dim == 128 && group == 4) most = 3;
   if (elem_bytes == 4 && head_dim == 64 && group <= 2) most = group == 1 ? 7 : 6;
-  // (slightly larger launches fit, too, as empty tiles leave early: 12 x 196 to 3125 pages, 1176 workgroups, 16.8 / 14.9)
-  if (most == 0 || workgroups > (most + 1) * kNumCUs * 5 / 4) return scores;
+  // Smaller launches fit either way. (Slightly larger ones still fit, as empty tiles leave early: 12 x 196 to 3125 pages, 1176
+  // workgroups, 16.8 / 14.9.)
+  if (most == 0 || workgroups <= most * kNumCUs || workgroups > (most + 1) * kNumCUs * 5 / 4) return scores;
   return std::max(scores, kLds / (most + 1) + 1024);
 }
 

@@ -160,10 +160,10 @@ def test_score_workgroups_per_unit_where_the_registers_allow_one_too_many(lib, e
     """The LDS of a compute unit (160 KB, handed out in pieces of at most 2 KB) holds exactly `most` workgroups of a launch
     that could otherwise be on the chip at once; a workgroup never gets less than its scores take."""
     for scores in (32, 4096, 32768):
-        for workgroups in (1, 1024, 1176, 4096):
+        for workgroups in [1, 4096] + ([] if most is None else [256 * most, 256 * most + 1, 256 * (most + 1)]):
             got = lib.lds(scores, elem_bytes, head_dim, group, workgroups)
             assert got >= scores
-            if most is None or workgroups > 2560:
+            if most is None or workgroups > 2560 or workgroups <= 256 * most:
                 assert got == scores
             elif scores < 8192:
                 assert -(-got // 2048) * 2048 * most <= 160 << 10 < got // 128 * 128 * (most + 1)
