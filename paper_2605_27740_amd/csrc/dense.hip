@@ -3,8 +3,8 @@
 // The host knows only the longest sequence, so most_splits cuts every row at the same multiples of 256 pages, and a ragged batch
 // leaves some compute units with two full chunks and others with one: 8 sequences of 2000 to 60000 tokens read 811 MB in 142 us,
 // 5.7 TB/s, where an even batch reaches 6.7. Here every workgroup adds up the pages of the batch, finds the smallest
-// chunk with which the non-empty chunks fit the workgroups that run at the same time (or a multiple of them), cuts every row into
-// chunks of equal length not above that, and takes the chunk of its index. That batch now takes 128 us, 6.3 TB/s; 32 sequences of 4K
+// chunk with which the chunks fit the workgroups that run at the same time (or a multiple of them), cuts every row into
+// equal chunks not longer than that, and takes the chunk of its index. That batch now takes 128 us, 6.3 TB/s; 32 sequences of 4K
 // to 131K tokens (5.7 GB) 1832 before, 911 now. Other sizes: dense_plan.hpp.
 #include <type_traits>
 
@@ -24,39 +24,23 @@ struct BatchChunks {
 
 __device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x), kWave - 1); }
 
-// Quotients are approximate where any value will do: a row may be cut into any number of chunks from one on, as long as all of
-// them have a workgroup. With the first length below they have: sum of ceil(pages / length) <= total / length + rows, and the margin
-// of a thousandth is far above the errors of the reciprocal and of pages as floats.
-__device__ __forceinline__ BatchChunks cut_batch(const CacheView& c, int S, int max_chunks) {
+// false: no chunk has the index w, or a larger one
+__device__ __forceinline__ bool cut_batch(const CacheView& c, int S, int max_chunks, int w, BatchChunks& bc) {
   const int lane = threadIdx.x % kWave;
-  BatchChunks bc;
   bc.len = lane < c.B ? c.seq_lens[lane] : 0;
   bc.pages = max(0, min((bc.len + S - 1) / S, c.max_pages_hint));
   const int rows = c.B * c.Hkv;
-  const int total = wave_sum(bc.pages) * c.Hkv;
-  const int slots = min(max(total / (kDenseSlots * kDensePages), 1) * kDenseSlots, max_chunks);
-  auto cut = [&](float length) {
-    return bc.pages > 0 ? max(1, (int)ceilf((float)bc.pages * __builtin_amdgcn_rcpf(length))) : 0;
-  };
-  // The chunk length is at least an equal share, and at most what is enough even if every row's last chunk is nearly empty;
-  // bisection down to a 64th of the length. Equally long sequences have as many chunks per row as there is room for.
-  const float share = (float)total * __builtin_amdgcn_rcpf((float)slots);
-  float fits = fmaxf((float)total * __builtin_amdgcn_rcpf((float)(slots - rows)) * 1.001f + 1.f, (float)kDecWaves), fails = share;
-  bc.chunks = cut(fits);
+  const int total = wave_sum(bc.pages) * c.Hkv, slots = dense_slots(total, max_chunks);
+  if (w >= slots) return false;  // most workgroups of a launch whose bound is far above the lengths
   if (__ballot(lane < c.B && bc.pages != __builtin_amdgcn_readfirstlane(bc.pages)) == 0) {
-    const int most = (bc.pages + kDecWaves - 1) / kDecWaves;  // of at least a page per wave
-    bc.chunks = lane < c.B ? min(slots / rows, most) : 0;
+    bc.chunks = lane < c.B ? dense_even_chunks(bc.pages, rows, slots) : 0;
   } else {
-#pragma unroll 1
-    while (fits - fails > fits * (1.f / 64.f) && fits > (float)kDecWaves) {
-      const float length = fmaxf(0.5f * (fits + fails), (float)kDecWaves);
-      const int chunks = cut(length);
-      if (wave_sum(chunks) * c.Hkv <= slots) { fits = length; bc.chunks = chunks; }
-      else fails = length;
-    }
+    bc.chunks = dense_row_chunks(bc.pages, dense_rate(total, rows, slots, [&](uint32_t rate) {
+      return wave_sum(dense_row_chunks(bc.pages, rate)) * c.Hkv;
+    }));
   }
   bc.before = wave_inclusive_scan(bc.chunks) - bc.chunks;
-  return bc;
+  return true;
 }
 
 template <typename T, int D, int S, int G, bool kNT>
@@ -65,8 +49,9 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_dense_kernel(Ca
                                                                               float* __restrict__ part_ml) {
   __shared__ DecodeShared<T, D, G> sh;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
-  const BatchChunks bc = cut_batch(c, S, max_chunks);
   const int w = blockIdx.x;
+  BatchChunks bc;
+  if (!cut_batch(c, S, max_chunks, w, bc)) return;
   const unsigned long long here = __ballot(w >= bc.before * c.Hkv && w < (bc.before + bc.chunks) * c.Hkv);
   if (here == 0) return;  // beyond the last chunk
   const int b = __ffsll(here) - 1;
@@ -93,7 +78,8 @@ __global__ __launch_bounds__(kWave) void paged_decode_dense_merge_kernel(CacheVi
                                                                          const float* __restrict__ part_ml, T* __restrict__ out,
                                                                          float* __restrict__ lse_out) {
   const int h = blockIdx.x, b = blockIdx.y, hkv = h / G;
-  const BatchChunks bc = cut_batch(c, c.S, max_chunks);
+  BatchChunks bc;
+  cut_batch(c, c.S, max_chunks, 0, bc);
   const int n = __builtin_amdgcn_readlane(bc.chunks, b);
   const int64_t base = (int64_t)__builtin_amdgcn_readlane(bc.before, b) * c.Hkv + (int64_t)hkv * n;
   merge_chunks<T, D, G>(c, b, h, base, n, part_o, part_ml, out, lse_out);

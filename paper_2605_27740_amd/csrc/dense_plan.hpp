@@ -1,5 +1,6 @@
-// Which dense decodes are cut by the lengths on the device (dense.hip), and into how many chunks at most. Host arithmetic on the
-// launch's bounds only (no HIP), so that it can be checked without a GPU.
+// Which dense decodes are cut by the lengths on the device (dense.hip), into how many chunks at most, and how. Whole numbers only (no
+// HIP), so that it can be checked without a GPU, and so that the kernel that writes the chunks and the one that merges them, which
+// find the cut each for itself, cannot differ. (constexpr functions are compiled for the device, too.)
 #pragma once
 #include <stdint.h>
 
@@ -28,6 +29,36 @@ inline bool dense_balances(int batch, int kv_heads, int max_pages, int page_byte
   const int64_t rows = (int64_t)batch * kv_heads;
   if (batch < 2 || batch > kDenseMaxBatch || rows > kDenseSlots / 2 || rows * max_pages > INT32_MAX) return false;
   return most_splits((int)rows, max_pages).num_splits > 1 && rows * max_pages * page_bytes >= kDenseLeastBytes;
+}
+
+// Workgroups that share the pages of a batch, `total` of them over all rows: those that run at the same time, or a multiple.
+constexpr int dense_slots(int total, int max_chunks) {
+  const int rounds = total / (kDenseSlots * kDensePages);
+  return std::min((rounds > 1 ? rounds : 1) * kDenseSlots, max_chunks);
+}
+
+// The cut: chunks per page as a fraction of 2^32, the same for all rows. It says into how many equal chunks a row is cut.
+constexpr uint32_t kDenseMostRate = (1u << 30) - 1;  // a page per wave
+constexpr int dense_row_chunks(int pages, uint32_t rate) { return pages > 0 ? (int)(((uint64_t)pages * rate) >> 32) + 1 : 0; }
+
+// The largest rate, within a 64th, at which there are no more chunks than slots; chunks(rate): those of all rows. The
+// first one is certain to fit, as a row's last chunk is its only one that is not full; no rate above an equal share can. slots > rows.
+template <typename Chunks>
+constexpr uint32_t dense_rate(int total, int rows, int slots, Chunks chunks) {
+  const uint32_t per = 0xffffffffu / (uint32_t)std::max(total, 1);
+  uint32_t fits = (uint32_t)std::min<uint64_t>((uint64_t)per * (uint32_t)(slots - rows), kDenseMostRate);
+  uint32_t fails = (uint32_t)std::min<uint64_t>(((uint64_t)per + 1) * (uint32_t)slots, 0xffffffffu);
+  while (fits < kDenseMostRate && fails - fits > std::max(fits / 64u, 1u)) {
+    const uint32_t rate = std::min(fits + (fails - fits) / 2, kDenseMostRate);
+    if (chunks(rate) <= slots) fits = rate;
+    else fails = rate;
+  }
+  return fits;
+}
+
+// Equally long sequences have as many chunks per row as there is room for, of at least a page per wave.
+constexpr int dense_even_chunks(int pages, int rows, int slots) {
+  return std::min(slots / rows, (pages + kDecWaves - 1) / kDecWaves);
 }
 
 }  // namespace unique

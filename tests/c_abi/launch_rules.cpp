@@ -30,3 +30,22 @@ extern "C" int dense_balances(int batch, int kv_heads, int max_pages, int page_b
 extern "C" int lds(int scores, int elem_bytes, int head_dim, int group, int workgroups) {
   return unique::score_lds(scores, elem_bytes, head_dim, group, workgroups);
 }
+// The cut of a dense batch as dense.hip finds it: chunks per row of every sequence; returns the workgroups that look for a chunk.
+extern "C" int dense_cut(const int* pages, int batch, int kv_heads, int max_pages, int* chunks) {
+  const int rows = batch * kv_heads, max_chunks = unique::dense_max_chunks(rows, max_pages);
+  int total = 0;
+  bool even = true;
+  for (int b = 0; b < batch; ++b) {
+    total += pages[b] * kv_heads;
+    even = even && pages[b] == pages[0];
+  }
+  const int slots = unique::dense_slots(total, max_chunks);
+  const uint32_t rate = unique::dense_rate(total, rows, slots, [&](uint32_t r) {
+    int n = 0;
+    for (int b = 0; b < batch; ++b) n += unique::dense_row_chunks(pages[b], r);
+    return n * kv_heads;
+  });
+  for (int b = 0; b < batch; ++b)
+    chunks[b] = even ? unique::dense_even_chunks(pages[b], rows, slots) : unique::dense_row_chunks(pages[b], rate);
+  return slots;
+}

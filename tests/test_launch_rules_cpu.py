@@ -44,6 +44,11 @@ def lib(tmp_path_factory):
             return bool(c.fuses(batch, heads, max_pages, top_k, page_bytes))
 
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
+
+        @staticmethod
+        def dense_cut(pages, heads, max_pages):
+            chunks = (C.c_int * len(pages))()
+            return c.dense_cut((C.c_int * len(pages))(*pages), len(pages), heads, max_pages, chunks), list(chunks)
     return Lib
 
 
@@ -167,3 +172,36 @@ def test_score_workgroups_per_unit_where_the_registers_allow_one_too_many(lib, e
                 assert got == scores
             elif scores < 8192:
                 assert -(-got // 2048) * 2048 * most <= 160 << 10 < got // 128 * 128 * (most + 1)
+
+
+def test_the_cut_of_a_dense_batch_gives_every_chunk_a_slot(lib):
+    """Rows of any mixture of lengths: no more chunks than workgroups that look for one and than slots of the workspace, at
+    least one per row that has pages, none longer than the share that is certain to fit (a 64th more for the search and a
+    rounding to whole pages), and no more of them than a chunk of four pages (one per wave) and one."""
+    r = random.Random(5)
+    seen = 0
+    while seen < 4000:
+        batch, heads = r.randint(2, 64), 1 << r.randint(0, 5)
+        bound = r.choice([r.randint(2, 3000), r.randint(2, 70000)])
+        if not lib.dense_balances(batch, heads, bound, r.choice([2048, 8192, 32768])):
+            continue
+        seen += 1
+        kind = r.randint(0, 4)
+        longest = r.choice([bound, max(1, bound // r.randint(1, 300))])
+        pages = [r.randint(0, longest) if kind == 0 else longest if kind == 1 else max(1, int(longest ** r.random())) if kind == 2 else
+                 longest - r.randint(0, min(3, longest)) if kind == 3 else r.randint(0, min(4, longest)) for _ in range(batch)]
+        if kind == 4:
+            pages[r.randrange(batch)] = longest
+        looking, chunks = lib.dense_cut(pages, heads, bound)
+        where = (pages, heads, bound, looking, chunks)
+        rows, total = batch * heads, sum(pages) * heads
+        assert sum(chunks) * heads <= looking <= lib.dense_chunks(rows, bound), where
+        slots = min(max(total // (512 * 256), 1) * 512, lib.dense_chunks(rows, bound))
+        even = len(set(pages)) == 1
+        for p, n in zip(pages, chunks):
+            assert (n >= 1) == (p > 0), where
+            if p:
+                length = -(-p // n)
+                assert n <= p // 4 + 1, where
+                share = p if even and n == slots // rows else total / (slots - rows)
+                assert length <= max(4, share * 65 / 64 + 1 + 4 * even), where
