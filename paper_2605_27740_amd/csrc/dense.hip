@@ -31,12 +31,13 @@ __device__ __forceinline__ bool cut_batch(const CacheView& c, int S, int max_chu
   bc.pages = max(0, min((bc.len + S - 1) / S, c.max_pages_hint));
   const int rows = c.B * c.Hkv;
   const int total = wave_sum(bc.pages) * c.Hkv, slots = dense_slots(total, max_chunks);
-  if (w >= slots) return false;  // most workgroups of a launch whose bound is far above the lengths
+  const bool room = dense_has_room(rows, slots, max_chunks);
+  if (w >= (room ? slots + rows : slots)) return false;  // most workgroups of a launch whose bound is far above the lengths
   if (__ballot(lane < c.B && bc.pages != __builtin_amdgcn_readfirstlane(bc.pages)) == 0) {
     bc.chunks = lane < c.B ? dense_even_chunks(bc.pages, rows, slots) : 0;
   } else {
     bc.chunks = dense_row_chunks(bc.pages, dense_rate(total, rows, slots, [&](uint32_t rate) {
-      return wave_sum(dense_row_chunks(bc.pages, rate)) * c.Hkv;
+      return wave_sum(dense_row_weight(bc.pages, rate, room)) * c.Hkv;
     }));
   }
   bc.before = wave_inclusive_scan(bc.chunks) - bc.chunks;

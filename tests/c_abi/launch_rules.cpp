@@ -40,12 +40,13 @@ extern "C" int dense_cut(const int* pages, int batch, int kv_heads, int max_page
     even = even && pages[b] == pages[0];
   }
   const int slots = unique::dense_slots(total, max_chunks);
+  const bool room = unique::dense_has_room(rows, slots, max_chunks);
   const uint32_t rate = unique::dense_rate(total, rows, slots, [&](uint32_t r) {
-    int n = 0;
-    for (int b = 0; b < batch; ++b) n += unique::dense_row_chunks(pages[b], r);
-    return n * kv_heads;
+    int weight = 0;
+    for (int b = 0; b < batch; ++b) weight += unique::dense_row_weight(pages[b], r, room);
+    return weight * kv_heads;
   });
   for (int b = 0; b < batch; ++b)
     chunks[b] = even ? unique::dense_even_chunks(pages[b], rows, slots) : unique::dense_row_chunks(pages[b], rate);
-  return slots;
+  return room ? slots + rows : slots;
 }

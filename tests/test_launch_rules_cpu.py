@@ -205,3 +205,6 @@ def test_the_cut_of_a_dense_batch_gives_every_chunk_a_slot(lib):
                 assert n <= p // 4 + 1, where
                 share = p if even and n == slots // rows else total / (slots - rows)
                 assert length <= max(4, share * 65 / 64 + 1 + 4 * even), where
+    # a long sequence among many short ones gets nearly all slots
+    _, chunks = lib.dense_cut([6250] + [4] * 30, 8, 6250)
+    assert chunks[0] * 8 > 400 and chunks[1:] == [1] * 30
