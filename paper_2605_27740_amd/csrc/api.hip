@@ -179,7 +179,7 @@ size_t group_max_bytes(const unique::CacheView& v) {
 }
 uint32_t* group_max_in(const unique::CacheView& v, int32_t top_k, float* buf, size_t bytes) {
   const size_t at = round_up(score_bytes(v), kAlign);
-  if (!unique::select_uses_groups(v, top_k) || bytes < at + group_max_bytes(v)) return nullptr;
+  if (!unique::select_uses_groups(v.max_pages_hint, top_k) || bytes < at + group_max_bytes(v)) return nullptr;
   return reinterpret_cast<uint32_t*>(buf + at / sizeof(float));
 }
 
@@ -262,7 +262,7 @@ int unique_workspace_bytes(const unique_cache_desc* desc, int32_t top_k, size_t*
   // selection may use the group maxima
   const unique::SplitPlan plan = unique::selection_plan(v, top_k);
   if (unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan)) need = std::max(need, fused_bytes(v, plan));
-  if (unique::select_uses_groups(v, top_k)) need = std::max(need, round_up(score_bytes(v), kAlign) + group_max_bytes(v));
+  if (unique::select_uses_groups(v.max_pages_hint, top_k)) need = std::max(need, round_up(score_bytes(v), kAlign) + group_max_bytes(v));
   *out_bytes = round_up(need, kAlign);
   return UNIQUE_OK;
 }

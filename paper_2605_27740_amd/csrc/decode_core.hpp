@@ -282,8 +282,8 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const float* __
 // Profiling build (-DUNIQUE_DEC_STAMPS, a second library next to the product one): every wave of the matrix-core
 // kernel records the 100 MHz wall clock at kernel entry, once its page ids are resolved, after its first tile, at
 // the end of its loop and after its stores, after every tile, and the compute unit it ran on, into a device array
-// that unique_debug_dec_stamps() hands out; unique_debug_gather_probe() (bottom of this file) is the bare memory
-// access of the kernel. The product build has none of it.
+// that unique_debug_dec_stamps() hands out; unique_debug_gather_probe() (decode.hip) is the bare memory access of the
+// kernel. The product build has none of it.
 #ifdef UNIQUE_DEC_STAMPS
 constexpr int kStampSlots = 32, kStampWaves = 1 << 14;
 __device__ unsigned long long g_dec_stamps[kStampWaves][kStampSlots];

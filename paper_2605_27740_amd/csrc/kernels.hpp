@@ -47,13 +47,12 @@ hipError_t launch_stats(const CacheView& c, const int32_t* d_tok_begin, const in
 hipError_t launch_score(const CacheView& c, const void* d_q, float lambda, float* d_scores, int score_stride,
                         float* d_scores_out, uint32_t* d_group_max, bool refresh_tail, hipStream_t stream);
 
-// d_group_max: of the same scores, or null
+// d_group_max: of the same scores, where select_uses_groups (step_rule.hpp) wants them, or null
 hipError_t launch_select(const CacheView& c, const float* d_scores, const uint32_t* d_group_max, int score_stride, int top_k,
                          int32_t* d_sel_pages, int32_t* d_sel_count, hipStream_t stream);
 
-// The selection for rows whose group maxima are known, which reads only the groups that can hold a selected page; whether a
-// launch is one of those that it is the faster one for.
-bool select_uses_groups(const CacheView& c, int top_k);
+// The selection for rows whose group maxima are known, which reads only the groups that can hold a selected page
+// (select_uses_groups in step_rule.hpp says for which launches).
 hipError_t launch_select_grouped(const CacheView& c, const float* d_scores, const uint32_t* d_group_max, int score_stride,
                                  int top_k, int32_t* d_sel_pages, int32_t* d_sel_count, hipStream_t stream);
 

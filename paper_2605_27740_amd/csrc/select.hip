@@ -302,7 +302,7 @@ hipError_t launch_t(const CacheView& c, const float* scores, int stride, int top
 
 hipError_t launch_select(const CacheView& c, const float* d_scores, const uint32_t* d_group_max, int score_stride, int top_k,
                          int32_t* d_sel_pages, int32_t* d_sel_count, hipStream_t stream) {
-  if (d_group_max && select_uses_groups(c, top_k))
+  if (d_group_max)
     return launch_select_grouped(c, d_scores, d_group_max, score_stride, top_k, d_sel_pages, d_sel_count, stream);
   const int P = c.max_pages_hint;
   auto go = [&](auto threads, auto vecs) {

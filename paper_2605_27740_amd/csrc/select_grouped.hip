@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "select_groups.hpp"
+#include "step_rule.hpp"
 
 namespace unique {
 namespace {
@@ -23,6 +24,10 @@ __global__ __launch_bounds__(kThreads) void topk_select_grouped_kernel(CacheView
   constexpr int kVecs = 8;            // 16-byte loads of scores per thread
   constexpr int kKept = 24 * kWave;   // keys from T0 on: what one wave holds
   __shared__ GroupShared<kThreads, kVecs, kKept> sh;
+  // the largest k of such rows fits (see gather_from_groups)
+  constexpr int kMostPages = kThreads * kGroupVecs * 4 * kGroupPages;
+  constexpr int kMostK = kMostPages / kGroupsPagesPerK < kGroupsMaxTopK ? kMostPages / kGroupsPagesPerK : kGroupsMaxTopK;
+  static_assert(kMostK <= kKept && 9 * kMostK <= 8 * GroupShared<kThreads, kVecs, kKept>::kMaxGroups, "");
 
   const int row = blockIdx.x;
   const int b = row / c.Hkv;
@@ -30,7 +35,7 @@ __global__ __launch_bounds__(kThreads) void topk_select_grouped_kernel(CacheView
   const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
   const int N = c.seq_lens[b];
   int P = min((N + c.S - 1) / c.S, c.max_pages_hint);
-  P = min(P, kThreads * kGroupVecs * 4 * kGroupPages);  // a row longer than the host bound is cut, never overrun
+  P = min(P, kMostPages);  // a row longer than the host bound is cut, never overrun
   const int kb = min(top_k, P);
   int32_t* out = sel_pages + (int64_t)row * top_k;
   const float* srow = scores + (int64_t)row * score_stride;
@@ -60,22 +65,10 @@ __global__ __launch_bounds__(kThreads) void topk_select_grouped_kernel(CacheView
 
 }  // namespace
 
-// Worth it while the kept groups are a small part of the row and fit the workgroup's registers (2048 of them, k and a quarter
-// and some more). Kernel us of select.hip / this one, planted normal scores, 8 rows: 4097 pages, k 64 7.8 / 5.9; 8192, 64 8.6 / 5.4;
-// 12000, 500 11.9 / 9.0; 16384, 64 9.7 / 6.8; 32768, 64 13.9 / 7.6; 62501, 1024 29.6 / 14.1; 64 rows: 8192, 256 8.9 / 7.3; 128 rows:
-// 16384, 680 13.5 / 11.0; 16 rows: 125001, 1024 45.2 / 18.3. Not worth it: 4097, 340 7.6 / 7.7; 16384, 1024 (128 rows) 14.0 / 16.4;
-// 62501, 2000 44.6 / 176 (too many groups). The maxima cost the score kernel 0.3 us (1 us of 90 at 16 x 16384 pages).
-// Scores that rise by two standard deviations along the row need a tighter bound and take longer, not longer than there but where k
-// is near its limit: 4097, 64 7.8 / 7.4; 8192, 256 8.4 / 9.4; 12000, 500 11.5 / 12.0; 16384, 680 12.8 / 14.4; 62501, 1024 28.7 /
-// 16.7. Scores of five values: 8192, 256 19.4 / 7.9; 62501, 1024 40.8 / 17.6; 125001, 1024 431 / 26.5.
-bool select_uses_groups(const CacheView& c, int top_k) {
-  const int P = c.max_pages_hint;
-  return P > 4096 && P <= 131072 && top_k <= std::min(P / 24, 1280);
-}
-
 hipError_t launch_select_grouped(const CacheView& c, const float* d_scores, const uint32_t* d_group_max, int score_stride,
                                  int top_k, int32_t* d_sel_pages, int32_t* d_sel_count, hipStream_t stream) {
   const int P = c.max_pages_hint;
+  if (!select_uses_groups(P, top_k)) return hipErrorInvalidValue;  // the kernels are made for these sizes alone
   auto go = [&](auto threads, auto vecs) {
     constexpr int kThreads = decltype(threads)::value, kVecs = decltype(vecs)::value;
     topk_select_grouped_kernel<kThreads, kVecs><<<dim3(c.B * c.Hkv), dim3(kThreads), 0, stream>>>(

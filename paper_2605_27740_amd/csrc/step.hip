@@ -124,6 +124,7 @@ struct SelectFromGroups {
   const uint32_t* grow;
   int P;
   using Shared = GroupShared<kThreads, 4, kSmallCap>;
+  static_assert(kStepMaxTopK <= kSmallCap && 9 * kStepMaxTopK <= 8 * Shared::kMaxGroups, "gather_from_groups");
   Shared& sh;
   template <typename EmitAll>
   __device__ __forceinline__ void operator()(int kb, const int32_t* page_table, EmitAll emit_all) const {
@@ -222,8 +223,7 @@ __global__ __launch_bounds__(kThreads) void whole_step_kernel(
       if (cl == 0 && p < P && !fresh) row_scores[p] = valid[u] ? s : __uint_as_float(0x7fc00000u);
     }
   }
-  if (tail_phys >= 0) {  // uniform; the tail wave
-    if (first) scorer.unpack(lambda);
+  if (tail_phys >= 0) {  // uniform; the tail wave. (P > 0, so the queries have been unpacked.)
     tail.reduce(n_tail, lane);
     tail.store_mean(tail_mean, sizeof(TS) == 2, lane);
     if (split == 0) {
@@ -252,23 +252,18 @@ hipError_t launch_t(const CacheView& c, const StepArgs& a, hipStream_t st) {
   const SplitPlan plan = selection_plan(c, a.top_k);
   const bool stream_nt = decode_streams(c, a.top_k);
   float* part_ml = a.partials + (size_t)rows * plan.num_splits * G * D;
-  auto go = [&](auto kernel) {
+  auto go = [&](auto kernel, auto... group_max) {
     const dim3 grid = plan.rotate ? dim3(c.Hkv, c.B, plan.num_splits) : dim3(plan.num_splits, c.Hkv, c.B);
-    kernel<<<grid, dim3(kThreads), 0, st>>>(c, reinterpret_cast<const T*>(a.q), a.scores, a.score_stride, a.top_k,
+    kernel<<<grid, dim3(kThreads), 0, st>>>(c, reinterpret_cast<const T*>(a.q), a.scores, group_max..., a.score_stride, a.top_k,
                                             a.sel_pages, a.sel_count, plan, decode_scale_log2(c, a.sm_scale), a.partials, part_ml,
                                             reinterpret_cast<T*>(a.out), a.lse_out);
     return hipGetLastError();
   };
-  if (a.group_max) {
-    auto go_groups = [&](auto kernel) {
-      const dim3 grid = plan.rotate ? dim3(c.Hkv, c.B, plan.num_splits) : dim3(plan.num_splits, c.Hkv, c.B);
-      kernel<<<grid, dim3(kThreads), 0, st>>>(c, reinterpret_cast<const T*>(a.q), a.scores, a.group_max, a.score_stride, a.top_k,
-                                              a.sel_pages, a.sel_count, plan, decode_scale_log2(c, a.sm_scale), a.partials, part_ml,
-                                              reinterpret_cast<T*>(a.out), a.lse_out);
-      return hipGetLastError();
-    };
-    return stream_nt ? go_groups(select_groups_decode_kernel<T, D, S, G, true>) : go_groups(select_groups_decode_kernel<T, D, S, G, false>);
-  }
+  // rows that no kernel here is made for would be cut without a word
+  if (a.top_k > kStepMaxTopK || c.max_pages_hint > (a.group_max ? kStepMaxGroupPages : kStepMaxPages)) return hipErrorInvalidValue;
+  if (a.group_max)
+    return stream_nt ? go(select_groups_decode_kernel<T, D, S, G, true>, a.group_max)
+                     : go(select_groups_decode_kernel<T, D, S, G, false>, a.group_max);
   if (c.max_pages_hint <= 4 * kThreads)
     return stream_nt ? go(select_decode_kernel<T, D, S, G, true, 1>) : go(select_decode_kernel<T, D, S, G, false, 1>);
   if (c.max_pages_hint <= 8 * kThreads)
@@ -278,6 +273,7 @@ hipError_t launch_t(const CacheView& c, const StepArgs& a, hipStream_t st) {
 
 template <typename T, int D, int S, int G>
 hipError_t launch_whole_t(const CacheView& c, const StepArgs& a, hipStream_t st) {
+  if (a.top_k > kStepMaxTopK || c.max_pages_hint > kStepWholePages) return hipErrorInvalidValue;
   const SplitPlan plan = selection_plan(c, a.top_k);
   float* part_ml = a.partials + (size_t)c.B * c.Hkv * plan.num_splits * G * D;
   auto go = [&](auto kernel) {

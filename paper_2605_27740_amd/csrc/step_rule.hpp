@@ -1,4 +1,4 @@
-// Which decode steps select and attend in one kernel. Host arithmetic on the launch's bounds only (no HIP), so that it can be
+// Which selections use the group maxima of the scores, and which decode steps select and attend in one kernel. Host arithmetic on the launch's bounds only (no HIP), so that it can be
 // checked without a GPU.
 #pragma once
 #include <stdint.h>
@@ -12,6 +12,21 @@ constexpr int kStepMaxGroupPages = 32768;  // pages of a row that is selected fr
 constexpr int kStepMaxTopK = 256;    // list entries that a workgroup keeps in the LDS
 
 constexpr int kStepWholePages = 384;  // pages of a row that are scored in the same kernel, too
+
+constexpr int kGroupsMaxPages = 131072, kGroupsMaxTopK = 1280, kGroupsPagesPerK = 24;  // selections from the group maxima
+
+// Selections of rows whose group maxima the score kernel leaves beside the scores: worth it while the kept groups are a small part of
+// the row and fit the workgroup's registers (2048 of them, k and a half and some more). Kernel us of select.hip / select_grouped.hip,
+// planted normal scores, 8 rows: 4097 pages, k 64 7.8 / 5.9; 8192, 64 8.6 / 5.4; 12000, 500 11.9 / 9.0; 16384, 64 9.7 / 6.8; 32768, 64
+// 13.9 / 7.6; 62501, 1024 29.6 / 14.1; 64 rows: 8192, 256 8.9 / 7.3; 128 rows: 16384, 680 13.5 / 11.0; 16 rows: 125001, 1024 45.2 /
+// 19.3. Not worth it: 4097, 340 7.6 / 7.7; 16384, 1024 (128 rows) 14.0 / 16.4. The maxima cost the score kernel 0.3 us (1 us of 90 at
+// 16 x 16384 pages).
+// Scores that rise by two standard deviations along the row need a tighter bound and take longer, not longer than there but where k
+// is near its limit: 4097, 64 7.8 / 7.4; 8192, 256 8.4 / 9.3; 12000, 500 11.4 / 11.9; 16384, 680 12.8 / 14.4; 62501, 1024 28.7 /
+// 17.0. Scores of five values: 8192, 256 19.4 / 8.0; 62501, 1024 40.8 / 17.7; 125001, 1024 431 / 26.5.
+inline bool select_uses_groups(int max_pages, int top_k) {
+  return max_pages > kStepMaxPages && max_pages <= kGroupsMaxPages && top_k <= std::min(max_pages / kGroupsPagesPerK, kGroupsMaxTopK);
+}
 
 // Saved are a launch and the round trips of writing and reading the list, paid is a selection by four waves in every
 // workgroup of a cut row. us of a whole step in separate kernels / so (bf16, 8 KV heads, G = 4, D = 128, pages of 16, fp32 means):
@@ -27,7 +42,7 @@ constexpr int kStepWholePages = 384;  // pages of a row that are scored in the s
 // 22.2 / 22.0; 4 x 16384, 64 63.0 / 60.4; 1 x 32768, 256 47.9 / 43.9.
 inline bool step_fuses(int rows, int max_pages, int top_k, const SplitPlan& plan) {
   if (max_pages > kStepMaxGroupPages || top_k > kStepMaxTopK || (max_pages > 512 && 4 * top_k > max_pages)) return false;
-  if (max_pages > kStepMaxPages) return 24 * top_k <= max_pages && (plan.num_splits == 1 || (int64_t)rows * plan.num_splits <= 512);
+  if (max_pages > kStepMaxPages) return select_uses_groups(max_pages, top_k) && (plan.num_splits == 1 || (int64_t)rows * plan.num_splits <= 512);
   return plan.num_splits == 1 || (int64_t)rows * plan.num_splits * std::max(max_pages, 2048) <= 1024 * 2048;
 }
 

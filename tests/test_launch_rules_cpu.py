@@ -44,6 +44,7 @@ def lib(tmp_path_factory):
             return bool(c.fuses(batch, heads, max_pages, top_k, page_bytes))
 
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
+        whole, uses_groups = c.whole, c.uses_groups
 
         @staticmethod
         def dense_cut(pages, heads, max_pages):
@@ -208,3 +209,22 @@ def test_the_cut_of_a_dense_batch_gives_every_chunk_a_slot(lib):
     # a long sequence among many short ones gets nearly all slots
     _, chunks = lib.dense_cut([6250] + [4] * 30, 8, 6250)
     assert chunks[0] * 8 > 400 and chunks[1:] == [1] * 30
+
+
+def test_steps_that_select_from_group_maxima_are_selections_that_have_them(lib):
+    """A fused step of more pages than a row in registers is selected from the group maxima, which the score kernel only
+    leaves where select_uses_groups says so; rows that are scored in the same kernel are short enough for its registers."""
+    r = random.Random(7)
+    fused = 0
+    for _ in range(50000):
+        batch, heads, pages = r.randint(1, 90), 1 << r.randint(0, 5), r.choice([r.randint(1, 5000), r.randint(1, 140000)])
+        top_k = r.choice([r.randint(1, 300), max(1, pages // 24 + r.randint(-2, 2))])
+        if lib.fuses(batch, heads, pages, top_k):
+            fused += pages > 4096
+            assert pages <= 4096 or (lib.uses_groups(pages, top_k) and pages <= 32768), (batch, heads, pages, top_k)
+            assert top_k <= 256
+        if lib.uses_groups(pages, top_k):
+            assert 4096 < pages <= 131072 and 24 * top_k <= pages and top_k <= 1280
+    assert fused > 500
+    for mean_bytes, most in ((256, 384), (512, 256)):
+        assert lib.whole(most, mean_bytes, 0) and not lib.whole(most + 1, mean_bytes, 0) and not lib.whole(1, mean_bytes, 1)
