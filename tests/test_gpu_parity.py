@@ -5,6 +5,7 @@ EVERY row through the oracle's whole-batch drivers. Tolerances are in tests/harn
 """
 import math
 import os
+import re
 
 import numpy as np
 import pytest
@@ -1140,7 +1141,7 @@ def test_select_ragged_rows(gpu_lib, B, Hkv, P, top_k, n):
 def test_step_with_the_selection_in_the_attention_kernel(gpu_lib, P):
     """unique_decode_step on planted scores against the separate calls, at the edges of the rows, budgets and score
     distributions that it serves in one kernel: every output is the same bits. Also with the smallest workspace that is
-    accepted, with which it has to take two kernels."""
+    accepted, with which some of them take more kernels (test_kernels_of_a_step says which)."""
     ks = sorted({1, min(P, 7), max(1, min(P // 4, 1100)), max(1, P // 24), max(1, min(P - 1, 200)), 256, 257})
     wl = W.build("planted", 9, dtype=torch.bfloat16 if P % 2 else torch.float32, B=2, H=8, Hkv=2, D=64, S=8,
                  seq_lens=[8 * P, max(8 * P - 3 - 8 * (P // 3), 1)], top_k=1, key_mode="iid", permute=True, poison=False).to(DEV)
@@ -1296,13 +1297,13 @@ def test_whole_step_in_one_kernel(gpu_lib, dtype, Hkv, G, D, S, pages, top_k, st
         wl.seq_lens.copy_(before)
 
 
-def _planted_rows(P, scores, top_k, dtype=torch.bfloat16):
+def _planted_rows(P, scores, top_k, dtype=torch.bfloat16, D=64):
     """Two sequences of P and P // 3 pages of 8 tokens over one pool whose page p scores scores[p % len] (two KV heads)."""
-    wl = W.build("planted", 9, dtype=dtype, B=2, H=8, Hkv=2, D=64, S=8, seq_lens=[8, 8], top_k=1, key_mode="iid",
+    wl = W.build("planted", 9, dtype=dtype, B=2, H=8, Hkv=2, D=D, S=8, seq_lens=[8, 8], top_k=1, key_mode="iid",
                  poison=False).to(DEV)
     pool = len(scores)
-    wl.k_cache = torch.zeros((pool, 2, 8, 64), dtype=dtype, device=DEV)
-    wl.v_cache = torch.randn((pool, 2, 8, 64), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV).to(dtype)
+    wl.k_cache = torch.zeros((pool, 2, 8, D), dtype=dtype, device=DEV)
+    wl.v_cache = torch.randn((pool, 2, 8, D), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV).to(dtype)
     wl.page_table = torch.arange(2 * P, dtype=torch.int32, device=DEV).remainder(pool).view(2, P)
     wl.seq_lens = torch.tensor([8 * P - 3, 8 * (P // 3) + 1], dtype=torch.int32, device=DEV)
     wl.q.zero_()
@@ -1371,3 +1372,51 @@ def test_time_does_not_depend_on_where_the_best_pages_are(gpu_lib, call, P, top_
     got = {kind: round(best(kind) / normal, 2) for kind in ("rising", "falling_to_zero", "mostly_padding", "five_values")}
     say(f"{call} P={P} k={top_k}: {normal:.1f} us, {got}")
     assert max(got.values()) < 1.7, got
+
+
+def _kernels_of(run):
+    from torch.profiler import ProfilerActivity, profile
+    run()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        run()
+        torch.cuda.synchronize()
+    names = {re.search(r"(\w+_kernel)", e.name) for e in p.events() if e.device_type == torch.autograd.DeviceType.CUDA}
+    return {m.group(1) for m in names if m}
+
+
+@pytest.mark.parametrize("P,D,top_k,workspace,want", [
+    (384, 64, 100, None, {"whole_step_kernel"}), (256, 128, 64, None, {"whole_step_kernel"}),
+    (385, 64, 96, None, {"page_score_kernel", "select_decode_kernel"}), (257, 128, 64, None, {"page_score_kernel", "select_decode_kernel"}),
+    (300, 128, 256, None, {"page_score_kernel", "select_decode_kernel"}),
+    (4096, 64, 256, None, {"page_score_kernel", "select_decode_kernel"}),
+    (4097, 64, 170, None, {"page_score_kernel", "select_groups_decode_kernel"}),
+    (4097, 64, 171, None, {"page_score_kernel", "topk_select_kernel", "paged_decode_partial_kernel"}),
+    (4096, 64, 257, None, {"page_score_kernel", "topk_select_kernel", "paged_decode_partial_kernel"}),
+    (32768, 64, 300, None, {"page_score_kernel", "topk_select_grouped_kernel", "paged_decode_partial_kernel"}),
+    # 2 x 2 score rows of 128 KB, their maxima of 16 KB each, and partial results
+    (32768, 64, 256, None, {"page_score_kernel", "select_groups_decode_kernel"}),
+    (32768, 64, 256, 576 << 10, {"page_score_kernel", "topk_select_grouped_kernel", "paged_decode_partial_kernel"}),
+    (32768, 64, 256, (576 << 10) - 256, {"page_score_kernel", "topk_select_kernel", "paged_decode_partial_kernel"}),
+    (32768, 64, 256, 512 << 10, {"page_score_kernel", "topk_select_kernel", "paged_decode_partial_kernel"})])
+def test_kernels_of_a_step(gpu_lib, P, D, top_k, workspace, want):
+    """Which kernels a decode step is made of, at the edges of its rules on rows, budgets and workspaces (and a merge where
+    rows are cut), so that the tests of each of them are known to run it; and the same results with every workspace."""
+    sess = _planted_rows(P, UNEVEN_MAKERS["rising"](P), top_k, D=D)
+    sess.decode_step(refresh_tail=False)
+    torch.cuda.synchronize()
+    all_of = [t.clone() for t in (sess.sel_pages, sess.sel_count, sess.out, sess.lse)]
+    if workspace is not None:
+        assert workspace < sess.workspace.numel()
+        sess.workspace = sess.workspace[:workspace]
+    assert _kernels_of(lambda: sess.decode_step(refresh_tail=False)) - {"paged_decode_merge_kernel"} == want
+    for a, b in zip(all_of, (sess.sel_pages, sess.sel_count, sess.out, sess.lse)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+def test_kernels_of_a_dense_decode(gpu_lib):
+    """Two sequences of which only one has more than a chunk are cut by the lengths on the device from 96 MB on."""
+    sess = _planted_rows(24576, UNEVEN_MAKERS["rising"](32768), 8)   # 2 x 2 rows of 24576 pages of 2 KB: 192 MB
+    assert _kernels_of(sess.dense_paged_decode) == {"paged_decode_dense_kernel", "paged_decode_dense_merge_kernel"}
+    sess = _planted_rows(12287, UNEVEN_MAKERS["rising"](32768), 8)
+    assert _kernels_of(sess.dense_paged_decode) == {"paged_decode_partial_kernel", "paged_decode_merge_kernel"}
