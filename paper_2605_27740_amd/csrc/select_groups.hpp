@@ -17,7 +17,7 @@ struct GroupShared {
   uint2 kept[kCap + kWave];            // key, page
 };
 
-// A row's gathered keys: `total` of them, at most kCap, all from T0 on and none above top, in sh.kept in page order.
+// A row's gathered keys: `total` of them, at most kCap, all from T0 on and fewer than kb above top, in sh.kept in page order.
 struct Gathered {
   uint32_t T0, top;
   int total;
@@ -52,7 +52,7 @@ __device__ __forceinline__ Gathered gather_from_groups(const float* srow, const 
       const uint32_t k = j % 4 == 0 ? raw[j / 4].x : (j % 4 == 1 ? raw[j / 4].y : (j % 4 == 2 ? raw[j / 4].z : raw[j / 4].w));
       const int g = group_of(j);
       gkey[j] = g >= groups ? 0u : (forced_from < P && (g + 1) * kGroupPages > forced_from ? kKeyForced : k);
-      top = max(top, gkey[j]);
+      top = max(top, g < groups ? k : 0u);  // (of scores alone, see search_top)
       least = min(least, g < groups ? gkey[j] : 0xffffffffu);
     }
   }
@@ -73,7 +73,8 @@ __device__ __forceinline__ Gathered gather_from_groups(const float* srow, const 
     if (kb <= groups && of_wave > 0 && !(drop && of_wave < kFull)) {  // uniform
       least = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<false>(least));
       const int share = (int)(((int64_t)kb * of_wave + counted - 1) / counted);
-      mine = bisect(least - 1u, top, of_wave, share, share + share / 8, [&](uint32_t x) { return count_above(gkey, x); }) + 1u;
+      const uint32_t high = forced_from < P ? search_top(gkey, share) : top;
+      mine = bisect(least - 1u, high, of_wave, share, share + share / 8, [&](uint32_t x) { return count_above(gkey, x); }) + 1u;
     }
     if (lane == 0) { sh.wave_max[wave] = top; sh.wave_min[wave] = mine; }
     __syncthreads();
@@ -81,7 +82,7 @@ __device__ __forceinline__ Gathered gather_from_groups(const float* srow, const 
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) { top = max(top, sh.wave_max[w]); low = min(low, sh.wave_min[w]); }
     if (kb <= groups) T0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)low);
-    top = (uint32_t)__builtin_amdgcn_readfirstlane((int)top);
+    top = P - forced_from < kb ? (uint32_t)__builtin_amdgcn_readfirstlane((int)top) : kKeyForced;
   }
 
   // ---- 2. the groups from T0 on, in page order

@@ -67,21 +67,20 @@ __device__ __forceinline__ uint32_t bisect(uint32_t lo, uint32_t hi, int n_lo, i
   return lo;
 }
 
-// The same from known counts at lo and hi, with rounds that aim at `enough` along the line between the counts. That halves the number
-// of rounds (9 to 5 where a third of the keys is to go) and costs as much as counting some keys. Keys are nearly logarithms of the
-// scores, which suits the tail of a distribution; across many octaves, zero above all, the line is drawn between the scores
-// themselves (8192 pages that score -p / 8192, k = 256: 31.1 us with keys alone, 27.3 so). An aim that leaves more than half of the
-// keys' range is followed by two halvings: where most keys are equal, every aim does. Leaves count(x) in n_lo.
+// The same from known counts at lo and hi, where two rounds of three aim between k and `enough` along the line between the counts. That halves
+// the number of rounds (9 to 5 where a third of the keys is to go) and costs as much as counting some keys. Keys are nearly
+// logarithms of the scores, which suits the tail of a distribution; across very many octaves, zero that is, the line is drawn between
+// the scores themselves (8192 pages that score -p / 8192, k = 256: 31.1 us with keys alone, 27.3 so). Where most keys are equal an aim
+// leaves nearly everything, so there are no more than twelve rounds with aims. Leaves count(x) in n_lo.
 template <typename Count>
 __device__ __forceinline__ uint32_t bisect_aimed(uint32_t lo, uint32_t hi, int& n_lo, int n_hi, int k, int enough, Count count) {
-  constexpr uint32_t kOctaves = 4u << 23;
-  int halvings = 0;
+  constexpr uint32_t kOctaves = 16u << 23;
 #pragma unroll 1
-  while ((n_lo > enough) & (hi - lo > 1u)) {
+  for (int i = 0; (n_lo > enough) & (hi - lo > 1u); ++i) {
     const uint32_t width = hi - lo;
     uint32_t x = lo + width / 2;
-    if (halvings == 0) {
-      const float part = (float)(n_lo - enough) * __builtin_amdgcn_rcpf((float)(n_lo - n_hi));
+    if (i % 3 != 2 && i < 12) {
+      const float part = (float)(n_lo - (k + enough) / 2) * __builtin_amdgcn_rcpf((float)(n_lo - n_hi));
       uint32_t aim = lo + (uint32_t)((float)width * part);
       if (width > kOctaves) {
         const float from = ordered_to_float(lo), f = fmaf(ordered_to_float(hi) - from, part, from);
@@ -92,9 +91,26 @@ __device__ __forceinline__ uint32_t bisect_aimed(uint32_t lo, uint32_t hi, int& 
     const int n = count(x);
     if (n >= k) { lo = x; n_lo = n; }
     else { hi = x; n_hi = n; }
-    halvings = halvings > 0 ? halvings - 1 : (hi - lo > width / 2 ? 2 : 0);
   }
   return lo;
+}
+
+// The upper end of a search for the k-th of the wave's values: the largest of them, or, with pages that are always selected (whose
+// keys are far above all others), the largest other one if fewer than k lie above it.
+template <int kN>
+__device__ __forceinline__ uint32_t search_top(const uint32_t (&v)[kN], int k) {
+  uint32_t top = 0u;
+#pragma unroll
+  for (int r = 0; r < kN; ++r) top = max(top, v[r]);
+  top = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<true>(top));
+  if (top == kKeyForced) {  // uniform
+    uint32_t other = 0u;
+#pragma unroll
+    for (int r = 0; r < kN; ++r) other = max(other, v[r] == kKeyForced ? 0u : v[r]);
+    other = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<true>(other));
+    if (count_above(v, other) < k) top = other;
+  }
+  return top;
 }
 
 // Number of a workgroup's keys above x, kN per thread; turns: 2 * waves ints of LDS. All threads call it; it holds a barrier.
@@ -120,7 +136,7 @@ struct SpreadCount {
   }
 };
 
-// A bound T0 that `total` > enough >= kb of a workgroup's keys reach is raised until at most `enough` do. Where so many are equal that
+// A bound T0 that `total` > enough >= kb of a workgroup's keys reach is raised until at most `enough` do; fewer than kb are above top. Where so many are equal that
 // none between kb and `enough` does, the first ones of them, in the order (v, thread, i) of key[kPer * v + i], are left that make kb,
 // and the others become 0: of equal keys the first are selected. equal: kVecs * waves ints, 16-byte aligned, turns as above; both
 // unused by others since the last barrier. All threads call it; no thread returns before all have come.
@@ -189,19 +205,17 @@ __device__ __forceinline__ int place_from(const uint32_t (&key)[kVecs * kPer], u
 template <int kN>
 __device__ __forceinline__ uint32_t bound_of_maxima(const uint32_t* group_max, int k) {
   const int lane = threadIdx.x % kWave;
-  uint32_t m[kN], top = 0u, least = 0xffffffffu;
+  uint32_t m[kN], least = 0xffffffffu;
 #pragma unroll
   for (int r = 0; r < kN; ++r) {
     m[r] = group_max[r * kWave + lane];
-    top = max(top, m[r]);
     least = min(least, m[r] - 1u);  // (0, no key, wraps around)
   }
-  top = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<true>(top));
   least = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<false>(least));
-  return bisect(least, top, kN * kWave, k, k + k / 8, [&](uint32_t x) { return count_above(m, x); }) + 1u;
+  return bisect(least, search_top(m, k), kN * kWave, k, k + k / 8, [&](uint32_t x) { return count_above(m, x); }) + 1u;
 }
 
-// The kb largest of `total` <= 64 * kN gathered keys, of which all are above `low` and none above `top`, in page order, by one
+// The kb largest of `total` <= 64 * kN gathered keys, of which all are above `low` and fewer than kb above `top`, in page order, by one
 // wave: emit(r, at, page) says that the page, which the lane holds as its r-th, is the at-th selected one, or with at = -1 that
 // it is none. ahead(page) is called for all kN pages of the lanes (0: none) before the search.
 template <int kN, typename Emit, typename Ahead>
@@ -263,10 +277,10 @@ __device__ __forceinline__ void select_kept(const uint2* kept, int total, uint32
   auto gathered = [&](auto per_lane) {
     constexpr int kN = decltype(per_lane)::value;
     int phys[kN];
-    uint32_t top = 0u;
+    uint32_t key[kN];
 #pragma unroll
-    for (int r = 0; r < kN; ++r) top = max(top, r * kWave + lane < total ? kept[r * kWave + lane].x : 0u);
-    top = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_allreduce_minmax<true>(top));
+    for (int r = 0; r < kN; ++r) key[r] = r * kWave + lane < total ? kept[r * kWave + lane].x : 0u;
+    const uint32_t top = search_top(key, kb);
     select_gathered<kN>(kept, total, low, top, kb, [&](int r, int at, int page) { emit_all(r, at, page, phys[r]); },
                         [&](const int(&page)[kN]) {
 #pragma unroll
@@ -321,7 +335,7 @@ __device__ __forceinline__ void select_small(uint32_t (&key)[4 * kVecs], int P, 
   int total = place_from<kThreads, kVecs, 4>(key, T0, sh.counts[0], place);
   if constexpr (kThreads * kVecs * 4 > kSmallCap) {
     if (total > kSmallCap) {  // uniform: masses of equal scores, or a k beyond the groups
-      T0 = tighten<kThreads, kVecs, 4>(key, T0, 0xffffffffu, total, kb, kSmallCap / 2, sh.counts[1], sh.turns);
+      T0 = tighten<kThreads, kVecs, 4>(key, T0, kKeyForced, total, kb, kSmallCap / 2, sh.counts[1], sh.turns);
       total = place_from<kThreads, kVecs, 4>(key, T0, sh.counts[0], place);
     }
   }
