@@ -214,7 +214,8 @@ int decode_step_launch(const unique::CacheView& v, const void* d_q, int32_t top_
   uint32_t* group_max = group_max_in(v, top_k, buf, bytes);
   const unique::SplitPlan plan = unique::selection_plan(v, top_k);
   const bool fuses = unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan);
-  const bool whole = fuses && unique::step_is_whole(v.max_pages_hint, v.D * (v.stats_bf16 ? 2 : 4), unique::decode_streams(v, top_k));
+  const bool whole = fuses && unique::step_is_whole(v.B * v.Hkv, v.max_pages_hint, v.D * (v.stats_bf16 ? 2 : 4),
+                                                    unique::decode_streams(v, top_k), plan);
   hipError_t e = hipSuccess;
   if (!whole) e = unique::launch_score(v, d_q, lambda, buf, stride, nullptr, group_max, refresh_tail != 0, st);
   if (e != hipSuccess) return hip_fail(e, "page score launch");

@@ -52,8 +52,10 @@ inline bool step_fuses(int rows, int max_pages, int top_k, const SplitPlan& plan
 //   1 x 250, 200 19.9 / 19.5 / 17.3; the toy model (2 heads, fp32, D = 64, 128 pages, k = 16) 14.9 / 13.5 / 11.4
 // Reading a row's means takes one compute unit longer than a launch costs from 128 KB on: 16 x 270 pages 18.4 / 15.8, but 4 x 320,
 // k = 64 18.7 / 20.5 and 4 x 512, 64 19.1 / 23.2; rows of 256 bytes: 2 x 400, 16 heads, G = 8 21.8 / 20.4, 6 x 500, G = 1 21.6 / 20.0,
-// 10 x 500, G = 8 21.0 / 22.2.
-inline bool step_is_whole(int max_pages, int mean_bytes, bool streams) {
+// 10 x 500, G = 8 21.0 / 22.2. Cut rows of more workgroups than run at the same time score their rows once more in a second round: 24 x
+// 250, 64 (576 workgroups) three kernels 36.5, so 42.0; 17 x 250, 48 28.9 / 33.9; 20 x 120, 64 31.1 / 32.1; 28 x 250, 64 41.7 / 41.5.
+inline bool step_is_whole(int rows, int max_pages, int mean_bytes, bool streams, const SplitPlan& plan) {
+  if (plan.num_splits > 1 && (int64_t)rows * plan.num_splits > 512) return false;
   return max_pages <= (mean_bytes > 256 ? 256 : kStepWholePages) && !streams;
 }
 

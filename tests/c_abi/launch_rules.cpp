@@ -23,7 +23,10 @@ extern "C" int fuses(int batch, int kv_heads, int max_pages, int top_k, int page
   return unique::step_fuses(batch * kv_heads, max_pages, top_k,
                             unique::plan_splits(batch, kv_heads, top_k, max_pages, page_bytes, false));
 }
-extern "C" int whole(int max_pages, int mean_bytes, int streams) { return unique::step_is_whole(max_pages, mean_bytes, streams != 0); }
+extern "C" int whole(int batch, int kv_heads, int max_pages, int top_k, int page_bytes, int mean_bytes, int streams) {
+  return unique::step_is_whole(batch * kv_heads, max_pages, mean_bytes, streams != 0,
+                               unique::plan_splits(batch, kv_heads, top_k, max_pages, page_bytes, false));
+}
 extern "C" int uses_groups(int max_pages, int top_k) { return unique::select_uses_groups(max_pages, top_k); }
 extern "C" int dense_chunks(int rows, int max_pages) { return unique::dense_max_chunks(rows, max_pages); }
 extern "C" int dense_balances(int batch, int kv_heads, int max_pages, int page_bytes) {

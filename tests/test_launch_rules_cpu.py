@@ -44,7 +44,11 @@ def lib(tmp_path_factory):
             return bool(c.fuses(batch, heads, max_pages, top_k, page_bytes))
 
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
-        whole, uses_groups = c.whole, c.uses_groups
+        uses_groups = c.uses_groups
+
+        @staticmethod
+        def whole(batch, heads, max_pages, top_k, mean_bytes=512, streams=0, page_bytes=8192):
+            return bool(c.whole(batch, heads, max_pages, top_k, page_bytes, mean_bytes, streams))
 
         @staticmethod
         def dense_cut(pages, heads, max_pages):
@@ -227,4 +231,11 @@ def test_steps_that_select_from_group_maxima_are_selections_that_have_them(lib):
             assert 4096 < pages <= 131072 and 24 * top_k <= pages and top_k <= 1280
     assert fused > 500
     for mean_bytes, most in ((256, 384), (512, 256)):
-        assert lib.whole(most, mean_bytes, 0) and not lib.whole(most + 1, mean_bytes, 0) and not lib.whole(1, mean_bytes, 1)
+        assert lib.whole(1, 8, most, 64, mean_bytes) and not lib.whole(1, 8, most + 1, 64, mean_bytes)
+        assert not lib.whole(1, 8, 8, 8, mean_bytes, streams=1)
+
+
+@pytest.mark.parametrize("batch,top_k,want", [(16, 64, True), (17, 64, False), (24, 64, False), (24, 16, True), (16, 200, True), (17, 200, True),
+                                              (20, 200, False), (80, 8, True)])
+def test_steps_scored_in_every_workgroup_fit_the_chip_at_once_or_are_not_cut(lib, batch, top_k, want):
+    assert lib.whole(batch, 8, 250, top_k) == want
