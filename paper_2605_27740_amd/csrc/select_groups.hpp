@@ -23,8 +23,8 @@ struct Gathered {
   int total;
 };
 
-// 0 < kb < P, kb at most kCap and 8/9 of kMaxGroups; pages from forced_from on are always selected. All threads
-// call it; ends with a barrier.
+// 0 < kb < P, kb at most kCap and 8/9 of kMaxGroups; pages from forced_from on, at most kb, are always selected. All threads call
+// it; ends with a barrier.
 template <int kThreads, int kGroupVecs, int kVecs, int kCap>
 __device__ __forceinline__ Gathered gather_from_groups(const float* srow, const uint32_t* grow, int P, int kb, int forced_from,
                                                        GroupShared<kThreads, kVecs, kCap>& sh) {
@@ -90,9 +90,9 @@ __device__ __forceinline__ Gathered gather_from_groups(const float* srow, const 
   int kept_groups = place_from<kThreads, kGroupVecs, 4>(gkey, T0, counts[0], gplace);
   // Scores that rise or fall along the row give the waves poor bounds (several times kb groups), and many groups may be equal, of
   // which the first are enough: each holds a key that equals the bound. Quotas of more waves leave more, so their number counts.
-  // step of 8192 pages, k = 256, as it is / with the rows that have too many groups read again: rising by two standard
-  // deviations 28.3 / 60.9 us, five values 29.2 / 109; 32768 pages, five values 44 / 378. Groups dealt to the waves in turn, so
-  // that their shares are alike, cost scores without an order 0.5 to 1 us and left the rising ones where they are.
+  // A step of 8192 pages, k = 256, so / with rows that have too many groups read again: rising by two standard deviations
+  // 28.2 / 60.9 us, five values 29.2 / 109; 32768 pages, five values 44 / 378. Groups dealt to the waves in turn, so that their
+  // shares are alike, cost scores without an order 0.5 to 1 us and left the rising ones where they are.
   if (kept_groups > min(kb + kb / 2 + 12 * kWaves, kMaxGroups)) {  // uniform
     T0 = tighten<kThreads, kGroupVecs, 4>(gkey, T0, top, kept_groups, kb, kb + kb / 8, counts[1], sh.turns);
     kept_groups = place_from<kThreads, kGroupVecs, 4>(gkey, T0, counts[0], gplace);

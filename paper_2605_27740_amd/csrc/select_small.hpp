@@ -67,11 +67,11 @@ __device__ __forceinline__ uint32_t bisect(uint32_t lo, uint32_t hi, int n_lo, i
   return lo;
 }
 
-// The same from known counts at lo and hi, where two rounds of three aim between k and `enough` along the line between the counts. That halves
-// the number of rounds (9 to 5 where a third of the keys is to go) and costs as much as counting some keys. Keys are nearly
-// logarithms of the scores, which suits the tail of a distribution; across very many octaves, zero that is, the line is drawn between
-// the scores themselves (8192 pages that score -p / 8192, k = 256: 31.1 us with keys alone, 27.3 so). Where most keys are equal an aim
-// leaves nearly everything, so there are no more than twelve rounds with aims. Leaves count(x) in n_lo.
+// The same from known counts at lo and hi, where two rounds of three aim between k and `enough` along the line between the counts.
+// That halves the number of rounds (9 to 5 where a third of the keys is to go) and costs as much as counting some keys. Keys are
+// nearly logarithms of the scores, which suits the tail of a distribution; across very many octaves, zero that is, the line is drawn
+// between the scores themselves (8192 pages that score -p / 8192, k = 256: 31.1 us with keys alone, 27.3 so). Where most keys are
+// equal an aim leaves nearly everything, so there are no more than twelve rounds with aims. Leaves count(x) in n_lo.
 template <typename Count>
 __device__ __forceinline__ uint32_t bisect_aimed(uint32_t lo, uint32_t hi, int& n_lo, int n_hi, int k, int enough, Count count) {
   constexpr uint32_t kOctaves = 16u << 23;
@@ -136,10 +136,10 @@ struct SpreadCount {
   }
 };
 
-// A bound T0 that `total` > enough >= kb of a workgroup's keys reach is raised until at most `enough` do; fewer than kb are above top. Where so many are equal that
-// none between kb and `enough` does, the first ones of them, in the order (v, thread, i) of key[kPer * v + i], are left that make kb,
-// and the others become 0: of equal keys the first are selected. equal: kVecs * waves ints, 16-byte aligned, turns as above; both
-// unused by others since the last barrier. All threads call it; no thread returns before all have come.
+// A bound T0 that `total` > enough >= kb of a workgroup's keys reach, of which fewer than kb are above `top`, is raised until at most
+// `enough` reach it. Where so many are equal that no bound leaves between kb and `enough`, the first of them, in the order (v, thread,
+// i) of key[kPer * v + i], are left that make kb, and the others become 0: of equal keys the first are selected. equal: kVecs * waves
+// ints, 16-byte aligned, turns as above; both unused by others since the last barrier. All threads call it; it holds barriers.
 template <int kThreads, int kVecs, int kPer>
 __device__ __forceinline__ uint32_t tighten(uint32_t (&key)[kVecs * kPer], uint32_t T0, uint32_t top, int total, int kb, int enough,
                                             int* equal, int* turns) {
