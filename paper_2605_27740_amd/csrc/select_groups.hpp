@@ -92,8 +92,9 @@ __device__ __forceinline__ Gathered gather_from_groups(const float* srow, const 
   // which the first are enough: each holds a key that equals the bound. Quotas of more waves leave more, so their number counts.
   // A step of 8192 pages, k = 256, so / with rows that have too many groups read again: rising by two standard deviations
   // 28.2 / 60.9 us, five values 29.2 / 109; 32768 pages, five values 44 / 378. Groups dealt to the waves in turn, so that their
-  // shares are alike, cost scores without an order 0.5 to 1 us and left the rising ones where they are.
-  if (kept_groups > min(kb + kb / 2 + 12 * kWaves, kMaxGroups)) {  // uniform
+  // shares are alike, cost scores without an order 0.5 to 1 us and left the rising ones where they are. The code for it is kept out
+  // of the way of the others (16 x 8192 pages, nothing in the caches: 53.7 us in line, 52.8 so).
+  if (__builtin_expect(kept_groups > min(kb + kb / 2 + 12 * kWaves, kMaxGroups), 0)) {  // uniform
     T0 = tighten<kThreads, kGroupVecs, 4>(gkey, T0, top, kept_groups, kb, kb + kb / 8, counts[1], sh.turns);
     kept_groups = place_from<kThreads, kGroupVecs, 4>(gkey, T0, counts[0], gplace);
   }
@@ -137,7 +138,7 @@ __device__ __forceinline__ Gathered gather_from_groups(const float* srow, const 
 
   // ---- 4. those from T0 on are gathered, in page order
   int total = place_from<kThreads, kVecs, 4>(key, T0, counts[1], place, loads);
-  if (total > kCap) {  // uniform
+  if (__builtin_expect(total > kCap, 0)) {  // uniform
     T0 = tighten<kThreads, kVecs, 4>(key, T0, top, total, kb, (kb + kCap) / 2, counts[0], sh.turns);
     total = place_from<kThreads, kVecs, 4>(key, T0, counts[1], place, loads);
   }

@@ -334,7 +334,7 @@ __device__ __forceinline__ void select_small(uint32_t (&key)[4 * kVecs], int P, 
   int place[kVecs];
   int total = place_from<kThreads, kVecs, 4>(key, T0, sh.counts[0], place);
   if constexpr (kThreads * kVecs * 4 > kSmallCap) {
-    if (total > kSmallCap) {  // uniform: masses of equal scores, or a k beyond the groups
+    if (__builtin_expect(total > kSmallCap, 0)) {  // uniform: masses of equal scores, or a k beyond the groups
       T0 = tighten<kThreads, kVecs, 4>(key, T0, kKeyForced, total, kb, kSmallCap / 2, sh.counts[1], sh.turns);
       total = place_from<kThreads, kVecs, 4>(key, T0, sh.counts[0], place);
     }
