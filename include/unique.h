@@ -178,8 +178,11 @@ int unique_sparse_paged_decode(const unique_cache_desc* desc, const void* d_q, c
  * selection, Eq. 5 sparse attention. The results are bit-identical to unique_update_page_stats (on the last
  * token of every sequence, when refresh_tail != 0) followed by unique_score_select_topk and
  * unique_sparse_paged_decode with sel_stride = top_k, in fewer kernels: the statistics refresh runs inside the one
- * that scores (same arithmetic), selection and attention are one kernel for budgets of up to 256 pages, and short rows
- * are scored in that one, too.
+ * that scores (same arithmetic); selection and attention are one kernel for most budgets of up to 256 pages (not above
+ * 32768 pages per sequence, nor where the budget is more than a quarter of more than 512 pages or a 24th of more than
+ * 4096, nor for large batches whose lists are cut); and sequences of up to 256 pages (384 with records of 256 bytes per
+ * head) are scored in that one, too, where all its workgroups run at once. How many kernels a step takes depends on the
+ * bounds in the descriptor and on the workspace, never on the data.
  *   refresh_tail : non-zero = recompute the statistics record of the page holding token seq_lens[b]-1 of every
  *                  sequence before scoring (what a serving loop needs after appending one token).
  *   outputs      : d_sel_pages / d_sel_count as unique_score_select_topk, d_out / d_lse_out as
@@ -204,7 +207,11 @@ int unique_decode_step_static(const unique_cache_desc* desc, const void* d_q, in
                               float sm_scale, int32_t refresh_tail, int32_t* d_sel_pages, int32_t* d_sel_count,
                               void* d_out, float* d_lse_out, void* stream);
 
-/* Dense paged decode attention, Eq. 4: the same kernels with every page of each sequence attended. */
+/* Dense paged decode attention, Eq. 4: every page of each sequence attended, with the arithmetic of the sparse call.
+ * Where the batch can read 96 MB or more, the sequences are cut into chunks according to the lengths of all of them, which
+ * the kernels read on the device: the fp32 sums of one sequence are then added in an order that depends on its neighbours'
+ * lengths, and its result may differ in rounding (about 1e-7 of the largest value; a neighbouring bf16 number) between
+ * batches. The same batch gives the same bits every time. */
 int unique_dense_paged_decode(const unique_cache_desc* desc, const void* d_q, float sm_scale, void* d_out,
                               float* d_lse_out, void* d_workspace, size_t workspace_bytes, void* stream);
 
