@@ -13,6 +13,8 @@
 // round trips); two or four records are in flight per wave, requested with unconditional loads so that the
 // loop is straight-line code with exact waits. Scores of a tile are staged in LDS and written as one
 // contiguous run per KV head (4-byte scattered stores cost a tenth of the kernel otherwise).
+#include <type_traits>
+
 #include "score_core.hpp"
 #include "score_tile.hpp"
 
@@ -41,10 +43,63 @@ __device__ __forceinline__ void refresh_tail_record(const CacheView& c, int b, i
   }
 }
 
+// The chunk of this workgroup, pages [first, first + pages) of sequence b or fewer, where the batch is cut by its lengths (score_tile.hpp);
+// N, P: the sequence's length and pages. false: there are no more chunks. most_pages: of a chunk. kSeqs: consecutive sequences that a lane
+// looks after (four for every batch cost 64 or fewer 0.3 us).
+template <int kSeqs>
+__device__ __forceinline__ bool find_chunk(const CacheView& c, int most_pages, int& b, int& first, int& pages, int& N, int& P) {
+  const int lane = threadIdx.x % kWave, w = blockIdx.x;
+  const int page_shift = __ffs(c.S) - 1;  // page sizes are powers of two
+  int len[kSeqs], units[kSeqs], all = 0;
+#pragma unroll
+  for (int i = 0; i < kSeqs; ++i) len[i] = lane * kSeqs + i < c.B ? c.seq_lens[lane * kSeqs + i] : 0;
+#pragma unroll
+  for (int i = 0; i < kSeqs; ++i) {
+    const int n = max(0, min((len[i] + c.S - 1) >> page_shift, c.max_pages_hint));
+    units[i] = (n + kCutUnit - 1) / kCutUnit;
+    all += units[i];
+  }
+  all = __builtin_amdgcn_readlane(wave_inclusive_scan(all), kWave - 1);
+  const int most = most_pages / kCutUnit, slots = kCutSlots * score_cut_rounds(all, c.B, most);
+  int chunk, chunks[kSeqs], mine, upto;
+  auto cut = [&](int waste) {
+    chunk = score_cut_chunk(all, slots, waste, most);
+    const float per_unit = __builtin_amdgcn_rcpf((float)chunk);
+    mine = 0;
+#pragma unroll
+    for (int i = 0; i < kSeqs; ++i) {
+      chunks[i] = score_cut_chunks(units[i], chunk, per_unit);
+      mine += chunks[i];
+    }
+    upto = wave_inclusive_scan(mine);
+  };
+  cut(c.B / 2);
+  if (__builtin_amdgcn_readlane(upto, kWave - 1) > slots) cut(c.B);  // uniform
+  const unsigned long long behind = __ballot(upto > w);
+  if (behind == 0) return false;
+  const int at = __ffsll(behind) - 1;
+  int i = w - __builtin_amdgcn_readlane(upto - mine, at), s = 0, n = __builtin_amdgcn_readlane(len[0], at);
+#pragma unroll
+  for (int j = 1; j < kSeqs; ++j) {
+    const int before = __builtin_amdgcn_readlane(chunks[j - 1], at), next = __builtin_amdgcn_readlane(len[j], at);
+    const bool on = s == j - 1 && i >= before;
+    i -= on ? before : 0;
+    s = on ? j : s;
+    n = on ? next : n;
+  }
+  b = at * kSeqs + s;
+  N = n;
+  P = min((N + c.S - 1) >> page_shift, c.max_pages_hint);
+  pages = chunk * kCutUnit;
+  first = i * pages;
+  return true;
+}
+
 // T: element type of q; TS: element type of the stored means (float, or bf16_t for bf16 statistics). The arguments are in an order
 // without gaps: 8 bytes more cost a small launch 0.2 us (16 x 400 pages 7.5 / 7.3).
 // kNT: the records are read with non-temporal loads (a launch that streams more than the caches hold).
-template <typename T, typename TS, int D, int G, bool kNT>
+// kCut: 0: grid (tile, sequence), tile_pages to each; else the batch is cut by its lengths (find_chunk), tile_pages at most to a chunk.
+template <typename T, typename TS, int D, int G, bool kNT, int kCut>
 __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheView c, const T* __restrict__ q, float lambda, int score_stride,
                                                                         float* __restrict__ scores, float* __restrict__ scores_out,
                                                                         uint32_t* __restrict__ group_max, int refresh_tail,
@@ -56,8 +111,15 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   // 1 us (2048 pages 8.0, two 7.0).
   constexpr int kDepth = sizeof(TS) == 2 && kNT ? 4 : 2;
 
-  const int b = blockIdx.y;
-  const int tile0 = blockIdx.x * tile_pages;  // tile_pages logical pages per workgroup (a power of two, 8..256)
+  int b, tile0, tile_stride, N, P;
+  if constexpr (kCut > 0) {
+    if (!find_chunk<kCut>(c, tile_pages, b, tile0, tile_pages, N, P)) return;
+    tile_stride = tile_pages == kCutUnit ? kCutUnit : 1 << (32 - __clz(tile_pages - 1));
+  } else {
+    b = blockIdx.y;
+    tile0 = blockIdx.x * tile_pages;  // tile_pages logical pages per workgroup (a power of two, 8..256)
+    tile_stride = tile_pages;
+  }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
   const int row8 = lane / kRowLanes, cl = lane % kRowLanes;
   // which head and which page of a step this lane's row is; both fixed for the whole kernel
@@ -82,7 +144,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   // workgroups are such tiles, and each kept a slot for the two round trips below (32 x 128 to 4096 pages 22.2 -> 21.8 us).
   // Without a known bound every tile would look first, which costs an even batch 3 % (16 x 8192 pages of one head 40.6 ->
   // 41.9).
-  if (c.min_pages_hint > 0 && tile0 >= c.min_pages_hint && tile0 >= (c.seq_lens[b] + c.S - 1) / c.S) return;
+  if (kCut == 0 && c.min_pages_hint > 0 && tile0 >= c.min_pages_hint && tile0 >= (c.seq_lens[b] + c.S - 1) / c.S) return;
 
   // The sequence length, the page ids of all of this wave's steps (lane L holds entry L = step *
   // pages_per_step + page_in_step) and the queries are requested together; the page-table row always has
@@ -92,13 +154,15 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   {
     const int st = lane / pages_per_step, po = lane % pages_per_step;
     my_page = tile0 + (wave_slot + st * wave_slots) * pages_per_step + po;
-    if (my_page < min(tile0 + tile_pages, c.max_pages_hint)) my_phys_raw = pt[my_page];
+    if (my_page < min(tile0 + tile_pages, kCut > 0 ? P : c.max_pages_hint)) my_phys_raw = pt[my_page];
   }
-  const int N = c.seq_lens[b];
+  if constexpr (kCut == 0) N = c.seq_lens[b];
   Scorer scorer;
   scorer.request(q + ((int64_t)b * c.H + hkv * G) * D, cl);
-  const int P = min((N + c.S - 1) / c.S, c.max_pages_hint);  // pages beyond the host bound are ignored
-  if (tile0 >= P) return;
+  if constexpr (kCut == 0) {
+    P = min((N + c.S - 1) / c.S, c.max_pages_hint);  // pages beyond the host bound are ignored
+    if (tile0 >= P) return;
+  }
   const int tile_end = min(tile0 + tile_pages, P);
   if (refresh_tail && tile_end == P) {  // this workgroup scores the last page: bring its record up to date first
     refresh_tail_record<T, D>(c, b, N, P);
@@ -108,7 +172,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
 
   const char* stats = reinterpret_cast<const char*>(c.page_stats);
   const int64_t std_off = (int64_t)c.Hkv * D * (int64_t)sizeof(TS);  // byte offset of the stds inside a record
-  extern __shared__ __attribute__((aligned(16))) float tile_scores[];  // [Hkv][tile_pages]
+  extern __shared__ __attribute__((aligned(16))) float tile_scores[];  // [Hkv][tile_stride]
 
   const int n_steps = (tile_end - (tile0 + wave_slot * pages_per_step) + step_pages - 1) / step_pages;  // may be <= 0
   const int my_phys = (my_page < tile_end && my_phys_raw >= 0 && (int64_t)my_phys_raw < c.num_phys) ? my_phys_raw : -1;
@@ -135,7 +199,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
     const float best = scorer.score(mc, sd_cur);
     const int p = tile0 + (wave_slot + st * wave_slots) * pages_per_step + page_in_step;
     // a page whose table entry points outside the pool gets NaN, which ranks below every score
-    if (cl == 0 && p < tile_end) tile_scores[hkv * tile_pages + p - tile0] = phys_cur >= 0 ? best : __uint_as_float(0x7fc00000u);
+    if (cl == 0 && p < tile_end) tile_scores[hkv * tile_stride + p - tile0] = phys_cur >= 0 ? best : __uint_as_float(0x7fc00000u);
   };
 #pragma unroll
   for (int u = 0; u < kDepth; ++u) issue(u, ring[u], ring_sd[u], ring_phys[u]);
@@ -150,9 +214,9 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   __syncthreads();
   // the tile's scores leave as one contiguous run per KV head
   const int tile_len = tile_end - tile0;
-  const int tshift = __ffs(tile_pages) - 1;  // the tile is a power of two
-  for (int idx = threadIdx.x; idx < c.Hkv * tile_pages; idx += kScoreWaves * kWave) {
-    const int h = idx >> tshift, pp = idx & (tile_pages - 1);
+  const int tshift = __ffs(tile_stride) - 1;  // the stride is a power of two
+  for (int idx = threadIdx.x; idx < c.Hkv * tile_stride; idx += kScoreWaves * kWave) {
+    const int h = idx >> tshift, pp = idx & (tile_stride - 1);
     if (pp < tile_len) {
       const float v = tile_scores[idx];
       scores[((int64_t)b * c.Hkv + h) * score_stride + tile0 + pp] = v;
@@ -160,8 +224,8 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
     }
   }
   if (group_max) {  // a thread per group of pages; tiles are multiples of it
-    for (int idx = threadIdx.x; idx < c.Hkv * tile_pages / kGroupPages; idx += kScoreWaves * kWave) {
-      const int first = idx * kGroupPages, h = first >> tshift, pp = first & (tile_pages - 1);
+    for (int idx = threadIdx.x; idx < c.Hkv * tile_stride / kGroupPages; idx += kScoreWaves * kWave) {
+      const int first = idx * kGroupPages, h = first >> tshift, pp = first & (tile_stride - 1);
       if (pp >= tile_len) continue;
       float top = __uint_as_float(0x7fc00000u);  // the maximum ignores NaN
 #pragma unroll
@@ -186,20 +250,25 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
   // A wave keeps the page ids of all its steps in its 64 lanes, which caps the tile at 64 pages per wave
   // slot (4 slots up to 8 KV heads, 2 at 16, 1 when one wave steps through all 32 heads of a page alone).
   const int wave_slots = c.Hkv <= 8 ? kScoreWaves : kScoreWaves * kRowsPerWave / c.Hkv;
-  const int tile = score_tile(c.B, c.Hkv, D, c.max_pages_hint, c.min_pages_hint, 64 * wave_slots);
-  dim3 grid((c.max_pages_hint + tile - 1) / tile, c.B), block(kScoreWaves * kWave);
-  const size_t lds = (size_t)score_lds(c.Hkv * tile * (int)sizeof(float), (int)sizeof(T), D, G, (int64_t)grid.x * grid.y);
+  const bool cut = score_cuts(c.B, c.max_pages_hint, c.min_pages_hint, D * (c.stats_bf16 ? 2 : 4), c.rec_bytes);
+  const int tile = cut ? 64 * wave_slots : score_tile(c.B, c.Hkv, D, c.max_pages_hint, c.min_pages_hint, 64 * wave_slots);
+  const dim3 grid = cut ? dim3(score_cut_grid(c.B, c.max_pages_hint, tile)) : dim3((c.max_pages_hint + tile - 1) / tile, c.B);
+  size_t lds = (size_t)c.Hkv * tile * sizeof(float);
+  if (!cut) lds = (size_t)score_lds((int)lds, (int)sizeof(T), D, G, (int64_t)grid.x * grid.y);
   auto go = [&](auto kernel) {
-    kernel<<<grid, block, lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, stride, scores, out, group_max, refresh_tail, tile);
+    kernel<<<grid, dim3(kScoreWaves * kWave), lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, stride, scores, out, group_max,
+                                                         refresh_tail, tile);
+    return hipGetLastError();
   };
-  if (c.stats_bf16) {
-    if (nt) go(page_score_kernel<T, bf16_t, D, G, true>);
-    else go(page_score_kernel<T, bf16_t, D, G, false>);
-  } else {
-    if (nt) go(page_score_kernel<T, float, D, G, true>);
-    else go(page_score_kernel<T, float, D, G, false>);
-  }
-  return hipGetLastError();
+  auto with = [&](auto mean, auto stream_nt) {
+    using TS = decltype(mean);
+    constexpr bool kNT = decltype(stream_nt)::value;
+    if (cut && c.B <= kWave) return go(page_score_kernel<T, TS, D, G, kNT, 1>);
+    if (cut) return go(page_score_kernel<T, TS, D, G, kNT, kCutMaxBatch / kWave>);
+    return go(page_score_kernel<T, TS, D, G, kNT, 0>);
+  };
+  if (c.stats_bf16) return nt ? with(bf16_t(), std::true_type()) : with(bf16_t(), std::false_type());
+  return nt ? with(float(), std::true_type()) : with(float(), std::false_type());
 }
 
 template <typename T, int D>

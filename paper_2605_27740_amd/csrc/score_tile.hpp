@@ -54,4 +54,60 @@ inline int score_lds(int scores, int elem_bytes, int head_dim, int group, int64_
   return std::max(scores, kLds / (most + 1) + 1024);
 }
 
+// Batches of unlike lengths are cut by the lengths on the device: every workgroup finds for itself how many pages each one takes, so
+// that the chunks of all sequences together fill kCutSlots workgroups, or a multiple where a chunk would be more than a workgroup can
+// hold, and which of them are its own. A chunk is a number of units of 8 pages (whole entries of the group maxima); whole numbers
+// but for one quotient (constexpr functions are compiled for the device, too).
+// Tiles of a fixed size leave a launch with many workgroups that have no pages, in whose slots those that have some wait, and with
+// full tiles that meet on a few units. Two workgroups per compute unit: three or four are no faster but for rows of 128 bytes below
+// 96 MB (16 x 128 to 4096 pages, bf16 means, log-uniform lengths 13.1 / 13.8 / 13.5 us; 8 heads, G = 8 on fp32 means have no room for them).
+constexpr int kCutSlots = 512;
+constexpr int kCutUnit = 8;             // pages
+constexpr int kCutMaxBatch = 256;       // four sequences per lane
+constexpr int kCutMaxPages = 1 << 20;   // of a sequence
+constexpr int kCutMaxUnits = 1 << 22;   // of a launch
+
+// Rounds of kCutSlots workgroups for so many units; a sequence's last chunk is its only one that is not full.
+constexpr int score_cut_rounds(int units, int batch, int most_units) {
+  const int round = (kCutSlots - batch) * most_units;
+  return units > round ? (units + round - 1) / round : 1;
+}
+// Units of a chunk, so that there are no more than `slots` chunks if the sequences' last ones waste no more than `waste` chunks
+// together; with waste = batch that is certain.
+constexpr int score_cut_chunk(int units, int slots, int waste, int most_units) {
+  const int chunks = slots - waste;
+  return units > 0 ? std::min((units + chunks - 1) / chunks, most_units) : 1;
+}
+// Chunks of a sequence; per_unit: 1 / chunk, off by a few units in the last place at most. The quotient is half a unit or more away
+// from the next whole number and off by less for kCutMaxPages.
+constexpr int score_cut_chunks(int units, int chunk, float per_unit) { return (int)(((float)(units + chunk - 1) + 0.5f) * per_unit); }
+// Workgroups that a launch may need, whatever the lengths are.
+inline int score_cut_grid(int batch, int max_pages, int most_pages) {
+  const int64_t units = (int64_t)batch * ((max_pages + kCutUnit - 1) / kCutUnit);
+  return (int)std::min<int64_t>(units, (int64_t)kCutSlots * score_cut_rounds((int)units, batch, most_pages / kCutUnit));
+}
+
+// It costs a round trip for the lengths before that for the page ids and the queries, 0.4 to 0.7 us, 0.2 more above 64 sequences; so
+// launches that can be no larger than what is read in a few of these keep their fixed tiles, and so do batches known to be nearly even,
+// whose tiles are large. kernel us with fixed tiles / so (8 heads, G = 4, D = 128 unless it says otherwise; lengths log-uniform from a
+// 30th, or uniform from a tenth of the longest; nothing in the caches):
+//   fp32 means, 16 x 4096 pages log 23.3 / 20.3, uniform 28.8 / 26.8; 32 x 2048 21.3 / 15.9, 30.0 / 26.0; 64 x 1024 28.9 / 15.0, 32.9 / 26.4;
+//   80 x 1000 36.2 / 19.2; 256 x 1024 102 / 63; 4 x 32768 42.3 / 41.7, 61.3 / 58.9; G = 8 32 x 2048 27.6 / 17.2, 37.0 / 27.5
+//   bf16 means, 16 x 4096 14.5 / 13.0; 64 x 1024 18.2 / 10.5; 12 x 3125 uniform 15.2 / 12.5
+//   one of 16 x 8192 pages, the others a quarter as long: fp32 means 40.5 / 28.5, bf16 means 22.9 / 16.9
+// By the bytes of the longest sequence times the batch, log / uniform: 32 MB 3 sequences 6.2 / 6.4, 6.6 / 6.9, 16 6.2 / 5.9, 7.0 / 7.3; 48 MB 3 x
+// 8.3 / 8.0, 16 x 8.1 / 7.4, 8.6 / 8.1; 64 MB 6 x 32 heads, G = 1, 7.7 / 7.8, 10.4 / 10.9, 16 x 11.0 / 6.7, 13.8 / 9.9; rows of 128 bytes (D = 64,
+// bf16 means) at 64 MB 16 x 7.8 / 7.2, 9.9 / 10.3, 100 x 10.5 / 11.9, at 128 MB 12.9 / 12.2, 17.8 / 17.9 and 11.7 / 10.8, 16.4 / 16.7.
+// Lengths within a factor of two, uniform: from 6.5 tenths of the longest at 100 MB 17.2 / 17.7, at 130 MB 24 x 22.2 / 22.5, at 145 MB 24 x 28.2 /
+// 22.9, at 300 MB 50.5 / 42.9; from 8 tenths at 400 MB 12 x 66.2 / 62.9; from 9 tenths at 180 MB 60 x 0.98 times as fast; 4 sequences of 16 heads, G
+// = 1, D = 64 at 400 MB 0.94 times. With every other sequence just half as long it is even at best (16 x 8192 64.8 / 65.8, bf16 means 35.5 /
+// 36.5), and so it is for two sequences (2 x 16384 uniform 20.4 / 20.5).
+inline bool score_cuts(int batch, int max_pages, int min_pages, int mean_bytes, int64_t rec_bytes) {
+  if (batch < 3 || batch > kCutMaxBatch || max_pages > kCutMaxPages) return false;
+  if ((int64_t)batch * ((max_pages + kCutUnit - 1) / kCutUnit) > kCutMaxUnits) return false;
+  const int64_t most = (int64_t)batch * max_pages * rec_bytes;
+  if (min_pages < (max_pages + 1) / 2) return most >= ((batch < 16 || mean_bytes <= 128 ? 96ll : 48ll) << 20);
+  return batch >= 8 && mean_bytes > 128 && min_pages <= max_pages / 8 * 7 && most >= (144ll << 20);
+}
+
 }  // namespace unique

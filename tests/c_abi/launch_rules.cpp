@@ -1,4 +1,7 @@
 // C interface of the launch rules for the CPU tests.
+#include <cmath>
+#include <cstdlib>
+
 #include "../../paper_2605_27740_amd/csrc/dense_plan.hpp"
 #include "../../paper_2605_27740_amd/csrc/score_tile.hpp"
 #include "../../paper_2605_27740_amd/csrc/split_plan.hpp"
@@ -54,4 +57,27 @@ extern "C" int dense_cut(const int* pages, int batch, int kv_heads, int max_page
   for (int b = 0; b < batch; ++b)
     chunks[b] = even ? unique::dense_even_chunks(pages[b], rows, slots) : unique::dense_row_chunks(pages[b], rate);
   return room ? slots + rows : slots;
+}
+extern "C" int score_cuts(int batch, int max_pages, int min_pages, int mean_bytes, long long rec_bytes) {
+  return unique::score_cuts(batch, max_pages, min_pages, mean_bytes, rec_bytes);
+}
+extern "C" int score_cut_grid(int batch, int max_pages, int most_pages) { return unique::score_cut_grid(batch, max_pages, most_pages); }
+// The cut of a batch's scores as score.hip finds it: chunks of every sequence; returns the pages of a chunk. The reciprocal is `ulps`
+// units in the last place off.
+extern "C" int score_cut(const int* pages, int batch, int most_pages, int ulps, int* chunks) {
+  const int most = most_pages / unique::kCutUnit;
+  int all = 0;
+  for (int b = 0; b < batch; ++b) all += (pages[b] + unique::kCutUnit - 1) / unique::kCutUnit;
+  const int slots = unique::kCutSlots * unique::score_cut_rounds(all, batch, most);
+  int chunk = 0;
+  for (int waste : {batch / 2, batch}) {
+    chunk = unique::score_cut_chunk(all, slots, waste, most);
+    float per_unit = 1.f / (float)chunk;
+    for (int i = 0; i < std::abs(ulps); ++i) per_unit = std::nextafter(per_unit, ulps < 0 ? 0.f : 2.f);
+    int sum = 0;
+    for (int b = 0; b < batch; ++b)
+      sum += chunks[b] = unique::score_cut_chunks((pages[b] + unique::kCutUnit - 1) / unique::kCutUnit, chunk, per_unit);
+    if (sum <= slots) break;
+  }
+  return chunk * unique::kCutUnit;
 }

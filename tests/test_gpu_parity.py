@@ -716,6 +716,66 @@ def test_large_score_tiles_on_a_ragged_batch(gpu_lib, Hkv, G, stats_dtype):
         assert torch.equal(truthful.scores[b, :, :P], sess.scores[b, :, :P]), f"scores of sequence {b} depend on the tile"
 
 
+@pytest.mark.parametrize("B,Hkv,G,D,dtype,stats_dtype,bound,longest", [
+    (3, 8, 4, 128, torch.bfloat16, torch.float32, 8192, 8192),     # 3 x 8192 pages: one round of workgroups
+    (64, 1, 8, 64, torch.bfloat16, torch.bfloat16, 6200, 6200),    # several rounds of chunks of 256 pages; eight pages to a step
+    (65, 32, 1, 64, torch.float32, torch.float32, 300, 300),       # more than a lane per sequence; a wave per head, chunks of up to 64
+    (256, 2, 2, 128, torch.bfloat16, torch.bfloat16, 1700, 90),    # the largest batch; sequences far below the bound
+    (16, 16, 4, 128, torch.float32, torch.bfloat16, 4500, 4500)])  # group maxima
+def test_scores_of_a_batch_cut_by_its_lengths(gpu_lib, B, Hkv, G, D, dtype, stats_dtype, bound, longest):
+    """Batches of unlike lengths, which the score kernel cuts by the lengths on the device: scores and lists are those of fixed
+    tiles (which a lower bound on the lengths asks for, true or not) bit for bit -- lengths of nothing, one page, the edges of
+    the unit of 8 pages, the bound -- invalid page ids score NaN, and nothing else is written."""
+    S = 16
+    rng = np.random.default_rng(B)
+    pages = [longest, 0, 1, 7, 8, 9, 16, 17][:min(B - 1, 8)] + [longest // 2 - 1]
+    more = rng.integers(1, longest, size=B - len(pages)) if B == 64 else np.exp(rng.uniform(0, np.log(longest), size=B - len(pages)))
+    pages += [int(n) for n in more]
+    total, rec = sum(pages), binding.stats_record_bytes(Hkv, D, stats_dtype)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(B)
+    mean = torch.randn((total, Hkv, D), generator=g, device=DEV).to(stats_dtype)
+    std = torch.rand((total, Hkv), generator=g, device=DEV) + 0.5
+    stats = torch.cat([mean.view(torch.uint8).view(total, -1), std.view(torch.uint8).view(total, -1),
+                       torch.full((total, rec - mean[0].numel() * mean.element_size() - 4 * Hkv), 0xFF, dtype=torch.uint8, device=DEV)], 1)
+    table = torch.full((B, bound), -1, dtype=torch.int32)
+    perm, at = torch.from_numpy(rng.permutation(total).astype(np.int32)), 0
+    for b, n in enumerate(pages):
+        table[b, :n] = perm[at:at + n]
+        at += n
+    table[0, longest // 3], table[0, longest - 1] = total, -7  # outside the pool
+    table = table.to(DEV)
+    lens = torch.tensor([max(n * S - int(rng.integers(0, S)), min(n, 1)) for n in pages], dtype=torch.int32, device=DEV)
+    q = torch.randn((B, Hkv * G, D), generator=g, device=DEV).to(dtype)
+    k = torch.zeros((total, Hkv, S, D), dtype=dtype, device=DEV) if total * Hkv * D < 1 << 26 else \
+        torch.zeros((1, Hkv, S, D), dtype=dtype, device=DEV).expand(total, -1, -1, -1)
+    top_k, got = 40, []
+    for least in (0, bound * S):
+        d = binding.make_desc(q_heads=Hkv * G, k_cache=k, v_cache=None, page_stats=stats, page_table=table, seq_lens=lens,
+                              max_seq_len_hint=bound * S, stats_dtype=stats_dtype, min_seq_len_hint=least)
+        d.kv_page_stride = d.kv_head_stride = 0
+        scores = torch.full((B, Hkv, bound), 3.0e38, device=DEV)
+        padded = torch.full((B, Hkv, (bound + 3) // 4 * 4), 3.0e38, device=DEV)
+        sel, cnt = torch.full((B, Hkv, top_k), -7, dtype=torch.int32, device=DEV), torch.full((B, Hkv), -7, dtype=torch.int32, device=DEV)
+        ws = torch.empty((max(gpu_lib.workspace_bytes(d, top_k), 256),), dtype=torch.uint8, device=DEV)
+        gpu_lib.page_scores(d, q, 0.5, padded)
+        gpu_lib.score_select_topk(d, q, top_k, 0.5, sel, cnt, scores, ws)
+        torch.cuda.synchronize()
+        got.append((scores, padded, sel, cnt))
+    for cut, fixed in zip(*got):
+        assert torch.equal(cut.view(torch.int32), fixed.view(torch.int32))
+    scores = got[0][0]
+    assert torch.isnan(scores[0, :, longest // 3]).all() and torch.isnan(scores[0, :, longest - 1]).all()
+    assert int(torch.isnan(scores).sum()) == 2 * Hkv
+    for b, n in enumerate(pages):
+        assert (scores[b, :, n:] == 3.0e38).all() and (scores[b, :, :n] != 3.0e38).all()
+    for b, p in ((0, 0), (B - 1, pages[-1] - 1), (min(4, B - 1), 0)):  # a few values against Eq. 6 in double
+        ph = int(table[b, p])
+        qd = q[b].double().view(Hkv, G, D)
+        want = ((qd * mean[ph].double()[:, None]).sum(-1) + 0.5 * qd.norm(dim=-1) * std[ph].double()[:, None]).amax(1)
+        assert (scores[b, :, p].double() - want).abs().max() <= 2e-5 * (1 + want.abs().max())
+
+
 @pytest.mark.parametrize("list_len", [6, 700])
 def test_empty_and_all_invalid_lists_bf16(gpu_lib, list_len):
     """bf16 caches (matrix-core kernel), a list short enough for one chunk per row (the partial kernel writes the

@@ -43,6 +43,16 @@ def lib(tmp_path_factory):
         def fuses(batch, heads, max_pages, top_k, page_bytes=8192):
             return bool(c.fuses(batch, heads, max_pages, top_k, page_bytes))
 
+        @staticmethod
+        def score_cuts(batch, max_pages, min_pages, mean_bytes, rec_bytes):
+            return bool(c.score_cuts(batch, max_pages, min_pages, mean_bytes, C.c_longlong(rec_bytes)))
+
+        @staticmethod
+        def score_cut(pages, most_pages, ulps=0):
+            chunks = (C.c_int * len(pages))()
+            return c.score_cut((C.c_int * len(pages))(*pages), len(pages), most_pages, ulps, chunks), list(chunks)
+
+        score_cut_grid = c.score_cut_grid
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
         uses_groups = c.uses_groups
 
@@ -128,6 +138,40 @@ def test_score_tiles_are_powers_of_two_within_their_bounds(lib):
     (8, 1, 128, 8192, 128), (1, 8, 128, 2048, 8)])
 def test_score_tiles_of_even_batches(lib, batch, heads, head_dim, pages, want):
     assert lib.tile(batch, heads, head_dim, pages, pages) == want
+
+
+def test_score_chunks_of_a_batch_cut_by_its_lengths_cover_every_page_once_and_fit_the_launch(lib):
+    """Batches of up to 256 sequences, empty ones among them, far below the launch's bound or at it, in one round or in many: a
+    sequence has just the chunks that its pages fill, also if the reciprocal that the device divides with is two units in the last place
+    off, and all have a workgroup."""
+    r = random.Random(4)
+    rounds = set()
+    for _ in range(20000):
+        batch, most = r.choice([3, 64, 65, 256, r.randint(3, 256)]), r.choice([64, 128, 256])
+        bound = r.choice([8, r.randint(1, 500), r.randint(1, 70000), 1 << 20])
+        if not -(-bound // 8) * batch <= 1 << 22:
+            continue
+        top = r.choice([1, min(9, bound), bound, r.randint(1, bound)])
+        pages = [r.choice([0, min(top, 1), top, r.randint(0, top), r.randint(0, top)]) for _ in range(batch)]
+        chunk, chunks = lib.score_cut(pages, most)
+        assert chunk % 8 == 0 and 8 <= chunk <= most, (batch, most, chunk)
+        assert chunks == [-(-n // chunk) for n in pages], (batch, most, chunk)
+        assert sum(chunks) <= lib.score_cut_grid(batch, bound, most), (batch, bound, most)
+        rounds.add(-(-sum(chunks) // 512))
+        for ulps in (-2, 2):
+            assert lib.score_cut(pages, most, ulps) == (chunk, chunks), (batch, most, chunk)
+    assert {1, 2, 3, 40} <= rounds
+
+
+@pytest.mark.parametrize("batch,max_pages,min_pages,mean_bytes,rec_bytes,want", [
+    (16, 4096, 300, 512, 4224, True), (2, 30000, 300, 512, 4224, False), (3, 30000, 300, 512, 4224, True), (256, 4096, 1, 512, 4224, True),
+    (257, 4096, 1, 512, 4224, False), (15, 1500, 0, 512, 4224, False), (16, 1500, 0, 512, 4224, True), (16, 700, 0, 512, 4224, False),
+    (16, 4096, 0, 128, 1152, False), (16, 6000, 0, 128, 1152, True), (3, (1 << 20) + 1, 0, 512, 4224, False),
+    (40, 1 << 20, 0, 512, 4224, False), (16, 1500, 749, 512, 4224, True), (16, 1500, 750, 512, 4224, False),
+    (16, 4096, 2048, 512, 4224, True), (16, 4096, 3584, 512, 4224, True), (16, 4096, 3585, 512, 4224, False), (7, 9000, 5000, 512, 4224, False),
+    (8, 9000, 5000, 512, 4224, True), (16, 20000, 10000, 128, 1152, False), (16, 4096, 4096, 512, 4224, False)])
+def test_batches_whose_scores_are_cut_by_the_lengths(lib, batch, max_pages, min_pages, mean_bytes, rec_bytes, want):
+    assert lib.score_cuts(batch, max_pages, min_pages, mean_bytes, rec_bytes) == want
 
 
 @pytest.mark.parametrize("head_dim,page_size,key_bytes,bf16_means,least_mb", [
