@@ -111,15 +111,14 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   // 1 us (2048 pages 8.0, two 7.0).
   constexpr int kDepth = sizeof(TS) == 2 && kNT ? 4 : 2;
 
-  int b, tile0, tile_stride, N, P;
+  int b, tile0, N, P;
   if constexpr (kCut > 0) {
     if (!find_chunk<kCut>(c, tile_pages, b, tile0, tile_pages, N, P)) return;
-    tile_stride = tile_pages == kCutUnit ? kCutUnit : 1 << (32 - __clz(tile_pages - 1));
   } else {
     b = blockIdx.y;
-    tile0 = blockIdx.x * tile_pages;  // tile_pages logical pages per workgroup (a power of two, 8..256)
-    tile_stride = tile_pages;
+    tile0 = blockIdx.x * tile_pages;  // tile_pages logical pages per workgroup (a multiple of 8, up to 256)
   }
+  const int tshift = 32 - __clz(tile_pages - 1), tile_stride = 1 << tshift;  // score_tile_stride
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
   const int row8 = lane / kRowLanes, cl = lane % kRowLanes;
   // which head and which page of a step this lane's row is; both fixed for the whole kernel
@@ -214,7 +213,6 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   __syncthreads();
   // the tile's scores leave as one contiguous run per KV head
   const int tile_len = tile_end - tile0;
-  const int tshift = __ffs(tile_stride) - 1;  // the stride is a power of two
   for (int idx = threadIdx.x; idx < c.Hkv * tile_stride; idx += kScoreWaves * kWave) {
     const int h = idx >> tshift, pp = idx & (tile_stride - 1);
     if (pp < tile_len) {
@@ -250,10 +248,15 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
   // A wave keeps the page ids of all its steps in its 64 lanes, which caps the tile at 64 pages per wave
   // slot (4 slots up to 8 KV heads, 2 at 16, 1 when one wave steps through all 32 heads of a page alone).
   const int wave_slots = c.Hkv <= 8 ? kScoreWaves : kScoreWaves * kRowsPerWave / c.Hkv;
-  const bool cut = score_cuts(c.B, c.max_pages_hint, c.min_pages_hint, D * (c.stats_bf16 ? 2 : 4), c.rec_bytes);
-  const int tile = cut ? 64 * wave_slots : score_tile(c.B, c.Hkv, D, c.max_pages_hint, c.min_pages_hint, 64 * wave_slots);
+  const int mean_bytes = D * (c.stats_bf16 ? 2 : 4), most = 64 * wave_slots;
+  const bool cut = score_cuts(c.B, c.max_pages_hint, c.min_pages_hint, mean_bytes, c.rec_bytes);
+  int tile = most;
+  if (!cut) {
+    tile = score_tile(c.B, c.Hkv, D, c.max_pages_hint, c.min_pages_hint, most);
+    tile = score_even_tile(tile, c.B, c.max_pages_hint, c.min_pages_hint, mean_bytes, most);
+  }
   const dim3 grid = cut ? dim3(score_cut_grid(c.B, c.max_pages_hint, tile)) : dim3((c.max_pages_hint + tile - 1) / tile, c.B);
-  size_t lds = (size_t)c.Hkv * tile * sizeof(float);
+  size_t lds = (size_t)c.Hkv * score_tile_stride(tile) * sizeof(float);
   if (!cut) lds = (size_t)score_lds((int)lds, (int)sizeof(T), D, G, (int64_t)grid.x * grid.y);
   auto go = [&](auto kernel) {
     kernel<<<grid, dim3(kScoreWaves * kWave), lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, stride, scores, out, group_max,

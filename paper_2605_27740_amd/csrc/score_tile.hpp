@@ -34,6 +34,35 @@ inline int score_tile(int batch, int kv_heads, int head_dim, int max_pages, int 
   return tile;
 }
 
+// The tile of a batch that is known to be even, or nearly, and has no more workgroups than run at the same time: not a power of two but
+// a multiple of 8 pages with which the workgroups are just below a multiple of the units, as the unit with the most pages bounds the
+// launch. What a unit needs in flight is one workgroup of rows of 512 bytes, two of 256, three of 128 (tile of score_tile for 6 x 2500 pages
+// of 16 heads, D = 64, fp32: 32 pages, 474 workgroups, 14.0 us; 64, 240, 16.7). kernel us with that tile / so (8 heads, D = 128, G = 4, fp32
+// means unless it says otherwise): 1 x 9000 pages 11.1 / 9.4, 1 x 20000 19.4 / 17.9, 5 x 2000 11.6 / 10.2, 60 x 300 18.6 / 16.8, 12 x 3125 30.3 /
+// 27.1 (G = 8 34.0 / 28.3), 10 x 8192 58.1 / 55.4, 80 x 1000 57.7 / 54.4; bf16 means 1 x 33000 17.9 / 16.2, 100 x 500 21.6 / 20.9, D = 64 24 x 1700
+// 11.7 / 11.3; one head, G = 8 4 x 5000 6.2 / 5.7. 50 x 1282 52.9 / 44.4; G = 8 33 x 2132 64.7 / 50.1.
+// Where the busiest unit gains less than a twentieth the tile stays.
+inline int score_even_tile(int tile, int batch, int max_pages, int min_pages, int mean_bytes, int max_tile) {
+  constexpr int kNumCUs = 256, kUnit = 8;
+  if (min_pages < max_pages - max_pages / 8) return tile;
+  auto busiest = [&](int t) { return ((int64_t)batch * ((max_pages + t - 1) / t) + kNumCUs - 1) / kNumCUs * t; };
+  int best = tile;
+  // (three where registers leave room for two: 150 x 30, G = 8 8.6 / 10.2)
+  for (int per_unit = mean_bytes >= 512 ? 1 : (mean_bytes >= 256 ? 2 : 3); per_unit <= (mean_bytes >= 256 ? 2 : 3); ++per_unit) {
+    const int tiles = kNumCUs * per_unit / batch;  // of a sequence
+    if (tiles < 1) continue;
+    const int64_t t = ((max_pages + tiles - 1) / tiles + kUnit - 1) / kUnit * kUnit;
+    if (t <= max_tile && busiest((int)t) * 20 < busiest(best) * 19) best = (int)t;
+  }
+  return best;
+}
+// Scores between two heads of a tile in the LDS.
+constexpr int score_tile_stride(int tile) {
+  int stride = 8;
+  while (stride < tile) stride *= 2;
+  return stride;
+}
+
 // Bytes of LDS with which a launch of so many workgroups of the page-score kernel gives each: `scores` of them are used, the rest
 // keeps the number of workgroups on a compute unit down where the registers would allow one more. The units are dealt the
 // workgroups of a launch in turn for as long as all fit, and with sequences whose lengths are regular the full tiles then meet on a

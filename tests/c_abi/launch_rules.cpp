@@ -19,6 +19,10 @@ extern "C" void plan(int batch, int kv_heads, int len, int max_pages, int page_b
 extern "C" int tile(int batch, int kv_heads, int head_dim, int max_pages, int min_pages, int max_tile) {
   return unique::score_tile(batch, kv_heads, head_dim, max_pages, min_pages, max_tile);
 }
+extern "C" int even_tile(int tile, int batch, int max_pages, int min_pages, int mean_bytes, int max_tile) {
+  return unique::score_even_tile(tile, batch, max_pages, min_pages, mean_bytes, max_tile);
+}
+extern "C" int tile_stride(int tile) { return unique::score_tile_stride(tile); }
 extern "C" int bulk(long long record_bytes, int head_dim, int page_size, int key_bytes, int bf16_means) {
   return unique::stats_bulk(record_bytes, head_dim, page_size, key_bytes, bf16_means != 0);
 }

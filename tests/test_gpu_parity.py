@@ -776,6 +776,23 @@ def test_scores_of_a_batch_cut_by_its_lengths(gpu_lib, B, Hkv, G, D, dtype, stat
         assert (scores[b, :, p].double() - want).abs().max() <= 2e-5 * (1 + want.abs().max())
 
 
+@pytest.mark.parametrize("B,P,Hkv,G,stats_dtype,top_k", [(5, 2000, 2, 4, torch.float32, 64), (1, 17000, 2, 4, torch.bfloat16, 200),
+                                                          (12, 700, 16, 1, torch.float32, 20)])
+def test_scores_with_a_tile_that_is_no_power_of_two(gpu_lib, B, P, Hkv, G, stats_dtype, top_k):
+    """Even batches whose tiles are fitted to the compute units: a multiple of 8 pages, rows of group maxima among them. Scores and
+    lists are those without a lower bound on the lengths, which keeps tiles of a power of two, bit for bit."""
+    wl = W.build("even", 50 + B, dtype=torch.bfloat16, B=B, H=G * Hkv, Hkv=Hkv, D=64, S=8, seq_lens=[P * 8 - 3] * B, top_k=top_k,
+                 key_mode="shift", plant_mode="one_percent", permute=True).to(DEV)
+    fitted = DecodeSession(wl, stats_dtype=stats_dtype)
+    Hn.full_check_batch(wl, sess=fitted, dense_heads=[(0, 0)])
+    other = DecodeSession(wl, stats_dtype=stats_dtype, min_seq_len_hint=0)
+    other.update_page_stats()
+    other.score_select_topk()
+    torch.cuda.synchronize()
+    assert torch.equal(fitted.scores[:, :, :P], other.scores[:, :, :P])
+    assert torch.equal(fitted.sel_pages, other.sel_pages) and torch.equal(fitted.sel_count, other.sel_count)
+
+
 @pytest.mark.parametrize("list_len", [6, 700])
 def test_empty_and_all_invalid_lists_bf16(gpu_lib, list_len):
     """bf16 caches (matrix-core kernel), a list short enough for one chunk per row (the partial kernel writes the

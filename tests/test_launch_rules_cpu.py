@@ -52,7 +52,7 @@ def lib(tmp_path_factory):
             chunks = (C.c_int * len(pages))()
             return c.score_cut((C.c_int * len(pages))(*pages), len(pages), most_pages, ulps, chunks), list(chunks)
 
-        score_cut_grid = c.score_cut_grid
+        score_cut_grid, even_tile, tile_stride = c.score_cut_grid, c.even_tile, c.tile_stride
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
         uses_groups = c.uses_groups
 
@@ -138,6 +138,36 @@ def test_score_tiles_are_powers_of_two_within_their_bounds(lib):
     (8, 1, 128, 8192, 128), (1, 8, 128, 2048, 8)])
 def test_score_tiles_of_even_batches(lib, batch, heads, head_dim, pages, want):
     assert lib.tile(batch, heads, head_dim, pages, pages) == want
+
+
+def test_score_tiles_fitted_to_an_even_batch_stay_inside_their_bounds_and_leave_the_busiest_unit_less(lib):
+    r = random.Random(6)
+    fitted = 0
+    for _ in range(20000):
+        batch, heads = r.choice([1, r.randint(1, 40), r.randint(1, 65535)]), 1 << r.randint(0, 5)
+        most = r.choice([r.randint(1, 3000), r.randint(1, 70000), r.randint(1, 1 << 28)])
+        least = r.choice([0, most, r.randint(0, most), most - most // 10])
+        max_tile = 256 if heads <= 8 else 2048 // heads
+        old = lib.tile(batch, heads, 128, most, least, max_tile)
+        t = lib.even_tile(old, batch, most, least, r.choice([128, 256, 512]), max_tile)
+        assert 8 <= t <= max_tile and t % 8 == 0 and lib.tile_stride(t) in (t, 1 << t.bit_length())
+        if t != old:
+            fitted += 1
+            assert least >= most - most // 8
+            assert batch * -(-most // t) <= 768
+            assert -(-batch * -(-most // t) // 256) * t < -(-batch * -(-most // old) // 256) * old
+    assert fitted > 300
+
+
+@pytest.mark.parametrize("batch,heads,pages,mean_bytes,want", [
+    (1, 8, 9000, 512, 40), (5, 8, 2000, 512, 40), (60, 8, 300, 512, 80), (12, 8, 3125, 512, 152), (10, 8, 8192, 512, 168),
+    (80, 8, 1000, 512, 168), (1, 8, 33000, 256, 72), (24, 8, 1700, 128, 56), (6, 16, 2500, 256, 32), (1, 8, 2048, 512, 8),
+    (16, 8, 8192, 512, 256), (4, 8, 16384, 512, 128), (1, 8, 62501, 256, 128), (80, 8, 4096, 256, 256), (24, 8, 5000, 512, 240), (150, 8, 30, 512, 16),
+    (30, 8, 3000, 256, 128)])
+def test_score_tiles_fitted_to_even_batches(lib, batch, heads, pages, mean_bytes, want):
+    most = 256 if heads <= 8 else 2048 // heads
+    tile = lib.tile(batch, heads, 128 if mean_bytes > 128 else 64, pages, pages, most)
+    assert lib.even_tile(tile, batch, pages, pages, mean_bytes, most) == want
 
 
 def test_score_chunks_of_a_batch_cut_by_its_lengths_cover_every_page_once_and_fit_the_launch(lib):
