@@ -65,19 +65,20 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_partial_kernel(
   decode_chunk<D, S, G, kNT>(c, q, chunk, wave, lane, lookup, scale_log2, to, sh);
 }
 
-template <typename T, int D, int G>
-__global__ __launch_bounds__(kWave) void paged_decode_merge_kernel(CacheView c, const int32_t* __restrict__ sel_count,
-                                                                   int sel_stride, bool dense, int pages_per_split,
-                                                                   int num_splits, const float* __restrict__ part_o,
-                                                                   const float* __restrict__ part_ml,
-                                                                   T* __restrict__ out, float* __restrict__ lse_out) {
+template <typename T, int D, int G, int kWaves>
+__global__ __launch_bounds__(kWaves* kWave) void paged_decode_merge_kernel(CacheView c, const int32_t* __restrict__ sel_count,
+                                                                            int sel_stride, bool dense, int pages_per_split,
+                                                                            int num_splits, const float* __restrict__ part_o,
+                                                                            const float* __restrict__ part_ml,
+                                                                            T* __restrict__ out, float* __restrict__ lse_out) {
+  __shared__ MergeShared<kWaves, D> sh;
   const int h = blockIdx.x, b = blockIdx.y;
   const int row = b * c.Hkv + h / G;
-  const int N = c.seq_lens[b];
-  const int P = min((N + c.S - 1) / c.S, c.max_pages_hint);
-  const int cnt = dense ? P : min(sel_count[row], sel_stride);
-  const int ns = min(num_splits, (cnt + pages_per_split - 1) / pages_per_split);
-  merge_chunks<T, D, G>(c, b, h, (int64_t)row * num_splits, ns, part_o, part_ml, out, lse_out);
+  auto chunks = [&] {
+    const int cnt = dense ? min((c.seq_lens[b] + c.S - 1) / c.S, c.max_pages_hint) : min(sel_count[row], sel_stride);
+    return min(num_splits, (cnt + pages_per_split - 1) / pages_per_split);
+  };
+  merge_chunks<T, D, G, kWaves>(c, b, h, (int64_t)row * num_splits, num_splits, chunks, part_o, part_ml, out, lse_out, sh);
 }
 
 template <typename T, int D, int S, int G>
@@ -288,10 +289,13 @@ hipError_t launch_merge(const CacheView& c, const int32_t* d_sel_count, int sel_
     using T = decltype(elem);
     constexpr int D = decltype(dim)::value, G = decltype(group)::value;
     const float* part_ml = d_partials + (size_t)c.B * c.Hkv * plan.num_splits * G * D;
-    paged_decode_merge_kernel<T, D, G><<<dim3(c.H, c.B), dim3(kWave), 0, stream>>>(
-        c, d_sel_count, sel_stride, d_sel_count == nullptr, plan.pages_per_split, plan.num_splits, d_partials, part_ml,
-        reinterpret_cast<T*>(d_out), d_lse_out);
-    return hipGetLastError();
+    auto go = [&](auto kernel, int waves) {
+      kernel<<<dim3(c.H, c.B), dim3(waves * kWave), 0, stream>>>(c, d_sel_count, sel_stride, d_sel_count == nullptr, plan.pages_per_split,
+                                                                 plan.num_splits, d_partials, part_ml, reinterpret_cast<T*>(d_out), d_lse_out);
+      return hipGetLastError();
+    };
+    return merge_alone(plan.num_splits) ? go(paged_decode_merge_kernel<T, D, G, 1>, 1)
+                                        : go(paged_decode_merge_kernel<T, D, G, kMergeWaves>, kMergeWaves);
   };
   auto with_group = [&](auto elem, auto dim) {
     switch (c.H / c.Hkv) {

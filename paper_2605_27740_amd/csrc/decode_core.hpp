@@ -561,49 +561,64 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const bf16_t* _
   DEC_STAMP(4);  // partial results stored
 }
 
-// Log-sum-exp merge of the chunk partials of one (sequence, query head); writes out (and lse).
-// One wave per head. Lane s takes the (m, l) pair of chunk s, so the maximum, the per-chunk scales and the
-// normaliser come from two wave reductions instead of a serial pass; the output rows of the chunks are then
-// accumulated with the scale of chunk s broadcast from lane s, eight independent loads in flight at a time
-// (a thread per element walking the chunks one dependent load after the other took 8 us for 32 chunks).
-template <typename T, int D, int G>
-__device__ __forceinline__ void merge_chunks(const CacheView& c, int b, int h, int64_t base /*the row's first slot*/, int ns,
+// Log-sum-exp merge of the chunk partials of one (sequence, query head) by kWaves waves; writes out (and lse). Lane s takes the (m, l)
+// pair of chunk s, so the maximum, the per-chunk scales and the normaliser come from two wave reductions, in every wave for itself;
+// wave w adds up the output rows of chunks w, w + kWaves, ... with the scale of chunk s broadcast from lane s, and the waves' sums
+// are added through the LDS.
+// What bounds it is the launch, 1.6 us in a chain of kernels, and round trips to what another kernel has just written. So the first
+// 64 pairs and the first eight rows of every wave are requested at once, before anything is known of the row: `have` chunks are there to be
+// read; the first ns_of() of them, whose loads are then on their way as well, hold results.
+// A step us with a chain of the count, the pairs and eight rows of one wave after the other / so: 32K tokens, 32 chunks 19.7 / 18.2, a million
+// tokens, 64 chunks 56.1 / 54.7, 96 rows of 5 chunks 61.9 / 61.2, 128 of 4 142.3 / 141.7.
+template <int kWaves, int D>
+struct MergeShared {
+  float o[kWaves][D];
+};
+template <typename T, int D, int G, int kWaves, typename Chunks>
+__device__ __forceinline__ void merge_chunks(const CacheView& c, int b, int h, int64_t base /*the row's first slot*/, int have, Chunks ns_of,
                                              const float* __restrict__ part_o, const float* __restrict__ part_ml,
-                                             T* __restrict__ out, float* __restrict__ lse_out) {
+                                             T* __restrict__ out, float* __restrict__ lse_out, MergeShared<kWaves, D>& sh) {
   constexpr int kPer = D / kWave;  // output elements per lane (1 or 2)
+  constexpr int kBatch = 8;        // rows in flight per wave
   static_assert(kPer == 1 || kPer == 2, "head_dim 64 or 128");
-  const int lane = threadIdx.x, g = h % G;
-  const float2* ml = reinterpret_cast<const float2*>(part_ml);  // (m, l) per (row, chunk, head)
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), g = h % G;
+  const float2* ml = reinterpret_cast<const float2*>(part_ml) + base * G + g;  // (m, l) per (row, chunk, head)
+  const float* po = part_o + (base * G + g) * D + lane * kPer;
 
-  float M = kNegBig;
-  for (int s0 = 0; s0 < ns; s0 += kWave)
-    if (s0 + lane < ns) M = fmaxf(M, ml[(base + s0 + lane) * G + g].x);
+  auto pair = [&](int s0) { return ml[(int64_t)min(s0 + lane, have - 1) * G]; };
+  float2 v[kBatch];
+  auto request = [&](int j0) {  // rows j0 + u * kWaves + wave; past the last chunk that chunk, whose scale is then zero
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const float* src = po + (int64_t)min(j0 + u * kWaves + wave, have - 1) * (G * D);
+      if constexpr (kPer == 2) v[u] = *reinterpret_cast<const float2*>(src);
+      else v[u] = make_float2(src[0], 0.f);
+    }
+  };
+  const float2 first = have > 0 ? pair(0) : make_float2(kNegBig, 0.f);
+  if (have > 0) request(0);
+  const int ns = ns_of();
+
+  float M = lane < ns ? first.x : kNegBig;
+  for (int s0 = kWave; s0 < ns; s0 += kWave)
+    if (s0 + lane < ns) M = fmaxf(M, pair(s0).x);
   M = group_allreduce<kWave>(M, OpMax());
 
   float L = 0.f, o[kPer];
 #pragma unroll
   for (int i = 0; i < kPer; ++i) o[i] = 0.f;
   for (int s0 = 0; s0 < ns; s0 += kWave) {
-    float sc = 0.f;
-    if (s0 + lane < ns) {
-      const float2 v = ml[(base + s0 + lane) * G + g];
-      sc = fast_exp2(v.x - M);
-      L = fmaf(v.y, sc, L);
-    }
+    const float2 p = s0 == 0 ? first : pair(s0);
+    const float sc = s0 + lane < ns ? fast_exp2(p.x - M) : 0.f;
+    L = s0 + lane < ns ? fmaf(p.y, sc, L) : L;
     const int n = min(kWave, ns - s0);
-    const float* po = part_o + ((base + s0) * G + g) * D + lane * kPer;
-    // blocks of eight chunks; a slot past the last chunk re-reads that chunk with the zero scale of its lane
-    for (int j0 = 0; j0 < n; j0 += 8) {
-      float2 v[8];
+    for (int j0 = 0; j0 < n; j0 += kBatch * kWaves) {
+      if (s0 + j0 > 0) request(s0 + j0);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float* src = po + (int64_t)min(j0 + u, n - 1) * G * D;
-        if constexpr (kPer == 2) v[u] = *reinterpret_cast<const float2*>(src);
-        else v[u] = make_float2(src[0], 0.f);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float scj = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sc), j0 + u));
+      for (int u = 0; u < kBatch; ++u) {
+        const int j = j0 + u * kWaves + wave;
+        if (j >= n) break;  // uniform; a chunk without results may hold anything
+        const float scj = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sc), j));
         o[0] = fmaf(v[u].x, scj, o[0]);
         if constexpr (kPer == 2) o[1] = fmaf(v[u].y, scj, o[1]);
       }
@@ -612,10 +627,23 @@ __device__ __forceinline__ void merge_chunks(const CacheView& c, int b, int h, i
   L = group_allreduce<kWave>(L, OpSum());
   const bool any = L > 0.f;
   T* dst = out + ((int64_t)b * c.H + h) * D + lane * kPer;
+  if constexpr (kWaves > 1) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) sh.o[wave][lane * kPer + i] = o[i];
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w)
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) o[i] += sh.o[w][lane * kPer + i];
+  }
 #pragma unroll
   for (int i = 0; i < kPer; ++i) store_elem(dst + i, any ? o[i] / L : 0.f);
   if (lse_out && lane == 0) lse_out[(int64_t)b * c.H + h] = any ? (M + log2f(L)) * kLn2 : -INFINITY;
 }
+
+constexpr int kMergeWaves = 4;  // (eight: 18.3 and 55.0 us)
+constexpr bool merge_alone(int chunks) { return chunks <= 8; }  // one wave
 
 }  // namespace
 }  // namespace unique

@@ -1026,6 +1026,42 @@ def test_decode_moving_softmax_reference(gpu_lib, dtype, G, D, S, kind):
                 assert ((lse[b, h * G:(h + 1) * G] - want_lse).abs() <= err + 2e-6 + 2.0 ** -23 * want_lse.abs()).all(), (width, b, h)
 
 
+@pytest.mark.parametrize("dtype,Hkv,G,D,S", [(torch.float32, 2, 4, 128, 8), (torch.bfloat16, 2, 1, 128, 16), (torch.bfloat16, 2, 8, 64, 32),
+                                             (torch.float32, 2, 2, 64, 16)])
+def test_merged_chunks(gpu_lib, dtype, Hkv, G, D, S):
+    """Chunks of four pages, merged by one wave (up to 8 chunks) or four, around 8, 32 and 64 chunks and beyond, in rows whose lists end
+    in the first chunk, at the edges of the waves' batches, or are empty; what lies in the workspace of chunks that are not is NaN."""
+    P, B = 300, 2
+    wl = W.build("merge", 15, dtype=dtype, B=B, H=G * Hkv, Hkv=Hkv, D=D, S=S, seq_lens=[P * S, P * S - 1], top_k=264, key_mode="iid", permute=True)
+    sess = DecodeSession(wl.to(DEV))
+    for width in (28, 32, 36, 128, 132, 256, 264):
+        for counts in ((0, 1, 4, 5), (width, 32, width - 1, 33), (31, 34, width - 4, width - 5), (min(width, 128), min(width, 129), 2, width)):
+            counts = [min(n, width) for n in counts]
+            lists = torch.arange(width, dtype=torch.int32).expand(B, Hkv, width).contiguous()
+            sess.workspace.fill_(0xFF)
+            sess.out.fill_(7.0)
+            sess.sparse_paged_decode(sel_pages=lists.to(DEV), sel_count=torch.tensor(counts, dtype=torch.int32, device=DEV).view(B, Hkv))
+            out, lse = sess.out.cpu().double(), sess.lse.cpu().double()
+            for i, n in enumerate(counts):
+                b, h = i // Hkv, i % Hkv
+                if n == 0:
+                    assert (out[b, h * G:(h + 1) * G] == 0).all() and (lse[b, h * G:(h + 1) * G] == -math.inf).all()
+                    continue
+                tok = torch.arange(min(n * S, int(wl.seq_lens[b])))
+                phys = wl.page_table[b, tok // S].long()
+                k, v = (c[phys, h, tok % S].double() for c in (wl.k_cache, wl.v_cache))
+                q = wl.q[b, h * G:(h + 1) * G].double()
+                logits = q @ k.T / D ** 0.5
+                want_lse = torch.logsumexp(logits, -1)
+                want = torch.exp(logits - want_lse[:, None]) @ v
+                # fp32 logits of D products, then a rounding to the cache's type
+                err = 12 * 2.0 ** -24 * (q.abs() @ k.abs().T).max() / D ** 0.5
+                rel = 2 ** -8 if dtype == torch.bfloat16 else 0.0
+                bad = (out[b, h * G:(h + 1) * G] - want).abs() - rel * want.abs() - (2 * err + 2e-6) * v.abs().max()
+                assert (bad <= 0).all(), (width, counts, i, float(bad.max()))
+                assert ((lse[b, h * G:(h + 1) * G] - want_lse).abs() <= err + 2e-6 + 2.0 ** -23 * want_lse.abs()).all(), (width, counts, i)
+
+
 @pytest.mark.parametrize("B,k", [(1, 16), (1, 200), (6, 64), (12, 200), (20, 32), (24, 150), (33, 300), (2, 1024)])
 def test_decode_split_plans(gpu_lib, B, k):
     """Full lists: uncut, cut in two unequal or equal chunks, 16 and 25 chunks: the attention over all pages of a list equals
