@@ -79,6 +79,7 @@ constexpr int kDppXor1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;        // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141; // lane i <-> 7-i inside each 8
 constexpr int kDppMirror = 0x140;     // lane i <-> 15-i inside each 16
+constexpr int kDppRor8 = 0x128;       // lane i <-> i^8 inside each 16
 
 // Minimum / maximum of an unsigned value over the 64 lanes of a wave (every lane gets the result): four DPP
 // exchanges inside the rows of 16 lanes, then two swaps between rows (a shuffle through the LDS takes 100 cycles more).
@@ -119,6 +120,18 @@ __device__ __forceinline__ uint32_t score_key(float f) {
 struct OpSum { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
 struct OpMax { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 
+// A value combined with that of the lane 16 or 32 away, by a swap of rows of 16 lanes between two copies of it; op commutes.
+template <typename Op>
+__device__ __forceinline__ float with_lane_xor16(float x, Op op) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <typename Op>
+__device__ __forceinline__ float with_lane_xor32(float x, Op op) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // All-reduce over aligned groups of kWidth consecutive lanes (kWidth in 1,2,4,8,16,32,64): every lane
 // of a group ends with the group's result.
 template <int kWidth, typename Op>
@@ -129,8 +142,8 @@ __device__ __forceinline__ float group_allreduce(float x, Op op) {
   if constexpr (kWidth >= 4) x = op(x, dpp_mov<kDppXor2>(x));
   if constexpr (kWidth >= 8) x = op(x, dpp_mov<kDppHalfMirror>(x));
   if constexpr (kWidth >= 16) x = op(x, dpp_mov<kDppMirror>(x));
-  if constexpr (kWidth >= 32) x = op(x, __shfl_xor(x, 16, kWave));
-  if constexpr (kWidth >= 64) x = op(x, __shfl_xor(x, 32, kWave));
+  if constexpr (kWidth >= 32) x = with_lane_xor16(x, op);
+  if constexpr (kWidth >= 64) x = with_lane_xor32(x, op);
   return x;
 }
 
@@ -138,9 +151,9 @@ __device__ __forceinline__ float group_allreduce(float x, Op op) {
 // lane % kStride. kStride in {8, 16, 32, 64}.
 template <int kStride, typename Op>
 __device__ __forceinline__ float cross_group_allreduce(float x, Op op) {
-  if constexpr (kStride <= 8) x = op(x, __shfl_xor(x, 8, kWave));
-  if constexpr (kStride <= 16) x = op(x, __shfl_xor(x, 16, kWave));
-  if constexpr (kStride <= 32) x = op(x, __shfl_xor(x, 32, kWave));
+  if constexpr (kStride <= 8) x = op(x, dpp_mov<kDppRor8>(x));
+  if constexpr (kStride <= 16) x = with_lane_xor16(x, op);
+  if constexpr (kStride <= 32) x = with_lane_xor32(x, op);
   return x;
 }
 
