@@ -43,19 +43,67 @@ __device__ __forceinline__ void refresh_tail_record(const CacheView& c, int b, i
   }
 }
 
+// The last (possibly partial) page of sequence b for KV head h, by one wave: its statistics are recomputed from its keys and stored, and it is
+// scored with them, from `mean`, D elements of LDS. The page size is a run-time value here.
+template <typename T, typename TS, int D, int G, int kMaxTokens>
+__device__ __forceinline__ void refresh_and_score(const CacheView& c, RowScorer<T, TS, D, G>& scorer, float lambda, int phys, int n, int h,
+                                                  TS* mean, float* score) {
+  using Scorer = RowScorer<T, TS, D, G>;
+  const int lane = threadIdx.x % kWave;
+  PageRefresh<T, D, kMaxTokens> page;
+  page.request(reinterpret_cast<const T*>(c.k_cache) + (int64_t)phys * c.kv_page_stride + (int64_t)h * c.kv_head_stride, n, lane);
+  page.reduce(n, lane);
+  page.store_mean(mean, sizeof(TS) == 2, lane);
+  char* rec = reinterpret_cast<char*>(c.page_stats) + (int64_t)phys * c.rec_bytes;
+  page.store_mean(rec + (int64_t)h * D * (int)sizeof(TS), sizeof(TS) == 2, lane);
+  if (lane == 0) reinterpret_cast<float*>(rec + (int64_t)c.Hkv * D * (int)sizeof(TS))[h] = page.std;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_sched_barrier(0);  // (unpacked earlier the queries would take the registers of two more waves)
+  scorer.unpack(lambda);
+  Raw16 md[Scorer::kChunks];
+#pragma unroll
+  for (int j = 0; j < Scorer::kChunks; ++j) md[j] = load_raw(mean + lane % kRowLanes * Scorer::kE + j * (Scorer::kE * kRowLanes));
+  const float s = scorer.score(md, page.std);
+  if (lane == 0) *score = s;
+}
+template <typename T, typename TS, int D, int G>
+__device__ __forceinline__ void score_last_page(const CacheView& c, const T* q, float lambda, int b, int h, TS* mean, int score_stride,
+                                                float* scores) {
+  const int lane = threadIdx.x % kWave;
+  const int32_t* pt = c.page_table + (int64_t)b * c.max_pages;
+  // the last of the page ids that there may be are requested with the length, and most often the last page's is one of them
+  const int late = pt[max(c.max_pages_hint - 1 - lane, 0)];
+  const int N = c.seq_lens[b];
+  RowScorer<T, TS, D, G> scorer;
+  scorer.request(q + ((int64_t)b * c.H + h * G) * D, lane % kRowLanes);
+  const int P = min((N + c.S - 1) / c.S, c.max_pages_hint);
+  if (P < 1) return;
+  const int phys = __builtin_amdgcn_readfirstlane(c.max_pages_hint - P < kWave ? __builtin_amdgcn_readlane(late, c.max_pages_hint - P) : pt[P - 1]);
+  float* score = scores + ((int64_t)b * c.Hkv + h) * score_stride + P - 1;
+  if (phys < 0 || (int64_t)phys >= c.num_phys) {
+    if (lane == 0) *score = __uint_as_float(0x7fc00000u);  // as below
+    return;
+  }
+  const int n = min(c.S, N - (P - 1) * c.S);
+  if (c.S == 8) refresh_and_score<T, TS, D, G, 8>(c, scorer, lambda, phys, n, h, mean, score);
+  else if (c.S == 16) refresh_and_score<T, TS, D, G, 16>(c, scorer, lambda, phys, n, h, mean, score);
+  else refresh_and_score<T, TS, D, G, 32>(c, scorer, lambda, phys, n, h, mean, score);
+}
+
 // The chunk of this workgroup, pages [first, first + pages) of sequence b or fewer, where the batch is cut by its lengths (score_tile.hpp);
-// N, P: the sequence's length and pages. false: there are no more chunks. most_pages: of a chunk. kSeqs: consecutive sequences that a lane
+// N: the sequence's length, P: its pages without the last `less`. w: the workgroup. false: there are no more chunks. most_pages: of a chunk. kSeqs: consecutive sequences that a lane
 // looks after (four for every batch cost 64 or fewer 0.3 us).
 template <int kSeqs>
-__device__ __forceinline__ bool find_chunk(const CacheView& c, int most_pages, int& b, int& first, int& pages, int& N, int& P) {
-  const int lane = threadIdx.x % kWave, w = blockIdx.x;
+__device__ __forceinline__ bool find_chunk(const CacheView& c, int w, int most_pages, int less, int& b, int& first, int& pages, int& N, int& P) {
+  const int lane = threadIdx.x % kWave;
   const int page_shift = __ffs(c.S) - 1;  // page sizes are powers of two
   int len[kSeqs], units[kSeqs], all = 0;
 #pragma unroll
   for (int i = 0; i < kSeqs; ++i) len[i] = lane * kSeqs + i < c.B ? c.seq_lens[lane * kSeqs + i] : 0;
 #pragma unroll
   for (int i = 0; i < kSeqs; ++i) {
-    const int n = max(0, min((len[i] + c.S - 1) >> page_shift, c.max_pages_hint));
+    const int n = max(0, min((len[i] + c.S - 1) >> page_shift, c.max_pages_hint) - less);
     units[i] = (n + kCutUnit - 1) / kCutUnit;
     all += units[i];
   }
@@ -89,7 +137,7 @@ __device__ __forceinline__ bool find_chunk(const CacheView& c, int most_pages, i
   }
   b = at * kSeqs + s;
   N = n;
-  P = min((N + c.S - 1) >> page_shift, c.max_pages_hint);
+  P = min((N + c.S - 1) >> page_shift, c.max_pages_hint) - less;
   pages = chunk * kCutUnit;
   first = i * pages;
   return true;
@@ -98,11 +146,14 @@ __device__ __forceinline__ bool find_chunk(const CacheView& c, int most_pages, i
 // T: element type of q; TS: element type of the stored means (float, or bf16_t for bf16 statistics). The arguments are in an order
 // without gaps: 8 bytes more cost a small launch 0.2 us (16 x 400 pages 7.5 / 7.3).
 // kNT: the records are read with non-temporal loads (a launch that streams more than the caches hold).
+// refresh: who renews the last page of every sequence before it is scored, a LastPage, and above its bits where these workgroups are (the grid's
+// extent would have to be fetched).
+// kOwn: last pages have workgroups of their own. (Where they have not, their code in the kernel would cost 0.3 to 0.8 us.)
 // kCut: 0: grid (tile, sequence), tile_pages to each; else the batch is cut by its lengths (find_chunk), tile_pages at most to a chunk.
-template <typename T, typename TS, int D, int G, bool kNT, int kCut>
+template <typename T, typename TS, int D, int G, bool kNT, int kCut, bool kOwn>
 __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheView c, const T* __restrict__ q, float lambda, int score_stride,
                                                                         float* __restrict__ scores, float* __restrict__ scores_out,
-                                                                        uint32_t* __restrict__ group_max, int refresh_tail,
+                                                                        uint32_t* __restrict__ group_max, int refresh,
                                                                         int tile_pages) {
   using Scorer = RowScorer<T, TS, D, G>;
   constexpr int kE = Scorer::kE, kChunks = Scorer::kChunks;
@@ -111,15 +162,29 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   // 1 us (2048 pages 8.0, two 7.0).
   constexpr int kDepth = sizeof(TS) == 2 && kNT ? 4 : 2;
 
+  extern __shared__ __attribute__((aligned(16))) float tile_scores[];  // [Hkv][tile_stride]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
+  constexpr int less = kOwn;  // pages that this workgroup's sequence has elsewhere
+  int row = blockIdx.y;       // of the grid; those beyond the sequences are for last pages
+  if constexpr (kOwn) {
+    const int groups = last_page_groups(c.Hkv), extra = refresh >> kLastPageBits;  // rows of them, or the workgroup that is the first
+    if (kCut == 0 && (refresh & kLastPageFirst)) row = row < extra ? c.B + row : row - extra;
+    const int at = kCut > 0 ? (int)blockIdx.x - extra : (row < c.B ? -1 : (int)blockIdx.x * extra + row - c.B);
+    if (at >= 0) {
+      const int which = at / groups, h = at % groups * kScoreWaves + wave;
+      if (which < c.B && h < c.Hkv)
+        score_last_page<T, TS, D, G>(c, q, lambda, which, h, reinterpret_cast<TS*>(tile_scores) + wave * D, score_stride, scores);
+      return;
+    }
+  }
   int b, tile0, N, P;
   if constexpr (kCut > 0) {
-    if (!find_chunk<kCut>(c, tile_pages, b, tile0, tile_pages, N, P)) return;
+    if (!find_chunk<kCut>(c, blockIdx.x, tile_pages, less, b, tile0, tile_pages, N, P)) return;
   } else {
-    b = blockIdx.y;
+    b = row;
     tile0 = blockIdx.x * tile_pages;  // tile_pages logical pages per workgroup (a multiple of 8, up to 256)
   }
   const int tshift = 32 - __clz(tile_pages - 1), tile_stride = 1 << tshift;  // score_tile_stride
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;  // wave: scalar
   const int row8 = lane / kRowLanes, cl = lane % kRowLanes;
   // which head and which page of a step this lane's row is; both fixed for the whole kernel
   int hkv, page_in_step, pages_per_step, wave_slot, wave_slots;
@@ -143,7 +208,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   // workgroups are such tiles, and each kept a slot for the two round trips below (32 x 128 to 4096 pages 22.2 -> 21.8 us).
   // Without a known bound every tile would look first, which costs an even batch 3 % (16 x 8192 pages of one head 40.6 ->
   // 41.9).
-  if (kCut == 0 && c.min_pages_hint > 0 && tile0 >= c.min_pages_hint && tile0 >= (c.seq_lens[b] + c.S - 1) / c.S) return;
+  if (kCut == 0 && c.min_pages_hint > 0 && tile0 >= c.min_pages_hint && tile0 >= (c.seq_lens[b] + c.S - 1) / c.S - less) return;
 
   // The sequence length, the page ids of all of this wave's steps (lane L holds entry L = step *
   // pages_per_step + page_in_step) and the queries are requested together; the page-table row always has
@@ -159,11 +224,11 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   Scorer scorer;
   scorer.request(q + ((int64_t)b * c.H + hkv * G) * D, cl);
   if constexpr (kCut == 0) {
-    P = min((N + c.S - 1) / c.S, c.max_pages_hint);  // pages beyond the host bound are ignored
+    P = min((N + c.S - 1) / c.S, c.max_pages_hint) - less;  // pages beyond the host bound are ignored
     if (tile0 >= P) return;
   }
   const int tile_end = min(tile0 + tile_pages, P);
-  if (refresh_tail && tile_end == P) {  // this workgroup scores the last page: bring its record up to date first
+  if (!kOwn && refresh && tile_end == P) {  // this workgroup scores the last page: bring its record up to date first
     refresh_tail_record<T, D>(c, b, N, P);
     __threadfence_block();
     __syncthreads();
@@ -171,7 +236,6 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
 
   const char* stats = reinterpret_cast<const char*>(c.page_stats);
   const int64_t std_off = (int64_t)c.Hkv * D * (int64_t)sizeof(TS);  // byte offset of the stds inside a record
-  extern __shared__ __attribute__((aligned(16))) float tile_scores[];  // [Hkv][tile_stride]
 
   const int n_steps = (tile_end - (tile0 + wave_slot * pages_per_step) + step_pages - 1) / step_pages;  // may be <= 0
   const int my_phys = (my_page < tile_end && my_phys_raw >= 0 && (int64_t)my_phys_raw < c.num_phys) ? my_phys_raw : -1;
@@ -255,20 +319,34 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
     tile = score_tile(c.B, c.Hkv, D, c.max_pages_hint, c.min_pages_hint, most);
     tile = score_even_tile(tile, c.B, c.max_pages_hint, c.min_pages_hint, mean_bytes, most);
   }
-  const dim3 grid = cut ? dim3(score_cut_grid(c.B, c.max_pages_hint, tile)) : dim3((c.max_pages_hint + tile - 1) / tile, c.B);
+  const int tiles = cut ? score_cut_grid(c.B, c.max_pages_hint, tile) : (c.max_pages_hint + tile - 1) / tile;
+  const int64_t workgroups = (int64_t)tiles * (cut ? 1 : c.B);
+  const int last_pages = last_page_groups(c.Hkv) * c.B;
+  int refresh = refresh_tail ? score_last_page_rule(cut, workgroups, last_pages, (int64_t)c.B * c.max_pages_hint * c.rec_bytes, G) : kLastPageNone;
+  dim3 grid(tiles, cut ? 1 : c.B);
   size_t lds = (size_t)c.Hkv * score_tile_stride(tile) * sizeof(float);
-  if (!cut) lds = (size_t)score_lds((int)lds, (int)sizeof(T), D, G, (int64_t)grid.x * grid.y);
+  if (refresh & kLastPageOwn) {
+    const int rows = (last_pages + tiles - 1) / tiles;
+    refresh |= (cut ? tiles : rows) << kLastPageBits;
+    if (cut) grid.x += last_pages;
+    else grid.y += rows;
+    lds = std::max<size_t>(lds, kScoreWaves * mean_bytes);
+  }
+  if (!cut) lds = (size_t)score_lds((int)lds, (int)sizeof(T), D, G, workgroups);
   auto go = [&](auto kernel) {
     kernel<<<grid, dim3(kScoreWaves * kWave), lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, stride, scores, out, group_max,
-                                                         refresh_tail, tile);
+                                                         refresh, tile);
     return hipGetLastError();
   };
   auto with = [&](auto mean, auto stream_nt) {
     using TS = decltype(mean);
     constexpr bool kNT = decltype(stream_nt)::value;
-    if (cut && c.B <= kWave) return go(page_score_kernel<T, TS, D, G, kNT, 1>);
-    if (cut) return go(page_score_kernel<T, TS, D, G, kNT, kCutMaxBatch / kWave>);
-    return go(page_score_kernel<T, TS, D, G, kNT, 0>);
+    auto of = [&](auto seqs) {
+      constexpr int kCut = decltype(seqs)::value;
+      return refresh & kLastPageOwn ? go(page_score_kernel<T, TS, D, G, kNT, kCut, true>) : go(page_score_kernel<T, TS, D, G, kNT, kCut, false>);
+    };
+    if (!cut) return of(std::integral_constant<int, 0>());
+    return c.B <= kWave ? of(std::integral_constant<int, 1>()) : of(std::integral_constant<int, kCutMaxBatch / kWave>());
   };
   if (c.stats_bf16) return nt ? with(bf16_t(), std::true_type()) : with(bf16_t(), std::false_type());
   return nt ? with(float(), std::true_type()) : with(float(), std::false_type());

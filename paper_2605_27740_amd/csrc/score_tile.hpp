@@ -139,4 +139,26 @@ inline bool score_cuts(int batch, int max_pages, int min_pages, int mean_bytes, 
   return batch >= 8 && mean_bytes > 128 && min_pages <= max_pages / 8 * 7 && most >= (144ll << 20);
 }
 
+// A decode step renews the statistics of the page that has received a token before that page is scored: in the workgroup whose tile it is in,
+// which takes two more round trips and some hundred instructions, or in workgroups of its own, a KV head to a wave, which come first or last
+// in the grid.
+enum LastPage { kLastPageNone, kLastPageInTile = 1, kLastPageOwn = 2, kLastPageFirst = 4, kLastPageBits = 3 };
+constexpr int last_page_groups(int kv_heads) { return (kv_heads + 3) / 4; }
+
+// Workgroups of their own cost the units that they land on what they read, and on these units a launch that gives every unit the same ends
+// later; a small launch, which is a chain of latencies, gains by them, and so do large ones, in which a late start of some tiles shows.
+// Below two workgroups per unit they are best first; in larger launches they then leave some units one more than others (16 x 8192 pages 141.3
+// in the tile, 157.3 first, 140.4 last).
+// A step us in the tile / so (8 heads, G = 4, D = 128): fp32 means, 1 x 1000 pages 16.2 / 14.5, 1 x 2048 18.2 / 16.6, 2 x 3000 20.8 / 19.3, 16 x 400
+// 20.3 / 18.1, bf16 means, pages of 8, 4 x 4096 23.6 / 20.9, 32 x 600 21.6 / 19.7; but fp32 means 16 x 1000 (67 MB) 31.3 / 32.5, 24 x 1000 44.9 / 45.6,
+// bf16 means 24 x 1000 (52 MB) 23.8 / 25.8; large: 4 x 16384 65.3 / 64.8, 80 x 4096, pages of 8 157.2 / 155.7, 48 x 2048 bf16 means 121.4 / 119.5, 160 x 700 fp32
+// means (320 of them) 183.3 / 184.3. Cut by the lengths: 32 x 4K-131K tokens 64.8 / 64.4, 16 x 1000 29.2 / 28.3, bf16 means 20.3 / 18.3. With 8 query
+// heads two workgroups fill a unit and the last ones wait for a place: 3 x 20000 pages of 32, cut, 60.5 / 63.1, but 24 x 1000 61.5 / 58.7.
+inline int score_last_page_rule(bool cut, int64_t workgroups, int last_pages, int64_t bytes, int group) {
+  constexpr int kNumCUs = 256;
+  if (cut) return group == 8 && bytes > (128ll << 20) ? kLastPageInTile : kLastPageOwn;
+  if (bytes <= (44ll << 20)) return workgroups <= kNumCUs ? (kLastPageOwn | kLastPageFirst) : kLastPageOwn;
+  return bytes >= (192ll << 20) && last_pages <= kNumCUs && group < 8 ? kLastPageOwn : kLastPageInTile;
+}
+
 }  // namespace unique

@@ -41,6 +41,9 @@ __device__ __forceinline__ Gathered gather_from_groups(const float* srow, const 
   uint32_t gkey[4 * kGroupVecs], top = 0u, least = 0xffffffffu;
   auto group_of = [&](int j) { return row_page<kThreads, 4>(j); };
   {
+    // the last page of a row may have been scored apart from its group, whose maximum then does not count it
+    const uint32_t last = score_key(srow[P - 1]);
+    const bool alone = P % kGroupPages == 1;
     uint4 raw[kGroupVecs];
 #pragma unroll
     for (int v = 0; v < kGroupVecs; ++v) {
@@ -49,8 +52,9 @@ __device__ __forceinline__ Gathered gather_from_groups(const float* srow, const 
     }
 #pragma unroll
     for (int j = 0; j < 4 * kGroupVecs; ++j) {
-      const uint32_t k = j % 4 == 0 ? raw[j / 4].x : (j % 4 == 1 ? raw[j / 4].y : (j % 4 == 2 ? raw[j / 4].z : raw[j / 4].w));
+      uint32_t k = j % 4 == 0 ? raw[j / 4].x : (j % 4 == 1 ? raw[j / 4].y : (j % 4 == 2 ? raw[j / 4].z : raw[j / 4].w));
       const int g = group_of(j);
+      if (g == groups - 1) k = alone ? last : max(k, last);
       gkey[j] = g >= groups ? 0u : (forced_from < P && (g + 1) * kGroupPages > forced_from ? kKeyForced : k);
       top = max(top, g < groups ? k : 0u);  // (of scores alone, see search_top)
       least = min(least, g < groups ? gkey[j] : 0xffffffffu);

@@ -22,6 +22,9 @@ extern "C" int tile(int batch, int kv_heads, int head_dim, int max_pages, int mi
 extern "C" int even_tile(int tile, int batch, int max_pages, int min_pages, int mean_bytes, int max_tile) {
   return unique::score_even_tile(tile, batch, max_pages, min_pages, mean_bytes, max_tile);
 }
+extern "C" int last_page_rule(int cut, int workgroups, int last_pages, int mb, int group) {
+  return unique::score_last_page_rule(cut != 0, workgroups, last_pages, (int64_t)mb << 20, group);
+}
 extern "C" int tile_stride(int tile) { return unique::score_tile_stride(tile); }
 extern "C" int bulk(long long record_bytes, int head_dim, int page_size, int key_bytes, int bf16_means) {
   return unique::stats_bulk(record_bytes, head_dim, page_size, key_bytes, bf16_means != 0);

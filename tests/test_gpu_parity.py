@@ -357,6 +357,58 @@ def test_fused_decode_step_is_bit_identical_to_the_separate_calls(gpu_lib, maker
     assert torch.equal(before, fused.page_stats) and torch.equal(ref.out.view(torch.uint8), fused.out.view(torch.uint8))
 
 
+@pytest.mark.parametrize("dtype,stats_dtype,Hkv,G,D,S,pages,bound,top_k", [
+    (torch.bfloat16, torch.float32, 8, 4, 128, 16, [700], 700, 32),               # workgroups of their own, first in the grid
+    (torch.bfloat16, torch.bfloat16, 1, 8, 128, 8, [1100, 1097], 1100, 20),       # a single head
+    (torch.float32, torch.float32, 2, 2, 64, 32, [900, 897, 1, 2], 900, 40),
+    (torch.bfloat16, torch.float32, 32, 1, 64, 16, [400] * 9, 400, 16),           # eight workgroups to a sequence
+    (torch.bfloat16, torch.bfloat16, 8, 4, 64, 16, [300, 513, 1, 290] * 12, 520, 24),    # last in the grid, several rows of them
+    (torch.bfloat16, torch.float32, 2, 4, 64, 8, [4097, 4104, 4105, 4106], 4106, 64),    # group maxima; a last page alone in its group
+    (torch.bfloat16, torch.bfloat16, 2, 2, 64, 8, [8193, 8200, 5001], 8200, 300),        # the same in a selection of its own
+    (torch.bfloat16, torch.float32, 8, 4, 128, 16, [700, 9], 24000, 32),          # last in a launch that may be large
+    (torch.bfloat16, torch.float32, 8, 4, 128, 16, [30 + 7 * b for b in range(20)], 700, 16),  # cut by the lengths
+    (torch.float32, torch.bfloat16, 8, 1, 128, 16, [5 + b % 90 for b in range(70)], 700, 8),   # the same, four sequences to a lane
+    (torch.bfloat16, torch.float32, 8, 8, 128, 16, [300 + b for b in range(16)], 2100, 16),    # cut; in the tile
+    (torch.bfloat16, torch.float32, 8, 4, 128, 32, [700, 1, 2, 31], 4000, 32)])                # in the tile
+def test_last_page_of_a_step_wherever_it_is_renewed(gpu_lib, dtype, stats_dtype, Hkv, G, D, S, pages, bound, top_k):
+    """The page that has received a token, whose new key points along a query of some heads, is scored with its new statistics: a step
+    gives the statistics, lists and outputs of the separate calls bit for bit, whoever renews the page; so it does where its id is
+    outside the pool."""
+    import dataclasses
+    rng = np.random.default_rng(len(pages) * bound)
+    lens = [(n - 1) * S + int(rng.integers(1, S + 1)) for n in pages]
+    wl = W.build("last", 16, dtype=dtype, B=len(pages), H=G * Hkv, Hkv=Hkv, D=D, S=S, seq_lens=lens, top_k=top_k, key_mode="shift",
+                 plant_mode="one_percent", permute=True).to(DEV)
+    for b, n in enumerate(lens):
+        page, slot = int(wl.page_table[b, pages[b] - 1]), (n - 1) % S
+        for h in range(0, Hkv, 2):
+            wl.k_cache[page, h, slot] = 3.0 * S * wl.q[b, h * G]
+    table = torch.zeros((wl.B, bound), dtype=torch.int32, device=DEV)
+    table[:, :wl.max_pages] = wl.page_table
+    wl = dataclasses.replace(wl, page_table=table)
+    sessions = [DecodeSession(wl, stats_dtype=stats_dtype, max_seq_len_hint=bound * S, want_scores=False) for _ in range(2)]
+    for broken in (False, True):
+        if broken:
+            table[-1, pages[-1] - 1] = wl.num_phys_pages
+        end = wl.seq_lens.clone()
+        for s in sessions:  # statistics of the last page as they were before its last token
+            wl.seq_lens -= 1
+            s.update_page_stats()
+            wl.seq_lens += 1
+        ref, fused = sessions
+        ref.update_page_stats(end - 1, end, 1)
+        ref.score_select_topk()
+        ref.sparse_paged_decode()
+        fused.decode_step(refresh_tail=True)
+        torch.cuda.synchronize()
+        assert torch.equal(ref.page_stats, fused.page_stats)
+        assert torch.equal(ref.sel_pages, fused.sel_pages) and torch.equal(ref.sel_count, fused.sel_count)
+        assert torch.equal(ref.out.view(torch.uint8), fused.out.view(torch.uint8)) and torch.equal(ref.lse, fused.lse)
+        for b in range(wl.B - broken):  # the planted page is the best of its rows
+            for h in range(0, Hkv, 2):
+                assert int(fused.sel_pages[b, h, int(fused.sel_count[b, h]) - 1]) == pages[b] - 1
+
+
 def test_fused_decode_step_against_the_oracle_with_appends(gpu_lib):
     wl = W.config4(batch=6, min_context=300, max_context=6000, top_k=8, spare_tokens=64).to(DEV)
     sess = DecodeSession(wl)

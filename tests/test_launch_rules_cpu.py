@@ -52,7 +52,7 @@ def lib(tmp_path_factory):
             chunks = (C.c_int * len(pages))()
             return c.score_cut((C.c_int * len(pages))(*pages), len(pages), most_pages, ulps, chunks), list(chunks)
 
-        score_cut_grid, even_tile, tile_stride = c.score_cut_grid, c.even_tile, c.tile_stride
+        score_cut_grid, even_tile, tile_stride, last_page_rule = c.score_cut_grid, c.even_tile, c.tile_stride, c.last_page_rule
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
         uses_groups = c.uses_groups
 
@@ -168,6 +168,14 @@ def test_score_tiles_fitted_to_even_batches(lib, batch, heads, pages, mean_bytes
     most = 256 if heads <= 8 else 2048 // heads
     tile = lib.tile(batch, heads, 128 if mean_bytes > 128 else 64, pages, pages, most)
     assert lib.even_tile(tile, batch, pages, pages, mean_bytes, most) == want
+
+
+@pytest.mark.parametrize("cut,workgroups,last_pages,mb,group,want", [
+    (0, 256, 2, 8, 4, 6), (0, 257, 2, 44, 8, 2), (0, 256, 32, 45, 4, 1), (0, 512, 32, 191, 4, 1), (0, 512, 32, 192, 4, 2),
+    (0, 512, 257, 400, 4, 1), (0, 512, 24, 400, 8, 1), (1, 512, 64, 400, 4, 2), (1, 512, 64, 128, 8, 2), (1, 512, 64, 129, 8, 1)])
+def test_who_renews_the_last_pages_of_a_step(lib, cut, workgroups, last_pages, mb, group, want):
+    """1: the workgroup of its tile, 2: workgroups of their own, 6: those first in the grid."""
+    assert lib.last_page_rule(cut, workgroups, last_pages, mb, group) == want
 
 
 def test_score_chunks_of_a_batch_cut_by_its_lengths_cover_every_page_once_and_fit_the_launch(lib):
