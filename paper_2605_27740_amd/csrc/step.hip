@@ -99,7 +99,7 @@ constexpr int step_workgroups() { return sizeof(T) == 2 && D == 128 && S >= 16 ?
 
 // kVecs: 16-byte loads of scores per thread.
 template <typename T, int D, int S, int G, bool kNT, int kVecs>
-__global__ __launch_bounds__(kThreads, step_workgroups<T, D, S>()) void select_decode_kernel(
+__global__ __launch_bounds__(kThreads, (step_workgroups<T, D, S>())) void select_decode_kernel(
     CacheView c, const T* __restrict__ q, const float* __restrict__ scores, int score_stride, int top_k,
     int32_t* __restrict__ sel_pages, int32_t* __restrict__ sel_count, SplitPlan plan, float scale_log2,
     float* __restrict__ part_o, float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse_out) {
@@ -140,7 +140,7 @@ struct SelectFromGroups {
 };
 
 template <typename T, int D, int S, int G, bool kNT>
-__global__ __launch_bounds__(kThreads, step_workgroups<T, D, S>()) void select_groups_decode_kernel(
+__global__ __launch_bounds__(kThreads, (step_workgroups<T, D, S>())) void select_groups_decode_kernel(
     CacheView c, const T* __restrict__ q, const float* __restrict__ scores, const uint32_t* __restrict__ group_max, int score_stride,
     int top_k, int32_t* __restrict__ sel_pages, int32_t* __restrict__ sel_count, SplitPlan plan, float scale_log2,
     float* __restrict__ part_o, float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse_out) {
