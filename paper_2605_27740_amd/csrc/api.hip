@@ -183,6 +183,12 @@ uint32_t* group_max_in(const unique::CacheView& v, int32_t top_k, float* buf, si
   return reinterpret_cast<uint32_t*>(buf + at / sizeof(float));
 }
 
+// Whether a step may select and attend in one kernel.
+bool step_may_fuse(const unique::CacheView& v, int32_t top_k, const unique::SplitPlan& plan) {
+  return unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan,
+                            unique::step_three_fit(v.dtype == UNIQUE_DTYPE_BF16, v.D, v.S));
+}
+
 // Where a step's partial results lie while its scores, and the group maxima of long rows, are still being read.
 size_t partials_at(const unique::CacheView& v) {
   return round_up(score_bytes(v), kAlign) + (v.max_pages_hint > unique::kStepMaxPages ? round_up(group_max_bytes(v), kAlign) : 0);
@@ -213,7 +219,7 @@ int decode_step_launch(const unique::CacheView& v, const void* d_q, int32_t top_
   const int stride = score_stride_of(v);
   uint32_t* group_max = group_max_in(v, top_k, buf, bytes);
   const unique::SplitPlan plan = unique::selection_plan(v, top_k);
-  const bool fuses = unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan);
+  const bool fuses = step_may_fuse(v, top_k, plan);
   const bool whole = fuses && unique::step_is_whole(v.B * v.Hkv, v.max_pages_hint, v.D * (v.stats_bf16 ? 2 : 4),
                                                     unique::decode_streams(v, top_k), plan);
   hipError_t e = hipSuccess;
@@ -262,7 +268,7 @@ int unique_workspace_bytes(const unique_cache_desc* desc, int32_t top_k, size_t*
   // more than any call insists on: with this much a decode step may take one kernel for selection and attention, and a
   // selection may use the group maxima
   const unique::SplitPlan plan = unique::selection_plan(v, top_k);
-  if (unique::step_fuses(v.B * v.Hkv, v.max_pages_hint, top_k, plan)) need = std::max(need, fused_bytes(v, plan));
+  if (step_may_fuse(v, top_k, plan)) need = std::max(need, fused_bytes(v, plan));
   if (unique::select_uses_groups(v.max_pages_hint, top_k)) need = std::max(need, round_up(score_bytes(v), kAlign) + group_max_bytes(v));
   *out_bytes = round_up(need, kAlign);
   return UNIQUE_OK;

@@ -35,16 +35,25 @@ inline bool select_uses_groups(int max_pages, int top_k) {
 // From some k on too many keys are gathered: 1 x 2048, 512 25.5 / 28.6; 1 x 1000, 300 23.1 / 24.2 (a bound on the k-th key needs
 // more than k groups of four pages; up to 512 pages it does not matter: 8 x 250, 200 34.0 / 32.4).
 // Workgroups that wait for a free unit select when the others already stream: 24 x 1000 pages cut in 5, 960 workgroups, 48.6 /
-// 47.2; but 31 x 4096, 64 120.6 / 122.4, so those rows are left apart from 512 workgroups on.
+// 47.2. Rows of 2048 pages and more are only cut into as many workgroups as find a place at once. These are 768 where a unit has room for
+// three (three_fit), k = 128 in separate kernels / so: 20 x 4096 (640 workgroups) bf16 means 75.0 / 72.7, fp32 means 101.1 / 98.9, 17 x 4096, k = 64
+// (544) 53.6 / 49.1, 31 x 4096, 64 121.5 / 115.3, 30 x 3000 (720) 90.4 / 86.6, 28 x 4064 (672) of D = 64 60.9 / 59.1, G = 8 102.5 / 97.9, pages of 32 96.4 / 89.3, of an fp32 cache, pages of 8
+// 132.8 / 131.6, lengths from a 20th of the longest 71.4 / 67.9. bf16 caches of 128 channels in pages of 8 have room for two: 20 x 4095, k = 256 104.6 /
+// 107.2, G = 8 81.2 / 83.6, so 512 there. Rows selected from their group maxima stay at 512: 17 x 5000 101.9 / 103.9, 22 x 6000 108.8 / 109.0.
 // Longer rows, from their group maxima, in kernels of their own (select_grouped.hip) / so: 1 x 4200, 64 24.8 / 22.1; 1 x 8192, 256 29.0 /
 // 27.8; 16 x 8192, 256 143.8 / 141.8; 1 x 32768, 128 41.7 / 40.0; 4 x 16384, 64 62.9 / 60.7. Scores that rise by two standard deviations
 // along the row, with a selection that reads every score / so: 1 x 8192, 256 27.7 / 28.3; 16 x 8192, 256 141.4 / 142.6; 1 x 4200, 64
 // 22.2 / 22.0; 4 x 16384, 64 63.0 / 60.4; 1 x 32768, 256 47.9 / 43.9.
-inline bool step_fuses(int rows, int max_pages, int top_k, const SplitPlan& plan) {
+inline bool step_fuses(int rows, int max_pages, int top_k, const SplitPlan& plan, bool three_fit = false) {
   if (max_pages > kStepMaxGroupPages || top_k > kStepMaxTopK || (max_pages > 512 && 4 * top_k > max_pages)) return false;
   if (max_pages > kStepMaxPages) return select_uses_groups(max_pages, top_k) && (plan.num_splits == 1 || (int64_t)rows * plan.num_splits <= 512);
-  return plan.num_splits == 1 || (int64_t)rows * plan.num_splits * std::max(max_pages, 2048) <= 1024 * 2048;
+  const int most = std::max(1024 * 2048 / std::max(max_pages, 2048), three_fit ? 768 : 0);
+  return plan.num_splits == 1 || (int64_t)rows * plan.num_splits <= most;
 }
+
+// Whether a unit has room for three workgroups of the kernels that select and attend (step_workgroups in step.hip). Eight heads of an fp32 cache
+// have not, and gain all the same (20 x 4000 pages of 8, k = 128 112.0 / 110.6), as their attention is bound by arithmetic.
+inline bool step_three_fit(bool bf16, int head_dim, int page_size) { return !bf16 || head_dim != 128 || page_size >= 16; }
 
 // Steps whose rows are so short that every workgroup of a row's chunks scores the row for itself: one launch, at most with a merge
 // behind it. us of a whole step, three or four kernels / two or three / so (bf16, 8 KV heads, G = 4, D = 128, pages of 16, fp32 means):

@@ -33,6 +33,11 @@ extern "C" int fuses(int batch, int kv_heads, int max_pages, int top_k, int page
   return unique::step_fuses(batch * kv_heads, max_pages, top_k,
                             unique::plan_splits(batch, kv_heads, top_k, max_pages, page_bytes, false));
 }
+extern "C" int fuses_of(int batch, int kv_heads, int max_pages, int top_k, int page_size, int head_dim, int bf16) {
+  return unique::step_fuses(batch * kv_heads, max_pages, top_k,
+                            unique::plan_splits(batch, kv_heads, top_k, max_pages, page_size * head_dim * (bf16 ? 4 : 8), false),
+                            unique::step_three_fit(bf16 != 0, head_dim, page_size));
+}
 extern "C" int whole(int batch, int kv_heads, int max_pages, int top_k, int page_bytes, int mean_bytes, int streams) {
   return unique::step_is_whole(batch * kv_heads, max_pages, mean_bytes, streams != 0,
                                unique::plan_splits(batch, kv_heads, top_k, max_pages, page_bytes, false));

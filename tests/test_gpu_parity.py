@@ -1579,6 +1579,50 @@ def test_kernels_of_a_step(gpu_lib, P, D, top_k, workspace, want):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
 
 
+@pytest.mark.parametrize("B,P,S,dtype,fused", [(17, 4096, 16, torch.bfloat16, True), (22, 2732, 16, torch.bfloat16, True),
+                                               (17, 4096, 8, torch.float32, True), (17, 4096, 8, torch.bfloat16, False)])
+def test_step_of_more_cut_rows_than_two_workgroups_per_unit(gpu_lib, B, P, S, dtype, fused):
+    """Cut rows of more than 2048 pages in 513 to 768 workgroups that select and attend (bf16 pages of 8 tokens and 128 channels:
+    in separate kernels) against the separate calls: the same bits, with the smallest workspace, too."""
+    g = torch.Generator(device=DEV).manual_seed(B + P)
+    r = np.random.default_rng(B + P)
+    lens = [S * P - 3] + [int(n) for n in r.integers(1, S * P, B - 1)]
+    wl = W.build("cut", 5, dtype=dtype, B=B, H=16, Hkv=8, D=128, S=S, seq_lens=[S] * B, top_k=128, key_mode="iid", permute=True,
+                 poison=False).to(DEV)
+    wl.k_cache = torch.randn((P + 64, 8, S, 128), generator=g, device=DEV).to(dtype)  # the sequences share their pages
+    wl.v_cache = torch.randn((P + 64, 8, S, 128), generator=g, device=DEV).to(dtype)
+    wl.page_table = torch.stack([torch.randperm(P + 64, generator=g, device=DEV)[:P] for _ in range(B)]).to(torch.int32)
+    wl.seq_lens = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    apart, step = DecodeSession(wl), DecodeSession(wl)
+    apart.page_stats.zero_()
+    apart.update_page_stats()
+    step.page_stats.copy_(apart.page_stats)
+    apart.score_select_topk()
+    apart.sparse_paged_decode()
+    names = _kernels_of(lambda: step.decode_step(refresh_tail=False))
+    assert ("select_decode_kernel" in names) == fused, names
+
+    def same():
+        torch.cuda.synchronize()
+        for name in ("sel_pages", "sel_count", "lse"):
+            assert torch.equal(getattr(apart, name), getattr(step, name)), name
+        assert torch.equal(apart.out.view(torch.uint8), step.out.view(torch.uint8))
+
+    same()
+    step.out.zero_()
+    whole, size = step.workspace, 256
+    while True:  # refused sizes are refused before anything is launched
+        step.workspace = whole[:size]
+        try:
+            step.decode_step(refresh_tail=False)
+            break
+        except binding.UniqueError as e:
+            assert e.code == binding.ERR_WORKSPACE
+            size += 256
+    assert size <= whole.numel()
+    same()
+
+
 def test_kernels_of_a_dense_decode(gpu_lib):
     """Two sequences of which only one has more than a chunk are cut by the lengths on the device from 96 MB on."""
     sess = _planted_rows(24576, UNEVEN_MAKERS["rising"](32768), 8)   # 2 x 2 rows of 24576 pages of 2 KB: 192 MB

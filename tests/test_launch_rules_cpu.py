@@ -44,6 +44,10 @@ def lib(tmp_path_factory):
             return bool(c.fuses(batch, heads, max_pages, top_k, page_bytes))
 
         @staticmethod
+        def fuses_of(batch, heads, max_pages, top_k, page_size=16, head_dim=128, bf16=True):
+            return bool(c.fuses_of(batch, heads, max_pages, top_k, page_size, head_dim, int(bf16)))
+
+        @staticmethod
         def score_cuts(batch, max_pages, min_pages, mean_bytes, rec_bytes):
             return bool(c.score_cuts(batch, max_pages, min_pages, mean_bytes, C.c_longlong(rec_bytes)))
 
@@ -228,6 +232,15 @@ def test_statistics_are_written_past_the_caches_where_that_measured_faster(lib, 
     (80, 8, 4096, 64, True), (24, 8, 1000, 64, True), (31, 8, 4096, 64, False)])
 def test_steps_that_select_and_attend_in_one_kernel(lib, batch, heads, pages, top_k, want):
     assert lib.fuses(batch, heads, pages, top_k) == want
+
+
+@pytest.mark.parametrize("batch,pages,top_k,page_size,head_dim,bf16,want", [
+    (16, 4096, 128, 16, 128, True, True), (17, 4096, 128, 16, 128, True, True), (31, 4096, 64, 16, 128, True, True),
+    (31, 2732, 128, 32, 128, True, True), (31, 4097, 64, 16, 128, True, False), (17, 4096, 257, 16, 128, True, False),
+    (20, 4096, 128, 8, 128, True, False), (16, 4096, 128, 8, 128, True, True), (20, 2600, 128, 8, 128, True, True),
+    (20, 4096, 128, 8, 64, True, True), (20, 4096, 128, 8, 128, False, True), (48, 1000, 60, 16, 128, True, True)])
+def test_cut_rows_are_selected_from_in_every_workgroup_where_all_find_a_place(lib, batch, pages, top_k, page_size, head_dim, bf16, want):
+    assert lib.fuses_of(batch, 8, pages, top_k, page_size, head_dim, bf16) == want
 
 
 def test_chunks_of_a_balanced_dense_batch_fit_the_workspace_and_leave_room_to_cut(lib):
