@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kStatsWaves* kWave) void page_stats_kernel(CacheVie
       const float inv_n = 1.0f / (float)m.n;
       float mean[kVec];
 #pragma unroll
-      for (int i = 0; i < kVec; ++i) mean[i] = cross_group_allreduce<kLanesPerTok>(sum[i], OpSum()) * inv_n;
+      for (int i = 0; i < kVec; ++i) mean[i] = cross_group_allreduce<kLanesPerTok, true>(sum[i], OpSum()) * inv_n;
 
       float ss = 0.f;
 #pragma unroll
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kStatsWaves* kWave) void page_stats_kernel(CacheVie
           }
         }
       }
-      ss = group_allreduce<kWave>(ss, OpSum());
+      ss = group_allreduce<kWave, true>(ss, OpSum());
 
       // this page's record (the descriptor bounds every store to it)
       const __amdgpu_buffer_rsrc_t rec = __builtin_amdgcn_make_buffer_rsrc(
