@@ -320,21 +320,13 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
     tile = score_even_tile(tile, c.B, c.max_pages_hint, c.min_pages_hint, mean_bytes, most);
   }
   const int tiles = cut ? score_cut_grid(c.B, c.max_pages_hint, tile) : (c.max_pages_hint + tile - 1) / tile;
-  const int64_t workgroups = (int64_t)tiles * (cut ? 1 : c.B);
-  const int last_pages = last_page_groups(c.Hkv) * c.B;
-  int refresh = refresh_tail ? score_last_page_rule(cut, workgroups, last_pages, (int64_t)c.B * c.max_pages_hint * c.rec_bytes, G) : kLastPageNone;
-  dim3 grid(tiles, cut ? 1 : c.B);
+  const ScoreGrid grid = score_grid(cut, tiles, c.B, c.Hkv, refresh_tail, (int64_t)c.B * c.max_pages_hint * c.rec_bytes, G);
+  const int refresh = grid.refresh;
   size_t lds = (size_t)c.Hkv * score_tile_stride(tile) * sizeof(float);
-  if (refresh & kLastPageOwn) {
-    const int rows = (last_pages + tiles - 1) / tiles;
-    refresh |= (cut ? tiles : rows) << kLastPageBits;
-    if (cut) grid.x += last_pages;
-    else grid.y += rows;
-    lds = std::max<size_t>(lds, kScoreWaves * mean_bytes);
-  }
-  if (!cut) lds = (size_t)score_lds((int)lds, (int)sizeof(T), D, G, workgroups);
+  if (refresh & kLastPageOwn) lds = std::max<size_t>(lds, kScoreWaves * mean_bytes);
+  if (!cut) lds = (size_t)score_lds((int)lds, (int)sizeof(T), D, G, (int64_t)tiles * c.B);
   auto go = [&](auto kernel) {
-    kernel<<<grid, dim3(kScoreWaves * kWave), lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, stride, scores, out, group_max,
+    kernel<<<dim3(grid.x, grid.y), dim3(kScoreWaves * kWave), lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, stride, scores, out, group_max,
                                                          refresh, tile);
     return hipGetLastError();
   };

@@ -161,4 +161,26 @@ inline int score_last_page_rule(bool cut, int64_t workgroups, int last_pages, in
   return bytes >= (192ll << 20) && last_pages <= kNumCUs && group < 8 ? kLastPageOwn : kLastPageInTile;
 }
 
+// The grid of a launch with `tiles` tiles to a sequence, or to the batch where it is cut by its lengths, and its `refresh` argument: a LastPage and,
+// above its bits, the rows of the grid that are for last pages, or the first workgroup that is.
+struct ScoreGrid {
+  int x, y, refresh;
+};
+constexpr int kMaxGridRows = 65535;
+inline ScoreGrid score_grid(bool cut, int tiles, int batch, int kv_heads, bool refresh_tail, int64_t bytes, int group) {
+  const int last_pages = last_page_groups(kv_heads) * batch;
+  ScoreGrid g = {tiles, cut ? 1 : batch, kLastPageNone};
+  if (refresh_tail) g.refresh = score_last_page_rule(cut, (int64_t)g.x * g.y, last_pages, bytes, group);
+  if (!(g.refresh & kLastPageOwn)) return g;
+  const int rows = (last_pages + tiles - 1) / tiles;
+  if (!cut && batch + rows > kMaxGridRows) {  // more sequences than a launch could have rows for beside them, of a few pages each
+    g.refresh = kLastPageInTile;
+    return g;
+  }
+  g.refresh |= (cut ? tiles : rows) << kLastPageBits;
+  if (cut) g.x += last_pages;
+  else g.y += rows;
+  return g;
+}
+
 }  // namespace unique

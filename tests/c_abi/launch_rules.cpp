@@ -25,6 +25,10 @@ extern "C" int even_tile(int tile, int batch, int max_pages, int min_pages, int 
 extern "C" int last_page_rule(int cut, int workgroups, int last_pages, int mb, int group) {
   return unique::score_last_page_rule(cut != 0, workgroups, last_pages, (int64_t)mb << 20, group);
 }
+extern "C" void score_grid(int cut, int tiles, int batch, int kv_heads, long long bytes, int group, int* out) {
+  const unique::ScoreGrid g = unique::score_grid(cut != 0, tiles, batch, kv_heads, true, bytes, group);
+  out[0] = g.x, out[1] = g.y, out[2] = g.refresh & ((1 << unique::kLastPageBits) - 1), out[3] = g.refresh >> unique::kLastPageBits;
+}
 extern "C" int tile_stride(int tile) { return unique::score_tile_stride(tile); }
 extern "C" int bulk(long long record_bytes, int head_dim, int page_size, int key_bytes, int bf16_means) {
   return unique::stats_bulk(record_bytes, head_dim, page_size, key_bytes, bf16_means != 0);

@@ -409,6 +409,33 @@ def test_last_page_of_a_step_wherever_it_is_renewed(gpu_lib, dtype, stats_dtype,
                 assert int(fused.sel_pages[b, h, int(fused.sel_count[b, h]) - 1]) == pages[b] - 1
 
 
+@pytest.mark.parametrize("B,Hkv,P", [(40000, 1, 4), (7282, 32, 1)])
+def test_step_of_more_short_sequences_than_rows_are_left_for_their_last_pages(gpu_lib, B, Hkv, P):
+    """So many sequences of a few pages that workgroups of their own for the last pages would take the grid's rows beyond 65535: the step
+    renews them all the same, bit for bit as the separate calls."""
+    D, S, top_k, dt = 64, 8, 300, torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(B)
+    table = torch.randperm(B * P, generator=g, device=DEV).view(B, P).to(torch.int32)
+    wl = W.Workload(name="short", dtype=dt, B=B, H=Hkv, Hkv=Hkv, D=D, S=S, top_k=top_k, lam=0.5,
+                    q=torch.randn((B, Hkv, D), generator=g, device=DEV).to(dt),
+                    k_cache=torch.randn((B * P, Hkv, S, D), generator=g, device=DEV).to(dt),
+                    v_cache=torch.randn((B * P, Hkv, S, D), generator=g, device=DEV).to(dt), page_table=table,
+                    seq_lens=torch.randint(1, P * S + 1, (B,), generator=g, device=DEV, dtype=torch.int32))
+    apart, step = (DecodeSession(wl, stats_dtype=dt, max_seq_len_hint=P * S, want_scores=False) for _ in range(2))
+    for s in (apart, step):
+        wl.seq_lens -= 1
+        s.update_page_stats()
+        wl.seq_lens += 1
+    apart.update_page_stats(wl.seq_lens - 1, wl.seq_lens.clone(), 1)
+    apart.score_select_topk()
+    apart.sparse_paged_decode()
+    step.decode_step(refresh_tail=True)
+    torch.cuda.synchronize()
+    for name in ("page_stats", "sel_pages", "sel_count", "lse"):
+        assert torch.equal(getattr(apart, name), getattr(step, name)), name
+    assert torch.equal(apart.out.view(torch.uint8), step.out.view(torch.uint8))
+
+
 def test_fused_decode_step_against_the_oracle_with_appends(gpu_lib):
     wl = W.config4(batch=6, min_context=300, max_context=6000, top_k=8, spare_tokens=64).to(DEV)
     sess = DecodeSession(wl)

@@ -48,6 +48,12 @@ def lib(tmp_path_factory):
             return bool(c.fuses_of(batch, heads, max_pages, top_k, page_size, head_dim, int(bf16)))
 
         @staticmethod
+        def score_grid(cut, tiles, batch, heads, n_bytes, group):
+            out = (C.c_int * 4)()
+            c.score_grid(int(cut), tiles, batch, heads, C.c_longlong(n_bytes), group, out)
+            return tuple(out)
+
+        @staticmethod
         def score_cuts(batch, max_pages, min_pages, mean_bytes, rec_bytes):
             return bool(c.score_cuts(batch, max_pages, min_pages, mean_bytes, C.c_longlong(rec_bytes)))
 
@@ -180,6 +186,27 @@ def test_score_tiles_fitted_to_even_batches(lib, batch, heads, pages, mean_bytes
 def test_who_renews_the_last_pages_of_a_step(lib, cut, workgroups, last_pages, mb, group, want):
     """1: the workgroup of its tile, 2: workgroups of their own, 6: those first in the grid."""
     assert lib.last_page_rule(cut, workgroups, last_pages, mb, group) == want
+
+
+@pytest.mark.parametrize("batch,heads,pages", [(40000, 1, 4), (65535, 1, 1), (32767, 1, 8), (32768, 1, 8), (21846, 8, 1), (13108, 16, 1),
+                                               (7282, 32, 1), (65535, 32, 3), (65530, 4, 16384), (65535, 2, 120000), (1, 1, 1), (16, 8, 700)])
+@pytest.mark.parametrize("group", [1, 8])
+def test_score_grid_of_a_step_stays_within_the_extents_of_a_launch(lib, batch, heads, pages, group):
+    """Up to 65535 sequences, of a page or more: the rows of the grid are no more than 65535, and there is a workgroup for every tile and,
+    where last pages have their own, for every four heads of a last page."""
+    most = 256 if heads <= 8 else 2048 // heads
+    for least in (0, pages):
+        for mean_bytes in (128, 256, 512):
+            tile = lib.even_tile(lib.tile(batch, heads, 128 if mean_bytes > 128 else 64, pages, least, most), batch, pages, least, mean_bytes, most)
+            x, y, rule, extra = lib.score_grid(False, -(-pages // tile), batch, heads, batch * pages * (heads * mean_bytes + 128), group)
+            assert y <= 65535 and x == -(-pages // tile)
+            if rule & 2:
+                assert y == batch + extra and x * extra >= batch * -(-heads // 4)
+            else:
+                assert (y, rule, extra) == (batch, 1, 0)
+    if batch <= 256:
+        x, y, rule, extra = lib.score_grid(True, 512, batch, heads, 64 << 20, group)
+        assert (x, y, rule, extra) == (512 + batch * -(-heads // 4), 1, 2, 512)
 
 
 def test_score_chunks_of_a_batch_cut_by_its_lengths_cover_every_page_once_and_fit_the_launch(lib):
