@@ -129,6 +129,10 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const float* __
   constexpr int kTilesPerPage = kLoads / kTileLoads;
   constexpr int kBuffers = 2;  // register tiles per wave (three and four measured no faster)
   static_assert(S % kTokPerLoad == 0 && kLoads % kTileLoads == 0, "page size / element type combination");
+  // Eight heads are bound by the vector ALUs, and four nearly, so their sums over lanes 16 and 32 apart go through the LDS. us with row swaps /
+  // so, D = 128, pages of 16: 8 heads, dense 1 x 11828 pages 280 / 270, steps of 53 x 891, k = 159 253 / 241, 36 x 96, 17 39.3 / 37.8; 4 heads 36 x 96,
+  // 17 28.9 / 28.4, 25 x 862, 336 212.6 / 211.2; 1 and 2 the same.
+  constexpr bool kLds = G >= 4;
 
   const int hkv = k.hkv, b = k.b, begin = k.begin, end = k.end;
 
@@ -194,7 +198,7 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const float* __
           float d = qv[g][0] * kf[0];
 #pragma unroll
           for (int i = 1; i < kVec; ++i) d = fmaf(qv[g][i], kf[i], d);
-          d = group_allreduce<kLanesPerTok>(d, OpSum());
+          d = group_allreduce<kLanesPerTok, kLds>(d, OpSum());
           s[j][g] = j * kTokPerLoad < rest ? d : -INFINITY;
         }
       }
@@ -257,12 +261,12 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const float* __
   // merge the lane groups of the wave (they hold disjoint token subsets)
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const float M = cross_group_allreduce<kLanesPerTok>(m[g], OpMax());
+    const float M = cross_group_allreduce<kLanesPerTok, kLds>(m[g], OpMax());
     const float sc = fast_exp2(m[g] - M);
     m[g] = M;
-    l[g] = cross_group_allreduce<kLanesPerTok>(l[g] * sc, OpSum());
+    l[g] = cross_group_allreduce<kLanesPerTok, kLds>(l[g] * sc, OpSum());
 #pragma unroll
-    for (int i = 0; i < kVec; ++i) acc[g][i] = cross_group_allreduce<kLanesPerTok>(acc[g][i] * sc, OpSum());
+    for (int i = 0; i < kVec; ++i) acc[g][i] = cross_group_allreduce<kLanesPerTok, kLds>(acc[g][i] * sc, OpSum());
   }
 
   if (tr == 0) {
