@@ -91,11 +91,9 @@ struct SelectFromScores {
   }
 };
 
-// Workgroups on a compute unit that the registers are held down for. bf16 caches of 128 channels take just more than a third of them when left
-// alone: 24 x 1000 pages, k = 64, 960 workgroups, 34.9 us, so 32.6, 100 x 1000, 32 81.8 / 80.3, launches that fit either way the same. Pages of 8
-// tokens and 8 heads of an fp32 cache would need scratch memory for it.
+// Workgroups on a compute unit that the registers are held down for.
 template <typename T, int D, int S>
-constexpr int step_workgroups() { return sizeof(T) == 2 && D == 128 && S >= 16 ? 3 : 1; }
+constexpr int step_workgroups() { return step_held(sizeof(T) == 2, D, S) ? 3 : 1; }
 
 // kVecs: 16-byte loads of scores per thread.
 template <typename T, int D, int S, int G, bool kNT, int kVecs>
@@ -258,9 +256,11 @@ hipError_t launch_t(const CacheView& c, const StepArgs& a, hipStream_t st) {
   const SplitPlan plan = selection_plan(c, a.top_k);
   const bool stream_nt = decode_streams(c, a.top_k);
   float* part_ml = a.partials + (size_t)rows * plan.num_splits * G * D;
-  auto go = [&](auto kernel, auto... group_max) {
+  const int64_t list_bytes = (int64_t)std::min(a.top_k, c.max_pages_hint) * S * D * 2 * (int)sizeof(T);
+  auto go = [&](auto kernel, size_t lds, auto... group_max) {
+    const int extra = step_extra_lds(step_held(sizeof(T) == 2, D, S), plan.num_splits, list_bytes, (int)lds);
     const dim3 grid = plan.rotate ? dim3(c.Hkv, c.B, plan.num_splits) : dim3(plan.num_splits, c.Hkv, c.B);
-    kernel<<<grid, dim3(kThreads), 0, st>>>(c, reinterpret_cast<const T*>(a.q), a.scores, group_max..., a.score_stride, a.top_k,
+    kernel<<<grid, dim3(kThreads), extra, st>>>(c, reinterpret_cast<const T*>(a.q), a.scores, group_max..., a.score_stride, a.top_k,
                                             a.sel_pages, a.sel_count, plan, decode_scale_log2(c, a.sm_scale), a.partials, part_ml,
                                             reinterpret_cast<T*>(a.out), a.lse_out);
     return hipGetLastError();
@@ -270,14 +270,19 @@ hipError_t launch_t(const CacheView& c, const StepArgs& a, hipStream_t st) {
   // A step, us, as it is / with plain loads of K and V where a launch streams: 60 x 1000 pages, k = 64 87.7 / 92.9, 12 x 3126, 200, G = 8
   // 71.9 / 76.3, 16 x 8192, 256 141.5 / 145.1, fp32 8 x 2000, 128 44.3 / 49.6; / with 16 scores per thread for all rows: 1 x 1000, 64
   // 17.2 / 18.9, 8 x 1024 23.3 / 24.4, 8 x 2048 30.0 / 30.8.
-  if (a.group_max)
-    return stream_nt ? go(select_groups_decode_kernel<T, D, S, G, true>, a.group_max)
-                     : go(select_groups_decode_kernel<T, D, S, G, false>, a.group_max);
-  if (c.max_pages_hint <= 4 * kThreads)
-    return stream_nt ? go(select_decode_kernel<T, D, S, G, true, 1>) : go(select_decode_kernel<T, D, S, G, false, 1>);
-  if (c.max_pages_hint <= 8 * kThreads)
-    return stream_nt ? go(select_decode_kernel<T, D, S, G, true, 2>) : go(select_decode_kernel<T, D, S, G, false, 2>);
-  return stream_nt ? go(select_decode_kernel<T, D, S, G, true, 4>) : go(select_decode_kernel<T, D, S, G, false, 4>);
+  if (a.group_max) {
+    constexpr size_t kLds = sizeof(StepShared<T, D, G, SelectFromGroups::Shared>);
+    return stream_nt ? go(select_groups_decode_kernel<T, D, S, G, true>, kLds, a.group_max)
+                     : go(select_groups_decode_kernel<T, D, S, G, false>, kLds, a.group_max);
+  }
+  auto go_vecs = [&](auto vecs) {
+    constexpr int kVecs = decltype(vecs)::value;
+    constexpr size_t kLds = sizeof(StepShared<T, D, G, SmallShared<kThreads, kVecs>>);
+    return stream_nt ? go(select_decode_kernel<T, D, S, G, true, kVecs>, kLds) : go(select_decode_kernel<T, D, S, G, false, kVecs>, kLds);
+  };
+  if (c.max_pages_hint <= 4 * kThreads) return go_vecs(std::integral_constant<int, 1>());
+  if (c.max_pages_hint <= 8 * kThreads) return go_vecs(std::integral_constant<int, 2>());
+  return go_vecs(std::integral_constant<int, 4>());
 }
 
 template <typename T, int D, int S, int G>

@@ -35,11 +35,11 @@ inline bool select_uses_groups(int max_pages, int top_k) {
 // From some k on too many keys are gathered: 1 x 2048, 512 25.5 / 28.6; 1 x 1000, 300 23.1 / 24.2 (a bound on the k-th key needs
 // more than k groups of four pages; up to 512 pages it does not matter: 8 x 250, 200 34.0 / 32.4).
 // Workgroups that wait for a free unit select when the others already stream: 24 x 1000 pages cut in 5, 960 workgroups, 48.6 /
-// 47.2. Rows of 2048 pages and more are only cut into as many workgroups as find a place at once. These are 768 where a unit has room for
-// three (three_fit), k = 128 in separate kernels / so: 20 x 4096 (640 workgroups) bf16 means 75.0 / 72.7, fp32 means 101.1 / 98.9, 17 x 4096, k = 64
+// 47.2. The longer the rows, the fewer workgroups they are cut into: 1024 up to 2048 pages, 512 at 4096, in between as many as read that many scores;
+// but always 768 where three_fit, k = 128 in separate kernels / so: 20 x 4096 (640 workgroups) bf16 means 75.0 / 72.7, fp32 means 101.1 / 98.9, 17 x 4096, k = 64
 // (544) 53.6 / 49.1, 31 x 4096, 64 121.5 / 115.3, 30 x 3000 (720) 90.4 / 86.6, 28 x 4064 (672) of D = 64 60.9 / 59.1, G = 8 102.5 / 97.9, pages of 32 96.4 / 89.3, of an fp32 cache, pages of 8
 // 132.8 / 131.6, lengths from a 20th of the longest 71.4 / 67.9. bf16 caches of 128 channels in pages of 8 have room for two: 20 x 4095, k = 256 104.6 /
-// 107.2, G = 8 81.2 / 83.6, so 512 there. Rows selected from their group maxima stay at 512: 17 x 5000 101.9 / 103.9, 22 x 6000 108.8 / 109.0.
+// 107.2, G = 8 81.2 / 83.6 (k = 128 gains at every length, 20 x 2100 50.8 / 49.9, 20 x 4000 62.6 / 62.0; k = 256 at none, 20 x 2600 65.9 / 66.8). Rows selected from their group maxima stay at 512: 17 x 5000 101.9 / 103.9, 22 x 6000 108.8 / 109.0.
 // Longer rows, from their group maxima, in kernels of their own (select_grouped.hip) / so: 1 x 4200, 64 24.8 / 22.1; 1 x 8192, 256 29.0 /
 // 27.8; 16 x 8192, 256 143.8 / 141.8; 1 x 32768, 128 41.7 / 40.0; 4 x 16384, 64 62.9 / 60.7. Scores that rise by two standard deviations
 // along the row, with a selection that reads every score / so: 1 x 8192, 256 27.7 / 28.3; 16 x 8192, 256 141.4 / 142.6; 1 x 4200, 64
@@ -51,9 +51,27 @@ inline bool step_fuses(int rows, int max_pages, int top_k, const SplitPlan& plan
   return plan.num_splits == 1 || (int64_t)rows * plan.num_splits <= most;
 }
 
-// Whether a unit has room for three workgroups of the kernels that select and attend (step_workgroups in step.hip). Eight heads of an fp32 cache
-// have not, and gain all the same (20 x 4000 pages of 8, k = 128 112.0 / 110.6), as their attention is bound by arithmetic.
-inline bool step_three_fit(bool bf16, int head_dim, int page_size) { return !bf16 || head_dim != 128 || page_size >= 16; }
+// Kernels that select and attend whose registers are held down to what leaves a unit room for three workgroups (step.hip): bf16 caches of 128
+// channels take just more than a third of them when left alone. 24 x 1000 pages, k = 64, 960 workgroups, 34.9 us, so 32.6, 100 x 1000, 32
+// 81.8 / 80.3, launches that fit either way the same. Pages of 8 tokens would need scratch memory for it.
+constexpr bool step_held(bool bf16, int head_dim, int page_size) { return bf16 && head_dim == 128 && page_size >= 16; }
+// Whether cut rows may have as many workgroups as three to a unit are: the held kernels have room for them, and so have the others but bf16
+// caches of 128 channels in pages of 8, and eight heads of an fp32 cache of 128 channels, which gain all the same, as their attention is bound by
+// arithmetic. us in separate kernels / so, fp32, G = 8, k = 128: 20 x 4000 pages of 8 89.5 / 87.6, of 16 124.0 / 122.9, of 32 189.5 / 189.0; of 16 17 x 4096,
+// 64 85.1 / 83.4, 31 x 4096, 64 125.2 / 122.8, 31 x 2732 150.8 / 152.0; of 32 24 x 3000, 64 140.3 / 137.8, 20 x 2200, 256 307.9 / 307.8.
+constexpr bool step_three_fit(bool bf16, int head_dim, int page_size) { return !bf16 || head_dim != 128 || step_held(bf16, head_dim, page_size); }
+
+// LDS that a launch of the held kernels adds to their own, so that only two of its workgroups find a place on a unit. Where rows are not cut and their
+// lists are long, three to a unit take a third longer each, and of rows of unlike lengths the long ones end on few units; two leave more rows
+// to the units that are done. By the bytes of K and V of a list, us with three / two (pages of 16, lengths log-uniform from a 20th, or one long and the
+// others a quarter or a tenth): 128 KB 180 x 300 pages 49.7 / 53.2, 256 KB 100 x 1000 58.6 / 60.0, 384 KB 110 x 171 59.1 / 60.3, G = 8 120 x 300 50.8 /
+// 52.5; 512 KB 80 x 300 66.1 / 62.7, G = 8 75 x 300 49.7 / 43.5, but G = 1 70 x 500 65.8 / 70.8; 768 KB 90 x 300 53.1 / 46.7; 1 MB G = 2 132 x 700 181 /
+// 169; 2 MB G = 1 83 x 500 148 / 121; 4 MB G = 2 70 x 300 393 / 354. Even batches are the same from 512 KB on (75 x 300 129.6 / 128.9).
+constexpr int64_t kStepLongList = 512 << 10;
+constexpr int step_extra_lds(bool held, int num_splits, int64_t list_bytes, int own_bytes) {
+  constexpr int kTwoFit = 56 << 10;  // more than a third of a unit's LDS
+  return held && num_splits == 1 && list_bytes >= kStepLongList ? std::max(kTwoFit - own_bytes, 0) : 0;
+}
 
 // Steps whose rows are so short that every workgroup of a row's chunks scores the row for itself: one launch, at most with a merge
 // behind it. us of a whole step, three or four kernels / two or three / so (bf16, 8 KV heads, G = 4, D = 128, pages of 16, fp32 means):

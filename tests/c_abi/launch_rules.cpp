@@ -42,6 +42,9 @@ extern "C" int fuses_of(int batch, int kv_heads, int max_pages, int top_k, int p
                             unique::plan_splits(batch, kv_heads, top_k, max_pages, page_size * head_dim * (bf16 ? 4 : 8), false),
                             unique::step_three_fit(bf16 != 0, head_dim, page_size));
 }
+extern "C" int extra_lds(int bf16, int head_dim, int page_size, int num_splits, long long list_bytes, int own_bytes) {
+  return unique::step_extra_lds(unique::step_held(bf16 != 0, head_dim, page_size), num_splits, list_bytes, own_bytes);
+}
 extern "C" int whole(int batch, int kv_heads, int max_pages, int top_k, int page_bytes, int mean_bytes, int streams) {
   return unique::step_is_whole(batch * kv_heads, max_pages, mean_bytes, streams != 0,
                                unique::plan_splits(batch, kv_heads, top_k, max_pages, page_bytes, false));

@@ -1650,6 +1650,33 @@ def test_step_of_more_cut_rows_than_two_workgroups_per_unit(gpu_lib, B, P, S, dt
     same()
 
 
+@pytest.mark.parametrize("S,G,P,top_k", [(16, 4, 70, 64), (16, 4, 70, 63), (32, 8, 400, 33), (16, 1, 4200, 100), (32, 2, 1500, 250)])
+def test_step_of_uncut_rows_with_long_lists(gpu_lib, S, G, P, top_k):
+    """Uncut rows of a bf16 cache of 128 channels whose lists reach 512 KB (in one case just not), with two workgroups to a unit: the bits
+    of the separate calls, in rows of every length and of none."""
+    B, dt = 65, torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(P)
+    r = np.random.default_rng(P)
+    wl = W.Workload(name="uncut", dtype=dt, B=B, H=8 * G, Hkv=8, D=128, S=S, top_k=top_k, lam=0.5,
+                    q=torch.randn((B, 8 * G, 128), generator=g, device=DEV).to(dt),
+                    k_cache=torch.randn((P + 64, 8, S, 128), generator=g, device=DEV).to(dt),  # the sequences share their pages
+                    v_cache=torch.randn((P + 64, 8, S, 128), generator=g, device=DEV).to(dt),
+                    page_table=torch.stack([torch.randperm(P + 64, generator=g, device=DEV)[:P] for _ in range(B)]).to(torch.int32),
+                    seq_lens=torch.tensor([P * S, 0, 1, top_k * S, top_k * S + 1] + [int(n) for n in r.integers(1, P * S, B - 5)], dtype=torch.int32, device=DEV))
+    apart, step = DecodeSession(wl), DecodeSession(wl)
+    apart.page_stats.zero_()
+    apart.update_page_stats()
+    step.page_stats.copy_(apart.page_stats)
+    apart.score_select_topk()
+    apart.sparse_paged_decode()
+    names = _kernels_of(lambda: step.decode_step(refresh_tail=False))
+    assert "page_score_kernel" in names and len(names) == 2, names
+    torch.cuda.synchronize()
+    for name in ("sel_pages", "sel_count", "lse"):
+        assert torch.equal(getattr(apart, name), getattr(step, name)), name
+    assert torch.equal(apart.out.view(torch.uint8), step.out.view(torch.uint8))
+
+
 def test_kernels_of_a_dense_decode(gpu_lib):
     """Two sequences of which only one has more than a chunk are cut by the lengths on the device from 96 MB on."""
     sess = _planted_rows(24576, UNEVEN_MAKERS["rising"](32768), 8)   # 2 x 2 rows of 24576 pages of 2 KB: 192 MB

@@ -62,6 +62,10 @@ def lib(tmp_path_factory):
             chunks = (C.c_int * len(pages))()
             return c.score_cut((C.c_int * len(pages))(*pages), len(pages), most_pages, ulps, chunks), list(chunks)
 
+        @staticmethod
+        def extra_lds(splits, list_kb, own, page_size=16, head_dim=128, bf16=True):
+            return c.extra_lds(int(bf16), head_dim, page_size, splits, C.c_longlong(list_kb << 10), own)
+
         score_cut_grid, even_tile, tile_stride, last_page_rule = c.score_cut_grid, c.even_tile, c.tile_stride, c.last_page_rule
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
         uses_groups = c.uses_groups
@@ -266,8 +270,19 @@ def test_steps_that_select_and_attend_in_one_kernel(lib, batch, heads, pages, to
     (31, 2732, 128, 32, 128, True, True), (31, 4097, 64, 16, 128, True, False), (17, 4096, 257, 16, 128, True, False),
     (20, 4096, 128, 8, 128, True, False), (16, 4096, 128, 8, 128, True, True), (20, 2600, 128, 8, 128, True, True),
     (20, 4096, 128, 8, 64, True, True), (20, 4096, 128, 8, 128, False, True), (48, 1000, 60, 16, 128, True, True)])
-def test_cut_rows_are_selected_from_in_every_workgroup_where_all_find_a_place(lib, batch, pages, top_k, page_size, head_dim, bf16, want):
+def test_cut_rows_are_selected_from_in_every_workgroup_up_to_a_number_of_them(lib, batch, pages, top_k, page_size, head_dim, bf16, want):
     assert lib.fuses_of(batch, 8, pages, top_k, page_size, head_dim, bf16) == want
+
+
+def test_uncut_rows_with_long_lists_have_two_workgroups_to_a_unit(lib):
+    unit = 160 << 10
+    for own in (18528, 37056, 40224, 48544, 57344, 70000):  # of the kernels, and more than any has
+        for kb in (512, 768, 4096):
+            total = own + lib.extra_lds(1, kb, own)
+            assert 3 * total > unit and (2 * total <= unit or total == own)
+    for other in (lib.extra_lds(2, 4096, 37056), lib.extra_lds(1, 511, 37056), lib.extra_lds(1, 4096, 37056, page_size=8),
+                  lib.extra_lds(1, 4096, 20000, head_dim=64), lib.extra_lds(1, 4096, 20000, bf16=False)):
+        assert other == 0
 
 
 def test_chunks_of_a_balanced_dense_batch_fit_the_workspace_and_leave_room_to_cut(lib):
