@@ -92,10 +92,11 @@ __device__ __forceinline__ void score_last_page(const CacheView& c, const T* q, 
 }
 
 // The chunk of this workgroup, pages [first, first + pages) of sequence b or fewer, where the batch is cut by its lengths (score_tile.hpp);
-// N: the sequence's length, P: its pages without the last `less`. w: the workgroup. false: there are no more chunks. most_pages: of a chunk. kSeqs: consecutive sequences that a lane
-// looks after (four for every batch cost 64 or fewer 0.3 us).
+// N: the sequence's length, P: its pages without the last `less`. w: the workgroup. false: there are no more chunks. most_pages: of a chunk;
+// three_fit, reserve: see score_cut_slots. kSeqs: consecutive sequences that a lane looks after (four for every batch cost 64 or fewer 0.3 us).
 template <int kSeqs>
-__device__ __forceinline__ bool find_chunk(const CacheView& c, int w, int most_pages, int less, int& b, int& first, int& pages, int& N, int& P) {
+__device__ __forceinline__ bool find_chunk(const CacheView& c, int w, int most_pages, bool three_fit, int reserve, int less, int& b, int& first, int& pages,
+                                           int& N, int& P) {
   const int lane = threadIdx.x % kWave;
   const int page_shift = __ffs(c.S) - 1;  // page sizes are powers of two
   int len[kSeqs], units[kSeqs], all = 0;
@@ -108,7 +109,7 @@ __device__ __forceinline__ bool find_chunk(const CacheView& c, int w, int most_p
     all += units[i];
   }
   all = __builtin_amdgcn_readlane(wave_inclusive_scan(all), kWave - 1);
-  const int most = most_pages / kCutUnit, slots = kCutSlots * score_cut_rounds(all, c.B, most);
+  const int most = most_pages / kCutUnit, slots = score_cut_slots(all, c.B, most, three_fit, reserve);
   int chunk, chunks[kSeqs], mine, upto;
   auto cut = [&](int waste) {
     chunk = score_cut_chunk(all, slots, waste, most);
@@ -126,19 +127,20 @@ __device__ __forceinline__ bool find_chunk(const CacheView& c, int w, int most_p
   const unsigned long long behind = __ballot(upto > w);
   if (behind == 0) return false;
   const int at = __ffsll(behind) - 1;
-  int i = w - __builtin_amdgcn_readlane(upto - mine, at), s = 0, n = __builtin_amdgcn_readlane(len[0], at);
+  int i = w - __builtin_amdgcn_readlane(upto - mine, at), s = 0, n = __builtin_amdgcn_readlane(len[0], at), parts = __builtin_amdgcn_readlane(chunks[0], at);
 #pragma unroll
   for (int j = 1; j < kSeqs; ++j) {
-    const int before = __builtin_amdgcn_readlane(chunks[j - 1], at), next = __builtin_amdgcn_readlane(len[j], at);
-    const bool on = s == j - 1 && i >= before;
-    i -= on ? before : 0;
+    const int next = __builtin_amdgcn_readlane(len[j], at), next_parts = __builtin_amdgcn_readlane(chunks[j], at);
+    const bool on = s == j - 1 && i >= parts;
+    i -= on ? parts : 0;
     s = on ? j : s;
     n = on ? next : n;
+    parts = on ? next_parts : parts;
   }
   b = at * kSeqs + s;
   N = n;
   P = min((N + c.S - 1) >> page_shift, c.max_pages_hint) - less;
-  pages = chunk * kCutUnit;
+  pages = score_cut_chunks((P + kCutUnit - 1) / kCutUnit, parts, __builtin_amdgcn_rcpf((float)parts)) * kCutUnit;
   first = i * pages;
   return true;
 }
@@ -179,7 +181,9 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   }
   int b, tile0, N, P;
   if constexpr (kCut > 0) {
-    if (!find_chunk<kCut>(c, blockIdx.x, tile_pages, less, b, tile0, tile_pages, N, P)) return;
+    constexpr bool kThreeFit = score_cut_three_fit(G, D, sizeof(TS) == 2);
+    const int reserve = kOwn && score_cut_two_fit(G, D, sizeof(TS) == 2) ? last_page_groups(c.Hkv) * c.B : 0;
+    if (!find_chunk<kCut>(c, blockIdx.x, tile_pages, kThreeFit, reserve, less, b, tile0, tile_pages, N, P)) return;
   } else {
     b = row;
     tile0 = blockIdx.x * tile_pages;  // tile_pages logical pages per workgroup (a multiple of 8, up to 256)
@@ -319,8 +323,11 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
     tile = score_tile(c.B, c.Hkv, D, c.max_pages_hint, c.min_pages_hint, most);
     tile = score_even_tile(tile, c.B, c.max_pages_hint, c.min_pages_hint, mean_bytes, most);
   }
-  const int tiles = cut ? score_cut_grid(c.B, c.max_pages_hint, tile) : (c.max_pages_hint + tile - 1) / tile;
-  const ScoreGrid grid = score_grid(cut, tiles, c.B, c.Hkv, refresh_tail, (int64_t)c.B * c.max_pages_hint * c.rec_bytes, G);
+  const int64_t bytes = (int64_t)c.B * c.max_pages_hint * c.rec_bytes;
+  const int reserve = score_cut_reserve(refresh_tail, c.B, c.Hkv, bytes, G, score_cut_two_fit(G, D, c.stats_bf16));
+  const int tiles = cut ? score_cut_grid(c.B, c.max_pages_hint, tile, score_cut_three_fit(G, D, c.stats_bf16), reserve)
+                        : (c.max_pages_hint + tile - 1) / tile;
+  const ScoreGrid grid = score_grid(cut, tiles, c.B, c.Hkv, refresh_tail, bytes, G);
   const int refresh = grid.refresh;
   size_t lds = (size_t)c.Hkv * score_tile_stride(tile) * sizeof(float);
   if (refresh & kLastPageOwn) lds = std::max<size_t>(lds, kScoreWaves * mean_bytes);

@@ -96,24 +96,34 @@ constexpr int kCutMaxBatch = 256;       // four sequences per lane
 constexpr int kCutMaxPages = 1 << 20;   // of a sequence
 constexpr int kCutMaxUnits = 1 << 22;   // of a launch
 
-// Rounds of kCutSlots workgroups for so many units; a sequence's last chunk is its only one that is not full.
-constexpr int score_cut_rounds(int units, int batch, int most_units) {
-  const int round = (kCutSlots - batch) * most_units;
-  return units > round ? (units + round - 1) / round : 1;
+// Workgroups for so many units: kCutSlots, or a multiple if chunks of most_units would be more with the sequences' last ones, which are
+// the only ones that are not full. `reserve` of them are left to others, which are to run at the same time. three_fit: three find a place on a unit, no
+// fourth, so that three to each come before four.
+constexpr int score_cut_slots(int units, int batch, int most_units, bool three_fit, int reserve) {
+  const int need = (units + most_units - 1) / most_units + batch + reserve;
+  if (three_fit && need > kCutSlots && need <= kCutSlots * 3 / 2) return kCutSlots * 3 / 2 - reserve;
+  return (need + kCutSlots - 1) / kCutSlots * kCutSlots - reserve;
 }
-// Units of a chunk, so that there are no more than `slots` chunks if the sequences' last ones waste no more than `waste` chunks
+// Eight heads on bf16 means. us with four to a unit / three, lengths from 85 hundredths of the longest: 64 x 2000 pages 52.8 / 49.0, 63 x 2951 70.4 / 68;
+// from 6 tenths 8 x 27105 72.4 / 69.5. Three where two are enough lose: 16 x 2108 log-uniform 21.3 / 22.8 (a step), 20 x 7000 44.1 / 47.4.
+constexpr bool score_cut_three_fit(int group, int head_dim, bool bf16_means) { return group == 8 && head_dim == 128 && bf16_means; }
+// Whether no third workgroup finds a place on a unit.
+constexpr bool score_cut_two_fit(int group, int head_dim, bool bf16_means) { return group == 8 && head_dim == 128 && !bf16_means; }
+// Units of a chunk at most, so that there are no more than `slots` chunks if the sequences' last ones waste no more than `waste` chunks
 // together; with waste = batch that is certain.
 constexpr int score_cut_chunk(int units, int slots, int waste, int most_units) {
   const int chunks = slots - waste;
   return units > 0 ? std::min((units + chunks - 1) / chunks, most_units) : 1;
 }
 // Chunks of a sequence; per_unit: 1 / chunk, off by a few units in the last place at most. The quotient is half a unit or more away
-// from the next whole number and off by less for kCutMaxPages.
+// from the next whole number and off by less for kCutMaxPages. The same function says how many units each of them has, with the chunks in the
+// place of the units of one: a sequence's chunks are alike, as full ones and a rest leave a batch of equal lengths uneven (200 x 372 pages 60.8 /
+// 54.4 us, 256 x 145 31.7 / 29.4, bf16 means 64 x 752 21.3 / 20.3).
 constexpr int score_cut_chunks(int units, int chunk, float per_unit) { return (int)(((float)(units + chunk - 1) + 0.5f) * per_unit); }
 // Workgroups that a launch may need, whatever the lengths are.
-inline int score_cut_grid(int batch, int max_pages, int most_pages) {
+inline int score_cut_grid(int batch, int max_pages, int most_pages, bool three_fit, int reserve) {
   const int64_t units = (int64_t)batch * ((max_pages + kCutUnit - 1) / kCutUnit);
-  return (int)std::min<int64_t>(units, (int64_t)kCutSlots * score_cut_rounds((int)units, batch, most_pages / kCutUnit));
+  return (int)std::min<int64_t>(units, score_cut_slots((int)units, batch, most_pages / kCutUnit, three_fit, reserve));
 }
 
 // It costs a round trip for the lengths before that for the page ids and the queries, 0.4 to 0.7 us, 0.2 more above 64 sequences; so
@@ -131,12 +141,21 @@ inline int score_cut_grid(int batch, int max_pages, int most_pages) {
 // 22.9, at 300 MB 50.5 / 42.9; from 8 tenths at 400 MB 12 x 66.2 / 62.9; from 9 tenths at 180 MB 60 x 0.98 times as fast; 4 sequences of 16 heads, G
 // = 1, D = 64 at 400 MB 0.94 times. With every other sequence just half as long it is even at best (16 x 8192 64.8 / 65.8, bf16 means 35.5 /
 // 36.5), and so it is for two sequences (2 x 16384 uniform 20.4 / 20.5).
+// Above 64 sequences, four to a lane, the way to a chunk is longer and what short sequences are cut into coarse: 128 x 12 to 96 pages 8.8 / 9.2, from 7
+// tenths on 12.4 / 12.9, even 256 x 96 19.6 / 20.6; 100 x 12 to 240 log 10.2 / 6.5, 128 x 20 to 188 uniform 16.5 / 14.4.
+// Without a lower bound (min_pages = 0) a batch may be even and gain nothing, so what even ones do not lose decides, a narrow range of lengths as little:
+// fp32 means, even 64 x 248 pages (63 MB) 15.8 / 16.7, 16 x 868 14.9 / 15.2, but 71 MB 4 x 19.1 / 17.6, 16 x 19.1 / 17.6, 64 x 19.3 / 17.7, 100 MB 64 x 22.2 / 20.1, 150 MB
+// 16 x 28.1 / 28.2, 300 MB 53.3 / 51.3; bf16 means, 50 MB 64 x 13.5 / 14.1, but 55 MB 16 x 17.4 / 14.9, 64 x 17.4 / 15.5, 150 MB 64 x 30.0 / 28.2; above 64
+// sequences 50 MB 65 x 13.2 / 13.9, 128 x 193 from 7 tenths on (85 MB) 18.2 / 19.0, but 99 MB even 128 x 22.0 / 20.8, 200 x 21.9 / 21.2, 149 MB 128 x 29.4 / 28.8, 200 x 29.0 /
+// 29.7, 219 MB 140 x 42.6 / 41.3, log-uniform 128 x 193 13.6 / 10.8.
 inline bool score_cuts(int batch, int max_pages, int min_pages, int mean_bytes, int64_t rec_bytes) {
   if (batch < 3 || batch > kCutMaxBatch || max_pages > kCutMaxPages) return false;
   if ((int64_t)batch * ((max_pages + kCutUnit - 1) / kCutUnit) > kCutMaxUnits) return false;
   const int64_t most = (int64_t)batch * max_pages * rec_bytes;
-  if (min_pages < (max_pages + 1) / 2) return most >= ((batch < 16 || mean_bytes <= 128 ? 96ll : 48ll) << 20);
-  return batch >= 8 && mean_bytes > 128 && min_pages <= max_pages / 8 * 7 && most >= (144ll << 20);
+  if (min_pages >= (max_pages + 1) / 2) return batch >= 8 && mean_bytes > 128 && min_pages <= max_pages / 8 * 7 && most >= (144ll << 20);
+  if (batch > 64 && max_pages < 128) return false;
+  if (batch < 16 || mean_bytes <= 128 || (batch > 64 && min_pages == 0)) return most >= (96ll << 20);
+  return most >= ((min_pages > 0 ? 48ll : (mean_bytes > 256 ? 68ll : 52ll)) << 20);
 }
 
 // A decode step renews the statistics of the page that has received a token before that page is scored: in the workgroup whose tile it is in,
@@ -159,6 +178,12 @@ inline int score_last_page_rule(bool cut, int64_t workgroups, int last_pages, in
   if (cut) return group == 8 && bytes > (128ll << 20) ? kLastPageInTile : kLastPageOwn;
   if (bytes <= (44ll << 20)) return workgroups <= kNumCUs ? (kLastPageOwn | kLastPageFirst) : kLastPageOwn;
   return bytes >= (192ll << 20) && last_pages <= kNumCUs && group < 8 ? kLastPageOwn : kLastPageInTile;
+}
+
+// Workgroups that a cut leaves to last pages, so that they run with the chunks where no third finds a place on a unit.
+inline int score_cut_reserve(bool refresh_tail, int batch, int kv_heads, int64_t bytes, int group, bool two_fit) {
+  const int last_pages = last_page_groups(kv_heads) * batch;
+  return two_fit && refresh_tail && (score_last_page_rule(true, 0, last_pages, bytes, group) & kLastPageOwn) ? last_pages : 0;
 }
 
 // The grid of a launch with `tiles` tiles to a sequence, or to the batch where it is cut by its lengths, and its `refresh` argument: a LastPage and,

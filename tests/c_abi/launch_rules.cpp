@@ -80,23 +80,32 @@ extern "C" int dense_cut(const int* pages, int batch, int kv_heads, int max_page
 extern "C" int score_cuts(int batch, int max_pages, int min_pages, int mean_bytes, long long rec_bytes) {
   return unique::score_cuts(batch, max_pages, min_pages, mean_bytes, rec_bytes);
 }
-extern "C" int score_cut_grid(int batch, int max_pages, int most_pages) { return unique::score_cut_grid(batch, max_pages, most_pages); }
-// The cut of a batch's scores as score.hip finds it: chunks of every sequence; returns the pages of a chunk. The reciprocal is `ulps`
-// units in the last place off.
-extern "C" int score_cut(const int* pages, int batch, int most_pages, int ulps, int* chunks) {
+extern "C" int score_cut_reserve(int batch, int kv_heads, long long bytes, int group, int head_dim, int bf16_means) {
+  return unique::score_cut_reserve(true, batch, kv_heads, bytes, group, unique::score_cut_two_fit(group, head_dim, bf16_means != 0));
+}
+extern "C" int score_cut_grid(int batch, int max_pages, int most_pages, int three_fit, int reserve) {
+  return unique::score_cut_grid(batch, max_pages, most_pages, three_fit != 0, reserve);
+}
+// The cut of a batch's scores as score.hip finds it: chunks of every sequence and the units of each of them; returns the pages of a chunk at
+// most. The reciprocals are `ulps` units in the last place off.
+extern "C" int score_cut(const int* pages, int batch, int most_pages, int three_fit, int reserve, int ulps, int* chunks, int* sizes) {
   const int most = most_pages / unique::kCutUnit;
+  auto units = [&](int b) { return (pages[b] + unique::kCutUnit - 1) / unique::kCutUnit; };
+  auto reciprocal = [&](int n) {
+    float r = 1.f / (float)n;
+    for (int i = 0; i < std::abs(ulps); ++i) r = std::nextafter(r, ulps < 0 ? 0.f : 2.f);
+    return r;
+  };
   int all = 0;
-  for (int b = 0; b < batch; ++b) all += (pages[b] + unique::kCutUnit - 1) / unique::kCutUnit;
-  const int slots = unique::kCutSlots * unique::score_cut_rounds(all, batch, most);
+  for (int b = 0; b < batch; ++b) all += units(b);
+  const int slots = unique::score_cut_slots(all, batch, most, three_fit != 0, reserve);
   int chunk = 0;
   for (int waste : {batch / 2, batch}) {
     chunk = unique::score_cut_chunk(all, slots, waste, most);
-    float per_unit = 1.f / (float)chunk;
-    for (int i = 0; i < std::abs(ulps); ++i) per_unit = std::nextafter(per_unit, ulps < 0 ? 0.f : 2.f);
     int sum = 0;
-    for (int b = 0; b < batch; ++b)
-      sum += chunks[b] = unique::score_cut_chunks((pages[b] + unique::kCutUnit - 1) / unique::kCutUnit, chunk, per_unit);
+    for (int b = 0; b < batch; ++b) sum += chunks[b] = unique::score_cut_chunks(units(b), chunk, reciprocal(chunk));
     if (sum <= slots) break;
   }
+  for (int b = 0; b < batch; ++b) sizes[b] = chunks[b] > 0 ? unique::score_cut_chunks(units(b), chunks[b], reciprocal(chunks[b])) : 0;
   return chunk * unique::kCutUnit;
 }

@@ -369,6 +369,7 @@ def test_fused_decode_step_is_bit_identical_to_the_separate_calls(gpu_lib, maker
     (torch.bfloat16, torch.float32, 8, 4, 128, 16, [30 + 7 * b for b in range(20)], 700, 16),  # cut by the lengths
     (torch.float32, torch.bfloat16, 8, 1, 128, 16, [5 + b % 90 for b in range(70)], 700, 8),   # the same, four sequences to a lane
     (torch.bfloat16, torch.float32, 8, 8, 128, 16, [300 + b for b in range(16)], 2100, 16),    # cut; in the tile
+    (torch.bfloat16, torch.float32, 8, 8, 128, 16, [300 + b for b in range(15)] + [1], 1800, 16),  # cut, with workgroups left to last pages
     (torch.bfloat16, torch.float32, 8, 4, 128, 32, [700, 1, 2, 31], 4000, 32)])                # in the tile
 def test_last_page_of_a_step_wherever_it_is_renewed(gpu_lib, dtype, stats_dtype, Hkv, G, D, S, pages, bound, top_k):
     """The page that has received a token, whose new key points along a query of some heads, is scored with its new statistics: a step
@@ -798,6 +799,7 @@ def test_large_score_tiles_on_a_ragged_batch(gpu_lib, Hkv, G, stats_dtype):
 @pytest.mark.parametrize("B,Hkv,G,D,dtype,stats_dtype,bound,longest", [
     (3, 8, 4, 128, torch.bfloat16, torch.float32, 8192, 8192),     # 3 x 8192 pages: one round of workgroups
     (64, 1, 8, 64, torch.bfloat16, torch.bfloat16, 6200, 6200),    # several rounds of chunks of 256 pages; eight pages to a step
+    (64, 1, 8, 128, torch.bfloat16, torch.bfloat16, 4500, 4500),   # three workgroups to a unit
     (65, 32, 1, 64, torch.float32, torch.float32, 300, 300),       # more than a lane per sequence; a wave per head, chunks of up to 64
     (256, 2, 2, 128, torch.bfloat16, torch.bfloat16, 1700, 90),    # the largest batch; sequences far below the bound
     (16, 16, 4, 128, torch.float32, torch.bfloat16, 4500, 4500)])  # group maxima

@@ -58,15 +58,24 @@ def lib(tmp_path_factory):
             return bool(c.score_cuts(batch, max_pages, min_pages, mean_bytes, C.c_longlong(rec_bytes)))
 
         @staticmethod
-        def score_cut(pages, most_pages, ulps=0):
-            chunks = (C.c_int * len(pages))()
-            return c.score_cut((C.c_int * len(pages))(*pages), len(pages), most_pages, ulps, chunks), list(chunks)
+        def score_cut(pages, most_pages, ulps=0, three_fit=False, reserve=0):
+            chunks, sizes = (C.c_int * len(pages))(), (C.c_int * len(pages))()
+            n = c.score_cut((C.c_int * len(pages))(*pages), len(pages), most_pages, int(three_fit), reserve, ulps, chunks, sizes)
+            return n, list(chunks), list(sizes)
+
+        @staticmethod
+        def score_cut_grid(batch, max_pages, most_pages, three_fit=False, reserve=0):
+            return c.score_cut_grid(batch, max_pages, most_pages, int(three_fit), reserve)
+
+        @staticmethod
+        def score_cut_reserve(batch, heads, mb, group, head_dim, bf16_means):
+            return c.score_cut_reserve(batch, heads, C.c_longlong(mb << 20), group, head_dim, int(bf16_means))
 
         @staticmethod
         def extra_lds(splits, list_kb, own, page_size=16, head_dim=128, bf16=True):
             return c.extra_lds(int(bf16), head_dim, page_size, splits, C.c_longlong(list_kb << 10), own)
 
-        score_cut_grid, even_tile, tile_stride, last_page_rule = c.score_cut_grid, c.even_tile, c.tile_stride, c.last_page_rule
+        even_tile, tile_stride, last_page_rule = c.even_tile, c.tile_stride, c.last_page_rule
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
         uses_groups = c.uses_groups
 
@@ -215,25 +224,43 @@ def test_score_grid_of_a_step_stays_within_the_extents_of_a_launch(lib, batch, h
 
 def test_score_chunks_of_a_batch_cut_by_its_lengths_cover_every_page_once_and_fit_the_launch(lib):
     """Batches of up to 256 sequences, empty ones among them, far below the launch's bound or at it, in one round or in many: a
-    sequence has just the chunks that its pages fill, also if the reciprocal that the device divides with is two units in the last place
-    off, and all have a workgroup."""
+    sequence has just the chunks that its pages fill, all alike and none empty, also if the reciprocals that the device divides with are two
+    units in the last place off, and all have a workgroup, those left to last pages not counted."""
     r = random.Random(4)
     rounds = set()
     for _ in range(20000):
         batch, most = r.choice([3, 64, 65, 256, r.randint(3, 256)]), r.choice([64, 128, 256])
+        three_fit, reserve = r.choice([(True, 0), (False, 0), (False, batch), (False, 2 * batch), (False, 8 * batch)])
         bound = r.choice([8, r.randint(1, 500), r.randint(1, 70000), 1 << 20])
         if not -(-bound // 8) * batch <= 1 << 22:
             continue
         top = r.choice([1, min(9, bound), bound, r.randint(1, bound)])
         pages = [r.choice([0, min(top, 1), top, r.randint(0, top), r.randint(0, top)]) for _ in range(batch)]
-        chunk, chunks = lib.score_cut(pages, most)
+        chunk, chunks, sizes = lib.score_cut(pages, most, 0, three_fit, reserve)
         assert chunk % 8 == 0 and 8 <= chunk <= most, (batch, most, chunk)
         assert chunks == [-(-n // chunk) for n in pages], (batch, most, chunk)
-        assert sum(chunks) <= lib.score_cut_grid(batch, bound, most), (batch, bound, most)
+        assert sum(chunks) <= lib.score_cut_grid(batch, bound, most, three_fit, reserve), (batch, bound, most)
+        for n, parts, size in zip(pages, chunks, sizes):
+            assert 8 * size <= chunk and (parts - 1) * 8 * size < n <= parts * 8 * size or n == parts == 0, (n, parts, size)
         rounds.add(-(-sum(chunks) // 512))
         for ulps in (-2, 2):
-            assert lib.score_cut(pages, most, ulps) == (chunk, chunks), (batch, most, chunk)
+            assert lib.score_cut(pages, most, ulps, three_fit, reserve) == (chunk, chunks, sizes), (batch, most, chunk)
     assert {1, 2, 3, 40} <= rounds
+
+
+def test_score_chunks_and_last_pages_run_at_the_same_time_where_two_workgroups_fit_a_unit(lib):
+    """Eight heads on fp32 means: the chunks of one round and the workgroups of the last pages are no more than 512."""
+    assert lib.score_cut_reserve(24, 8, 101, 8, 128, False) == 48
+    assert lib.score_cut_reserve(24, 8, 101, 8, 128, True) == lib.score_cut_reserve(24, 8, 101, 4, 128, False) == 0
+    assert lib.score_cut_reserve(24, 8, 129, 8, 128, False) == 0  # in the tile
+    r = random.Random(5)
+    for _ in range(2000):
+        batch = r.randint(3, 100)
+        reserve = 2 * batch
+        pages = [r.randint(0, 4000) for _ in range(batch)]
+        _, chunks, _ = lib.score_cut(pages, 256, 0, False, reserve)
+        need = -(-sum(-(-n // 8) for n in pages) // 32) + batch + reserve
+        assert sum(chunks) + reserve <= 512 * -(-need // 512)
 
 
 @pytest.mark.parametrize("batch,max_pages,min_pages,mean_bytes,rec_bytes,want", [
@@ -242,7 +269,10 @@ def test_score_chunks_of_a_batch_cut_by_its_lengths_cover_every_page_once_and_fi
     (16, 4096, 0, 128, 1152, False), (16, 6000, 0, 128, 1152, True), (3, (1 << 20) + 1, 0, 512, 4224, False),
     (40, 1 << 20, 0, 512, 4224, False), (16, 1500, 749, 512, 4224, True), (16, 1500, 750, 512, 4224, False),
     (16, 4096, 2048, 512, 4224, True), (16, 4096, 3584, 512, 4224, True), (16, 4096, 3585, 512, 4224, False), (7, 9000, 5000, 512, 4224, False),
-    (8, 9000, 5000, 512, 4224, True), (16, 20000, 10000, 128, 1152, False), (16, 4096, 4096, 512, 4224, False)])
+    (8, 9000, 5000, 512, 4224, True), (16, 20000, 10000, 128, 1152, False), (16, 4096, 4096, 512, 4224, False),
+    (16, 1000, 0, 512, 4224, False), (16, 1060, 0, 512, 4224, True), (16, 1000, 1, 512, 4224, True), (64, 380, 0, 256, 2176, False), (64, 395, 0, 256, 2176, True),
+    (64, 195, 60, 512, 4224, True), (65, 195, 60, 512, 4224, True), (256, 127, 1, 512, 4224, False), (256, 128, 1, 512, 4224, True),
+    (100, 237, 0, 512, 4224, False), (100, 240, 0, 512, 4224, True), (100, 237, 20, 512, 4224, True)])
 def test_batches_whose_scores_are_cut_by_the_lengths(lib, batch, max_pages, min_pages, mean_bytes, rec_bytes, want):
     assert lib.score_cuts(batch, max_pages, min_pages, mean_bytes, rec_bytes) == want
 
