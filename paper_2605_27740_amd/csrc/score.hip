@@ -318,16 +318,13 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
   const int wave_slots = c.Hkv <= 8 ? kScoreWaves : kScoreWaves * kRowsPerWave / c.Hkv;
   const int mean_bytes = D * (c.stats_bf16 ? 2 : 4), most = 64 * wave_slots;
   const bool cut = score_cuts(c.B, c.max_pages_hint, c.min_pages_hint, mean_bytes, c.rec_bytes);
-  int tile = most;
-  if (!cut) {
-    tile = score_tile(c.B, c.Hkv, D, c.max_pages_hint, c.min_pages_hint, most);
-    tile = score_even_tile(tile, c.B, c.max_pages_hint, c.min_pages_hint, mean_bytes, most);
-  }
+  const int plain = cut ? most : score_tile(c.B, c.Hkv, D, c.max_pages_hint, c.min_pages_hint, most);
+  const int tile = cut ? most : score_even_tile(plain, c.B, c.max_pages_hint, c.min_pages_hint, mean_bytes, most);
   const int64_t bytes = (int64_t)c.B * c.max_pages_hint * c.rec_bytes;
   const int reserve = score_cut_reserve(refresh_tail, c.B, c.Hkv, bytes, G, score_cut_two_fit(G, D, c.stats_bf16));
   const int tiles = cut ? score_cut_grid(c.B, c.max_pages_hint, tile, score_cut_three_fit(G, D, c.stats_bf16), reserve)
                         : (c.max_pages_hint + tile - 1) / tile;
-  const ScoreGrid grid = score_grid(cut, tiles, c.B, c.Hkv, refresh_tail, bytes, G);
+  const ScoreGrid grid = score_grid(cut, tiles, c.B, c.Hkv, refresh_tail, bytes, G, tile != plain);
   const int refresh = grid.refresh;
   size_t lds = (size_t)c.Hkv * score_tile_stride(tile) * sizeof(float);
   if (refresh & kLastPageOwn) lds = std::max<size_t>(lds, kScoreWaves * mean_bytes);

@@ -173,11 +173,15 @@ constexpr int last_page_groups(int kv_heads) { return (kv_heads + 3) / 4; }
 // bf16 means 24 x 1000 (52 MB) 23.8 / 25.8; large: 4 x 16384 65.3 / 64.8, 80 x 4096, pages of 8 157.2 / 155.7, 48 x 2048 bf16 means 121.4 / 119.5, 160 x 700 fp32
 // means (320 of them) 183.3 / 184.3. Cut by the lengths: 32 x 4K-131K tokens 64.8 / 64.4, 16 x 1000 29.2 / 28.3, bf16 means 20.3 / 18.3. With 8 query
 // heads two workgroups fill a unit and the last ones wait for a place: 3 x 20000 pages of 32, cut, 60.5 / 63.1, but 24 x 1000 61.5 / 58.7.
-inline int score_last_page_rule(bool cut, int64_t workgroups, int last_pages, int64_t bytes, int group) {
+// A tile that was fitted to an even batch (`fitted`) leaves the last workgroup of a sequence about as many pages as the others, and renewing one of them
+// comes on top: a step with the tile of score_tile / fitted, in the tile / fitted, last: 78 x 142 pages of 16 heads, bf16 means (45 MB), 66.0 / 67.4 / 63.3, 2 x 13697
+// 40.0 / 41.6 / 39.6, 60 x 588 of 16 heads 117.8 / 116.3 / 113.3, 10 x 2578 28.7 / 29.0 / 27.6, fp32 means 7 x 1161 of 16 heads 33.1 / 30.6 / 29.9; 120 x 810 of D = 64
+// 54.3 / 52.4 / 52.7.
+inline int score_last_page_rule(bool cut, int64_t workgroups, int last_pages, int64_t bytes, int group, bool fitted = false) {
   constexpr int kNumCUs = 256;
   if (cut) return group == 8 && bytes > (128ll << 20) ? kLastPageInTile : kLastPageOwn;
   if (bytes <= (44ll << 20)) return workgroups <= kNumCUs ? (kLastPageOwn | kLastPageFirst) : kLastPageOwn;
-  return bytes >= (192ll << 20) && last_pages <= kNumCUs && group < 8 ? kLastPageOwn : kLastPageInTile;
+  return group < 8 && last_pages <= (fitted ? 2 * kNumCUs : (bytes >= (192ll << 20) ? kNumCUs : 0)) ? kLastPageOwn : kLastPageInTile;
 }
 
 // Workgroups that a cut leaves to last pages, so that they run with the chunks where no third finds a place on a unit.
@@ -187,15 +191,15 @@ inline int score_cut_reserve(bool refresh_tail, int batch, int kv_heads, int64_t
 }
 
 // The grid of a launch with `tiles` tiles to a sequence, or to the batch where it is cut by its lengths, and its `refresh` argument: a LastPage and,
-// above its bits, the rows of the grid that are for last pages, or the first workgroup that is.
+// above its bits, the rows of the grid that are for last pages, or the first workgroup that is. fitted: the tile is score_even_tile's own.
 struct ScoreGrid {
   int x, y, refresh;
 };
 constexpr int kMaxGridRows = 65535;
-inline ScoreGrid score_grid(bool cut, int tiles, int batch, int kv_heads, bool refresh_tail, int64_t bytes, int group) {
+inline ScoreGrid score_grid(bool cut, int tiles, int batch, int kv_heads, bool refresh_tail, int64_t bytes, int group, bool fitted) {
   const int last_pages = last_page_groups(kv_heads) * batch;
   ScoreGrid g = {tiles, cut ? 1 : batch, kLastPageNone};
-  if (refresh_tail) g.refresh = score_last_page_rule(cut, (int64_t)g.x * g.y, last_pages, bytes, group);
+  if (refresh_tail) g.refresh = score_last_page_rule(cut, (int64_t)g.x * g.y, last_pages, bytes, group, fitted);
   if (!(g.refresh & kLastPageOwn)) return g;
   const int rows = (last_pages + tiles - 1) / tiles;
   if (!cut && batch + rows > kMaxGridRows) {  // more sequences than a launch could have rows for beside them, of a few pages each

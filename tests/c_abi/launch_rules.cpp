@@ -22,11 +22,11 @@ extern "C" int tile(int batch, int kv_heads, int head_dim, int max_pages, int mi
 extern "C" int even_tile(int tile, int batch, int max_pages, int min_pages, int mean_bytes, int max_tile) {
   return unique::score_even_tile(tile, batch, max_pages, min_pages, mean_bytes, max_tile);
 }
-extern "C" int last_page_rule(int cut, int workgroups, int last_pages, int mb, int group) {
-  return unique::score_last_page_rule(cut != 0, workgroups, last_pages, (int64_t)mb << 20, group);
+extern "C" int last_page_rule(int cut, int workgroups, int last_pages, int mb, int group, int fitted) {
+  return unique::score_last_page_rule(cut != 0, workgroups, last_pages, (int64_t)mb << 20, group, fitted != 0);
 }
-extern "C" void score_grid(int cut, int tiles, int batch, int kv_heads, long long bytes, int group, int* out) {
-  const unique::ScoreGrid g = unique::score_grid(cut != 0, tiles, batch, kv_heads, true, bytes, group);
+extern "C" void score_grid(int cut, int tiles, int batch, int kv_heads, long long bytes, int group, int fitted, int* out) {
+  const unique::ScoreGrid g = unique::score_grid(cut != 0, tiles, batch, kv_heads, true, bytes, group, fitted != 0);
   out[0] = g.x, out[1] = g.y, out[2] = g.refresh & ((1 << unique::kLastPageBits) - 1), out[3] = g.refresh >> unique::kLastPageBits;
 }
 extern "C" int tile_stride(int tile) { return unique::score_tile_stride(tile); }

@@ -370,6 +370,7 @@ def test_fused_decode_step_is_bit_identical_to_the_separate_calls(gpu_lib, maker
     (torch.float32, torch.bfloat16, 8, 1, 128, 16, [5 + b % 90 for b in range(70)], 700, 8),   # the same, four sequences to a lane
     (torch.bfloat16, torch.float32, 8, 8, 128, 16, [300 + b for b in range(16)], 2100, 16),    # cut; in the tile
     (torch.bfloat16, torch.float32, 8, 8, 128, 16, [300 + b for b in range(15)] + [1], 1800, 16),  # cut, with workgroups left to last pages
+    (torch.bfloat16, torch.bfloat16, 16, 1, 128, 8, [142] * 78, 142, 24),         # last, with a fitted tile
     (torch.bfloat16, torch.float32, 8, 4, 128, 32, [700, 1, 2, 31], 4000, 32)])                # in the tile
 def test_last_page_of_a_step_wherever_it_is_renewed(gpu_lib, dtype, stats_dtype, Hkv, G, D, S, pages, bound, top_k):
     """The page that has received a token, whose new key points along a query of some heads, is scored with its new statistics: a step

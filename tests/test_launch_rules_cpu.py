@@ -48,9 +48,9 @@ def lib(tmp_path_factory):
             return bool(c.fuses_of(batch, heads, max_pages, top_k, page_size, head_dim, int(bf16)))
 
         @staticmethod
-        def score_grid(cut, tiles, batch, heads, n_bytes, group):
+        def score_grid(cut, tiles, batch, heads, n_bytes, group, fitted=False):
             out = (C.c_int * 4)()
-            c.score_grid(int(cut), tiles, batch, heads, C.c_longlong(n_bytes), group, out)
+            c.score_grid(int(cut), tiles, batch, heads, C.c_longlong(n_bytes), group, int(fitted), out)
             return tuple(out)
 
         @staticmethod
@@ -75,7 +75,11 @@ def lib(tmp_path_factory):
         def extra_lds(splits, list_kb, own, page_size=16, head_dim=128, bf16=True):
             return c.extra_lds(int(bf16), head_dim, page_size, splits, C.c_longlong(list_kb << 10), own)
 
-        even_tile, tile_stride, last_page_rule = c.even_tile, c.tile_stride, c.last_page_rule
+        @staticmethod
+        def last_page_rule(cut, workgroups, last_pages, mb, group, fitted=False):
+            return c.last_page_rule(cut, workgroups, last_pages, mb, group, int(fitted))
+
+        even_tile, tile_stride = c.even_tile, c.tile_stride
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
         uses_groups = c.uses_groups
 
@@ -201,6 +205,13 @@ def test_who_renews_the_last_pages_of_a_step(lib, cut, workgroups, last_pages, m
     assert lib.last_page_rule(cut, workgroups, last_pages, mb, group) == want
 
 
+@pytest.mark.parametrize("mb,last_pages,group,want", [(45, 2, 4, 2), (100, 512, 1, 2), (100, 513, 4, 1), (191, 32, 8, 1), (400, 32, 4, 2), (44, 2, 4, 2)])
+def test_last_pages_of_batches_with_a_fitted_tile_have_workgroups_of_their_own(lib, mb, last_pages, group, want):
+    assert lib.last_page_rule(0, 468, last_pages, mb, group, True) == want
+    assert lib.last_page_rule(0, 468, last_pages, mb, group) == (1 if 44 < mb < 192 else want)
+
+
+
 @pytest.mark.parametrize("batch,heads,pages", [(40000, 1, 4), (65535, 1, 1), (32767, 1, 8), (32768, 1, 8), (21846, 8, 1), (13108, 16, 1),
                                                (7282, 32, 1), (65535, 32, 3), (65530, 4, 16384), (65535, 2, 120000), (1, 1, 1), (16, 8, 700)])
 @pytest.mark.parametrize("group", [1, 8])
@@ -210,8 +221,9 @@ def test_score_grid_of_a_step_stays_within_the_extents_of_a_launch(lib, batch, h
     most = 256 if heads <= 8 else 2048 // heads
     for least in (0, pages):
         for mean_bytes in (128, 256, 512):
-            tile = lib.even_tile(lib.tile(batch, heads, 128 if mean_bytes > 128 else 64, pages, least, most), batch, pages, least, mean_bytes, most)
-            x, y, rule, extra = lib.score_grid(False, -(-pages // tile), batch, heads, batch * pages * (heads * mean_bytes + 128), group)
+            plain = lib.tile(batch, heads, 128 if mean_bytes > 128 else 64, pages, least, most)
+            tile = lib.even_tile(plain, batch, pages, least, mean_bytes, most)
+            x, y, rule, extra = lib.score_grid(False, -(-pages // tile), batch, heads, batch * pages * (heads * mean_bytes + 128), group, tile != plain)
             assert y <= 65535 and x == -(-pages // tile)
             if rule & 2:
                 assert y == batch + extra and x * extra >= batch * -(-heads // 4)
