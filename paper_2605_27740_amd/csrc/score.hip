@@ -328,7 +328,7 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
   const int refresh = grid.refresh;
   size_t lds = (size_t)c.Hkv * score_tile_stride(tile) * sizeof(float);
   if (refresh & kLastPageOwn) lds = std::max<size_t>(lds, kScoreWaves * mean_bytes);
-  if (!cut) lds = (size_t)score_lds((int)lds, (int)sizeof(T), D, G, (int64_t)tiles * c.B);
+  if (!cut) lds = (size_t)std::max(score_lds((int)lds, (int)sizeof(T), D, G, (int64_t)tiles * c.B), score_held_lds((int)sizeof(T), D, G));
   auto go = [&](auto kernel) {
     kernel<<<dim3(grid.x, grid.y), dim3(kScoreWaves * kWave), lds, st>>>(c, reinterpret_cast<const T*>(q), lambda, stride, scores, out, group_max,
                                                          refresh, tile);

@@ -83,6 +83,15 @@ inline int score_lds(int scores, int elem_bytes, int head_dim, int group, int64_
   return std::max(scores, kLds / (most + 1) + 1024);
 }
 
+// bf16 caches of 64 channels leave room for one workgroup more than this, which costs batches with empty tiles and does nothing for the others. us of
+// a kernel with one more / so, bf16 means: G = 8, 8 x 10240 pages from 3 tenths of the longest on 22.4 / 19.9, 8 x 4551 from half on 13.6 / 12.0; of a step: G = 4, 2 heads,
+// 16 x 22186 37.8 / 36.4, G = 2 56 x 1733 55.8 / 54.5; 20 x 4000 from half on, G = 8, is better with it, 22.9 / 23.9.
+inline int score_held_lds(int elem_bytes, int head_dim, int group) {
+  constexpr int kLds = 160 << 10;
+  const int most = elem_bytes == 2 && head_dim == 64 ? (group == 8 ? 4 : (group == 4 ? 5 : (group == 2 ? 6 : 7))) : 0;
+  return most > 0 ? kLds / (most + 1) + 1024 : 0;
+}
+
 // Batches of unlike lengths are cut by the lengths on the device: every workgroup finds for itself how many pages each one takes, so
 // that the chunks of all sequences together fill kCutSlots workgroups, or a multiple where a chunk would be more than a workgroup can
 // hold, and which of them are its own. A chunk is a number of units of 8 pages (whole entries of the group maxima); whole numbers

@@ -79,7 +79,7 @@ def lib(tmp_path_factory):
         def last_page_rule(cut, workgroups, last_pages, mb, group, fitted=False):
             return c.last_page_rule(cut, workgroups, last_pages, mb, group, int(fitted))
 
-        even_tile, tile_stride = c.even_tile, c.tile_stride
+        even_tile, tile_stride, held_lds = c.even_tile, c.tile_stride, c.held_lds
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
         uses_groups = c.uses_groups
 
@@ -195,6 +195,12 @@ def test_score_tiles_fitted_to_even_batches(lib, batch, heads, pages, mean_bytes
     most = 256 if heads <= 8 else 2048 // heads
     tile = lib.tile(batch, heads, 128 if mean_bytes > 128 else 64, pages, pages, most)
     assert lib.even_tile(tile, batch, pages, pages, mean_bytes, most) == want
+
+
+@pytest.mark.parametrize("elem,head_dim,group,most", [(2, 64, 1, 7), (2, 64, 2, 6), (2, 64, 4, 5), (2, 64, 8, 4), (2, 128, 4, None), (4, 64, 8, None)])
+def test_score_workgroups_per_unit_of_bf16_caches_of_64_channels(lib, elem, head_dim, group, most):
+    lds = lib.held_lds(elem, head_dim, group)
+    assert lds == 0 if most is None else most * lds <= 160 << 10 < (most + 1) * lds and 2048 <= lds
 
 
 @pytest.mark.parametrize("cut,workgroups,last_pages,mb,group,want", [
