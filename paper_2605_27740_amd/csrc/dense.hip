@@ -73,18 +73,18 @@ __global__ __launch_bounds__(kDecWaves* kWave) void paged_decode_dense_kernel(Ca
   decode_chunk<D, S, G, kNT>(c, q, chunk, wave, lane, lookup, scale_log2, to, sh);
 }
 
-template <typename T, int D, int G>
-__global__ __launch_bounds__(kMergeWaves* kWave) void paged_decode_dense_merge_kernel(CacheView c, int max_chunks,
-                                                                                       const float* __restrict__ part_o,
-                                                                                       const float* __restrict__ part_ml, T* __restrict__ out,
-                                                                                       float* __restrict__ lse_out) {
-  __shared__ MergeShared<kMergeWaves, D> sh;
+template <typename T, int D, int G, int kWaves>
+__global__ __launch_bounds__(kWaves* kWave) void paged_decode_dense_merge_kernel(CacheView c, int max_chunks,
+                                                                                  const float* __restrict__ part_o,
+                                                                                  const float* __restrict__ part_ml, T* __restrict__ out,
+                                                                                  float* __restrict__ lse_out) {
+  __shared__ MergeShared<kWaves, D> sh;
   const int h = blockIdx.x, b = blockIdx.y, hkv = h / G;
   BatchChunks bc;
   cut_batch(c, c.S, max_chunks, 0, bc);
   const int n = __builtin_amdgcn_readlane(bc.chunks, b);
   const int64_t base = (int64_t)__builtin_amdgcn_readlane(bc.before, b) * c.Hkv + (int64_t)hkv * n;
-  merge_chunks<T, D, G, kMergeWaves>(c, b, h, base, n, [&] { return n; }, part_o, part_ml, out, lse_out, sh);
+  merge_chunks<T, D, G, kWaves>(c, b, h, base, n, [&] { return n; }, part_o, part_ml, out, lse_out, sh);
 }
 
 template <typename T, int D, int S, int G>
@@ -99,9 +99,12 @@ hipError_t launch_t(const CacheView& c, const void* q, float sm_scale, void* out
   else go(paged_decode_dense_kernel<T, D, S, G, false>);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  paged_decode_dense_merge_kernel<T, D, G><<<dim3(c.H, c.B), dim3(kMergeWaves * kWave), 0, st>>>(c, max_chunks, partials, part_ml,
-                                                                                   reinterpret_cast<T*>(out), lse);
-  return hipGetLastError();
+  auto merge = [&](auto kernel, int waves) {
+    kernel<<<dim3(c.H, c.B), dim3(waves * kWave), 0, st>>>(c, max_chunks, partials, part_ml, reinterpret_cast<T*>(out), lse);
+    return hipGetLastError();
+  };
+  return dense_merge_alone(c.B * c.Hkv) ? merge(paged_decode_dense_merge_kernel<T, D, G, 1>, 1)
+                                        : merge(paged_decode_dense_merge_kernel<T, D, G, kMergeWaves>, kMergeWaves);
 }
 
 template <typename T, int D, int S>

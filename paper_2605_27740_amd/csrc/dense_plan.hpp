@@ -31,6 +31,11 @@ inline bool dense_balances(int batch, int kv_heads, int max_pages, int page_byte
   return most_splits((int)rows, max_pages).num_splits > 1 && rows * max_pages * page_bytes >= kDenseLeastBytes;
 }
 
+// One wave merges a head's chunks where the slots are four or fewer to a row, on average: every wave finds the cut for itself, which costs more
+// than it gains by reading an eighth or so of the rows. kernel us with four / one: 32 x 8 rows of 8 heads, lengths uniform 8.0 / 4.7, 64 x 2 of 8 heads 5.8 / 4.3, 16 x 8
+// of 4 heads 4.3 / 4.3 (the call 141.2 / 140.8); 4 x 8 of 8 heads 4.3 / 5.2, 64 x 1 of 8 heads, log-uniform 4.2 / 5.2, 2 x 32 4.3 / 4.6.
+constexpr bool dense_merge_alone(int rows) { return rows >= kDenseSlots / 4; }
+
 // Workgroups that share the pages of a batch, `total` of them over all rows: those that run at the same time, or a multiple.
 constexpr int dense_slots(int total, int max_chunks) {
   const int rounds = total / (kDenseSlots * kDensePages);

@@ -81,6 +81,7 @@ extern "C" int score_cuts(int batch, int max_pages, int min_pages, int mean_byte
   return unique::score_cuts(batch, max_pages, min_pages, mean_bytes, rec_bytes);
 }
 extern "C" int held_lds(int elem_bytes, int head_dim, int group) { return unique::score_held_lds(elem_bytes, head_dim, group); }
+extern "C" int dense_merge_alone(int rows) { return unique::dense_merge_alone(rows); }
 extern "C" int score_cut_reserve(int batch, int kv_heads, long long bytes, int group, int head_dim, int bf16_means) {
   return unique::score_cut_reserve(true, batch, kv_heads, bytes, group, unique::score_cut_two_fit(group, head_dim, bf16_means != 0));
 }

@@ -1420,6 +1420,7 @@ def test_selection_from_group_maxima(gpu_lib, P, ks):
     (torch.bfloat16, 4, 4, 128, 8, [0, 0, 3]),                   # next to nothing
     (torch.float32, 16, 2, 64, 32, [20000, 12345, 1]),
     (torch.bfloat16, 8, 4, 128, 16, [150_000, 30_001, 129_999, 90_000]),  # more than 512 chunks of 256 pages
+    (torch.bfloat16, 8, 4, 64, 16, [200_000] + [20] * 15),        # many rows, one of them of many chunks
 ])
 def test_dense_decode_cut_by_the_lengths_on_the_device(gpu_lib, dtype, Hkv, G, D, S, lens):
     """A dense decode whose chunks come from the lengths on the device (a launch that could read 96 MB or more, which the

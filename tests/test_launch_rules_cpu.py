@@ -79,7 +79,7 @@ def lib(tmp_path_factory):
         def last_page_rule(cut, workgroups, last_pages, mb, group, fitted=False):
             return c.last_page_rule(cut, workgroups, last_pages, mb, group, int(fitted))
 
-        even_tile, tile_stride, held_lds = c.even_tile, c.tile_stride, c.held_lds
+        even_tile, tile_stride, held_lds, dense_merge_alone = c.even_tile, c.tile_stride, c.held_lds, c.dense_merge_alone
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
         uses_groups = c.uses_groups
 
@@ -331,6 +331,10 @@ def test_uncut_rows_with_long_lists_have_two_workgroups_to_a_unit(lib):
     for other in (lib.extra_lds(2, 4096, 37056), lib.extra_lds(1, 511, 37056), lib.extra_lds(1, 4096, 37056, page_size=8),
                   lib.extra_lds(1, 4096, 20000, head_dim=64), lib.extra_lds(1, 4096, 20000, bf16=False)):
         assert other == 0
+
+
+def test_chunks_of_many_dense_rows_are_merged_by_one_wave(lib):
+    assert [lib.dense_merge_alone(n) for n in (2, 64, 127, 128, 256)] == [0, 0, 0, 1, 1]
 
 
 def test_chunks_of_a_balanced_dense_batch_fit_the_workspace_and_leave_room_to_cut(lib):
