@@ -357,22 +357,30 @@ def test_fused_decode_step_is_bit_identical_to_the_separate_calls(gpu_lib, maker
     assert torch.equal(before, fused.page_stats) and torch.equal(ref.out.view(torch.uint8), fused.out.view(torch.uint8))
 
 
-@pytest.mark.parametrize("dtype,stats_dtype,Hkv,G,D,S,pages,bound,top_k", [
-    (torch.bfloat16, torch.float32, 8, 4, 128, 16, [700], 700, 32),               # workgroups of their own, first in the grid
-    (torch.bfloat16, torch.bfloat16, 1, 8, 128, 8, [1100, 1097], 1100, 20),       # a single head
-    (torch.float32, torch.float32, 2, 2, 64, 32, [900, 897, 1, 2], 900, 40),
-    (torch.bfloat16, torch.float32, 32, 1, 64, 16, [400] * 9, 400, 16),           # eight workgroups to a sequence
-    (torch.bfloat16, torch.bfloat16, 8, 4, 64, 16, [300, 513, 1, 290] * 12, 520, 24),    # last in the grid, several rows of them
-    (torch.bfloat16, torch.float32, 2, 4, 64, 8, [4097, 4104, 4105, 4106], 4106, 64),    # group maxima; a last page alone in its group
-    (torch.bfloat16, torch.bfloat16, 2, 2, 64, 8, [8193, 8200, 5001], 8200, 300),        # the same in a selection of its own
-    (torch.bfloat16, torch.float32, 8, 4, 128, 16, [700, 9], 24000, 32),          # last in a launch that may be large
-    (torch.bfloat16, torch.float32, 8, 4, 128, 16, [30 + 7 * b for b in range(20)], 700, 16),  # cut by the lengths
-    (torch.float32, torch.bfloat16, 8, 1, 128, 16, [5 + b % 90 for b in range(70)], 700, 8),   # the same, four sequences to a lane
-    (torch.bfloat16, torch.float32, 8, 8, 128, 16, [300 + b for b in range(16)], 2100, 16),    # cut; in the tile
-    (torch.bfloat16, torch.float32, 8, 8, 128, 16, [300 + b for b in range(15)] + [1], 1800, 16),  # cut, with workgroups left to last pages
-    (torch.bfloat16, torch.bfloat16, 16, 1, 128, 8, [142] * 78, 142, 24),         # last, with a fitted tile
-    (torch.bfloat16, torch.float32, 8, 4, 128, 32, [700, 1, 2, 31], 4000, 32)])                # in the tile
-def test_last_page_of_a_step_wherever_it_is_renewed(gpu_lib, dtype, stats_dtype, Hkv, G, D, S, pages, bound, top_k):
+# Shapes, and who renews the last pages there (tests/test_launch_rules_cpu.py holds the rules to it): "first" / "last" in the grid, the "tile" that
+# the page is in; "cut" where the batch is cut by its lengths. And what selects, where group maxima are used.
+LAST_PAGE_CASES = [
+    (torch.bfloat16, torch.float32, 8, 4, 128, 16, [700], 700, 32, "first", None),
+    (torch.bfloat16, torch.bfloat16, 1, 8, 128, 8, [1000, 993], 1000, 20, "first", None),                     # a single head
+    (torch.float32, torch.float32, 2, 2, 64, 32, [500, 497, 1, 2], 500, 40, "first", None),
+    (torch.bfloat16, torch.float32, 32, 1, 64, 16, [400] * 9, 400, 16, "last", None),                          # eight workgroups to a sequence
+    (torch.bfloat16, torch.bfloat16, 8, 4, 64, 16, [300, 513, 1, 290] * 12, 520, 24, "last", None),            # several rows of them
+    (torch.bfloat16, torch.float32, 2, 4, 64, 8, [4097, 4104, 4105, 4106], 4106, 64, "last", "step"),          # a last page alone in its group
+    (torch.bfloat16, torch.bfloat16, 2, 2, 64, 8, [8193, 8200, 5001], 8200, 300, "last", "own"),
+    (torch.bfloat16, torch.float32, 8, 4, 128, 16, [700, 9], 24000, 32, "last", "step"),                       # a launch that may be large
+    (torch.bfloat16, torch.float32, 8, 4, 128, 16, [30 + 7 * b for b in range(20)], 700, 16, "cut", None),
+    (torch.float32, torch.bfloat16, 8, 1, 128, 16, [5 + b % 90 for b in range(70)], 700, 8, "cut", None),      # four sequences to a lane
+    (torch.bfloat16, torch.float32, 8, 8, 128, 16, [300 + b for b in range(16)], 2100, 16, "cut, tile", None),
+    (torch.bfloat16, torch.float32, 8, 8, 128, 16, [300 + b for b in range(15)] + [1], 1800, 16, "cut", None),  # workgroups left to last pages
+    # cut, and selected from group maxima that may miss the last page: lengths on both sides of an edge of the groups
+    (torch.bfloat16, torch.float32, 2, 4, 128, 8, [4105, 1, 4104, 4099, 4500, 9, 8, 17, 2001, 4096, 130, 65, 33, 700, 641, 4097], 4500, 100, "cut", "step"),
+    (torch.bfloat16, torch.float32, 2, 4, 128, 8, [4105, 1, 4104, 4099, 4500, 9, 8, 17, 2001, 8000, 130, 65, 33, 700, 641, 7993], 8000, 300, "cut", "own"),
+    (torch.bfloat16, torch.bfloat16, 16, 1, 128, 8, [142] * 78, 142, 24, "last", None),                        # a fitted tile
+    (torch.bfloat16, torch.float32, 8, 4, 128, 32, [700, 1, 2, 31], 4000, 32, "tile", None)]
+
+
+@pytest.mark.parametrize("dtype,stats_dtype,Hkv,G,D,S,pages,bound,top_k,renewed,from_groups", LAST_PAGE_CASES)
+def test_last_page_of_a_step_wherever_it_is_renewed(gpu_lib, dtype, stats_dtype, Hkv, G, D, S, pages, bound, top_k, renewed, from_groups):
     """The page that has received a token, whose new key points along a query of some heads, is scored with its new statistics: a step
     gives the statistics, lists and outputs of the separate calls bit for bit, whoever renews the page; so it does where its id is
     outside the pool."""
@@ -409,6 +417,10 @@ def test_last_page_of_a_step_wherever_it_is_renewed(gpu_lib, dtype, stats_dtype,
         for b in range(wl.B - broken):  # the planted page is the best of its rows
             for h in range(0, Hkv, 2):
                 assert int(fused.sel_pages[b, h, int(fused.sel_count[b, h]) - 1]) == pages[b] - 1
+    names = _kernels_of(lambda: fused.decode_step(refresh_tail=True))
+    assert "page_score_kernel" in names
+    assert {"select_groups_decode_kernel": "step", "topk_select_grouped_kernel": "own"}.get(
+        next(iter(names & {"select_groups_decode_kernel", "topk_select_grouped_kernel"}), None)) == from_groups, names
 
 
 @pytest.mark.parametrize("B,Hkv,P", [(40000, 1, 4), (7282, 32, 1)])

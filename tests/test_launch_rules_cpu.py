@@ -211,6 +211,32 @@ def test_who_renews_the_last_pages_of_a_step(lib, cut, workgroups, last_pages, m
     assert lib.last_page_rule(cut, workgroups, last_pages, mb, group) == want
 
 
+def test_cases_of_last_pages_take_the_routes_that_they_name(lib):
+    """The steps on a GPU whose last pages are renewed in every way there is: where the rules that a launch asks send them."""
+    from tests.test_gpu_parity import LAST_PAGE_CASES
+    seen = set()
+    for dtype, stats, heads, group, head_dim, page_size, pages, bound, top_k, renewed, from_groups in LAST_PAGE_CASES:
+        bf16, mean_bytes, batch = dtype.itemsize == 2, head_dim * stats.itemsize, len(pages)
+        least, page_bytes = min(pages) - 1, page_size * head_dim * 2 * dtype.itemsize  # full pages of the shortest sequence
+        streams = batch * heads * min(top_k, bound) * page_bytes > 96 << 20
+        fuses = lib.fuses_of(batch, heads, bound, top_k, page_size, head_dim, bf16)
+        assert not (fuses and lib.whole(batch, heads, bound, top_k, mean_bytes, streams, page_bytes))
+        assert ("step" if fuses else "own") == from_groups if lib.uses_groups(bound, top_k) else from_groups is None
+        record, most = heads * mean_bytes + 128, 256 if heads <= 8 else 2048 // heads
+        n_bytes = batch * bound * record
+        if lib.score_cuts(batch, bound, least, mean_bytes, record):
+            _, _, rule, _ = lib.score_grid(True, 512, batch, heads, n_bytes, group)
+            route = "cut, tile" if rule == 1 else "cut"
+        else:
+            plain = lib.tile(batch, heads, head_dim, bound, least, most)
+            tile = lib.even_tile(plain, batch, bound, least, mean_bytes, most)
+            _, _, rule, _ = lib.score_grid(False, -(-bound // tile), batch, heads, n_bytes, group, tile != plain)
+            route = {1: "tile", 2: "last", 6: "first"}[rule]
+        assert route == renewed, (batch, heads, bound, route)
+        seen.add((route, from_groups))
+    assert {"first", "last", "tile", "cut", "cut, tile"} == {r for r, _ in seen} and {("cut", "step"), ("cut", "own"), ("last", "step"), ("last", "own")} <= seen
+
+
 @pytest.mark.parametrize("mb,last_pages,group,want", [(45, 2, 4, 2), (100, 512, 1, 2), (100, 513, 4, 1), (191, 32, 8, 1), (400, 32, 4, 2), (44, 2, 4, 2)])
 def test_last_pages_of_batches_with_a_fitted_tile_have_workgroups_of_their_own(lib, mb, last_pages, group, want):
     assert lib.last_page_rule(0, 468, last_pages, mb, group, True) == want
