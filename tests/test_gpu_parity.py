@@ -1652,7 +1652,8 @@ def test_step_of_more_cut_rows_than_two_workgroups_per_unit(gpu_lib, B, P, S, dt
         assert torch.equal(apart.out.view(torch.uint8), step.out.view(torch.uint8))
 
     same()
-    step.out.zero_()
+    for t in (step.sel_pages, step.sel_count, step.out, step.lse):
+        t.fill_(-9)
     whole, size = step.workspace, 256
     while True:  # refused sizes are refused before anything is launched
         step.workspace = whole[:size]
@@ -1664,6 +1665,8 @@ def test_step_of_more_cut_rows_than_two_workgroups_per_unit(gpu_lib, B, P, S, dt
             size += 256
     assert size <= whole.numel()
     same()
+    names = _kernels_of(lambda: step.decode_step(refresh_tail=False))
+    assert "select_decode_kernel" not in names and "paged_decode_partial_kernel" in names, names
 
 
 @pytest.mark.parametrize("S,G,P,top_k", [(16, 4, 70, 64), (16, 4, 70, 63), (32, 8, 400, 33), (16, 1, 4200, 100), (32, 2, 1500, 250)])
