@@ -72,42 +72,45 @@ struct DecodeShared {  // the waves' results, merged at the end; bf16 caches: ou
 
 // The waves' results, all in `sh`, become the chunk's: partial results, or the output of a row with one chunk. A thread takes as many
 // consecutive channels of a head as there are: a loop over single ones repeated the scales and waited for the LDS twice with four heads of
-// 128 channels (a step of 32K tokens 18.5 / 18.3 us, 12 x 50K with eight heads 61.3 / 60.8, the toy model 10.8 / 10.6).
+// 128 channels (a step of 32K tokens 18.5 / 18.3 us, 12 x 50K with eight heads 61.3 / 60.8, the toy model 10.8 / 10.6). It is written as a loop of one
+// turn all the same: with an early return in its place every instance becomes longer, and one-kernel steps of two heads took 9.7 us for 9.6 (10 x 40 pages) and
+// 9.9 for 9.8 (25 x 81), the step of 32K tokens 16.1 for 15.9 to 16.1.
 template <typename T, int D, int G>
 __device__ __forceinline__ void finish_chunk(const CacheView& c, const Chunk& k, const ChunkOut<T>& to, const DecodeShared<T, D, G>& sh) {
   constexpr int kSlots = DecodeShared<T, D, G>::kSlots;
   constexpr int kPer = G * D <= kDecWaves * kWave ? 1 : G * D / (kDecWaves * kWave);
   static_assert(kPer <= 4, "a 16-byte access");
   typedef float vec_t __attribute__((ext_vector_type(kPer)));
-  const int at = threadIdx.x * kPer, g = at / D, d = at % D;
-  if (at >= G * D) return;
-  float M = sh.m[0][g];
+  for (int at = threadIdx.x * kPer; at < G * D; at += kDecWaves * kWave * kPer) {  // once
+    const int g = at / D, d = at % D;
+    float M = sh.m[0][g];
 #pragma unroll
-  for (int w = 1; w < kDecWaves; ++w) M = fmaxf(M, sh.m[w][g]);
-  float o[kPer], L = 0.f;
+    for (int w = 1; w < kDecWaves; ++w) M = fmaxf(M, sh.m[w][g]);
+    float o[kPer], L = 0.f;
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) o[i] = 0.f;
+    for (int i = 0; i < kPer; ++i) o[i] = 0.f;
 #pragma unroll
-  for (int w = 0; w < kDecWaves; ++w) {
-    const float sc = fast_exp2(sh.m[w][g] - M);
-    vec_t ow = *reinterpret_cast<const vec_t*>(&sh.acc[w][g][d]);
+    for (int w = 0; w < kDecWaves; ++w) {
+      const float sc = fast_exp2(sh.m[w][g] - M);
+      vec_t ow = *reinterpret_cast<const vec_t*>(&sh.acc[w][g][d]);
 #pragma unroll
-    for (int r = G + g; r < kSlots; r += G) ow += *reinterpret_cast<const vec_t*>(&sh.acc[w][r][d]);
+      for (int r = G + g; r < kSlots; r += G) ow += *reinterpret_cast<const vec_t*>(&sh.acc[w][r][d]);
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) o[i] = fmaf(ow[i], sc, o[i]);
-    L = fmaf(sh.l[w][g], sc, L);
-  }
-  if (to.num_splits == 1) {
+      for (int i = 0; i < kPer; ++i) o[i] = fmaf(ow[i], sc, o[i]);
+      L = fmaf(sh.l[w][g], sc, L);
+    }
+    if (to.num_splits == 1) {
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) write_final(c, to.out, to.lse_out, k.b, k.hkv * G + g, d + i, D, o[i], M, L);
-  } else {
-    vec_t out;
+      for (int i = 0; i < kPer; ++i) write_final(c, to.out, to.lse_out, k.b, k.hkv * G + g, d + i, D, o[i], M, L);
+    } else {
+      vec_t out;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) out[i] = o[i];
-    *reinterpret_cast<vec_t*>(&to.part_o[(k.slot * G + g) * D + d]) = out;
-    if (d == 0) {
-      to.part_ml[(k.slot * G + g) * 2 + 0] = M;
-      to.part_ml[(k.slot * G + g) * 2 + 1] = L;
+      for (int i = 0; i < kPer; ++i) out[i] = o[i];
+      *reinterpret_cast<vec_t*>(&to.part_o[(k.slot * G + g) * D + d]) = out;
+      if (d == 0) {
+        to.part_ml[(k.slot * G + g) * 2 + 0] = M;
+        to.part_ml[(k.slot * G + g) * 2 + 1] = L;
+      }
     }
   }
 }
@@ -567,7 +570,7 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const bf16_t* _
 // 64 pairs and the first eight rows of every wave are requested at once, before anything is known of the row: `have` chunks are there to be
 // read; the first ns_of() of them, whose loads are then on their way as well, hold results.
 // A step us with a chain of the count, the pairs and eight rows of one wave after the other / so: 32K tokens, 32 chunks 19.7 / 18.2, a million
-// tokens, 64 chunks 56.1 / 54.7, 96 rows of 5 chunks 61.9 / 61.2, 128 of 4 142.3 / 141.7.
+// tokens, 32 chunks 56.1 / 54.7, 96 rows of 5 chunks 61.9 / 61.2, 128 of 4 142.3 / 141.7.
 template <int kWaves, int D>
 struct MergeShared {
   float o[kWaves][D];
