@@ -42,7 +42,7 @@ hipError_t launch_stats(const CacheView& c, const int32_t* d_tok_begin, const in
                         int max_pages_touched, hipStream_t stream);
 
 // refresh_tail: the statistics of the last page of every sequence are recomputed from the keys (the same arithmetic as launch_stats) and
-// stored before that page is scored. d_group_max may then not count a last page that is scored apart from its group: whoever reads the
+// stored before that page is scored; d_scores_out is null then. d_group_max may then not count a last page that is scored apart from its group: whoever reads the
 // maxima takes that page's score itself.
 // d_group_max: [rows][score_stride / kGroupPages], the largest key (score_key) of every group of pages; null: not wanted.
 hipError_t launch_score(const CacheView& c, const void* d_q, float lambda, float* d_scores, int score_stride,

@@ -371,6 +371,7 @@ bool score_supported(int dtype, int D, int G, int Hkv) {
 
 hipError_t launch_score(const CacheView& c, const void* d_q, float lambda, float* d_scores, int score_stride,
                         float* d_scores_out, uint32_t* d_group_max, bool refresh_tail, hipStream_t stream) {
+  if (refresh_tail && d_scores_out) return hipErrorInvalidValue;  // last pages with workgroups of their own leave no second copy of their score
   if (c.dtype == 0) {
     return c.D == 64 ? dispatch_g<float, 64>(c, d_q, lambda, d_scores, score_stride, d_scores_out, d_group_max, refresh_tail, stream)
                      : dispatch_g<float, 128>(c, d_q, lambda, d_scores, score_stride, d_scores_out, d_group_max, refresh_tail, stream);
