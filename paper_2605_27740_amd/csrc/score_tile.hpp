@@ -175,8 +175,9 @@ constexpr int last_page_groups(int kv_heads) { return (kv_heads + 3) / 4; }
 
 // Workgroups of their own cost the units that they land on what they read, and on these units a launch that gives every unit the same ends
 // later; a small launch, which is a chain of latencies, gains by them, and so do large ones, in which a late start of some tiles shows.
-// Below two workgroups per unit they are best first; in larger launches they then leave some units one more than others (16 x 8192 pages 141.3
-// in the tile, 157.3 first, 140.4 last).
+// In launches of at most one workgroup per unit they are best first; in larger ones they then leave some units one more than others (16 x 8192 pages
+// 141.3 in the tile, 157.3 first, 140.4 last). Between 44 and 192 MB the bytes decide, from batches of 16 and 24 sequences; one or two long
+// ones there were measured with a fitted tile only.
 // A step us in the tile / so (8 heads, G = 4, D = 128): fp32 means, 1 x 1000 pages 16.2 / 14.5, 1 x 2048 18.2 / 16.6, 2 x 3000 20.8 / 19.3, 16 x 400
 // 20.3 / 18.1, bf16 means, pages of 8, 4 x 4096 23.6 / 20.9, 32 x 600 21.6 / 19.7; but fp32 means 16 x 1000 (67 MB) 31.3 / 32.5, 24 x 1000 44.9 / 45.6,
 // bf16 means 24 x 1000 (52 MB) 23.8 / 25.8; large: 4 x 16384 65.3 / 64.8, 80 x 4096, pages of 8 157.2 / 155.7, 48 x 2048 bf16 means 121.4 / 119.5, 160 x 700 fp32
