@@ -181,9 +181,9 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void page_score_kernel(CacheVie
   }
   int b, tile0, N, P;
   if constexpr (kCut > 0) {
-    constexpr bool kThreeFit = score_cut_three_fit(G, D, sizeof(TS) == 2);
+    const bool three_fit = score_cut_three_fit(G, D, sizeof(TS) == 2, sizeof(T), c.B);
     const int reserve = kOwn && score_cut_two_fit(G, D, sizeof(TS) == 2) ? last_page_groups(c.Hkv) * c.B : 0;
-    if (!find_chunk<kCut>(c, blockIdx.x, tile_pages, kThreeFit, reserve, less, b, tile0, tile_pages, N, P)) return;
+    if (!find_chunk<kCut>(c, blockIdx.x, tile_pages, three_fit, reserve, less, b, tile0, tile_pages, N, P)) return;
   } else {
     b = row;
     tile0 = blockIdx.x * tile_pages;  // tile_pages logical pages per workgroup (a multiple of 8, up to 256)
@@ -322,7 +322,7 @@ hipError_t launch_t(const CacheView& cv, const void* q, float lambda, float* sco
   const int tile = cut ? most : score_even_tile(plain, c.B, c.max_pages_hint, c.min_pages_hint, mean_bytes, most);
   const int64_t bytes = (int64_t)c.B * c.max_pages_hint * c.rec_bytes;
   const int reserve = score_cut_reserve(refresh_tail, c.B, c.Hkv, bytes, G, score_cut_two_fit(G, D, c.stats_bf16));
-  const int tiles = cut ? score_cut_grid(c.B, c.max_pages_hint, tile, score_cut_three_fit(G, D, c.stats_bf16), reserve)
+  const int tiles = cut ? score_cut_grid(c.B, c.max_pages_hint, tile, score_cut_three_fit(G, D, c.stats_bf16, (int)sizeof(T), c.B), reserve)
                         : (c.max_pages_hint + tile - 1) / tile;
   const ScoreGrid grid = score_grid(cut, tiles, c.B, c.Hkv, refresh_tail, bytes, G, tile != plain);
   const int refresh = grid.refresh;

@@ -106,8 +106,8 @@ constexpr int kCutMaxPages = 1 << 20;   // of a sequence
 constexpr int kCutMaxUnits = 1 << 22;   // of a launch
 
 // Workgroups for so many units: kCutSlots, or a multiple if chunks of most_units would be more with the sequences' last ones, which are
-// the only ones that are not full. `reserve` of them are left to others, which are to run at the same time. three_fit: three find a place on a unit, no
-// fourth, so that three to each come before four.
+// the only ones that are not full. `reserve` of them are left to others, which are to run at the same time. three_fit: three to a unit come before four
+// (score_cut_three_fit).
 constexpr int score_cut_slots(int units, int batch, int most_units, bool three_fit, int reserve) {
   const int need = (units + most_units - 1) / most_units + batch + reserve;
   if (three_fit && need > kCutSlots && need <= kCutSlots * 3 / 2) return kCutSlots * 3 / 2 - reserve;
@@ -115,7 +115,11 @@ constexpr int score_cut_slots(int units, int batch, int most_units, bool three_f
 }
 // Eight heads on bf16 means. us with four to a unit / three, lengths from 85 hundredths of the longest: 64 x 2000 pages 52.8 / 49.0, 63 x 2951 70.4 / 68;
 // from 6 tenths 8 x 27105 72.4 / 69.5. Three where two are enough lose: 16 x 2108 log-uniform 21.3 / 22.8 (a step), 20 x 7000 44.1 / 47.4.
-constexpr bool score_cut_three_fit(int group, int head_dim, bool bf16_means) { return group == 8 && head_dim == 128 && bf16_means; }
+// On fp32 caches only two of them fit, and 768 workgroups are better than 1024 for many sequences all the same: a step of 64 x 4000 pages of one head, log-uniform
+// from a quarter of the longest 32.1 / 31.0, 64 x 2200 of 4 from 85 hundredths on 61.1 / 57.8, 64 x 2700 66.6 / 63.1, but 8 x 27105 from 6 tenths on 62.5 / 63.2, 8 x 20000 56.5 / 58.3.
+constexpr bool score_cut_three_fit(int group, int head_dim, bool bf16_means, int elem_bytes, int batch) {
+  return group == 8 && head_dim == 128 && bf16_means && (elem_bytes == 2 || batch >= 64);
+}
 // Whether no third workgroup finds a place on a unit.
 constexpr bool score_cut_two_fit(int group, int head_dim, bool bf16_means) { return group == 8 && head_dim == 128 && !bf16_means; }
 // Units of a chunk at most, so that there are no more than `slots` chunks if the sequences' last ones waste no more than `waste` chunks

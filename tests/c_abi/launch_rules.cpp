@@ -85,6 +85,9 @@ extern "C" int dense_merge_alone(int rows) { return unique::dense_merge_alone(ro
 extern "C" int score_cut_reserve(int batch, int kv_heads, long long bytes, int group, int head_dim, int bf16_means) {
   return unique::score_cut_reserve(true, batch, kv_heads, bytes, group, unique::score_cut_two_fit(group, head_dim, bf16_means != 0));
 }
+extern "C" int score_cut_three_fit(int group, int head_dim, int bf16_means, int elem_bytes, int batch) {
+  return unique::score_cut_three_fit(group, head_dim, bf16_means != 0, elem_bytes, batch);
+}
 extern "C" int score_cut_grid(int batch, int max_pages, int most_pages, int three_fit, int reserve) {
   return unique::score_cut_grid(batch, max_pages, most_pages, three_fit != 0, reserve);
 }

@@ -81,7 +81,7 @@ def lib(tmp_path_factory):
 
         even_tile, tile_stride, held_lds, dense_merge_alone = c.even_tile, c.tile_stride, c.held_lds, c.dense_merge_alone
         dense_chunks, dense_balances, lds = c.dense_chunks, c.dense_balances, c.lds
-        uses_groups = c.uses_groups
+        uses_groups, score_cut_three_fit = c.uses_groups, c.score_cut_three_fit
 
         @staticmethod
         def whole(batch, heads, max_pages, top_k, mean_bytes=512, streams=0, page_bytes=8192):
@@ -290,6 +290,12 @@ def test_score_chunks_of_a_batch_cut_by_its_lengths_cover_every_page_once_and_fi
         for ulps in (-2, 2):
             assert lib.score_cut(pages, most, ulps, three_fit, reserve) == (chunk, chunks, sizes), (batch, most, chunk)
     assert {1, 2, 3, 40} <= rounds
+
+
+@pytest.mark.parametrize("group,head_dim,bf16_means,elem,batch,want", [
+    (8, 128, 1, 2, 3, 1), (8, 128, 1, 4, 63, 0), (8, 128, 1, 4, 64, 1), (8, 128, 0, 2, 64, 0), (4, 128, 1, 2, 64, 0), (8, 64, 1, 2, 64, 0)])
+def test_batches_of_eight_heads_that_are_cut_for_three_workgroups_to_a_unit(lib, group, head_dim, bf16_means, elem, batch, want):
+    assert lib.score_cut_three_fit(group, head_dim, bf16_means, elem, batch) == want
 
 
 def test_score_chunks_and_last_pages_run_at_the_same_time_where_two_workgroups_fit_a_unit(lib):
