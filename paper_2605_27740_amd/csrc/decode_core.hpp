@@ -134,7 +134,8 @@ __device__ __forceinline__ void decode_chunk(const CacheView& c, const float* __
   static_assert(S % kTokPerLoad == 0 && kLoads % kTileLoads == 0, "page size / element type combination");
   // Eight heads are bound by the vector ALUs, and four nearly, so their sums over lanes 16 and 32 apart go through the LDS. us with row swaps /
   // so, D = 128, pages of 16: 8 heads, dense 1 x 11828 pages 284 / 270 (275 with the sums of the logits alone), steps of 53 x 891, 4 KV heads, k = 159
-  // 148.4 / 145.2, 36 x 96, 17 39.7 / 37.7; 4 heads 36 x 96, 17 29.1 / 28.5, 25 x 862, 336 215.3 / 212.6; 1 and 2 the same. A token of 64 channels is in 16 lanes,
+  // 148.4 / 145.2, 36 x 96, 17 39.7 / 37.7; 4 heads 36 x 96, 17 29.1 / 28.5, 25 x 862, 336 215.3 / 212.6; 1 and 2 the same. Eight heads over short chunks of cut
+  // rows lose (20 x 9000 pages of 8, k = 64 19.4 / 20.0), which the same instances cannot tell. A token of 64 channels is in 16 lanes,
   // so that only the end has such sums, a chain of them: the toy model 10.1 / 10.4, 1 x 2048 pages, 8 heads 16.5 / 16.8, 40 x 300 the same.
   constexpr bool kLds = G >= 4 && D == 128;
 
